@@ -31,8 +31,8 @@ FORM_NAMES = {0: None, 1: "edge_records", 2: "byte_scatter", 3: "temporal"}
 COUNTERS = os.path.join(ROOT, "profiles", "compact_step_triangle_r16_counters.txt")
 CSRC = os.path.join(ROOT, "paper_2110_12952_amd", "csrc")
 # the device code of the step kernels: a counter summary taken on other sources is stale
-KERNEL_SOURCES = ("kernels.hip", "device_common.hpp", "params.hpp", "edges.hpp", "edges_inst.hip", "tiled.hpp",
-                  "tiled_inst.hip")
+KERNEL_SOURCES = ("kernels.hip", "device_common.hpp", "params.hpp", "matrix.hpp", "matrix_inst.hip",
+                  "matrix_plan.cpp", "edges.hpp", "edges_inst.hip", "tiled.hpp", "tiled_inst.hip")
 
 
 def kernel_sources_hash():
@@ -625,8 +625,9 @@ def main():
                    "tile_level": info.tile_level},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBPS, "traffic": traffic,
-                     "kernel": ("k_step_direct" if info.strategy == N.STRATEGY_DIRECT else
-                                "k_step_edges" if info.tiled_form == 1 else "k_step_tiled"),
+                     # TILED runs the matrix-core form on every fractal of the workloads
+                     "kernel": {N.STRATEGY_DIRECT: "k_step_direct", N.STRATEGY_TILED: "k_step_matrix"}.get(
+                         info.strategy, "k_step_tiled"),
                      "alg_bytes_per_launch": alg_bytes},
         "cpu_baseline": cpu,
         "compact_repeats": repeats,

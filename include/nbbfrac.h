@@ -72,7 +72,11 @@ typedef enum {
  * the Moore neighbourhood; counts then run 0..4. */
 #define NBB_RULE_VON_NEUMANN (1u << 31)
 
-/* How nbb_step_compact evaluates a step (nbb_configure). */
+/* How nbb_step_compact evaluates a step (nbb_configure).  TILED runs the step
+ * on the matrix cores, at a tile level of its own, for every fractal that has
+ * a block level with 16 to 64 cells (k = 2 to 8 and 16); for others, and for
+ * the strategies that name a form, it runs in the form and at the level that
+ * nbb_query reports.  Every form gives the same states. */
 #define NBB_STRATEGY_AUTO 0u   /* TILED when the fractal allows it, else DIRECT */
 #define NBB_STRATEGY_TILED 1u  /* level-m tiles staged in LDS with their halo */
 #define NBB_STRATEGY_DIRECT 2u /* one thread per cell: lambda, 8 x nu, rule */
@@ -101,7 +105,8 @@ typedef struct {
      * high-level squares when SL is not a multiple of 16. */
     uint32_t box_low_side;  /* SL */
     uint32_t box_high_side; /* NH (0 when the box is too large to exist) */
-    /* How a tiled strategy runs the step: 1 = edge records (each block's
+    /* The vector form of a tiled strategy (the form TILED takes where the
+     * matrix-core form does not apply): 1 = edge records (each block's
      * cells loaded into registers, only the blocks' edge rows and columns
      * exchanged through LDS; TILED_EDGE, and TILED where the level allows
      * the form and its blocks fill at least three quarters of the work-group

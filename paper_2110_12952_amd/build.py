@@ -26,7 +26,7 @@ NOISE = "is not a recognized feature for this target"
 
 def units():
     """(source, object name, extra flags) of every translation unit."""
-    out = [("plan.cpp", "plan.o", []), ("kernels.hip", "kernels.o", []), ("api.hip", "api.o", []),
+    out = [("plan.cpp", "plan.o", []), ("matrix_plan.cpp", "matrix_plan.o", []), ("kernels.hip", "kernels.o", []), ("api.hip", "api.o", []),
            ("temporal.hip", "temporal.o", [])]
     for batch in (0, 1):
         for team in (64, 256):
@@ -37,6 +37,11 @@ def units():
         for edge, rule in ((0, 0), (0, 1), (0, 2), (1, 1)):
             out.append(("edges_inst.hip", f"edges_b{batch}_e{edge}_r{rule}.o",
                         [f"-DNBB_INST_BATCH={batch}", f"-DNBB_INST_EDGE={edge}", f"-DNBB_INST_RULE={rule}"]))
+    for batch in (0, 1):
+        for rule in (0, 1):
+            for al in (1, 4, 16):
+                out.append(("matrix_inst.hip", f"matrix_b{batch}_r{rule}_a{al}.o",
+                            [f"-DNBB_INST_BATCH={batch}", f"-DNBB_INST_RULE={rule}", f"-DNBB_INST_AL={al}"]))
     return out
 
 

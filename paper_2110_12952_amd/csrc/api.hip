@@ -56,6 +56,12 @@ struct nbb_fractal {
     bool use_edges = false;
     DevBlob dedge;
     EdgeParams ep{};
+    // The tiled step on the matrix cores (k_step_matrix), at a tile level of
+    // its own: taken by the TILED strategy wherever its plan applies.
+    MatPlan mat;
+    bool use_matrix = false;
+    DevBlob dmat;
+    MatParams matp{};
     // Several generations per launch (NBB_STRATEGY_TEMPORAL): the plan and
     // its device tables; the tile plan above stays for batches.
     TemporalPlan temporal;
@@ -335,6 +341,52 @@ nbb_status upload_edges(const EdgePlan &p, const TileParams &T, DevBlob *blob, E
     return NBB_OK;
 }
 
+// Block alignment in a state: states start 16-aligned, tiles and blocks are
+// whole blocks.
+uint32_t mat_align_of(uint32_t CB) { return CB % 16 == 0 ? 16 : (CB % 4 == 0 ? 4 : 1); }
+
+// Uploads the matrix plan's tables (operands, record addresses, halo blocks,
+// neighbour tiles) into one allocation.
+nbb_status upload_matrix(const MatPlan &p, DevBlob *blob, MatParams *T) {
+    const void *src[4] = {p.A.data(), p.raddr.data(), p.halo.data(), p.nbr.data()};
+    size_t bytes[4] = {p.A.size(), p.raddr.size() * 4, p.halo.size() * 4, p.nbr.size() * 4};
+    void *dst[4];
+    nbb_status s = upload(blob, src, bytes, 4, dst);
+    if (s != NBB_OK) return s;
+    *T = MatParams{};
+    T->K = p.K;
+    T->CB = p.CB;
+    T->lanes = p.lanes;
+    T->nblk = p.nblk;
+    T->nhalo = p.nhalo;
+    T->nrecs = p.nrecs;
+    T->buf_bytes = p.buf_bytes;
+    T->waves = p.waves;
+    T->ntiles = uint32_t(p.ntiles);
+    T->A = static_cast<const int8_t *>(dst[0]);
+    T->raddr = static_cast<const uint32_t *>(dst[1]);
+    T->halo = static_cast<const uint32_t *>(dst[2]);
+    T->nbr = static_cast<const uint32_t *>(dst[3]);
+    return NBB_OK;
+}
+
+// Builds and uploads the matrix plan of a descriptor at its own tile level
+// (nothing where the form does not apply).
+nbb_status setup_matrix(nbb_fractal *F) {
+    const uint32_t cus = uint32_t(F->cu_count), m = auto_mat_level(F->f, {F->f.r}, cus);
+    std::string msg;
+    MatPlan p;
+    if (!m || !build_mat_plan(F->f, m, 0, cus, &p, &msg)) return NBB_OK;
+    nbb_status st = upload_matrix(p, &F->dmat, &F->matp);
+    if (st != NBB_OK) return st;
+    p.A.clear();
+    p.raddr.clear();
+    p.halo.clear();
+    p.nbr.clear();
+    F->mat = std::move(p);
+    return NBB_OK;
+}
+
 // Builds and uploads the edge plan at the tile plan's level for a TILED
 // descriptor; leaves the byte-scatter form in place where it does not apply.
 // The edge form gives each thread whole blocks, one per pass of the
@@ -348,6 +400,7 @@ nbb_status setup_edges(nbb_fractal *F, bool force = false) {
     blob_free(&F->dedge);
     F->use_edges = false;
     F->edge = EdgePlan();
+    F->use_matrix = !force && F->strategy == NBB_STRATEGY_TILED && F->tile.team == 256 && F->mat.ok;
     if (F->strategy != NBB_STRATEGY_TILED || F->tile.team != 256) return NBB_OK;
     std::string msg;
     EdgePlan p;
@@ -579,6 +632,7 @@ nbb_status nbb_create(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r
             if (build_tile_plan(F->f, auto_tile_level(F->f), &F->tile, &msg)) {
                 st = upload_tile(F, F->tile, &F->dtile, &F->tp);
                 if (st == NBB_OK) F->strategy = NBB_STRATEGY_TILED;
+                if (st == NBB_OK) st = setup_matrix(F);
                 if (st == NBB_OK) st = setup_edges(F);
             }
         }
@@ -588,6 +642,7 @@ nbb_status nbb_create(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r
         blob_free(&F->dbox);
         blob_free(&F->dtile);
         blob_free(&F->dedge);
+        blob_free(&F->dmat);
         blob_free(&F->dmfma);
         delete F;
         return st;
@@ -605,6 +660,7 @@ void nbb_destroy(nbb_fractal *F) {
     blob_free(&F->dbox);
     blob_free(&F->dtile);
     blob_free(&F->dedge);
+    blob_free(&F->dmat);
     blob_free(&F->dmfma);
     delete F;
 }
@@ -630,7 +686,7 @@ nbb_status nbb_query(const nbb_fractal *F, nbb_info *info) {
         info->tile_side = 1;
     }
     info->bbox_pitch = box_pitch(F->f);
-    info->device_table_bytes = F->dmap.bytes + F->dbox.bytes + F->dtile.bytes + F->dedge.bytes + F->dmfma.bytes;
+    info->device_table_bytes = F->dmap.bytes + F->dbox.bytes + F->dtile.bytes + F->dedge.bytes + F->dmat.bytes + F->dmfma.bytes;
     uint32_t ebpt = 0, ehpt = 0;
     if (F->use_edges && edge_case(F->edge.nblk, F->edge.nhalo, &ebpt, &ehpt)) info->lds_bytes = edge_lds_bytes(ebpt, ehpt);
     info->tiled_form = F->strategy == NBB_STRATEGY_DIRECT ? 0u : (F->use_edges ? 1u : 2u);
@@ -663,6 +719,7 @@ nbb_status nbb_configure(nbb_fractal *F, uint32_t strategy, uint32_t tile_level)
         F->temporal = TemporalPlan();
         blob_free(&F->dedge);
         F->use_edges = false;
+        F->use_matrix = false;
         return NBB_OK;
     }
     if (strategy != NBB_STRATEGY_TILED && strategy != NBB_STRATEGY_TILED_WAVE &&
@@ -694,6 +751,7 @@ nbb_status nbb_configure(nbb_fractal *F, uint32_t strategy, uint32_t tile_level)
     if (strategy == NBB_STRATEGY_TILED_BOX) {
         blob_free(&F->dedge);
         F->use_edges = false;
+        F->use_matrix = false;
         F->edge = EdgePlan();
         return NBB_OK;
     }
@@ -785,6 +843,7 @@ nbb_status nbb_autotune(nbb_fractal *F, uint8_t *a, uint8_t *b, uint64_t len, ui
     };
     std::vector<Cand> cand;
     if (tiled_supported(F->f)) {
+        if (F->mat.ok) cand.push_back({NBB_STRATEGY_TILED, 0, 0});  // the matrix form, at its own level
         std::vector<uint32_t> fit;
         for (uint32_t m = 1; m <= F->f.r; ++m) {
             uint64_t K = 1, S = 1;
@@ -1728,6 +1787,14 @@ nbb_status nbb_step_compact(const nbb_fractal *F, uint8_t *a, uint8_t *b, uint64
             const uint32_t g = steps / L + (i < steps % L ? 1u : 0u);
             hipError_t e = launch_step_temporal(F->tmp, in, out, rule, g, s);
             if (e != hipSuccess) return hip_fail(e, "temporal step launch");
+            std::swap(in, out);
+        }
+    } else if (F->use_matrix) {
+        const MatPlan &p = F->mat;
+        for (uint32_t i = 0; i < steps; ++i) {
+            hipError_t e = launch_step_matrix(F->matp, mat_align_of(p.CB), p.nr, p.nh, p.gpw, in, out, F->f.cells, rule,
+                                              nullptr, F->cu_count, s);
+            if (e != hipSuccess) return hip_fail(e, "matrix step launch");
             std::swap(in, out);
         }
     } else if (F->use_edges) {

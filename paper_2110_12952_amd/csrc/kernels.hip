@@ -15,6 +15,7 @@
 
 #include "device_common.hpp"
 #include "edges_launch.hpp"
+#include "matrix_launch.hpp"
 #include "tiled_launch.hpp"
 
 namespace nbb {
@@ -1147,6 +1148,26 @@ hipError_t launch_step_edges(const EdgeParams &E0, uint32_t BS, uint32_t nsrc, c
     if (rec) NBB_EDGES_GO(true);
     NBB_EDGES_GO(false);
 #undef NBB_EDGES_GO
+}
+hipError_t launch_step_matrix(const MatParams &E0, uint32_t al, uint32_t nr, uint32_t nh, uint32_t gpw,
+                              const uint8_t *in, uint8_t *out, uint64_t limit, uint32_t rule, const uint32_t *rec,
+                              int cu_count, hipStream_t st) {
+    MatParams E = E0;
+    E.limit = limit;
+    const bool life = rule == kRuleB3S23;
+#define NBB_MAT_GO(B, R)                                                                                     \
+    do {                                                                                                      \
+        if (al == 16) return launch_matrix_inst<B, R, 16>(E, nr, nh, gpw, in, out, rule, rec, cu_count, st);  \
+        if (al == 4) return launch_matrix_inst<B, R, 4>(E, nr, nh, gpw, in, out, rule, rec, cu_count, st);    \
+        return launch_matrix_inst<B, R, 1>(E, nr, nh, gpw, in, out, rule, rec, cu_count, st);                 \
+    } while (0)
+    if (rec) {
+        if (life) NBB_MAT_GO(true, 0);
+        NBB_MAT_GO(true, 1);
+    }
+    if (life) NBB_MAT_GO(false, 0);
+    NBB_MAT_GO(false, 1);
+#undef NBB_MAT_GO
 }
 hipError_t launch_step_tiled(const MapParams &P, const TileParams &T, const uint8_t *in, uint8_t *out,
                              uint32_t rule, int cu_count, hipStream_t st) {

@@ -47,6 +47,12 @@ hipError_t launch_step_tiled(const MapParams &P, const TileParams &T, const uint
 // `in` the step may read (the state's k^r, or the arena's length).
 hipError_t launch_step_edges(const EdgeParams &E, uint32_t BS, uint32_t nsrc, const uint8_t *in, uint8_t *out,
                              uint64_t limit, uint32_t rule, const uint32_t *rec, int cu_count, hipStream_t st);
+// The tiled step on the matrix cores (matrix.hpp) for a plan with `al`-aligned
+// blocks (1, 4 or 16), nr record results, nh halo operands and gpw groups per
+// wavefront; rec and limit as above, four words per batch tile.
+hipError_t launch_step_matrix(const MatParams &E, uint32_t al, uint32_t nr, uint32_t nh, uint32_t gpw,
+                              const uint8_t *in, uint8_t *out, uint64_t limit, uint32_t rule, const uint32_t *rec,
+                              int cu_count, hipStream_t st);
 // The tiled step over the tiles of a batch (tables from launch_batch_tiles,
 // T.ntiles = batch tiles, T.nbr = the batch neighbour table).
 hipError_t launch_step_tiled_batch(const TileParams &T, const uint32_t *rec, const uint8_t *arena_in,

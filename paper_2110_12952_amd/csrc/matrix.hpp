@@ -1,0 +1,345 @@
+// The compact step on the matrix cores (k_step_matrix) and its launchers.
+// Included by matrix_inst.hip, which is compiled once per (BATCH, RULE, AL).
+//
+// Section 3's stencil procedure on the blocked approach, for compact storage,
+// with the neighbour counts of a level-q block (CB consecutive compact cells,
+// 16 to 64 of them) as a contraction of the block's bytes with a constant
+// matrix.  A wavefront holds 64 / L blocks (a group), L lanes per block, lane
+// `sub` the 16 cells from min(16 sub, CB - 16) (the last lane's cells overlap
+// the lane's before where CB is no multiple of 16: both compute and store the
+// same bytes, so that every load and store is a whole 16 bytes inside the
+// block).  A lane's 16 bytes are loaded as they lie and are its share of the
+// B operand of v_mfma_i32_16x16x64_i8 (column = lane % 16, products of quarter
+// lane / 16); the operand A is block-diagonal over the blocks that share a
+// column.  Row 4 g + i of result t holds the counts of cells 8 t + i (weight
+// 1) and 8 t + 4 + i (weight 16) of the lanes of quarter g, so a lane
+// receives the counts of its own 16 cells, eight neighbours at most in each
+// nibble, in the order of its own bytes: no cross-lane move, no unpacking into
+// rows and no packing back.
+//
+// Per tile a work-group
+//   1. publishes the record of every block (the cells its neighbours need, as
+//      bytes; a contraction with 0/1 rows picks them) in LDS, own blocks and
+//      the blocks of the eight neighbour tiles that a block of the tile reads
+//      (zeros where a neighbour tile does not exist: their loads are out of
+//      the buffer's range);
+//   2. reads, per lane, 4 NH record dwords of the neighbouring blocks
+//      (addresses from the plan), which are the B operand of the halo's
+//      contraction, adds both, applies the rule (v_perm tables on four counts
+//      per dword) and stores the lane's 16 next states.
+// Work-groups are persistent over XCD-contiguous tile ranges; the next tile's
+// loads are issued before the barrier of the current one, the records are
+// double-buffered (one barrier per tile), and lanes without a block load and
+// store out of the buffers' range (dropped by the hardware), so that no
+// memory operation sits behind a branch.
+//
+// BATCH: tiles of many instances of one plan in an arena: batch tile g is
+// local tile rec[4g+1] of the state of rec[4g+2] cells at byte 16 rec[4g].  An
+// instance of a lower level than the tile (its cells are the first copy of
+// that level in a tile) is one tile without neighbours whose blocks past the
+// last cell load as zeros and are not stored.
+// RULE: 0 = B3/S23, 1 = any rule (tables, or bit extract where an entry at
+// eight neighbours is set).
+// AL: alignment of the blocks in a state: 16 or 4 bytes, or 1 (loads then
+// take five aligned dwords and v_alignbyte: measured 103 to 106 us for a copy
+// of 282 MB in this layout at 27 and 49 bytes per block against 111 to 116
+// with unaligned 16-byte loads and 99 for aligned blocks).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+#include <atomic>
+
+#include "device_common.hpp"
+#include "plan.hpp"
+
+namespace nbb {
+
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// A voffset beyond every state (k^r stays below it for every fractal the
+// form takes): loads there return 0 and stores are dropped, since no resource
+// covers it.
+constexpr uint32_t kNowhere = 0xFFFFFE00u;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t mat_rsrc(const uint8_t *base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(base), 0, int(bytes), 0x00020000);
+}
+
+template <int AL>
+struct MatRaw {
+    u32x4 v;
+    uint32_t hi;  // the fifth dword (AL 1)
+};
+template <int AL>
+__device__ __forceinline__ MatRaw<AL> mat_load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    MatRaw<AL> m;
+    m.hi = 0;
+    if (AL == 1) {
+        const uint32_t s = off & ~3u;
+        m.v = __builtin_amdgcn_raw_buffer_load_b128(r, s, 0, 0);
+        m.hi = __builtin_amdgcn_raw_buffer_load_b32(r, s + 16, 0, 0);
+    } else {
+        m.v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+    }
+    return m;
+}
+// The 16 bytes at byte off % 4 of the loaded dwords.
+template <int AL>
+__device__ __forceinline__ u32x4 mat_align(const MatRaw<AL> &m, uint32_t off) {
+    if (AL != 1) return m.v;
+    u32x4 x;
+    x[0] = alignbyte(m.v[1], m.v[0], off);
+    x[1] = alignbyte(m.v[2], m.v[1], off);
+    x[2] = alignbyte(m.v[3], m.v[2], off);
+    x[3] = alignbyte(m.hi, m.v[3], off);
+    return x;
+}
+
+__device__ __forceinline__ i32x4 mat_mul(u32x4 a, u32x4 b, i32x4 c) {
+    return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), c, 0, 0, 0);
+}
+// Four results of at most 255 each as the bytes of a dword.
+__device__ __forceinline__ uint32_t mat_bytes(i32x4 d) {
+    return ((uint32_t(d[3]) << 8 | uint32_t(d[2])) << 8 | uint32_t(d[1])) << 8 | uint32_t(d[0]);
+}
+
+// Next states of four cells: n their live-neighbour counts, o the cells.
+template <int RULE>
+__device__ __forceinline__ uint32_t mat_rule(uint32_t n, uint32_t o, uint32_t rule, const RuleTables &RT, bool tables) {
+    if (RULE == 0) return __builtin_amdgcn_perm(0u, 0x01000000u, n | o);
+    if (tables) {  // uniform
+        const uint32_t born = __builtin_amdgcn_perm(RT.born_hi, RT.born_lo, n);
+        const uint32_t surv = __builtin_amdgcn_perm(RT.surv_hi, RT.surv_lo, n);
+        const uint32_t smask = __builtin_amdgcn_perm(0u, 0x0000FF00u, o);  // 0xFF where alive
+        return (surv & smask) | (born & ~smask);
+    }
+    const uint32_t I = n + (o << 4);  // v_bfe takes its offset from the low 5 bits
+    uint32_t v = __builtin_amdgcn_ubfe(rule, I, 1);
+#pragma unroll
+    for (int c = 1; c < 4; ++c) v |= __builtin_amdgcn_ubfe(rule, I >> (8 * c), 1) << (8 * c);
+    return v;
+}
+
+template <int AL, int NR, int NH, int GPW, bool BATCH, int RULE>
+__global__ __launch_bounds__(64 * kMatMaxWaves) void k_step_matrix(MatParams E, const uint8_t *__restrict__ in,
+                                                                   uint8_t *__restrict__ out, uint32_t rule,
+                                                                   const uint32_t *__restrict__ rec) {
+    extern __shared__ __align__(16) uint8_t lds_m[];
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
+    const XcdRange R64 = xcd_range(blockIdx.x, gridDim.x, E.ntiles);
+    const uint32_t first = uint32_t(R64.first), end = uint32_t(R64.end), step = uint32_t(R64.step);
+    if (first >= end) return;
+    // the work-group's tiles are first + i step; loads past the last read it again
+    const uint32_t last = first + (end - 1 - first) / step * step;
+    auto tile = [&](uint32_t i) -> uint32_t { return min(first + i * step, last); };
+
+    // This lane's share of its wavefront's groups: quarter = lane / 16 holds
+    // lane `sub` of block in / of the group's 64 / L blocks.
+    const uint32_t L = E.lanes, quarter = lane >> 4, col = lane & 15;
+    const uint32_t sub = quarter & (L - 1), bpg = 64 / L;
+    const uint32_t slot = (L == 4 ? 0u : (L == 2 ? quarter >> 1 : quarter)) * 16 + col;
+    const uint32_t coff = min(16 * sub, E.CB - 16);
+    const bool edge = (rule >> 31) != 0;
+    const uint8_t *A8 = reinterpret_cast<const uint8_t *>(E.A) + 16 * lane;
+    auto operand = [&](uint32_t off) -> u32x4 { return *reinterpret_cast<const u32x4 *>(A8 + off); };
+    u32x4 Aself[2], Ahalo[NH][2], Arec[NR];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) Aself[t] = operand(mat_self_off(NH, edge, t));
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) Ahalo[h][t] = operand(mat_halo_off(NH, edge, h, t));
+#pragma unroll
+    for (int t = 0; t < NR; ++t) Arec[t] = operand(mat_rec_off(NH, t));
+    const uint32_t rstride = 4 * L * E.nrecs;  // from one record result's dwords to the next's
+    uint32_t voff[GPW], waddr[GPW], raddr[GPW][2 * NH];
+#pragma unroll
+    for (int u = 0; u < GPW; ++u) {
+        const uint32_t g = wave * GPW + u, b = g * bpg + slot;
+        const bool ok = b < E.nblk;
+        voff[u] = ok ? b * E.CB + coff : kNowhere;
+        waddr[u] = 4 * (sub * E.nrecs + (ok ? b : E.nrecs - 1));
+#pragma unroll
+        for (int d = 0; d < 2 * NH; ++d) raddr[u][d] = E.raddr[(g * 64 + lane) * (2 * NH) + d];
+    }
+    const uint32_t h = wave * bpg + slot;
+    const bool hlane = h < E.nhalo;
+    const uint32_t hitem = E.halo[hlane ? h : 0u];
+    const uint32_t hoff = (hitem & 0x1FFFFFFFu) * E.CB + coff, hdir = hitem >> 29;
+    uint32_t hwaddr = 4 * (sub * E.nrecs + (hlane ? E.nblk + h : E.nrecs - 1));
+    if (tid < 2) *reinterpret_cast<uint32_t *>(lds_m + tid * E.buf_bytes + 4 * (L * NR * E.nrecs)) = 0;
+
+    const RuleTables RT = rule_tables(rule);
+    const bool tables = RT.perm || edge;
+
+    // A tile's loads.
+    struct Pending {
+        MatRaw<AL> raw[GPW], hraw;
+        uint32_t hpos;    // halo block's offset in its state
+        uint32_t phase;   // the tile's first byte in its dword
+        uint8_t *dst;     // the tile's output
+        uint32_t bytes;   // and its length
+    } P;
+    auto prefetch = [&](uint32_t t, uint32_t nt) {
+        uint64_t base = 0;
+        uint32_t local = t;
+        uint32_t cells = 0xFFFFFFFFu;
+        if (BATCH) {
+            base = uint64_t(rec[4 * uint64_t(t)]) << 4;
+            local = rec[4 * uint64_t(t) + 1];
+            cells = rec[4 * uint64_t(t) + 2];
+        }
+        const uint8_t *src = in + base;
+        const uint64_t room = (E.limit - base + 3) & ~uint64_t(3);  // whole dwords
+        const uint32_t lim = room > kNowhere ? kNowhere : uint32_t(room);
+        const uint32_t toff = local * E.K, tal = toff & ~3u;
+        P.phase = toff & 3;
+        P.dst = out + base + toff;
+        P.bytes = BATCH ? min(E.K, cells) : E.K;
+        const __amdgpu_buffer_rsrc_t own = mat_rsrc(src + tal, lim - tal), all = mat_rsrc(src, lim);
+#pragma unroll
+        for (int u = 0; u < GPW; ++u) {
+            const uint32_t off = BATCH && voff[u] >= P.bytes ? kNowhere : voff[u];
+            P.raw[u] = mat_load<AL>(own, AL == 1 ? off + P.phase : off);
+        }
+        P.hpos = hlane && nt != kOutside ? nt * E.K + hoff : kNowhere;
+        P.hraw = mat_load<AL>(all, P.hpos);
+    };
+    auto entry = [&](uint32_t t) -> uint32_t { return E.nbr[uint64_t(t) * 8 + hdir]; };
+
+    uint32_t nt = entry(tile(1));
+    prefetch(tile(0), entry(tile(0)));
+    // As many stores after the first tile's loads as after any later tile's
+    // (into an empty range, so dropped): the compiler then counts the same
+    // outstanding operations on both ways into the loop and waits for the
+    // loads alone, not for the stores behind them.
+#pragma unroll
+    for (int u = 0; u < GPW; ++u)
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{0, 0, 0, 0}, mat_rsrc(P.dst, 0), voff[u], 0, 0);
+    int32_t delta = int32_t(E.buf_bytes);  // to the other record buffer
+    for (uint32_t i = 0;; ++i) {
+        // step 1: the records
+        u32x4 x[GPW];
+        const i32x4 zero = {0, 0, 0, 0};
+#pragma unroll
+        for (int u = 0; u < GPW; ++u) {
+            x[u] = mat_align<AL>(P.raw[u], AL == 1 ? voff[u] + P.phase : 0u);
+#pragma unroll
+            for (int t = 0; t < NR; ++t)
+                *reinterpret_cast<uint32_t *>(lds_m + waddr[u] + t * rstride) = mat_bytes(mat_mul(Arec[t], x[u], zero));
+        }
+        const u32x4 hx = mat_align<AL>(P.hraw, P.hpos);
+#pragma unroll
+        for (int t = 0; t < NR; ++t)
+            *reinterpret_cast<uint32_t *>(lds_m + hwaddr + t * rstride) = mat_bytes(mat_mul(Arec[t], hx, zero));
+        const __amdgpu_buffer_rsrc_t gout = mat_rsrc(P.dst, P.bytes);
+        // the next tile's loads, the neighbour tile of the one after it
+        const uint32_t nt1 = nt;
+        nt = entry(tile(i + 2));
+        prefetch(tile(i + 1), nt1);
+        __syncthreads();
+        // step 2: counts and rule
+#pragma unroll
+        for (int u = 0; u < GPW; ++u) {
+            i32x4 d0 = mat_mul(Aself[0], x[u], zero), d1 = mat_mul(Aself[1], x[u], zero);
+#pragma unroll
+            for (int hh = 0; hh < NH; ++hh) {
+                u32x4 r;
+#pragma unroll
+                for (int d = 0; d < 2; ++d) {
+                    const uint32_t a = raddr[u][2 * hh + d];
+                    r[2 * d] = *reinterpret_cast<const uint32_t *>(lds_m + (a & 0xFFFFu));
+                    r[2 * d + 1] = *reinterpret_cast<const uint32_t *>(lds_m + (a >> 16));
+                }
+                d0 = mat_mul(Ahalo[hh][0], r, d0);
+                d1 = mat_mul(Ahalo[hh][1], r, d1);
+            }
+            const uint32_t c0 = mat_bytes(d0), c1 = mat_bytes(d1);
+            u32x4 w;
+            w[0] = mat_rule<RULE>(c0 & 0x0F0F0F0Fu, x[u][0], rule, RT, tables);
+            w[1] = mat_rule<RULE>((c0 >> 4) & 0x0F0F0F0Fu, x[u][1], rule, RT, tables);
+            w[2] = mat_rule<RULE>(c1 & 0x0F0F0F0Fu, x[u][2], rule, RT, tables);
+            w[3] = mat_rule<RULE>((c1 >> 4) & 0x0F0F0F0Fu, x[u][3], rule, RT, tables);
+            __builtin_amdgcn_raw_buffer_store_b128(w, gout, voff[u], 0, 0);
+        }
+        if (first + (i + 1) * step >= end) break;
+        // the other record buffer: its reads ended before the barrier above
+#pragma unroll
+        for (int u = 0; u < GPW; ++u) {
+            waddr[u] += delta;
+#pragma unroll
+            for (int d = 0; d < 2 * NH; ++d) raddr[u][d] += uint32_t(delta) * 0x10001u;
+        }
+        hwaddr += delta;
+        delta = -delta;
+    }
+}
+
+// Persistent launch: as many work-groups as can be resident at once, capped
+// by the tiles.
+template <int AL, int NR, int NH, int GPW, bool BATCH, int RULE>
+static hipError_t launch_matrix_t(const MatParams &E, const uint8_t *in, uint8_t *out, uint32_t rule,
+                                  const uint32_t *rec, int cu_count, hipStream_t st) {
+    const uint32_t lds = 2 * E.buf_bytes, threads = 64 * E.waves;
+    static std::atomic<uint64_t> cached{0};  // lds << 32 | threads << 8 | work-groups per CU
+    int per_cu = 0;
+    const uint64_t key = uint64_t(lds) << 32 | threads << 8;
+    const uint64_t c = cached.load(std::memory_order_relaxed);
+    if ((c & ~uint64_t(0xFF)) == key && (c & 0xFF)) {
+        per_cu = int(c & 0xFF);
+    } else {
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu, k_step_matrix<AL, NR, NH, GPW, BATCH, RULE>, int(threads), lds);
+        if (e != hipSuccess) return e;
+        per_cu = std::max(1, std::min(per_cu, 255));
+        cached.store(key | uint64_t(per_cu), std::memory_order_relaxed);
+    }
+    // Work-groups per CU: the fewest tile rounds times work-groups (the tiles
+    // the busiest CU works through) that leaves six wavefronts on a CU, fewer
+    // work-groups first.  Triangle r16 (6,561 tiles, two wavefronts each) with
+    // 2 / 3 / 4 / 6 / 8: 17.6 / 15.9 / 15.8 / 17.4 / 17.0 us; Vicsek r10
+    // (3,125 tiles) 7.2 / 6.5 / 6.7 / 7.5 / 8.5; H r10 with 1 / 2: 115.6 / 117.9.
+    uint64_t best = 0;
+    int use = per_cu;
+    for (int c = 1; c <= per_cu; ++c) {
+        if (c < per_cu && uint32_t(c) * E.waves < 6) continue;
+        const uint64_t wgs = uint64_t(c) * cu_count, work = (E.ntiles + wgs - 1) / wgs * c;
+        if (best && work >= best) continue;
+        best = work;
+        use = c;
+    }
+    const uint64_t grid = std::min<uint64_t>(uint64_t(use) * cu_count, E.ntiles);
+    if (!grid) return hipSuccess;
+    hipLaunchKernelGGL((k_step_matrix<AL, NR, NH, GPW, BATCH, RULE>), dim3(uint32_t(grid)), dim3(threads), lds, st, E,
+                       in, out, rule, rec);
+    return hipGetLastError();
+}
+
+// The instantiation for a plan: exact operand counts (the kernel's operand
+// offsets follow them).
+template <int AL, bool BATCH, int RULE>
+static hipError_t launch_matrix_shape(const MatParams &E, uint32_t nr, uint32_t nh, uint32_t gpw, const uint8_t *in,
+                                      uint8_t *out, uint32_t rule, const uint32_t *rec, int cu_count, hipStream_t st) {
+#define NBB_MAT_CASE(R, H, G)           \
+    if (nr == R && nh == H && gpw == G) \
+    return launch_matrix_t<AL, R, H, G, BATCH, RULE>(E, in, out, rule, rec, cu_count, st)
+#define NBB_MAT_CASES(R, H)  \
+    NBB_MAT_CASE(R, H, 1);   \
+    NBB_MAT_CASE(R, H, 2);   \
+    NBB_MAT_CASE(R, H, 4)
+    NBB_MAT_CASES(1, 1);
+    NBB_MAT_CASES(2, 1);
+    NBB_MAT_CASES(3, 1);
+    NBB_MAT_CASES(1, 2);
+    NBB_MAT_CASES(2, 2);
+    NBB_MAT_CASES(3, 2);
+#undef NBB_MAT_CASES
+#undef NBB_MAT_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace nbb

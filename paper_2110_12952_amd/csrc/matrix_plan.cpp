@@ -1,0 +1,340 @@
+// Host-side plan of the matrix-core form of the tiled step.  See MatParams in
+// params.hpp for the scheme.
+#include <algorithm>
+#include <map>
+
+#include "plan.hpp"
+
+namespace nbb {
+
+namespace {
+
+uint64_t ipow(uint64_t b, uint32_t e) {
+    uint64_t p = 1;
+    while (e--) p *= b;
+    return p;
+}
+
+const int kDirX[8] = {-1, 0, 1, -1, 1, -1, 0, 1};  // as the neighbour tables: row-major without the centre
+const int kDirY[8] = {-1, -1, -1, 0, 0, 1, 1, 1};
+
+// What a block of level q needs from its neighbours and how its record holds
+// what they need from it.
+struct BlockShape {
+    uint32_t q = 0, CB = 0, BS = 0, lanes = 0, nr = 0, nh = 0;
+    std::vector<int64_t> x, y;               // the block's cells
+    std::vector<std::vector<uint32_t>> need;  // per direction: cells of that neighbour next to one of ours
+    std::vector<int32_t> rec;                // lanes * nr * 4 record bytes: cell or -1
+    std::vector<std::pair<uint32_t, uint32_t>> reads;  // (direction, record dword)
+};
+
+// The record dwords that hold all of `cells`, first found first.
+void reads_of(const std::vector<int32_t> &rec, uint32_t dir, const std::vector<uint32_t> &cells,
+              std::vector<std::pair<uint32_t, uint32_t>> *reads) {
+    std::vector<uint32_t> left = cells;
+    while (!left.empty()) {
+        // the dword with the most of what is left
+        size_t best = 0, most = 0;
+        for (size_t d = 0; d < rec.size() / 4; ++d) {
+            size_t n = 0;
+            for (size_t b = 0; b < 4; ++b)
+                n += rec[4 * d + b] >= 0 && std::count(left.begin(), left.end(), uint32_t(rec[4 * d + b]));
+            if (n > most) {
+                most = n;
+                best = d;
+            }
+        }
+        reads->push_back({dir, uint32_t(best)});
+        std::vector<uint32_t> rest;
+        for (uint32_t c : left) {
+            bool in = false;
+            for (size_t b = 0; b < 4; ++b) in |= rec[4 * best + b] == int32_t(c);
+            if (!in) rest.push_back(c);
+        }
+        left.swap(rest);
+    }
+}
+
+bool block_shape(const Fractal &f, uint32_t q, BlockShape *s) {
+    s->q = q;
+    s->CB = uint32_t(ipow(f.k, q));
+    s->BS = uint32_t(ipow(f.s, q));
+    s->lanes = s->CB <= 16 ? 1 : (s->CB <= 32 ? 2 : 4);
+    s->x.resize(s->CB);
+    s->y.resize(s->CB);
+    for (uint32_t c = 0; c < s->CB; ++c) lambda_levels(f, q, c, &s->x[c], &s->y[c]);
+    s->need.assign(8, {});
+    size_t total = 0;
+    for (uint32_t d = 0; d < 8; ++d)
+        for (uint32_t e = 0; e < s->CB; ++e) {
+            const int64_t ex = s->x[e] + kDirX[d] * int64_t(s->BS), ey = s->y[e] + kDirY[d] * int64_t(s->BS);
+            for (uint32_t c = 0; c < s->CB; ++c)
+                if (std::abs(ex - s->x[c]) <= 1 && std::abs(ey - s->y[c]) <= 1) {
+                    s->need[d].push_back(e);
+                    ++total;
+                    break;
+                }
+        }
+    // Two ways to lay the record out, the better kept: every needed cell once
+    // (few cells in all: fewer record dwords), or each direction's cells in
+    // dwords of their own (fewer reads per block).
+    bool found = false;
+    for (int way = 0; way < 2; ++way) {
+        std::vector<int32_t> rec;
+        std::vector<uint32_t> order = {3, 4, 1, 6, 0, 2, 5, 7};
+        std::stable_sort(order.begin(), order.end(),
+                         [&](uint32_t a, uint32_t b) { return s->need[a].size() > s->need[b].size(); });
+        for (uint32_t d : order) {
+            std::vector<uint32_t> fresh;
+            std::vector<uint32_t> missing;
+            for (uint32_t e : s->need[d])
+                if (std::find(rec.begin(), rec.end(), int32_t(e)) == rec.end()) missing.push_back(e);
+            // a direction whose cells are already in at most one more dword
+            // than a run of its own would take reads those
+            fresh = way == 0 || missing.empty() || s->need[d].size() == 1 ? missing : s->need[d];
+            for (uint32_t e : fresh) rec.push_back(int32_t(e));
+            if (way == 1)
+                while (rec.size() % 4) rec.push_back(-1);
+        }
+        while (rec.size() % 4) rec.push_back(-1);
+        std::vector<std::pair<uint32_t, uint32_t>> reads;
+        for (uint32_t d = 0; d < 8; ++d) reads_of(rec, d, s->need[d], &reads);
+        const uint32_t nr = std::max<uint32_t>(1, uint32_t((rec.size() / 4 + s->lanes - 1) / s->lanes));
+        const uint32_t nh = std::max<uint32_t>(1, uint32_t((reads.size() + 4 * s->lanes - 1) / (4 * s->lanes)));
+        if (nr > 3 || nh > 2) continue;
+        if (found && (nh > s->nh || (nh == s->nh && nr >= s->nr))) continue;
+        found = true;
+        s->nr = nr;
+        s->nh = nh;
+        s->rec = rec;
+        s->rec.resize(size_t(nr) * s->lanes * 4, -1);
+        s->reads = reads;
+    }
+    return found;
+}
+
+// The largest block level with 16 to 64 cells whose ring fits.
+bool pick_shape(const Fractal &f, BlockShape *s) {
+    if (!tiled_supported(f) || f.k < 2) return false;
+    uint32_t q = 0;
+    while (q < f.r && ipow(f.k, q + 1) <= 64) ++q;
+    for (; q >= 1 && ipow(f.k, q) >= 16; --q) {
+        BlockShape t;
+        if (block_shape(f, q, &t)) {
+            *s = std::move(t);
+            return true;
+        }
+    }
+    return false;
+}
+
+}  // namespace
+
+static bool build_mat_shape(const Fractal &f, const BlockShape &s, uint32_t m, uint64_t tiles, uint32_t cus,
+                            MatPlan *p, std::string *msg, bool with_nbr) {
+    *p = MatPlan();
+    if (m < s.q || m > f.r) {
+        *msg = "the matrix form needs q <= m <= r";
+        return false;
+    }
+    const uint32_t bpg = 64 / s.lanes;
+    const uint64_t nb = ipow(f.k, m - s.q);
+    if (nb > uint64_t(4) * kMatMaxWaves * bpg) {
+        *msg = "more groups than a work-group takes";
+        return false;
+    }
+    p->m = m;
+    p->q = s.q;
+    p->K = uint32_t(ipow(f.k, m));
+    p->CB = s.CB;
+    p->lanes = s.lanes;
+    p->nblk = uint32_t(nb);
+    p->nr = s.nr;
+    p->nh = s.nh;
+    p->groups = (p->nblk + bpg - 1) / bpg;
+    p->ntiles = ipow(f.k, f.r - m);
+    const int64_t G = int64_t(ipow(f.s, m - s.q));
+    // the neighbouring record of every read of every block: an own block, a
+    // halo block (numbered as first met), or none
+    std::map<std::pair<int64_t, int64_t>, uint32_t> halo;
+    const uint32_t none = 0xFFFFFFFFu;
+    std::vector<uint32_t> source(size_t(p->nblk) * s.reads.size(), none);
+    for (uint32_t b = 0; b < p->nblk; ++b) {
+        int64_t X, Y;
+        lambda_levels(f, m - s.q, b, &X, &Y);
+        for (size_t i = 0; i < s.reads.size(); ++i) {
+            const uint32_t d = s.reads[i].first;
+            const int64_t nx = X + kDirX[d], ny = Y + kDirY[d];
+            uint32_t &src = source[b * s.reads.size() + i];
+            if (nx >= 0 && ny >= 0 && nx < G && ny < G) {
+                const int64_t v = nu_levels(f, m - s.q, nx, ny);
+                if (v >= 0) src = uint32_t(v);
+                continue;
+            }
+            const int tx = nx < 0 ? -1 : (nx >= G ? 1 : 0), ty = ny < 0 ? -1 : (ny >= G ? 1 : 0);
+            const int64_t v = nu_levels(f, m - s.q, nx - tx * G, ny - ty * G);
+            if (v < 0) continue;
+            const auto it = halo.find({nx, ny});
+            if (it != halo.end()) {
+                src = it->second;
+                continue;
+            }
+            uint32_t dir = 0;
+            while (kDirX[dir] != tx || kDirY[dir] != ty) ++dir;
+            src = p->nblk + uint32_t(p->halo.size());
+            halo[{nx, ny}] = src;
+            p->halo.push_back(dir << 29 | uint32_t(v));
+        }
+    }
+    p->nhalo = uint32_t(p->halo.size());
+    if (p->halo.empty()) p->halo.push_back(0);
+    p->nrecs = p->nblk + p->nhalo + 1;
+    const uint64_t words = uint64_t(s.lanes) * s.nr * p->nrecs + 1;  // and one dword of zeros
+    p->buf_bytes = uint32_t((words * 4 + 15) & ~uint64_t(15));
+    if (p->buf_bytes > 32 * 1024 - 16) {  // two buffers, 16-bit offsets
+        *msg = "records beyond 32 KiB";
+        return false;
+    }
+    // Groups per wavefront: the most of 4, 2, 1 that leaves two wavefronts
+    // per work-group and, with the tiles at hand, six per CU (a wavefront
+    // with more groups has more loads in flight and does the tile's uniform
+    // work less often: triangle r16 at level 8, 1 / 2 / 4 groups per
+    // wavefront 18.3 / 16.2 / 15.8 us; carpet r7, two tiles per CU, 3.70 /
+    // 3.85 / 4.66); each wavefront also takes at most one group of halo blocks.
+    const uint32_t hgroups = (p->nhalo + bpg - 1) / bpg;
+    const uint64_t per_cu = (tiles + cus - 1) / cus;
+    for (uint32_t g : {4u, 2u, 1u}) {
+        const uint32_t w = std::max((p->groups + g - 1) / g, hgroups);
+        if (w > kMatMaxWaves) break;
+        p->gpw = g;
+        p->waves = w;
+        if (w >= 2 && w * per_cu >= 6) break;
+    }
+    if (!p->gpw) {
+        *msg = "more groups than a work-group takes";
+        return false;
+    }
+    // record reads: read i is dword i % 4 of lane (i / 4) % lanes, halo operand i / (4 lanes)
+    const uint32_t zero = uint32_t((words - 1) * 4);
+    p->raddr.assign(size_t(p->waves) * p->gpw * 64 * 2 * p->nh, zero | zero << 16);
+    for (uint32_t b = 0; b < p->nblk; ++b)
+        for (size_t i = 0; i < s.reads.size(); ++i) {
+            const uint32_t src = source[b * s.reads.size() + i];
+            if (src == none) continue;
+            const uint32_t h = uint32_t(i) / (4 * s.lanes), sub = uint32_t(i) / 4 % s.lanes, d = uint32_t(i) % 4;
+            const uint32_t in = b % bpg;  // block of the group: 16 columns by 4 / lanes
+            const uint32_t lane = (in / 16 * s.lanes + sub) * 16 + in % 16;
+            uint32_t &w = p->raddr[((size_t(b / bpg) * 64 + lane) * 2 * p->nh) + 2 * h + d / 2];
+            const uint32_t addr = 4 * (s.reads[i].second * p->nrecs + src);
+            w = d % 2 ? (w & 0xFFFFu) | addr << 16 : (w & 0xFFFF0000u) | addr;
+        }
+    // operands: lane l of an operand holds row l % 16, products 16 (l / 16) ..
+    const uint32_t nh = s.nh;
+    p->A.assign(size_t(1024) * (2 * (2 + 2 * nh) + s.nr), 0);
+    auto first_cell = [&](uint32_t sub) { return std::min(16 * sub, s.CB - 16); };
+    auto put = [&](uint32_t off, uint32_t row, uint32_t quarter, uint32_t byte, int w) {
+        p->A[off + (quarter * 16 + row) * 16 + byte] = int8_t(p->A[off + (quarter * 16 + row) * 16 + byte] + w);
+    };
+    for (int edge = 0; edge < 2; ++edge) {
+        auto adjacent = [&](int64_t dx, int64_t dy) {
+            dx = std::abs(dx);
+            dy = std::abs(dy);
+            return edge ? dx + dy == 1 : (dx <= 1 && dy <= 1 && dx + dy != 0);
+        };
+        for (uint32_t g = 0; g < 4; ++g)
+            for (uint32_t row = 4 * g; row < 4 * g + 4; ++row)
+                for (uint32_t t = 0; t < 2; ++t)
+                    for (uint32_t hi = 0; hi < 2; ++hi) {
+                        const uint32_t c = first_cell(g % s.lanes) + 8 * t + 4 * hi + row % 4;
+                        const int w = hi ? 16 : 1;
+                        for (uint32_t sub = 0; sub < s.lanes; ++sub) {
+                            const uint32_t quarter = g / s.lanes * s.lanes + sub;
+                            for (uint32_t j = 0; j < 16; ++j) {
+                                const uint32_t e = first_cell(sub) + j;
+                                if (e < 16 * sub) continue;  // held by an earlier lane
+                                if (adjacent(s.x[e] - s.x[c], s.y[e] - s.y[c]))
+                                    put(mat_self_off(nh, edge, t), row, quarter, j, w);
+                            }
+                        }
+                        std::vector<std::pair<uint32_t, int32_t>> seen;
+                        for (size_t i = 0; i < s.reads.size(); ++i)
+                            for (uint32_t b = 0; b < 4; ++b) {
+                                const uint32_t dir = s.reads[i].first;
+                                const int32_t e = s.rec[4 * s.reads[i].second + b];
+                                if (e < 0 || !std::count(s.need[dir].begin(), s.need[dir].end(), uint32_t(e))) continue;
+                                const std::pair<uint32_t, int32_t> id{dir, e};
+                                if (std::count(seen.begin(), seen.end(), id)) continue;
+                                seen.push_back(id);
+                                const int64_t ex = s.x[e] + kDirX[dir] * int64_t(s.BS);
+                                const int64_t ey = s.y[e] + kDirY[dir] * int64_t(s.BS);
+                                if (!adjacent(ex - s.x[c], ey - s.y[c])) continue;
+                                const uint32_t h = uint32_t(i) / (4 * s.lanes), sub = uint32_t(i) / 4 % s.lanes;
+                                put(mat_halo_off(nh, edge, h, t), row, g / s.lanes * s.lanes + sub,
+                                    4 * (uint32_t(i) % 4) + b, w);
+                            }
+                    }
+    }
+    // record result t: lane `sub` of a block gets record dword t lanes + sub
+    for (uint32_t g = 0; g < 4; ++g)
+        for (uint32_t i = 0; i < 4; ++i)
+            for (uint32_t t = 0; t < s.nr; ++t) {
+                const int32_t e = s.rec[4 * (t * s.lanes + g % s.lanes) + i];
+                if (e < 0) continue;
+                const uint32_t sub = uint32_t(e) / 16;  // its first holder
+                put(mat_rec_off(nh, t), 4 * g + i, g / s.lanes * s.lanes + sub, uint32_t(e) - first_cell(sub), 1);
+            }
+    if (with_nbr) {
+        p->nbr.assign(size_t(p->ntiles) * 8, none);
+        for (uint64_t t = 0; t < p->ntiles; ++t) {
+            int64_t X, Y;
+            lambda_levels(f, f.r - m, t, &X, &Y);
+            for (uint32_t d = 0; d < 8; ++d) {
+                const int64_t v = nu_levels(f, f.r - m, X + kDirX[d], Y + kDirY[d]);
+                if (v >= 0) p->nbr[size_t(t) * 8 + d] = uint32_t(v);
+            }
+        }
+    }
+    p->ok = true;
+    return true;
+}
+
+bool build_mat_plan(const Fractal &f, uint32_t m, uint64_t tiles, uint32_t cus, MatPlan *p, std::string *msg,
+                    bool with_nbr) {
+    BlockShape s;
+    if (!pick_shape(f, &s)) {
+        *msg = "no block level of this fractal fits the matrix form";
+        return false;
+    }
+    return build_mat_shape(f, s, m, tiles ? tiles : m <= f.r ? ipow(f.k, f.r - m) : 0, std::max(cus, 1u), p, msg,
+                           with_nbr);
+}
+
+// The level with the least work on the busiest CU: its tiles times the
+// groups of a tile, a group of halo blocks (loaded and published, no rule and
+// no store) counted half.  Of the measured best levels (triangle r14 and r16:
+// 8, carpet r7: 4, r9: 5, H r9 and r10: 5, Vicsek r10: 5, chandelier r13: 7,
+// each against its neighbours) it picks every one.
+uint32_t auto_mat_level(const Fractal &f, const std::vector<uint32_t> &levels, uint32_t cus) {
+    BlockShape s;
+    if (!pick_shape(f, &s) || levels.empty()) return 0;
+    const uint32_t rmax = *std::max_element(levels.begin(), levels.end());
+    uint32_t best = 0;
+    double best_cost = 0.0;
+    for (uint32_t m = s.q; m <= rmax; ++m) {
+        uint64_t tiles = 0;
+        for (uint32_t r : levels) tiles += r > m ? ipow(f.k, r - m) : 1;
+        MatPlan p;
+        std::string msg;
+        if (!build_mat_shape(f, s, m, tiles, cus, &p, &msg, false)) continue;
+        const uint32_t bpg = 64 / p.lanes;
+        const double cost = double((tiles + cus - 1) / cus) *
+                            (p.waves * p.gpw + 0.5 * p.nhalo / bpg);
+        if (!best || cost < best_cost) {
+            best = m;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+}  // namespace nbb

@@ -146,6 +146,34 @@ struct EdgeCaps {
 constexpr uint32_t edge_rec_stride(uint32_t bpt, uint32_t hpt) { return 256 * (bpt + hpt) + 4; }
 constexpr uint32_t edge_lds_bytes(uint32_t bpt, uint32_t hpt) { return 16 * edge_rec_stride(bpt, hpt); }
 
+// The matrix-core form of the tiled step.  The tile is cut into level-q
+// blocks of CB consecutive compact cells, 16 <= CB <= 64; a block is held by
+// `lanes` (1, 2 or 4) lanes of a wavefront, lane `sub` of a block holding the
+// 16 cells from min(16 sub, CB - 16), so 64 / lanes blocks make a group, one
+// load and one store of 16 bytes per lane.  A group is the B operand of
+// v_mfma_i32_16x16x64_i8 as it is loaded (column = lane % 16, the lane's 16
+// bytes its 16 of the 64 products), and the neighbour count is the
+// contraction with a constant A: rows 4 g + i of result t = cells 8 t + i
+// (weight 1) and 8 t + 4 + i (weight 16) of the lanes of quarter g, so the
+// counts arrive in the lanes that hold the cells, two per byte.
+// The cells around the block come the same way from 4 nh record dwords per
+// lane: block b publishes the cells its neighbours need (lanes x nr dwords,
+// picked by a contraction with 0/1 rows) in LDS, dword rd of record b at
+// 4 (rd nrecs + b).
+struct MatParams {
+    uint32_t K, CB, lanes;   // cells per tile, per block; lanes per block
+    uint32_t nblk, nhalo;    // blocks per tile, blocks of neighbour tiles that are read
+    uint32_t nrecs;          // records: the blocks, the halo blocks, and one never read
+    uint32_t buf_bytes;      // one record buffer (a multiple of 16); LDS holds two
+    uint32_t waves;          // wavefronts per work-group
+    uint32_t ntiles;
+    const int8_t *A;         // 1 KiB operands: Moore self x 2, halo x 2 nh; four-cell the same; records x nr
+    const uint32_t *raddr;   // per group and lane 2 nh dwords: two LDS offsets each
+    const uint32_t *halo;    // per halo block: direction << 29 | block
+    const uint32_t *nbr;     // 8 neighbour tiles per tile (0xFFFFFFFF = none)
+    uint64_t limit;          // bytes of the input that may be read (the state, or the whole arena)
+};
+
 // Temporal blocking (several generations per launch): work-group t holds
 // tile t's square and a ring of depth h as a B x B box (pitch P bytes) in
 // LDS, three times: two state copies and the member mask.

@@ -86,6 +86,41 @@ struct EdgePlan {
 // 2 loads' width, more than 1024 blocks or more than 512 halo items.
 bool build_edge_plan(const Fractal &f, uint32_t m, EdgePlan *p, std::string *msg);
 
+// The matrix-core form of the tiled step (MatParams) at tile level m.
+struct MatPlan {
+    bool ok = false;
+    uint32_t m = 0, q = 0, K = 0, CB = 0, lanes = 0, nblk = 0, nhalo = 0, nrecs = 0;
+    uint32_t nr = 0;    // record results (lanes dwords of a block's record each)
+    uint32_t nh = 0;    // halo operands (4 record dwords per lane each)
+    uint32_t gpw = 0;   // groups per wavefront
+    uint32_t waves = 0; // wavefronts per work-group
+    uint32_t groups = 0;
+    uint32_t buf_bytes = 0;
+    uint64_t ntiles = 0;
+    std::vector<int8_t> A;       // see MatParams
+    std::vector<uint32_t> raddr; // waves * gpw groups
+    std::vector<uint32_t> halo;
+    std::vector<uint32_t> nbr;
+};
+constexpr uint32_t kMatMaxWaves = 8;
+// Byte offsets of the operands in MatPlan::A (edge: the four-cell stencil).
+constexpr uint32_t mat_self_off(uint32_t nh, bool edge, uint32_t t) { return 1024 * ((edge ? 2 + 2 * nh : 0) + t); }
+constexpr uint32_t mat_halo_off(uint32_t nh, bool edge, uint32_t h, uint32_t t) {
+    return 1024 * ((edge ? 2 + 2 * nh : 0) + 2 + 2 * h + t);
+}
+constexpr uint32_t mat_rec_off(uint32_t nh, uint32_t t) { return 1024 * (2 * (2 + 2 * nh) + t); }
+// false (with *msg) where the form does not apply: no block level with 16 to
+// 64 cells, more record dwords around a block than two operands hold, or more
+// groups than a work-group of kMatMaxWaves wavefronts takes.  tiles: those of
+// a launch (0: the fractal's own), over `cus` CUs.  `with_nbr`: also the
+// neighbour table (8 entries per tile).
+bool build_mat_plan(const Fractal &f, uint32_t m, uint64_t tiles, uint32_t cus, MatPlan *p, std::string *msg,
+                    bool with_nbr = true);
+// The tile level the matrix form takes for one launch over instances of the
+// fractal at these levels r (an instance below the tile level is one tile);
+// 0 if the form does not apply.
+uint32_t auto_mat_level(const Fractal &f, const std::vector<uint32_t> &levels, uint32_t cus);
+
 // Several generations per launch (temporal blocking) for small instances: a
 // work-group holds tile t's S x S square and a ring of depth h around it (the
 // cells of the eight neighbour tiles within h of the square) as a box of side

@@ -1,0 +1,201 @@
+// The matrix-core plan of random and named NBB fractals, driven lane by lane
+// as the kernel drives it (operands, record writes and reads, halo blocks of
+// the neighbour tiles), against neighbour counts taken cell by cell through
+// lambda and nu, for both stencils.  Prints what was compared and the shapes.
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include <set>
+#include <string>
+#include <vector>
+
+#include "plan.hpp"
+using namespace nbb;
+
+static int count_ref(const Fractal &f, const std::vector<uint8_t> &st, uint64_t i, bool edge) {
+    int64_t x, y;
+    lambda_levels(f, f.r, i, &x, &y);
+    int n = 0;
+    for (int dy = -1; dy <= 1; ++dy)
+        for (int dx = -1; dx <= 1; ++dx) {
+            if (!dx && !dy) continue;
+            if (edge && dx && dy) continue;
+            const int64_t v = nu_levels(f, f.r, x + dx, y + dy);
+            if (v >= 0) n += st[size_t(v)];
+        }
+    return n;
+}
+
+// D[row][col] = sum over quarters and bytes of A and B, lanes as the kernel's
+static void contract(const int8_t *A, const std::vector<uint8_t> &B, int (&D)[64][4]) {
+    for (int l = 0; l < 64; ++l)
+        for (int i = 0; i < 4; ++i) {
+            const int row = 4 * (l / 16) + i, col = l % 16;
+            for (int q = 0; q < 4; ++q)
+                for (int j = 0; j < 16; ++j) D[l][i] += A[(q * 16 + row) * 16 + j] * B[(q * 16 + col) * 16 + j];
+        }
+}
+
+static void check(const Fractal &f, const MatPlan &p, std::mt19937 &rng, bool edge) {
+    std::vector<uint8_t> st(f.cells);
+    for (auto &c : st) c = rng() & 1;
+    const uint32_t bpg = 64 / p.lanes;
+    for (uint64_t tile = 0; tile < p.ntiles; ++tile) {
+        if (p.ntiles > 40 && rng() % (p.ntiles / 20)) continue;
+        std::vector<uint8_t> lds(p.buf_bytes, 0xEE);
+        const uint32_t zero = (p.lanes * p.nr * p.nrecs) * 4;
+        if (zero + 4 > p.buf_bytes) std::abort();
+        for (int i = 0; i < 4; ++i) lds[zero + i] = 0;
+        auto load = [&](uint64_t t, uint32_t b, uint32_t sub, uint8_t *dst) {
+            const uint32_t off = std::min(16 * sub, p.CB - 16);
+            for (uint32_t j = 0; j < 16; ++j) dst[j] = st[t * p.K + b * p.CB + off + j];
+        };
+        auto publish = [&](const std::vector<uint8_t> &B, const std::vector<int64_t> &rec) {
+            for (uint32_t t = 0; t < p.nr; ++t) {
+                int D[64][4] = {};
+                contract(p.A.data() + mat_rec_off(p.nh, t), B, D);
+                for (int l = 0; l < 64; ++l) {
+                    const uint32_t in = (l / 16) / p.lanes * 16 + l % 16, sub = (l / 16) % p.lanes;
+                    if (rec[in] < 0) continue;
+                    for (int i = 0; i < 4; ++i)
+                        lds[4 * ((t * p.lanes + sub) * p.nrecs + rec[in]) + i] = uint8_t(D[l][i]);
+                }
+            }
+        };
+        auto gather = [&](uint32_t n, auto block_of, std::vector<uint8_t> *B, std::vector<int64_t> *rec, uint32_t g,
+                          uint32_t rec0) {
+            B->assign(1024, 0);
+            rec->assign(bpg, -1);
+            for (int l = 0; l < 64; ++l) {
+                const uint32_t in = (l / 16) / p.lanes * 16 + l % 16, sub = (l / 16) % p.lanes;
+                const uint32_t b = g * bpg + in;
+                if (b >= n) continue;
+                (*rec)[in] = rec0 + b;
+                uint64_t t;
+                uint32_t lb;
+                if (block_of(b, &t, &lb)) load(t, lb, sub, B->data() + 16 * l);
+            }
+        };
+        std::vector<uint8_t> B;
+        std::vector<int64_t> rec;
+        auto own = [&](uint32_t b, uint64_t *t, uint32_t *lb) {
+            *t = tile;
+            *lb = b;
+            return true;
+        };
+        auto halo = [&](uint32_t h, uint64_t *t, uint32_t *lb) {
+            const uint32_t nt = p.nbr[tile * 8 + (p.halo[h] >> 29)];
+            *t = nt;
+            *lb = p.halo[h] & 0x1FFFFFFFu;
+            return nt != 0xFFFFFFFFu;
+        };
+        for (uint32_t g = 0; g < p.groups; ++g) {
+            gather(p.nblk, own, &B, &rec, g, 0);
+            publish(B, rec);
+        }
+        for (uint32_t g = 0; g * bpg < p.nhalo; ++g) {
+            if (g >= p.waves) std::abort();
+            gather(p.nhalo, halo, &B, &rec, g, p.nblk);
+            publish(B, rec);
+        }
+        if (p.groups > p.waves * p.gpw) std::abort();
+        for (uint32_t g = 0; g < p.groups; ++g) {
+            gather(p.nblk, own, &B, &rec, g, 0);
+            for (uint32_t t = 0; t < 2; ++t) {
+                int D[64][4] = {};
+                contract(p.A.data() + mat_self_off(p.nh, edge, t), B, D);
+                for (uint32_t h = 0; h < p.nh; ++h) {
+                    std::vector<uint8_t> R(1024);
+                    for (int l = 0; l < 64; ++l)
+                        for (int d = 0; d < 4; ++d) {
+                            const uint32_t w = p.raddr[(size_t(g) * 64 + l) * 2 * p.nh + 2 * h + d / 2];
+                            const uint32_t a = d & 1 ? w >> 16 : w & 0xFFFFu;
+                            if (a + 4 > p.buf_bytes) std::abort();
+                            for (int i = 0; i < 4; ++i) R[16 * l + 4 * d + i] = lds[a + i];
+                        }
+                    contract(p.A.data() + mat_halo_off(p.nh, edge, h, t), R, D);
+                }
+                for (int l = 0; l < 64; ++l) {
+                    const uint32_t in = (l / 16) / p.lanes * 16 + l % 16, sub = (l / 16) % p.lanes;
+                    const uint32_t b = g * bpg + in;
+                    if (b >= p.nblk) continue;
+                    for (int i = 0; i < 4; ++i)
+                        for (int hi = 0; hi < 2; ++hi) {
+                            const uint32_t c = std::min(16 * sub, p.CB - 16) + 8 * t + 4 * hi + i;
+                            const int want = count_ref(f, st, tile * p.K + b * p.CB + c, edge);
+                            const int got = hi ? D[l][i] >> 4 : D[l][i] & 15;
+                            if (want != got || D[l][i] < 0 || D[l][i] > 255) {
+                                std::printf("mismatch k %u s %u r %u m %u tile %llu block %u cell %u: %d %d\n", f.k, f.s,
+                                            f.r, p.m, (unsigned long long)tile, b, c, want, got);
+                                std::exit(1);
+                            }
+                        }
+                }
+            }
+        }
+    }
+}
+
+static bool make(uint32_t s, const std::vector<int32_t> &off, uint32_t r, Fractal *f) {
+    std::string msg;
+    return validate_fractal(uint32_t(off.size() / 2), s, off.data(), r, f, &msg) == 0;
+}
+
+int main(int argc, char **argv) {
+    std::mt19937 rng(7);
+    int plans = 0;
+    std::vector<std::pair<uint32_t, std::vector<int32_t>>> named = {
+        {2, {0, 0, 1, 0, 0, 1}},                                      // triangle
+        {3, {0, 0, 1, 0, 2, 0, 0, 1, 2, 1, 0, 2, 1, 2, 2, 2}},        // carpet
+        {3, {0, 0, 0, 1, 0, 2, 1, 1, 2, 0, 2, 1, 2, 2}},              // H
+        {3, {0, 0, 1, 0, 2, 0, 1, 1}},                                // chandelier-like
+        {2, {0, 0, 1, 0, 0, 1, 1, 1}},                                // full square
+        {3, {1, 0, 0, 1, 1, 1, 2, 1, 1, 2}},                          // Vicsek
+        {3, {0, 0, 2, 0, 1, 1, 0, 2, 2, 2}},                          // X
+        {3, {0, 0, 2, 0, 0, 2, 2, 2}},                                // Cantor dust
+        {3, {0, 0, 2, 0}},                                            // Cantor set
+    };
+    for (auto &n : named)
+        for (uint32_t r = 2; r <= 7; ++r) {
+            Fractal f;
+            if (!make(n.first, n.second, r, &f) || f.cells > 60000) continue;
+            for (uint32_t m = 1; m <= r; ++m) {
+                MatPlan p;
+                std::string msg;
+                if (!build_mat_plan(f, m, 0, 1 + rng() % 300, &p, &msg)) continue;
+                for (bool edge : {false, true}) check(f, p, rng, edge);
+                ++plans;
+                if (r == 7 || argc > 1)
+                    std::printf("# k %u s %u r %u m %u: q %u CB %u lanes %u nblk %u nhalo %u nr %u nh %u gpw %u waves %u buf %u\n",
+                                f.k, f.s, r, m, p.q, p.CB, p.lanes, p.nblk, p.nhalo, p.nr, p.nh, p.gpw, p.waves,
+                                p.buf_bytes);
+            }
+        }
+    for (int it = 0; it < 300; ++it) {
+        const uint32_t s = 2 + rng() % 3, k = 1 + rng() % (s * s);
+        std::vector<int> cells(s * s);
+        for (uint32_t i = 0; i < s * s; ++i) cells[i] = int(i);
+        std::shuffle(cells.begin(), cells.end(), rng);
+        std::vector<int32_t> off;
+        for (uint32_t j = 0; j < k; ++j) {
+            off.push_back(int32_t(cells[j] % s));
+            off.push_back(int32_t(cells[j] / s));
+        }
+        Fractal f;
+        if (!make(s, off, 1 + rng() % 7, &f) || f.cells > 20000) continue;
+        for (uint32_t m = 1; m <= f.r; ++m) {
+            MatPlan p;
+            std::string msg;
+            if (!build_mat_plan(f, m, 0, 1 + rng() % 300, &p, &msg)) continue;
+            check(f, p, rng, rng() & 1);
+            ++plans;
+        }
+        const uint32_t a = auto_mat_level(f, {f.r}, 256);
+        MatPlan p;
+        std::string msg;
+        if (a && !build_mat_plan(f, a, 0, 256, &p, &msg, false)) std::abort();
+    }
+    std::printf("plans %d\n", plans);
+    return 0;
+}

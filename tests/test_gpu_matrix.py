@@ -1,0 +1,73 @@
+"""The compact step on the matrix cores (the default plan's form wherever a
+block level has 16 to 64 cells) against the CPU oracle, whole states, bit by
+bit: blocks of 16, 25, 27, 32, 36, 49 and 64 cells, every number of lanes per
+block, tiles of one block up to several groups per wavefront, groups with
+lanes left over, every rule form."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2110_12952_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+gpu = pytest.mark.gpu
+
+# (fractal, r): the smallest states the form takes, one tile, few and many
+# tiles; the levels change with r
+STATES = [("triangle", r) for r in (3, 4, 5, 7, 8, 9, 10, 11, 12, 13)] + \
+         [("carpet", r) for r in (2, 3, 4, 5, 6)] + [("hfractal", r) for r in (2, 3, 4, 5, 6, 7)] + \
+         [("chandelier", r) for r in (3, 4, 7, 8, 9)] + [("fullsquare", r) for r in (3, 5, 8, 9)] + \
+         [("vicsek", r) for r in (2, 3, 6, 7, 8)] + [("xfractal", r) for r in (2, 5, 7)] + \
+         [("cantordust", 7), ("cantor", 6), ("cantor", 14), ("grid4_12", 3)]
+RULES = ["B3/S23", "B36/S23", "B1357/S02468", "B35/S0123456", "vN:B2/S12", "vN:B13/S024"]
+
+
+@pytest.fixture(scope="module")
+def N():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2110_12952_amd import nbbfrac
+    nbbfrac.lib()
+    return nbbfrac
+
+
+def check(N, fd, r, rules, seed=5):
+    o, g = O.Fractal(fd.s, fd.offsets, r), N.Fractal(fd.s, fd.offsets, r)
+    st0 = o.init_compact(seed, 0.45)
+    for rule in rules:
+        rm = W.rule_mask(rule)
+        for steps in (1, 2):
+            a = torch.from_numpy(st0).cuda()
+            b = torch.full_like(a, 0xEE)
+            res = g.step_compact(a, b, steps, rm).cpu().numpy()
+            want = o.compact_steps(st0, rm, steps)
+            np.testing.assert_array_equal(res, want, err_msg=f"{fd.name} r={r} {rule} steps={steps}")
+
+
+@gpu
+@pytest.mark.parametrize("name,r", STATES)
+def test_default_step_against_oracle(N, name, r):
+    check(N, W.FRACTALS[name], r, RULES)
+
+
+@gpu
+@pytest.mark.parametrize("seed", range(24))
+def test_random_fractals_against_oracle(N, seed):
+    fd = W.random_fractal(seed + 100)
+    r = 1
+    while fd.k > 1 and fd.k ** (r + 1) <= 200_000 and fd.s ** (r + 1) < 4000:
+        r += 1
+    check(N, fd, r, RULES[:3] + RULES[4:5], seed)
+
+
+@gpu
+def test_full_rule_words(N):
+    # births and survivals at eight neighbours (the bit-extract form) on the
+    # fractals that have such cells
+    for name, r in (("fullsquare", 6), ("carpet", 4), ("grid4_12", 3)):
+        fd = W.FRACTALS[name]
+        o, g = O.Fractal(fd.s, fd.offsets, r), N.Fractal(fd.s, fd.offsets, r)
+        st0 = o.init_compact(3, 0.9)
+        for rule in (1 << 8, 1 << 24, 0x01FF01FF, 0x00AA0155):
+            a = torch.from_numpy(st0).cuda()
+            res = g.step_compact(a, torch.empty_like(a), 3, rule).cpu().numpy()
+            np.testing.assert_array_equal(res, o.compact_steps(st0, rule, 3), err_msg=f"{name} {rule:#x}")
