@@ -62,6 +62,17 @@ struct nbb_fractal {
     bool use_matrix = false;
     DevBlob dmat;
     MatParams matp{};
+    std::vector<MatDims> mat_levels;
+    // For batches, made on first use and kept: plans without neighbours by
+    // (tile level, groups per wavefront), neighbour tables by tile level.
+    struct MatTables {
+        MatPlan plan;
+        DevBlob blob;
+        MatParams p{};
+    };
+    mutable std::mutex mat_mu;
+    mutable std::map<std::pair<uint32_t, uint32_t>, MatTables> mat_plans;
+    mutable std::map<uint32_t, DevBlob> mat_nbrs;
     // Several generations per launch (NBB_STRATEGY_TEMPORAL): the plan and
     // its device tables; the tile plan above stays for batches.
     TemporalPlan temporal;
@@ -105,7 +116,10 @@ struct nbb_temporal_plan {
 // launch over the group's tiles, and instances stepped one by one.
 struct BatchGroup {
     TileParams tp;           // the plan of the group's first descriptor; nbr / ntiles are the batch's
-    bool edges = false;      // stepped in edge-record form (ep, with the batch's nbr / ntiles)
+    bool matrix = false;     // stepped on the matrix cores (mp, with the batch's nbr / ntiles)
+    MatParams mp{};
+    uint32_t al = 0, nr = 0, nh = 0, gpw = 0;
+    bool edges = false;      // else in edge-record form (ep, with the batch's nbr / ntiles)
     EdgeParams ep{};
     uint32_t BS = 0, nsrc = 0;
     const uint32_t *rec = nullptr;
@@ -173,6 +187,14 @@ nbb_status upload(DevBlob *blob, const void *const *src, const size_t *bytes, in
         off[i] = total;
         total += align256(std::max<size_t>(bytes[i], 1));
     }
+    std::vector<uint8_t> staged;
+    try {
+        staged.resize(total);
+    } catch (const std::bad_alloc &) {
+        return fail(NBB_E_NOMEM, "host allocation failed");
+    }
+    for (int i = 0; i < nparts; ++i)
+        if (bytes[i]) std::memcpy(staged.data() + off[i], src[i], bytes[i]);
     void *p = nullptr;
     hipError_t e = hipMalloc(&p, total);
     if (e != hipSuccess) {
@@ -180,16 +202,12 @@ nbb_status upload(DevBlob *blob, const void *const *src, const size_t *bytes, in
         return e == hipErrorOutOfMemory ? fail(NBB_E_NOMEM, "device table allocation failed")
                                         : hip_fail(e, "hipMalloc");
     }
-    for (int i = 0; i < nparts; ++i) {
-        if (bytes[i]) {
-            e = hipMemcpy(static_cast<char *>(p) + off[i], src[i], bytes[i], hipMemcpyHostToDevice);
-            if (e != hipSuccess) {
-                (void)hipFree(p);
-                return hip_fail(e, "hipMemcpy");
-            }
-        }
-        dst[i] = static_cast<char *>(p) + off[i];
+    e = hipMemcpy(p, staged.data(), total, hipMemcpyHostToDevice);  // one copy: each costs a round trip
+    if (e != hipSuccess) {
+        (void)hipFree(p);
+        return hip_fail(e, "hipMemcpy");
     }
+    for (int i = 0; i < nparts; ++i) dst[i] = static_cast<char *>(p) + off[i];
     blob->ptr = p;
     blob->bytes = total;
     return NBB_OK;
@@ -373,10 +391,12 @@ nbb_status upload_matrix(const MatPlan &p, DevBlob *blob, MatParams *T) {
 // Builds and uploads the matrix plan of a descriptor at its own tile level
 // (nothing where the form does not apply).
 nbb_status setup_matrix(nbb_fractal *F) {
-    const uint32_t cus = uint32_t(F->cu_count), m = auto_mat_level(F->f, {F->f.r}, cus);
+    F->mat_levels = mat_dims(F->f);
+    uint32_t gpw = 0;
+    const uint32_t m = pick_mat_level(F->mat_levels, F->f.k, {F->f.r}, uint32_t(F->cu_count), &gpw);
     std::string msg;
     MatPlan p;
-    if (!m || !build_mat_plan(F->f, m, 0, cus, &p, &msg)) return NBB_OK;
+    if (!m || !build_mat_plan(F->f, m, gpw, &p, &msg)) return NBB_OK;
     nbb_status st = upload_matrix(p, &F->dmat, &F->matp);
     if (st != NBB_OK) return st;
     p.A.clear();
@@ -385,6 +405,37 @@ nbb_status setup_matrix(nbb_fractal *F) {
     p.nbr.clear();
     F->mat = std::move(p);
     return NBB_OK;
+}
+
+// Tables of F for a batch at tile level m <= r (nullptr if they cannot be had:
+// the batch then takes another form).
+const nbb_fractal::MatTables *batch_mat_plan(const nbb_fractal *F, uint32_t m, uint32_t gpw) {
+    std::lock_guard<std::mutex> lock(F->mat_mu);
+    const auto key = std::make_pair(m, gpw);
+    auto it = F->mat_plans.find(key);
+    if (it != F->mat_plans.end()) return &it->second;
+    nbb_fractal::MatTables t;
+    std::string msg;
+    if (!build_mat_plan(F->f, m, gpw, &t.plan, &msg, false)) return nullptr;
+    t.plan.nbr.assign(8, 0xFFFFFFFFu);
+    if (upload_matrix(t.plan, &t.blob, &t.p) != NBB_OK) return nullptr;
+    return &(F->mat_plans[key] = std::move(t));
+}
+const uint32_t *batch_mat_nbr(const nbb_fractal *F, uint32_t m) {
+    if (m == F->mat.m && F->matp.nbr) return F->matp.nbr;
+    std::lock_guard<std::mutex> lock(F->mat_mu);
+    auto it = F->mat_nbrs.find(m);
+    if (it == F->mat_nbrs.end()) {
+        std::vector<uint32_t> nbr;
+        mat_neighbours(F->f, m, &nbr);
+        const void *src[1] = {nbr.data()};
+        size_t bytes[1] = {nbr.size() * 4};
+        void *dst[1];
+        DevBlob blob;
+        if (upload(&blob, src, bytes, 1, dst) != NBB_OK) return nullptr;
+        it = F->mat_nbrs.emplace(m, blob).first;
+    }
+    return static_cast<const uint32_t *>(it->second.ptr);
 }
 
 // Builds and uploads the edge plan at the tile plan's level for a TILED
@@ -653,6 +704,8 @@ nbb_status nbb_create(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r
 
 void nbb_destroy(nbb_fractal *F) {
     if (!F) return;
+    for (auto &t : F->mat_plans) blob_free(&t.second.blob);
+    for (auto &t : F->mat_nbrs) blob_free(&t.second);
     blob_free(&F->dres);
     blob_free(&F->dpk);
     blob_free(&F->dtemp);
@@ -1121,14 +1174,68 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         else
             launch.add(F, i, I, same_plan);
     }
-    // One device allocation: per group the instance table, the records
-    // (2 words per tile) and the neighbour table (8 words per tile); per
-    // resident group its instance table.
     const size_t ng = launch.reps.size(), nr = res.reps.size();
+    // A group whose descriptors all run the matrix form takes it, at one tile
+    // level for all of its instances (those below it are one tile each).  Not
+    // without allocation: its tables are made on first use.
+    struct MatGroup {
+        const nbb_fractal::MatTables *plan = nullptr;
+        std::vector<MatInstance> members;
+    };
+    std::vector<MatGroup> mat(ng);
+    for (size_t g = 0; g < ng && !fixed; ++g) {
+        const std::vector<uint32_t> &index = launch.index[g];
+        std::vector<uint32_t> levels;
+        const nbb_fractal *top = nullptr;  // the descriptor of the largest level
+        bool all = true;
+        for (uint32_t i : index) {
+            const nbb_fractal *F = fractals[i];
+            all = all && F->use_matrix;
+            levels.push_back(F->f.r);
+            if (!top || F->f.r > top->f.r) top = F;
+        }
+        uint32_t gpw = 0;
+        const uint32_t m = all ? pick_mat_level(top->mat_levels, top->f.k, levels, uint32_t(top->cu_count), &gpw) : 0;
+        if (!m) continue;
+        MatGroup M;
+        M.plan = batch_mat_plan(top, m, gpw);
+        uint64_t t = 0;
+        for (size_t j = 0; j < index.size() && M.plan; ++j) {
+            const nbb_fractal *F = fractals[index[j]];
+            MatInstance I{};
+            I.base16 = uint32_t(offsets[index[j]] >> 4);
+            I.tile0 = uint32_t(t);
+            I.ntiles = 1;
+            I.cells = uint32_t(F->f.cells);
+            if (F->f.r > m) {
+                for (uint32_t l = m; l < F->f.r; ++l) I.ntiles *= F->f.k;
+                I.nbr = batch_mat_nbr(F, m);
+                if (!I.nbr) M.plan = nullptr;
+            }
+            t += I.ntiles;
+            M.members.push_back(I);
+        }
+        if (M.plan && t * 8 <= (uint64_t(1) << 31)) mat[g] = std::move(M);
+    }
+    // One device allocation: per group the instance table, the records
+    // (2 words per tile, 4 for the matrix form) and the neighbour table (8
+    // words per tile); per resident group its instance table.
     std::vector<size_t> off_inst(ng), off_rec(ng), off_nbr(ng), ntiles(ng);
     size_t total = 0;
     for (size_t g = 0; g < ng; ++g) {
         uint64_t t = 0;
+        if (mat[g].plan) {
+            for (const BatchInstance &I : launch.members[g]) B->tiles += I.ntiles;
+            t = mat[g].members.back().tile0 + mat[g].members.back().ntiles;
+            ntiles[g] = t;
+            off_inst[g] = total;
+            total += align256(mat[g].members.size() * sizeof(MatInstance));
+            off_rec[g] = total;
+            total += align256(t * 16);
+            off_nbr[g] = total;
+            total += align256(t * 32);
+            continue;
+        }
         for (BatchInstance &I : launch.members[g]) {
             I.tile0 = uint32_t(t);
             t += I.ntiles;
@@ -1178,6 +1285,35 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         auto *inst = reinterpret_cast<BatchInstance *>(base + off_inst[g]);
         auto *rec = reinterpret_cast<uint32_t *>(base + off_rec[g]);
         auto *nbr = reinterpret_cast<uint32_t *>(base + off_nbr[g]);
+        if (mat[g].plan) {
+            const std::vector<MatInstance> &mem = mat[g].members;
+            auto *minst = reinterpret_cast<MatInstance *>(base + off_inst[g]);
+            e = hipMemcpyAsync(minst, mem.data(), mem.size() * sizeof(MatInstance), hipMemcpyHostToDevice, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host table goes out of scope
+            if (e == hipSuccess)
+                e = launch_batch_tiles_matrix(minst, uint32_t(mem.size()), uint32_t(ntiles[g]), rec, nbr, s);
+            if (e != hipSuccess) {
+                batch_free(B);
+                return hip_fail(e, "batch table build");
+            }
+            BatchGroup G;
+            G.tp = launch.reps[g]->tp;
+            G.matrix = true;
+            const MatPlan &p = mat[g].plan->plan;
+            G.mp = mat[g].plan->p;
+            G.mp.nbr = nbr;
+            G.mp.ntiles = uint32_t(ntiles[g]);
+            G.al = mat_align_of(p.CB);
+            G.nr = p.nr;
+            G.nh = p.nh;
+            G.gpw = p.gpw;
+            G.rec = rec;
+            G.index = launch.index[g];
+            for (const MatInstance &I : mem) G.tiles_end.push_back(uint64_t(I.tile0) + I.ntiles);
+            B->groups.push_back(std::move(G));
+            B->cu_count = launch.reps[g]->cu_count;
+            continue;
+        }
         static_assert(sizeof(BatchInstance) % 4 == 0, "instance records upload as words");
         if (fixed) {
             e = launch_set_words(reinterpret_cast<uint32_t *>(inst),
@@ -1398,8 +1534,10 @@ nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t a
         const hipStream_t gs = batch_group_stream(B, k, s);
         uint8_t *in = a, *out = b;
         for (uint32_t i = 0; i < steps && e == hipSuccess; ++i) {
-            e = G.edges ? launch_step_edges(G.ep, G.BS, G.nsrc, in, out, arena_len, rule, G.rec, B->cu_count, gs)
-                        : launch_step_tiled_batch(G.tp, G.rec, in, out, rule, B->cu_count, gs);
+            e = G.matrix  ? launch_step_matrix(G.mp, G.al, G.nr, G.nh, G.gpw, in, out, arena_len, rule, G.rec,
+                                               B->cu_count, gs)
+                : G.edges ? launch_step_edges(G.ep, G.BS, G.nsrc, in, out, arena_len, rule, G.rec, B->cu_count, gs)
+                          : launch_step_tiled_batch(G.tp, G.rec, in, out, rule, B->cu_count, gs);
             std::swap(in, out);
         }
     }
@@ -1462,7 +1600,11 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
             while (live && steps[G.index[live - 1]] <= g) --live;
             if (!live) break;
             const uint32_t nt = uint32_t(G.tiles_end[live - 1]);
-            if (G.edges) {
+            if (G.matrix) {
+                MatParams E = G.mp;
+                E.ntiles = nt;
+                e = launch_step_matrix(E, G.al, G.nr, G.nh, G.gpw, in, out, arena_len, rule, G.rec, B->cu_count, gs);
+            } else if (G.edges) {
                 EdgeParams E = G.ep;
                 E.ntiles = nt;
                 e = launch_step_edges(E, G.BS, G.nsrc, in, out, arena_len, rule, G.rec, B->cu_count, gs);
@@ -1573,7 +1715,7 @@ nbb_status nbb_batch_autotune(nbb_fractal *const *fractals, const uint64_t *offs
         if (!cached) {
             // candidates: every tile level up to the set's smallest r whose
             // tiles hold at least 64 cells (or the largest level), in the
-            // edge-record and the byte-scatter form
+            // edge-record and the byte-scatter form, and the matrix form
             std::vector<uint64_t> offs;
             std::vector<const nbb_fractal *> inst;
             for (uint32_t i : set) {
@@ -1582,11 +1724,15 @@ nbb_status nbb_batch_autotune(nbb_fractal *const *fractals, const uint64_t *offs
             }
             float best_ms = -1.0f;
             uint64_t K = 1;
+            bool matrix_timed = false;
             for (uint32_t m = 1; m <= rmin && st == NBB_OK; ++m) {
                 K *= f0.k;
                 if (K < 64 && m < rmin) continue;
-                for (uint32_t strategy : {NBB_STRATEGY_TILED_EDGE, NBB_STRATEGY_TILED_BOX}) {
+                for (uint32_t strategy : {NBB_STRATEGY_TILED, NBB_STRATEGY_TILED_EDGE, NBB_STRATEGY_TILED_BOX}) {
+                    // (the matrix form has a level of its own: timed once)
+                    if (strategy == NBB_STRATEGY_TILED && (matrix_timed || !desc[0]->mat.ok)) continue;
                     if (configure_all(strategy, m) != NBB_OK) continue;  // does not fit: skip it
+                    matrix_timed = matrix_timed || strategy == NBB_STRATEGY_TILED;
                     nbb_batch *B = nullptr;
                     st = batch_create(inst.data(), offs.data(), uint32_t(inst.size()), NBB_BATCH_NO_RESIDENT,
                                       stream, nullptr, 0, &B);

@@ -1244,6 +1244,36 @@ hipError_t launch_batch_tiles(const BatchInstance *inst, uint32_t ninst, uint32_
     hipLaunchKernelGGL(k_batch_tiles, dim3(grid), dim3(256), 0, st, inst, ninst, total, rec, nbr);
     return hipGetLastError();
 }
+__global__ __launch_bounds__(256) void k_batch_tiles_matrix(const MatInstance *__restrict__ inst, uint32_t ninst,
+                                                            uint32_t total, uint32_t *__restrict__ rec,
+                                                            uint32_t *__restrict__ nbr) {
+    for (uint32_t g = blockIdx.x * 256 + threadIdx.x; g < total; g += gridDim.x * 256) {
+        uint32_t lo = 0, hi = ninst - 1;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1) >> 1;
+            if (inst[mid].tile0 <= g) lo = mid;
+            else hi = mid - 1;
+        }
+        const MatInstance &I = inst[lo];
+        const uint32_t t = g - I.tile0;
+        reinterpret_cast<uint4 *>(rec)[g] = make_uint4(I.base16, t, I.cells, 0);
+        uint4 *d4 = reinterpret_cast<uint4 *>(nbr + 8 * uint64_t(g));
+        if (I.nbr) {
+            const uint4 *s4 = reinterpret_cast<const uint4 *>(I.nbr + 8 * uint64_t(t));
+            d4[0] = s4[0];
+            d4[1] = s4[1];
+        } else {
+            d4[0] = d4[1] = make_uint4(kOutside, kOutside, kOutside, kOutside);
+        }
+    }
+}
+hipError_t launch_batch_tiles_matrix(const MatInstance *inst, uint32_t ninst, uint32_t total, uint32_t *rec,
+                                     uint32_t *nbr, hipStream_t st) {
+    if (!total || !ninst) return hipSuccess;
+    const uint32_t grid = std::min<uint32_t>((total + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_batch_tiles_matrix, dim3(grid), dim3(256), 0, st, inst, ninst, total, rec, nbr);
+    return hipGetLastError();
+}
 hipError_t launch_pack_bits(const uint8_t *bytes, uint32_t *words, uint64_t cells, int grid, hipStream_t st) {
     const uint64_t nwords = (cells + 31) / 32;
     if (!nwords) return hipSuccess;

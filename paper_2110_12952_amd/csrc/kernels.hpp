@@ -79,6 +79,10 @@ hipError_t launch_set_words(uint32_t *dst, const uint32_t *src, uint32_t n, hipS
 // Builds the per-tile record and neighbour tables of a batch on the device.
 hipError_t launch_batch_tiles(const BatchInstance *inst, uint32_t ninst, uint32_t total, uint32_t *rec,
                               uint32_t *nbr, hipStream_t st);
+// The same for the matrix form: four words per tile (arena offset / 16, local
+// tile, cells of the instance, 0) and eight neighbours.
+hipError_t launch_batch_tiles_matrix(const MatInstance *inst, uint32_t ninst, uint32_t total, uint32_t *rec,
+                                     uint32_t *nbr, hipStream_t st);
 // `gens` <= T.h generations of every tile of a temporal plan in one launch
 // (temporal.hip); one work-group per tile.
 hipError_t launch_step_temporal(const TemporalParams &T, const uint8_t *in, uint8_t *out, uint32_t rule,

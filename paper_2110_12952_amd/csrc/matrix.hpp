@@ -184,15 +184,18 @@ __global__ __launch_bounds__(64 * kMatMaxWaves) void k_step_matrix(MatParams E, 
         uint8_t *dst;     // the tile's output
         uint32_t bytes;   // and its length
     } P;
-    auto prefetch = [&](uint32_t t, uint32_t nt) {
-        uint64_t base = 0;
-        uint32_t local = t;
-        uint32_t cells = 0xFFFFFFFFu;
-        if (BATCH) {
-            base = uint64_t(rec[4 * uint64_t(t)]) << 4;
-            local = rec[4 * uint64_t(t) + 1];
-            cells = rec[4 * uint64_t(t) + 2];
-        }
+    // A tile's record, read one tile before its loads.
+    struct Where {
+        uint32_t base16, local, cells;
+    };
+    auto where = [&](uint32_t t) -> Where {
+        if (!BATCH) return {0, t, 0};
+        const uint32_t *r = rec + 4 * uint64_t(t);
+        return {r[0], r[1], r[2]};
+    };
+    auto prefetch = [&](const Where &w, uint32_t nt) {
+        const uint64_t base = uint64_t(w.base16) << 4;
+        const uint32_t local = w.local, cells = w.cells;
         const uint8_t *src = in + base;
         const uint64_t room = (E.limit - base + 3) & ~uint64_t(3);  // whole dwords
         const uint32_t lim = room > kNowhere ? kNowhere : uint32_t(room);
@@ -212,7 +215,8 @@ __global__ __launch_bounds__(64 * kMatMaxWaves) void k_step_matrix(MatParams E, 
     auto entry = [&](uint32_t t) -> uint32_t { return E.nbr[uint64_t(t) * 8 + hdir]; };
 
     uint32_t nt = entry(tile(1));
-    prefetch(tile(0), entry(tile(0)));
+    Where wh = where(tile(1));
+    prefetch(where(tile(0)), entry(tile(0)));
     // As many stores after the first tile's loads as after any later tile's
     // (into an empty range, so dropped): the compiler then counts the same
     // outstanding operations on both ways into the loop and waits for the
@@ -239,8 +243,10 @@ __global__ __launch_bounds__(64 * kMatMaxWaves) void k_step_matrix(MatParams E, 
         const __amdgpu_buffer_rsrc_t gout = mat_rsrc(P.dst, P.bytes);
         // the next tile's loads, the neighbour tile of the one after it
         const uint32_t nt1 = nt;
+        const Where wh1 = wh;
         nt = entry(tile(i + 2));
-        prefetch(tile(i + 1), nt1);
+        wh = where(tile(i + 2));
+        prefetch(wh1, nt1);
         __syncthreads();
         // step 2: counts and rule
 #pragma unroll

@@ -130,8 +130,25 @@ bool pick_shape(const Fractal &f, BlockShape *s) {
 
 }  // namespace
 
-static bool build_mat_shape(const Fractal &f, const BlockShape &s, uint32_t m, uint64_t tiles, uint32_t cus,
-                            MatPlan *p, std::string *msg, bool with_nbr) {
+void mat_neighbours(const Fractal &f, uint32_t m, std::vector<uint32_t> *nbr) {
+    const uint64_t tiles = ipow(f.k, f.r - m);
+    nbr->assign(size_t(tiles) * 8, 0xFFFFFFFFu);
+    for (uint64_t t = 0; t < tiles; ++t) {
+        int64_t X, Y;
+        lambda_levels(f, f.r - m, t, &X, &Y);
+        for (uint32_t d = 0; d < 8; ++d) {
+            const int64_t v = nu_levels(f, f.r - m, X + kDirX[d], Y + kDirY[d]);
+            if (v >= 0) (*nbr)[size_t(t) * 8 + d] = uint32_t(v);
+        }
+    }
+}
+
+// The blocks of the tile at level m and of its neighbour tiles: `source`
+// gets the record of every read of every block (an own block, a halo block
+// numbered as first met, or none).
+const uint32_t kNone = 0xFFFFFFFFu;
+static bool build_ring(const Fractal &f, const BlockShape &s, uint32_t m, MatPlan *p, std::vector<uint32_t> *source,
+                       std::string *msg) {
     *p = MatPlan();
     if (m < s.q || m > f.r) {
         *msg = "the matrix form needs q <= m <= r";
@@ -154,18 +171,15 @@ static bool build_mat_shape(const Fractal &f, const BlockShape &s, uint32_t m, u
     p->groups = (p->nblk + bpg - 1) / bpg;
     p->ntiles = ipow(f.k, f.r - m);
     const int64_t G = int64_t(ipow(f.s, m - s.q));
-    // the neighbouring record of every read of every block: an own block, a
-    // halo block (numbered as first met), or none
     std::map<std::pair<int64_t, int64_t>, uint32_t> halo;
-    const uint32_t none = 0xFFFFFFFFu;
-    std::vector<uint32_t> source(size_t(p->nblk) * s.reads.size(), none);
+    source->assign(size_t(p->nblk) * s.reads.size(), kNone);
     for (uint32_t b = 0; b < p->nblk; ++b) {
         int64_t X, Y;
         lambda_levels(f, m - s.q, b, &X, &Y);
         for (size_t i = 0; i < s.reads.size(); ++i) {
             const uint32_t d = s.reads[i].first;
             const int64_t nx = X + kDirX[d], ny = Y + kDirY[d];
-            uint32_t &src = source[b * s.reads.size() + i];
+            uint32_t &src = (*source)[b * s.reads.size() + i];
             if (nx >= 0 && ny >= 0 && nx < G && ny < G) {
                 const int64_t v = nu_levels(f, m - s.q, nx, ny);
                 if (v >= 0) src = uint32_t(v);
@@ -195,32 +209,45 @@ static bool build_mat_shape(const Fractal &f, const BlockShape &s, uint32_t m, u
         *msg = "records beyond 32 KiB";
         return false;
     }
-    // Groups per wavefront: the most of 4, 2, 1 that leaves two wavefronts
-    // per work-group and, with the tiles at hand, six per CU (a wavefront
-    // with more groups has more loads in flight and does the tile's uniform
-    // work less often: triangle r16 at level 8, 1 / 2 / 4 groups per
-    // wavefront 18.3 / 16.2 / 15.8 us; carpet r7, two tiles per CU, 3.70 /
-    // 3.85 / 4.66); each wavefront also takes at most one group of halo blocks.
-    const uint32_t hgroups = (p->nhalo + bpg - 1) / bpg;
+    return true;
+}
+
+// Groups per wavefront: the most of 4, 2, 1 that leaves two wavefronts per
+// work-group and, with the tiles at hand, six per CU (a wavefront with more
+// groups has more loads in flight and does the tile's uniform work less
+// often: triangle r16 at level 8, 1 / 2 / 4 groups per wavefront 18.3 / 16.2 /
+// 15.8 us; carpet r7, two tiles per CU, 3.70 / 3.85 / 4.66); each wavefront
+// also takes at most one group of halo blocks.  0 if none fits.
+static uint32_t pick_gpw(uint32_t groups, uint32_t hgroups, uint64_t tiles, uint32_t cus) {
     const uint64_t per_cu = (tiles + cus - 1) / cus;
+    uint32_t gpw = 0;
     for (uint32_t g : {4u, 2u, 1u}) {
-        const uint32_t w = std::max((p->groups + g - 1) / g, hgroups);
+        const uint32_t w = std::max((groups + g - 1) / g, hgroups);
         if (w > kMatMaxWaves) break;
-        p->gpw = g;
-        p->waves = w;
+        gpw = g;
         if (w >= 2 && w * per_cu >= 6) break;
     }
-    if (!p->gpw) {
+    return gpw;
+}
+
+static bool build_mat_shape(const Fractal &f, const BlockShape &s, uint32_t m, uint32_t gpw, MatPlan *p,
+                            std::string *msg, bool with_nbr) {
+    std::vector<uint32_t> source;
+    if (!build_ring(f, s, m, p, &source, msg)) return false;
+    const uint32_t bpg = 64 / s.lanes, hgroups = (p->nhalo + bpg - 1) / bpg;
+    p->gpw = gpw ? gpw : pick_gpw(p->groups, hgroups, p->ntiles, 256);
+    p->waves = p->gpw ? std::max((p->groups + p->gpw - 1) / p->gpw, hgroups) : 0;
+    if (!p->gpw || p->waves > kMatMaxWaves) {
         *msg = "more groups than a work-group takes";
         return false;
     }
     // record reads: read i is dword i % 4 of lane (i / 4) % lanes, halo operand i / (4 lanes)
-    const uint32_t zero = uint32_t((words - 1) * 4);
+    const uint32_t zero = 4 * s.lanes * s.nr * p->nrecs;
     p->raddr.assign(size_t(p->waves) * p->gpw * 64 * 2 * p->nh, zero | zero << 16);
     for (uint32_t b = 0; b < p->nblk; ++b)
         for (size_t i = 0; i < s.reads.size(); ++i) {
             const uint32_t src = source[b * s.reads.size() + i];
-            if (src == none) continue;
+            if (src == kNone) continue;
             const uint32_t h = uint32_t(i) / (4 * s.lanes), sub = uint32_t(i) / 4 % s.lanes, d = uint32_t(i) % 4;
             const uint32_t in = b % bpg;  // block of the group: 16 columns by 4 / lanes
             const uint32_t lane = (in / 16 * s.lanes + sub) * 16 + in % 16;
@@ -283,30 +310,33 @@ static bool build_mat_shape(const Fractal &f, const BlockShape &s, uint32_t m, u
                 const uint32_t sub = uint32_t(e) / 16;  // its first holder
                 put(mat_rec_off(nh, t), 4 * g + i, g / s.lanes * s.lanes + sub, uint32_t(e) - first_cell(sub), 1);
             }
-    if (with_nbr) {
-        p->nbr.assign(size_t(p->ntiles) * 8, none);
-        for (uint64_t t = 0; t < p->ntiles; ++t) {
-            int64_t X, Y;
-            lambda_levels(f, f.r - m, t, &X, &Y);
-            for (uint32_t d = 0; d < 8; ++d) {
-                const int64_t v = nu_levels(f, f.r - m, X + kDirX[d], Y + kDirY[d]);
-                if (v >= 0) p->nbr[size_t(t) * 8 + d] = uint32_t(v);
-            }
-        }
-    }
+    if (with_nbr) mat_neighbours(f, m, &p->nbr);
     p->ok = true;
     return true;
 }
 
-bool build_mat_plan(const Fractal &f, uint32_t m, uint64_t tiles, uint32_t cus, MatPlan *p, std::string *msg,
-                    bool with_nbr) {
+bool build_mat_plan(const Fractal &f, uint32_t m, uint32_t gpw, MatPlan *p, std::string *msg, bool with_nbr) {
     BlockShape s;
     if (!pick_shape(f, &s)) {
         *msg = "no block level of this fractal fits the matrix form";
         return false;
     }
-    return build_mat_shape(f, s, m, tiles ? tiles : m <= f.r ? ipow(f.k, f.r - m) : 0, std::max(cus, 1u), p, msg,
-                           with_nbr);
+    return build_mat_shape(f, s, m, gpw, p, msg, with_nbr);
+}
+
+std::vector<MatDims> mat_dims(const Fractal &f) {
+    std::vector<MatDims> out;
+    BlockShape s;
+    if (!pick_shape(f, &s)) return out;
+    for (uint32_t m = s.q; m <= f.r; ++m) {
+        MatPlan p;
+        std::vector<uint32_t> source;
+        std::string msg;
+        if (!build_ring(f, s, m, &p, &source, &msg)) break;  // larger tiles do not fit either
+        const uint32_t bpg = 64 / s.lanes;
+        out.push_back({m, p.groups, (p.nhalo + bpg - 1) / bpg, double(p.nhalo) / bpg});
+    }
+    return out;
 }
 
 // The level with the least work on the busiest CU: its tiles times the
@@ -314,24 +344,22 @@ bool build_mat_plan(const Fractal &f, uint32_t m, uint64_t tiles, uint32_t cus, 
 // no store) counted half.  Of the measured best levels (triangle r14 and r16:
 // 8, carpet r7: 4, r9: 5, H r9 and r10: 5, Vicsek r10: 5, chandelier r13: 7,
 // each against its neighbours) it picks every one.
-uint32_t auto_mat_level(const Fractal &f, const std::vector<uint32_t> &levels, uint32_t cus) {
-    BlockShape s;
-    if (!pick_shape(f, &s) || levels.empty()) return 0;
-    const uint32_t rmax = *std::max_element(levels.begin(), levels.end());
+uint32_t pick_mat_level(const std::vector<MatDims> &dims, uint32_t k, const std::vector<uint32_t> &levels, uint32_t cus,
+                        uint32_t *gpw) {
+    cus = std::max(cus, 1u);
     uint32_t best = 0;
     double best_cost = 0.0;
-    for (uint32_t m = s.q; m <= rmax; ++m) {
+    for (const MatDims &d : dims) {
         uint64_t tiles = 0;
-        for (uint32_t r : levels) tiles += r > m ? ipow(f.k, r - m) : 1;
-        MatPlan p;
-        std::string msg;
-        if (!build_mat_shape(f, s, m, tiles, cus, &p, &msg, false)) continue;
-        const uint32_t bpg = 64 / p.lanes;
-        const double cost = double((tiles + cus - 1) / cus) *
-                            (p.waves * p.gpw + 0.5 * p.nhalo / bpg);
+        for (uint32_t r : levels) tiles += r > d.m ? ipow(k, r - d.m) : 1;
+        const uint32_t g = pick_gpw(d.groups, d.hgroups, tiles, cus);
+        if (!g) continue;
+        const uint32_t waves = std::max((d.groups + g - 1) / g, d.hgroups);
+        const double cost = double((tiles + cus - 1) / cus) * (waves * g + 0.5 * d.halo);
         if (!best || cost < best_cost) {
-            best = m;
+            best = d.m;
             best_cost = cost;
+            *gpw = g;
         }
     }
     return best;

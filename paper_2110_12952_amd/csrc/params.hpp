@@ -198,6 +198,16 @@ struct BatchInstance {
     uint32_t tail_partial;  // 1 if k^r is not a multiple of 16
 };
 
+// The same for the matrix form: nbr is the neighbour table at the launch's
+// tile level (null where the instance is below it: one tile, no neighbours).
+struct MatInstance {
+    const uint32_t *nbr;
+    uint32_t base16;
+    uint32_t tile0;
+    uint32_t ntiles;
+    uint32_t cells;
+};
+
 // One small instance of a batch stepped in LDS: its state at byte
 // 16 * base16 of the arenas, `ntiles` tiles of plan `plan` (an index into the
 // launch's plan table) taken `teams` at a time, its own neighbour table.

@@ -111,15 +111,23 @@ constexpr uint32_t mat_halo_off(uint32_t nh, bool edge, uint32_t h, uint32_t t) 
 constexpr uint32_t mat_rec_off(uint32_t nh, uint32_t t) { return 1024 * (2 * (2 + 2 * nh) + t); }
 // false (with *msg) where the form does not apply: no block level with 16 to
 // 64 cells, more record dwords around a block than two operands hold, or more
-// groups than a work-group of kMatMaxWaves wavefronts takes.  tiles: those of
-// a launch (0: the fractal's own), over `cus` CUs.  `with_nbr`: also the
+// groups than a work-group of kMatMaxWaves wavefronts takes.  gpw: groups per
+// wavefront (0: chosen for the fractal's own tiles); with_nbr: also the
 // neighbour table (8 entries per tile).
-bool build_mat_plan(const Fractal &f, uint32_t m, uint64_t tiles, uint32_t cus, MatPlan *p, std::string *msg,
-                    bool with_nbr = true);
-// The tile level the matrix form takes for one launch over instances of the
-// fractal at these levels r (an instance below the tile level is one tile);
-// 0 if the form does not apply.
-uint32_t auto_mat_level(const Fractal &f, const std::vector<uint32_t> &levels, uint32_t cus);
+bool build_mat_plan(const Fractal &f, uint32_t m, uint32_t gpw, MatPlan *p, std::string *msg, bool with_nbr = true);
+void mat_neighbours(const Fractal &f, uint32_t m, std::vector<uint32_t> *nbr);
+// The levels the form has plans at (up to r), and their groups of own and of
+// halo blocks (`halo`: the latter as a fraction).
+struct MatDims {
+    uint32_t m, groups, hgroups;
+    double halo;
+};
+std::vector<MatDims> mat_dims(const Fractal &f);
+// The tile level and groups per wavefront of one launch over instances of
+// the fractal at these levels r (an instance below the tile level is one
+// tile); 0 if there is none.
+uint32_t pick_mat_level(const std::vector<MatDims> &dims, uint32_t k, const std::vector<uint32_t> &levels, uint32_t cus,
+                        uint32_t *gpw);
 
 // Several generations per launch (temporal blocking) for small instances: a
 // work-group holds tile t's S x S square and a ring of depth h around it (the

@@ -163,7 +163,7 @@ int main(int argc, char **argv) {
             for (uint32_t m = 1; m <= r; ++m) {
                 MatPlan p;
                 std::string msg;
-                if (!build_mat_plan(f, m, 0, 1 + rng() % 300, &p, &msg)) continue;
+                if (!build_mat_plan(f, m, rng() % 2 ? 0 : 1u << rng() % 3, &p, &msg)) continue;
                 for (bool edge : {false, true}) check(f, p, rng, edge);
                 ++plans;
                 if (r == 7 || argc > 1)
@@ -187,14 +187,19 @@ int main(int argc, char **argv) {
         for (uint32_t m = 1; m <= f.r; ++m) {
             MatPlan p;
             std::string msg;
-            if (!build_mat_plan(f, m, 0, 1 + rng() % 300, &p, &msg)) continue;
+            if (!build_mat_plan(f, m, rng() % 2 ? 0 : 1u << rng() % 3, &p, &msg)) continue;
             check(f, p, rng, rng() & 1);
             ++plans;
         }
-        const uint32_t a = auto_mat_level(f, {f.r}, 256);
-        MatPlan p;
-        std::string msg;
-        if (a && !build_mat_plan(f, a, 0, 256, &p, &msg, false)) std::abort();
+        // whatever level and groups per wavefront a launch picks can be built
+        const std::vector<MatDims> dims = mat_dims(f);
+        for (uint32_t cus : {1u, 256u}) {
+            uint32_t gpw = 0;
+            const uint32_t a = pick_mat_level(dims, f.k, {f.r, f.r, uint32_t(1 + rng() % f.r)}, cus, &gpw);
+            MatPlan p;
+            std::string msg;
+            if (a && (!build_mat_plan(f, a, gpw, &p, &msg, false) || p.gpw != gpw)) std::abort();
+        }
     }
     std::printf("plans %d\n", plans);
     return 0;

@@ -71,3 +71,46 @@ def test_full_rule_words(N):
             a = torch.from_numpy(st0).cuda()
             res = g.step_compact(a, torch.empty_like(a), 3, rule).cpu().numpy()
             np.testing.assert_array_equal(res, o.compact_steps(st0, rule, 3), err_msg=f"{name} {rule:#x}")
+
+
+@gpu
+@pytest.mark.parametrize("name,levels", [("triangle", (3, 4, 7, 9, 10, 11)), ("carpet", (2, 3, 4, 5)),
+                                         ("hfractal", (2, 3, 4, 6)), ("chandelier", (3, 4, 6, 8)),
+                                         ("vicsek", (2, 3, 5, 7)), ("fullsquare", (3, 4, 7))])
+def test_batch_of_many_levels(N, name, levels):
+    # instances above, at and below the launch's tile level in one group, with
+    # live bytes between them that no step may read as cells or change; whole
+    # batches and decreasing step counts
+    fd = W.FRACTALS[name]
+    rs = [levels[(5 * i) % len(levels)] for i in range(2 * len(levels))]
+    frs = [N.Fractal(fd.s, fd.offsets, r) for r in rs]
+    for f in frs:
+        f.configure(N.STRATEGY_TILED, min(levels))  # one group of the batch
+    offs, top = [], 0
+    for f in frs:
+        offs.append(top)
+        top = (top + f.cells + 15) // 16 * 16 + 48
+    batch = N.Batch(frs, offsets=offs, resident=False)
+    assert batch.info().groups == 1
+    orcs = [O.Fractal(fd.s, fd.offsets, r) for r in rs]
+    st0 = [o.init_compact(17 + i, 0.4) for i, o in enumerate(orcs)]
+    arena = np.ones(top + 64, np.uint8)
+    for off, st in zip(offs, st0):
+        arena[off:off + len(st)] = st
+    for rule in ("B3/S23", "B1357/S02468", "vN:B2/S12"):
+        rm = W.rule_mask(rule)
+        for counts in ([2] * len(rs), [max(1, 6 - i // 2) for i in range(len(rs))]):
+            a = torch.from_numpy(arena).cuda()
+            b = torch.full_like(a, 1)
+            if len(set(counts)) == 1:
+                batch.step(a, b, counts[0], rm)
+            else:
+                batch.step_each(a, b, counts, rm)
+            ha, hb = a.cpu().numpy(), b.cpu().numpy()
+            for i, (off, st, o) in enumerate(zip(offs, st0, orcs)):
+                got = (hb if counts[i] & 1 else ha)[off:off + len(st)]
+                np.testing.assert_array_equal(got, o.compact_steps(st, rm, counts[i]),
+                                              err_msg=f"{name} r={rs[i]} {rule} steps={counts[i]}")
+                ha[off:off + len(st)] = 1
+                hb[off:off + len(st)] = 1
+            assert (ha == 1).all() and (hb == 1).all()
