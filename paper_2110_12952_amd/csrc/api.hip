@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <array>
 #include <cstring>
 #include <functional>
 #include <map>
@@ -63,6 +64,11 @@ struct nbb_fractal {
     DevBlob dmat;
     MatParams matp{};
     std::vector<MatDims> mat_levels;
+    // Several generations per launch in the same form, for calls of several.
+    HoldPlan hold;
+    DevBlob dhold;
+    HoldParams holdp{};
+    std::vector<HoldDims> hold_levels;
     // For batches, made on first use and kept: plans without neighbours by
     // (tile level, groups per wavefront), neighbour tables by tile level.
     struct MatTables {
@@ -73,11 +79,18 @@ struct nbb_fractal {
     mutable std::mutex mat_mu;
     mutable std::map<std::pair<uint32_t, uint32_t>, MatTables> mat_plans;
     mutable std::map<uint32_t, DevBlob> mat_nbrs;
+    struct HoldTables {
+        HoldPlan plan;
+        DevBlob blob;
+        HoldParams p{};
+    };
+    mutable std::map<std::array<uint32_t, 3>, HoldTables> hold_plans;  // by level, rings, groups per wavefront
     // Several generations per launch (NBB_STRATEGY_TEMPORAL): the plan and
     // its device tables; the tile plan above stays for batches.
     TemporalPlan temporal;
     DevBlob dtemp;
     TemporalParams tmp{};
+    bool temporal_auto = false;  // no level or depth asked for: the held plan where there is one
     int device = 0;
     int cu_count = 256;
     DevBlob dmap, dtile, dbox, dmfma;
@@ -112,6 +125,19 @@ struct nbb_temporal_plan {
     TemporalPlan plan;
 };
 
+// Instances of one fractal stepped several generations per launch in the
+// matrix form: `hp` with the set's tiles and their neighbours.
+struct HeldSet {
+    bool ok = false;
+    bool in_place = false;            // every tile is a whole instance: results without alternating arenas
+    HoldParams hp{};
+    uint32_t al = 0, nr = 0, nh = 0, gpw = 0;
+    const uint32_t *rec = nullptr;
+    uint32_t *steps = nullptr;        // device: one generation count per instance (nbb_batch_step_each)
+    std::vector<uint32_t> index;      // the instances (caller's numbering), in tile order
+    std::vector<uint64_t> tiles_end;  // tiles of the first j+1 of them
+};
+
 // A batch: groups of instances that share a tile plan, each stepped by one
 // launch over the group's tiles, and instances stepped one by one.
 struct BatchGroup {
@@ -119,6 +145,7 @@ struct BatchGroup {
     bool matrix = false;     // stepped on the matrix cores (mp, with the batch's nbr / ntiles)
     MatParams mp{};
     uint32_t al = 0, nr = 0, nh = 0, gpw = 0;
+    HeldSet held;            // and several generations per launch (tiles of its own)
     bool edges = false;      // else in edge-record form (ep, with the batch's nbr / ntiles)
     EdgeParams ep{};
     uint32_t BS = 0, nsrc = 0;
@@ -152,6 +179,7 @@ struct nbb_batch {
     uint64_t cells = 0, tiles = 0, arena_bytes = 0;
     std::vector<BatchGroup> groups;
     ResidentSet resident;
+    std::vector<HeldSet> small;  // instances counted as resident that one work-group each holds in registers
     std::vector<BatchDirect> direct;
     DevBlob dtab;
     // with group or direct launches beside it, the resident launch runs on the
@@ -388,6 +416,31 @@ nbb_status upload_matrix(const MatPlan &p, DevBlob *blob, MatParams *T) {
     return NBB_OK;
 }
 
+// The same for a held plan; `nbr`: its tiles' neighbours.
+nbb_status upload_hold(const HoldPlan &p, const std::vector<uint32_t> &nbr, DevBlob *blob, HoldParams *T) {
+    const void *src[4] = {p.A.data(), p.raddr.data(), p.halo.data(), nbr.data()};
+    size_t bytes[4] = {p.A.size(), p.raddr.size() * 4, p.halo.size() * 4, nbr.size() * 4};
+    void *dst[4];
+    nbb_status s = upload(blob, src, bytes, 4, dst);
+    if (s != NBB_OK) return s;
+    *T = HoldParams{};
+    T->K = p.K;
+    T->CB = p.CB;
+    T->lanes = p.lanes;
+    T->nblk = p.nblk;
+    T->ntot = p.ntot;
+    T->rs = p.rs;
+    T->zero = p.zero;
+    T->waves = p.waves;
+    T->gens = p.gens;
+    T->ntiles = uint32_t(p.ntiles);
+    T->A = static_cast<const int8_t *>(dst[0]);
+    T->raddr = static_cast<const uint32_t *>(dst[1]);
+    T->halo = static_cast<const uint32_t *>(dst[2]);
+    T->nbr = static_cast<const uint32_t *>(dst[3]);
+    return NBB_OK;
+}
+
 // Builds and uploads the matrix plan of a descriptor at its own tile level
 // (nothing where the form does not apply).
 nbb_status setup_matrix(nbb_fractal *F) {
@@ -404,6 +457,20 @@ nbb_status setup_matrix(nbb_fractal *F) {
     p.halo.clear();
     p.nbr.clear();
     F->mat = std::move(p);
+    F->hold_levels = hold_dims(F->f);
+    HoldDims d{};
+    HoldPlan h;
+    if (!pick_hold(F->hold_levels, F->f.k, {F->f.r}, uint32_t(F->cu_count), &d, &gpw) ||
+        !build_hold_plan(F->f, d.m, d.rings, gpw, &h, &msg))
+        return NBB_OK;
+    std::vector<uint32_t> nbr;
+    mat_neighbours(F->f, d.m, &nbr);
+    st = upload_hold(h, nbr, &F->dhold, &F->holdp);
+    if (st != NBB_OK) return st;
+    h.A.clear();
+    h.raddr.clear();
+    h.halo.clear();
+    F->hold = std::move(h);
     return NBB_OK;
 }
 
@@ -420,6 +487,17 @@ const nbb_fractal::MatTables *batch_mat_plan(const nbb_fractal *F, uint32_t m, u
     t.plan.nbr.assign(8, 0xFFFFFFFFu);
     if (upload_matrix(t.plan, &t.blob, &t.p) != NBB_OK) return nullptr;
     return &(F->mat_plans[key] = std::move(t));
+}
+const nbb_fractal::HoldTables *batch_hold_plan(const nbb_fractal *F, const HoldDims &d, uint32_t gpw) {
+    std::lock_guard<std::mutex> lock(F->mat_mu);
+    const std::array<uint32_t, 3> key = {d.m, d.rings, gpw};
+    auto it = F->hold_plans.find(key);
+    if (it != F->hold_plans.end()) return &it->second;
+    nbb_fractal::HoldTables t;
+    std::string msg;
+    if (!build_hold_plan(F->f, d.m, d.rings, gpw, &t.plan, &msg)) return nullptr;
+    if (upload_hold(t.plan, std::vector<uint32_t>(8, 0xFFFFFFFFu), &t.blob, &t.p) != NBB_OK) return nullptr;
+    return &(F->hold_plans[key] = std::move(t));
 }
 const uint32_t *batch_mat_nbr(const nbb_fractal *F, uint32_t m) {
     if (m == F->mat.m && F->matp.nbr) return F->matp.nbr;
@@ -694,6 +772,7 @@ nbb_status nbb_create(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r
         blob_free(&F->dtile);
         blob_free(&F->dedge);
         blob_free(&F->dmat);
+        blob_free(&F->dhold);
         blob_free(&F->dmfma);
         delete F;
         return st;
@@ -706,6 +785,7 @@ void nbb_destroy(nbb_fractal *F) {
     if (!F) return;
     for (auto &t : F->mat_plans) blob_free(&t.second.blob);
     for (auto &t : F->mat_nbrs) blob_free(&t.second);
+    for (auto &t : F->hold_plans) blob_free(&t.second.blob);
     blob_free(&F->dres);
     blob_free(&F->dpk);
     blob_free(&F->dtemp);
@@ -714,6 +794,7 @@ void nbb_destroy(nbb_fractal *F) {
     blob_free(&F->dtile);
     blob_free(&F->dedge);
     blob_free(&F->dmat);
+    blob_free(&F->dhold);
     blob_free(&F->dmfma);
     delete F;
 }
@@ -739,7 +820,7 @@ nbb_status nbb_query(const nbb_fractal *F, nbb_info *info) {
         info->tile_side = 1;
     }
     info->bbox_pitch = box_pitch(F->f);
-    info->device_table_bytes = F->dmap.bytes + F->dbox.bytes + F->dtile.bytes + F->dedge.bytes + F->dmat.bytes + F->dmfma.bytes;
+    info->device_table_bytes = F->dmap.bytes + F->dbox.bytes + F->dtile.bytes + F->dedge.bytes + F->dmat.bytes + F->dhold.bytes + F->dmfma.bytes;
     uint32_t ebpt = 0, ehpt = 0;
     if (F->use_edges && edge_case(F->edge.nblk, F->edge.nhalo, &ebpt, &ehpt)) info->lds_bytes = edge_lds_bytes(ebpt, ehpt);
     info->tiled_form = F->strategy == NBB_STRATEGY_DIRECT ? 0u : (F->use_edges ? 1u : 2u);
@@ -872,6 +953,7 @@ nbb_status nbb_configure_temporal(nbb_fractal *F, uint32_t tile_level, uint32_t 
     F->dtemp = blob;
     F->temporal = std::move(plan);
     F->tmp = T;
+    F->temporal_auto = tile_level == 0 && depth == 0;
     F->strategy = NBB_STRATEGY_TEMPORAL;
     return NBB_OK;
 }
@@ -1174,7 +1256,83 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         else
             launch.add(F, i, I, same_plan);
     }
+    // Resident instances of a fractal that one work-group holds in registers
+    // (its largest as one tile of a held plan) leave the LDS launch.
+    struct HeldBuild {
+        const nbb_fractal::HoldTables *plan = nullptr;
+        const nbb_fractal *top = nullptr;
+        std::vector<MatInstance> members;
+        std::vector<uint32_t> index;
+        size_t off_inst = 0, off_rec = 0, off_nbr = 0, off_steps = 0, tiles = 0;
+    };
+    auto held_members = [&](HeldBuild &H, uint32_t m) {
+        uint64_t t = 0;
+        for (uint32_t i : H.index) {
+            const nbb_fractal *F = fractals[i];
+            MatInstance I{};
+            I.base16 = uint32_t(offsets[i] >> 4);
+            I.tile0 = uint32_t(t);
+            I.ntiles = 1;
+            I.cells = uint32_t(F->f.cells);
+            if (F->f.r > m) {
+                for (uint32_t l = m; l < F->f.r; ++l) I.ntiles *= F->f.k;
+                I.nbr = batch_mat_nbr(F, m);
+                if (!I.nbr) return false;
+            }
+            t += I.ntiles;
+            H.members.push_back(I);
+        }
+        H.tiles = t;
+        return t * 8 <= (uint64_t(1) << 31);
+    };
+    std::vector<HeldBuild> small;
+    if (!fixed) {
+        for (size_t g = 0; g < res.reps.size(); ++g) {
+            const nbb_fractal *R = res.reps[g];
+            size_t h = 0;
+            auto same_fractal = [&](const nbb_fractal *x) {
+                if (x->f.k != R->f.k || x->f.s != R->f.s) return false;
+                for (uint32_t j = 0; j < x->f.k; ++j)
+                    if (x->f.ox[j] != R->f.ox[j] || x->f.oy[j] != R->f.oy[j]) return false;
+                return true;
+            };
+            while (h < small.size() && !same_fractal(small[h].top)) ++h;
+            if (h == small.size()) {
+                small.emplace_back();
+                small[h].top = R;
+            }
+            for (uint32_t i : res.index[g]) {
+                small[h].index.push_back(i);
+                if (fractals[i]->f.r > small[h].top->f.r) small[h].top = fractals[i];
+            }
+        }
+        for (size_t h = 0; h < small.size();) {
+            HeldBuild &H = small[h];
+            bool all = true;
+            for (uint32_t i : H.index) all = all && fractals[i]->use_matrix;
+            const HoldDims *d = nullptr;
+            for (const HoldDims &x : H.top->hold_levels)
+                if (!x.rings) d = &x;
+            if (all && d) H.plan = batch_hold_plan(H.top, *d, d->groups <= 16 ? 1 : (d->groups <= 32 ? 2 : 4));
+            if (H.plan && !held_members(H, d->m)) H.plan = nullptr;
+            if (H.plan) ++h;
+            else small.erase(small.begin() + ptrdiff_t(h));
+        }
+        // the rest stays with the LDS launch
+        std::vector<uint8_t> taken(count, 0);
+        for (const HeldBuild &H : small)
+            for (uint32_t i : H.index) taken[i] = 1;
+        Part rest;
+        for (size_t g = 0; g < res.reps.size(); ++g)
+            for (size_t j = 0; j < res.index[g].size(); ++j) {
+                const uint32_t i = res.index[g][j];
+                if (taken[i]) B->tiles += res.members[g][j].ntiles;
+                else rest.add(fractals[i], i, res.members[g][j], same_resident);
+            }
+        res = std::move(rest);
+    }
     const size_t ng = launch.reps.size(), nr = res.reps.size();
+    std::vector<HeldBuild> held(ng);
     // A group whose descriptors all run the matrix form takes it, at one tile
     // level for all of its instances (those below it are one tile each).  Not
     // without allocation: its tables are made on first use.
@@ -1215,7 +1373,15 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             t += I.ntiles;
             M.members.push_back(I);
         }
-        if (M.plan && t * 8 <= (uint64_t(1) << 31)) mat[g] = std::move(M);
+        if (!M.plan || t * 8 > (uint64_t(1) << 31)) continue;
+        mat[g] = std::move(M);
+        HoldDims d{};
+        if (!pick_hold(top->hold_levels, top->f.k, levels, uint32_t(top->cu_count), &d, &gpw)) continue;
+        HeldBuild H;
+        H.top = top;
+        H.index = index;
+        H.plan = batch_hold_plan(top, d, gpw);
+        if (H.plan && held_members(H, d.m)) held[g] = std::move(H);
     }
     // One device allocation: per group the instance table, the records
     // (2 words per tile, 4 for the matrix form) and the neighbour table (8
@@ -1253,6 +1419,19 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         off_nbr[g] = total;
         total += align256(std::max<size_t>(t * 32, 1));
     }
+    auto place_held = [&](HeldBuild &H) {
+        if (!H.plan) return;
+        H.off_inst = total;
+        total += align256(H.members.size() * sizeof(MatInstance));
+        H.off_rec = total;
+        total += align256(H.tiles * 16);
+        H.off_nbr = total;
+        total += align256(H.tiles * 32);
+        H.off_steps = total;
+        total += align256(H.members.size() * 4);
+    };
+    for (HeldBuild &H : held) place_held(H);
+    for (HeldBuild &H : small) place_held(H);
     size_t nres = 0;
     for (size_t g = 0; g < nr; ++g) {
         for (const BatchInstance &I : res.members[g]) B->tiles += I.ntiles;
@@ -1281,6 +1460,43 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *base = fixed ? reinterpret_cast<char *>(fixed) : static_cast<char *>(B->dtab.ptr);
+    auto make_held = [&](const HeldBuild &H, HeldSet *S) -> hipError_t {
+        if (!H.plan) return hipSuccess;
+        auto *inst = reinterpret_cast<MatInstance *>(base + H.off_inst);
+        auto *rec = reinterpret_cast<uint32_t *>(base + H.off_rec);
+        auto *nbr = reinterpret_cast<uint32_t *>(base + H.off_nbr);
+        hipError_t err = hipMemcpyAsync(inst, H.members.data(), H.members.size() * sizeof(MatInstance),
+                                        hipMemcpyHostToDevice, s);
+        if (err == hipSuccess) err = hipStreamSynchronize(s);  // the host table goes out of scope
+        if (err == hipSuccess)
+            err = launch_batch_tiles_matrix(inst, uint32_t(H.members.size()), uint32_t(H.tiles), rec, nbr, s);
+        if (err != hipSuccess) return err;
+        const HoldPlan &p = H.plan->plan;
+        S->ok = true;
+        S->hp = H.plan->p;
+        S->hp.nbr = nbr;
+        S->hp.ntiles = uint32_t(H.tiles);
+        S->al = mat_align_of(p.CB);
+        S->nr = p.nr;
+        S->nh = p.nh;
+        S->gpw = p.gpw;
+        S->rec = rec;
+        S->steps = reinterpret_cast<uint32_t *>(base + H.off_steps);
+        S->index = H.index;
+        for (const MatInstance &I : H.members) S->tiles_end.push_back(uint64_t(I.tile0) + I.ntiles);
+        return hipSuccess;
+    };
+    for (const HeldBuild &H : small) {
+        HeldSet S;
+        e = make_held(H, &S);
+        if (e != hipSuccess) {
+            batch_free(B);
+            return hip_fail(e, "batch table build");
+        }
+        S.in_place = true;
+        B->small.push_back(std::move(S));
+        B->cu_count = H.top->cu_count;
+    }
     for (size_t g = 0; g < ng; ++g) {
         auto *inst = reinterpret_cast<BatchInstance *>(base + off_inst[g]);
         auto *rec = reinterpret_cast<uint32_t *>(base + off_rec[g]);
@@ -1310,6 +1526,11 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             G.rec = rec;
             G.index = launch.index[g];
             for (const MatInstance &I : mem) G.tiles_end.push_back(uint64_t(I.tile0) + I.ntiles);
+            e = make_held(held[g], &G.held);
+            if (e != hipSuccess) {
+                batch_free(B);
+                return hip_fail(e, "batch table build");
+            }
             B->groups.push_back(std::move(G));
             B->cu_count = launch.reps[g]->cu_count;
             continue;
@@ -1402,8 +1623,8 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             return hip_fail(e, "batch stream");
         }
     }
-    if (!fixed && B->groups.size() > 1) {
-        const size_t ns = std::min<size_t>(B->groups.size() - 1, kGroupStreams);
+    if (!fixed && B->groups.size() + B->small.size() > 1) {
+        const size_t ns = std::min<size_t>(B->groups.size() + B->small.size() - 1, kGroupStreams);
         e = hipEventCreateWithFlags(&B->gfork, hipEventDisableTiming);
         for (size_t i = 0; i < ns && e == hipSuccess; ++i) {
             hipStream_t gs = nullptr;
@@ -1440,6 +1661,7 @@ nbb_status nbb_batch_query(const nbb_batch *B, nbb_batch_info *info) {
     info->groups = uint32_t(B->groups.size());
     info->direct = uint32_t(B->direct.size());
     info->resident = uint32_t(B->resident.index.size());
+    for (const HeldSet &S : B->small) info->resident += uint32_t(S.index.size());
     info->cells = B->cells;
     info->tiles = B->tiles;
     info->arena_bytes = B->arena_bytes;
@@ -1499,6 +1721,68 @@ static hipError_t batch_fork_groups(const nbb_batch *B, hipStream_t s) {
 static hipStream_t batch_group_stream(const nbb_batch *B, size_t k, hipStream_t s) {
     return (k == 0 || B->gstream.empty()) ? s : B->gstream[(k - 1) % B->gstream.size()];
 }
+// Launches of a held set that take `n` generations of an instance.
+static uint32_t held_launches(const HeldSet &S, uint32_t n) {
+    uint32_t L = n / S.hp.gens + (n % S.hp.gens != 0);
+    if (!S.in_place) L += (L ^ n) & 1;
+    return L;
+}
+// `steps` generations of every instance of the set, or counts[i] of instance
+// i; *used = false (nothing enqueued) where that takes about as many launches
+// as one per generation.
+static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t arena_len, uint32_t steps,
+                            const uint32_t *counts, uint32_t rule, hipStream_t s, bool *used) {
+    *used = false;
+    if (!S.ok) return hipSuccess;
+    uint32_t L = 0, most = steps;
+    std::vector<uint32_t> n;
+    if (counts) {
+        most = 0;
+        n.resize(S.index.size());
+        for (size_t j = 0; j < n.size(); ++j) {
+            n[j] = counts[S.index[j]];
+            most = std::max(most, n[j]);
+            L = std::max(L, held_launches(S, n[j]));
+        }
+    } else {
+        L = held_launches(S, steps);
+    }
+    if (!S.in_place && 2 * uint64_t(L) > most) return hipSuccess;
+    *used = true;
+    if (!L) return hipSuccess;
+    if (counts) {
+        hipError_t e = launch_set_words(S.steps, n.data(), uint32_t(n.size()), s);
+        if (e != hipSuccess) return e;
+    }
+    uint8_t *in = a, *out = b;
+    size_t live = S.index.size();
+    for (uint32_t i = 0; i < L; ++i) {
+        HoldParams E = S.hp;
+        if (counts) {
+            while (live && held_launches(S, n[live - 1]) <= i) --live;  // (instances before may be done too: those tiles end at once)
+            if (!live) break;
+            E.ntiles = uint32_t(S.tiles_end[live - 1]);
+        }
+        // in place: back to a until the last launch of a whole-batch call
+        uint8_t *dst = S.in_place && !counts && (i + 1 < L || !(steps & 1)) ? a : out;
+        const uint32_t g = counts ? 0 : steps / L + (i < steps % L ? 1u : 0u);
+        hipError_t e = launch_step_hold(E, S.al, S.nr, S.nh, S.gpw, in, dst, arena_len, rule, g, S.rec,
+                                        counts ? S.steps : nullptr, i, S.in_place ? 1u : 0u, s);
+        if (e != hipSuccess) return e;
+        if (!S.in_place) std::swap(in, out);
+    }
+    return hipSuccess;
+}
+static hipError_t held_step_small(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t arena_len, uint32_t steps,
+                                  const uint32_t *counts, uint32_t rule, hipStream_t s) {
+    hipError_t e = hipSuccess;
+    for (size_t k = 0; k < B->small.size() && e == hipSuccess; ++k) {
+        bool used = false;
+        e = held_step(B->small[k], a, b, arena_len, steps, counts, rule,
+                      batch_group_stream(B, B->groups.size() + k, s), &used);
+    }
+    return e;
+}
 static hipError_t batch_join_groups(const nbb_batch *B, hipStream_t s) {
     hipError_t e = hipSuccess;
     for (size_t i = 0; i < B->gstream.size() && e == hipSuccess; ++i) {
@@ -1532,8 +1816,10 @@ nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t a
     for (size_t k = 0; k < B->groups.size() && e == hipSuccess; ++k) {
         const BatchGroup &G = B->groups[k];
         const hipStream_t gs = batch_group_stream(B, k, s);
+        bool used = false;
+        e = held_step(G.held, a, b, arena_len, steps, nullptr, rule, gs, &used);
         uint8_t *in = a, *out = b;
-        for (uint32_t i = 0; i < steps && e == hipSuccess; ++i) {
+        for (uint32_t i = 0; i < steps && e == hipSuccess && !used; ++i) {
             e = G.matrix  ? launch_step_matrix(G.mp, G.al, G.nr, G.nh, G.gpw, in, out, arena_len, rule, G.rec,
                                                B->cu_count, gs)
                 : G.edges ? launch_step_edges(G.ep, G.BS, G.nsrc, in, out, arena_len, rule, G.rec, B->cu_count, gs)
@@ -1541,6 +1827,7 @@ nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t a
             std::swap(in, out);
         }
     }
+    if (e == hipSuccess) e = held_step_small(B, a, b, arena_len, steps, nullptr, rule, s);
     const char *what = "batch step launch";
     for (size_t j = 0; j < B->direct.size() && e == hipSuccess; ++j) {
         const nbb_fractal *F = B->direct[j].f;
@@ -1595,8 +1882,10 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
         const BatchGroup &G = B->groups[k];
         const hipStream_t gs = batch_group_stream(B, k, s);
         size_t live = G.index.size();
+        bool used = false;
+        e = held_step(G.held, a, b, arena_len, 0, steps, rule, gs, &used);
         uint8_t *in = a, *out = b;
-        for (uint32_t g = 0; g < most && e == hipSuccess; ++g) {
+        for (uint32_t g = 0; g < most && e == hipSuccess && !used; ++g) {
             while (live && steps[G.index[live - 1]] <= g) --live;
             if (!live) break;
             const uint32_t nt = uint32_t(G.tiles_end[live - 1]);
@@ -1616,6 +1905,7 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
             std::swap(in, out);
         }
     }
+    if (e == hipSuccess) e = held_step_small(B, a, b, arena_len, 0, steps, rule, s);
     const char *what = "batch step launch";
     for (size_t j = 0; j < B->direct.size() && e == hipSuccess; ++j) {
         const BatchDirect &d = B->direct[j];
@@ -1922,7 +2212,17 @@ nbb_status nbb_step_compact(const nbb_fractal *F, uint8_t *a, uint8_t *b, uint64
     if (result_in_b) *result_in_b = int(steps & 1);
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *in = a, *out = b;
-    if (F->strategy == NBB_STRATEGY_TEMPORAL) {
+    if (F->strategy == NBB_STRATEGY_TEMPORAL && F->temporal_auto && F->hold.ok) {
+        const HoldPlan &h = F->hold;
+        uint32_t L = steps / h.gens + (steps % h.gens != 0);
+        L += (L ^ steps) & 1;
+        for (uint32_t i = 0; i < L; ++i) {
+            hipError_t e = launch_step_hold(F->holdp, mat_align_of(h.CB), h.nr, h.nh, h.gpw, in, out, F->f.cells, rule,
+                                            steps / L + (i < steps % L ? 1u : 0u), nullptr, nullptr, 0, 0, s);
+            if (e != hipSuccess) return hip_fail(e, "held step launch");
+            std::swap(in, out);
+        }
+    } else if (F->strategy == NBB_STRATEGY_TEMPORAL) {
         // L launches of up to h generations each; the result must end in b
         // iff steps is odd, so L takes the parity of steps (one more launch
         // when needed: then L < steps, so every launch still has one)
@@ -1937,7 +2237,25 @@ nbb_status nbb_step_compact(const nbb_fractal *F, uint8_t *a, uint8_t *b, uint64
         }
     } else if (F->use_matrix) {
         const MatPlan &p = F->mat;
-        for (uint32_t i = 0; i < steps; ++i) {
+        uint32_t left = steps;
+        // All but the last generation several at a time, in a number of
+        // launches of the same parity, so that both buffers end as they would
+        // with one launch per generation.
+        if (F->hold.ok && steps >= 4) {
+            const HoldPlan &h = F->hold;
+            const uint32_t T = steps - 1;
+            uint32_t L = T / h.gens + (T % h.gens != 0);
+            L += (L ^ T) & 1;
+            for (uint32_t i = 0; i < L && 2 * L <= T; ++i) {
+                const uint32_t g = T / L + (i < T % L ? 1u : 0u);
+                hipError_t e = launch_step_hold(F->holdp, mat_align_of(h.CB), h.nr, h.nh, h.gpw, in, out, F->f.cells,
+                                                rule, g, nullptr, nullptr, 0, 0, s);
+                if (e != hipSuccess) return hip_fail(e, "held step launch");
+                std::swap(in, out);
+                left -= g;
+            }
+        }
+        for (uint32_t i = 0; i < left; ++i) {
             hipError_t e = launch_step_matrix(F->matp, mat_align_of(p.CB), p.nr, p.nh, p.gpw, in, out, F->f.cells, rule,
                                               nullptr, F->cu_count, s);
             if (e != hipSuccess) return hip_fail(e, "matrix step launch");

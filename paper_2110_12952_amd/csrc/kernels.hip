@@ -1169,6 +1169,28 @@ hipError_t launch_step_matrix(const MatParams &E0, uint32_t al, uint32_t nr, uin
     NBB_MAT_GO(false, 1);
 #undef NBB_MAT_GO
 }
+hipError_t launch_step_hold(const HoldParams &E0, uint32_t al, uint32_t nr, uint32_t nh, uint32_t gpw,
+                            uint8_t *in, uint8_t *out, uint64_t limit, uint32_t rule, uint32_t gens,
+                            const uint32_t *rec, const uint32_t *steps_of, uint32_t launch, uint32_t in_place, hipStream_t st) {
+    HoldParams E = E0;
+    E.limit = limit;
+    const bool life = rule == kRuleB3S23;
+#define NBB_HOLD_GO(B, R)                                                                                          \
+    do {                                                                                                            \
+        if (al == 16)                                                                                               \
+            return launch_hold_inst<B, R, 16>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, in_place, st);      \
+        if (al == 4)                                                                                                \
+            return launch_hold_inst<B, R, 4>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, in_place, st);       \
+        return launch_hold_inst<B, R, 1>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, in_place, st);           \
+    } while (0)
+    if (rec) {
+        if (life) NBB_HOLD_GO(true, 0);
+        NBB_HOLD_GO(true, 1);
+    }
+    if (life) NBB_HOLD_GO(false, 0);
+    NBB_HOLD_GO(false, 1);
+#undef NBB_HOLD_GO
+}
 hipError_t launch_step_tiled(const MapParams &P, const TileParams &T, const uint8_t *in, uint8_t *out,
                              uint32_t rule, int cu_count, hipStream_t st) {
     return launch_tiled_any<false>(P, T, in, out, rule, nullptr, cu_count, st);
@@ -1256,7 +1278,7 @@ __global__ __launch_bounds__(256) void k_batch_tiles_matrix(const MatInstance *_
         }
         const MatInstance &I = inst[lo];
         const uint32_t t = g - I.tile0;
-        reinterpret_cast<uint4 *>(rec)[g] = make_uint4(I.base16, t, I.cells, 0);
+        reinterpret_cast<uint4 *>(rec)[g] = make_uint4(I.base16, t, I.cells, lo);
         uint4 *d4 = reinterpret_cast<uint4 *>(nbr + 8 * uint64_t(g));
         if (I.nbr) {
             const uint4 *s4 = reinterpret_cast<const uint4 *>(I.nbr + 8 * uint64_t(t));

@@ -53,6 +53,12 @@ hipError_t launch_step_edges(const EdgeParams &E, uint32_t BS, uint32_t nsrc, co
 hipError_t launch_step_matrix(const MatParams &E, uint32_t al, uint32_t nr, uint32_t nh, uint32_t gpw,
                               const uint8_t *in, uint8_t *out, uint64_t limit, uint32_t rule, const uint32_t *rec,
                               int cu_count, hipStream_t st);
+// `gens` <= E.gens generations of every tile of a held plan in one launch; in a
+// batch with steps_of (device array, one count per instance) launch number
+// `launch` of a call, see k_step_hold.
+hipError_t launch_step_hold(const HoldParams &E, uint32_t al, uint32_t nr, uint32_t nh, uint32_t gpw,
+                            uint8_t *in, uint8_t *out, uint64_t limit, uint32_t rule, uint32_t gens,
+                            const uint32_t *rec, const uint32_t *steps_of, uint32_t launch, uint32_t in_place, hipStream_t st);
 // The tiled step over the tiles of a batch (tables from launch_batch_tiles,
 // T.ntiles = batch tiles, T.nbr = the batch neighbour table).
 hipError_t launch_step_tiled_batch(const TileParams &T, const uint32_t *rec, const uint8_t *arena_in,
@@ -80,7 +86,7 @@ hipError_t launch_set_words(uint32_t *dst, const uint32_t *src, uint32_t n, hipS
 hipError_t launch_batch_tiles(const BatchInstance *inst, uint32_t ninst, uint32_t total, uint32_t *rec,
                               uint32_t *nbr, hipStream_t st);
 // The same for the matrix form: four words per tile (arena offset / 16, local
-// tile, cells of the instance, 0) and eight neighbours.
+// tile, cells of the instance, number of the instance) and eight neighbours.
 hipError_t launch_batch_tiles_matrix(const MatInstance *inst, uint32_t ninst, uint32_t total, uint32_t *rec,
                                      uint32_t *nbr, hipStream_t st);
 // `gens` <= T.h generations of every tile of a temporal plan in one launch

@@ -50,6 +50,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "device_common.hpp"
 #include "plan.hpp"
@@ -101,10 +102,22 @@ __device__ __forceinline__ u32x4 mat_align(const MatRaw<AL> &m, uint32_t off) {
 __device__ __forceinline__ i32x4 mat_mul(u32x4 a, u32x4 b, i32x4 c) {
     return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), c, 0, 0, 0);
 }
-// Four results of at most 255 each as the bytes of a dword.
+// Four results of at most 255 each as the bytes of a dword, in three
+// instructions (left to itself the compiler regroups the shifts into four).
 __device__ __forceinline__ uint32_t mat_bytes(i32x4 d) {
-    return ((uint32_t(d[3]) << 8 | uint32_t(d[2])) << 8 | uint32_t(d[1])) << 8 | uint32_t(d[0]);
+    const uint32_t lo = uint32_t(d[0]) | uint32_t(d[1]) << 8, hi = uint32_t(d[2]) | uint32_t(d[3]) << 8;
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
+// LDS by address: kept in a register as it is (left to itself the compiler
+// keeps packed 16-bit offsets and unpacks them at every use).
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+__device__ __forceinline__ uint32_t lds_at(const uint8_t *base, uint32_t off) {
+    uint32_t a = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const uint8_t *)base)) + off;
+    asm("" : "+v"(a));
+    return a;
+}
+__device__ __forceinline__ uint32_t lds_get(uint32_t a) { return *reinterpret_cast<lds_u32 *>(uintptr_t(a)); }
+__device__ __forceinline__ void lds_put(uint32_t a, uint32_t v) { *reinterpret_cast<lds_u32 *>(uintptr_t(a)) = v; }
 
 // Next states of four cells: n their live-neighbour counts, o the cells.
 template <int RULE>
@@ -325,6 +338,172 @@ static hipError_t launch_matrix_t(const MatParams &E, const uint8_t *in, uint8_t
     return hipGetLastError();
 }
 
+// Several generations of the matrix form per launch (HoldParams): a work-group
+// per tile holds the tile's blocks and those around it in registers, 16 cells
+// per lane as above, for all of the launch's generations; only the records go
+// through LDS (double-buffered, one barrier per generation).  The state is
+// read and written once per launch instead of once per generation, and a
+// generation of a small state costs a barrier instead of a launch.
+//   BUF: the second record buffer's offset (an instruction offset).
+//   BATCH: rec as above; word 3 of a tile's record indexes steps_of, the
+//   generations its instance takes in the whole call (steps_of NULL: every
+//   instance takes `gens` now).  The call's launches number `launch` from 0;
+//   an instance takes its generations in as few launches as E.gens allows
+//   and nothing in launches past those.  in_place 0: launches alternate the
+//   buffers, so there is one more where needed for their number to have the
+//   parity of its generations (the result's buffer).  in_place 1 (tiles that
+//   are whole instances): every launch writes back to `in`, an instance's last
+//   one to `out` if its count is odd.
+template <int AL, int NR, int NH, int GPW, int BUF, bool BATCH, int RULE>
+__global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, uint8_t *in, uint8_t *out,
+                                                                  uint32_t rule, uint32_t gens,
+                                                                  const uint32_t *__restrict__ rec,
+                                                                  const uint32_t *__restrict__ steps_of,
+                                                                  uint32_t launch, uint32_t in_place) {
+    extern __shared__ __align__(16) uint8_t lds_m[];
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
+    // work-groups go round-robin over the 8 XCDs: each takes consecutive tiles
+    const uint32_t xcd = blockIdx.x & 7, share = E.ntiles >> 3, more = E.ntiles & 7;
+    const uint32_t t = xcd * share + min(xcd, more) + (blockIdx.x >> 3);
+    uint64_t base = 0;
+    uint32_t local = t, bytes = E.K;
+    if (BATCH) {
+        const uint32_t *r = rec + 4 * uint64_t(t);
+        base = uint64_t(r[0]) << 4;
+        local = r[1];
+        bytes = min(E.K, r[2]);
+        if (steps_of) {
+            const uint32_t n = steps_of[r[3]];
+            uint32_t L = n / E.gens + (n % E.gens != 0);
+            if (!in_place) L += (L ^ n) & 1;
+            if (launch >= L) return;
+            gens = n / L + (launch < n % L ? 1u : 0u);
+            if (in_place && (launch + 1 < L || !(n & 1))) out = in;
+        }
+    }
+    const uint32_t L = E.lanes, quarter = lane >> 4, col = lane & 15;
+    const uint32_t sub = quarter & (L - 1), bpg = 64 / L;
+    const uint32_t slot = (L == 4 ? 0u : (L == 2 ? quarter >> 1 : quarter)) * 16 + col;
+    const uint32_t coff = min(16 * sub, E.CB - 16);
+    const uint8_t *src = in + base;
+    const uint64_t room = (E.limit - base + 3) & ~uint64_t(3);
+    const __amdgpu_buffer_rsrc_t all = mat_rsrc(src, room > kNowhere ? kNowhere : uint32_t(room));
+    const uint32_t toff = local * E.K;
+    // the blocks: own ones, those of the neighbour tiles, none
+    uint32_t soff[GPW], live[GPW];
+    u32x4 x[GPW];
+    MatRaw<AL> raw[GPW];
+    uint32_t pos[GPW];
+#pragma unroll
+    for (int u = 0; u < GPW; ++u) {
+        const uint32_t b = (wave * GPW + u) * bpg + slot;
+        const bool own = b < E.nblk && b * E.CB < bytes, ring = b >= E.nblk && b < E.ntot;
+        const uint32_t item = E.halo[ring ? b - E.nblk : 0u];
+        const uint32_t nt = E.nbr[uint64_t(t) * 8 + (item >> 29)];
+        soff[u] = own ? b * E.CB + coff : kNowhere;
+        pos[u] = own ? toff + b * E.CB + coff
+                     : (ring && nt != kOutside ? nt * E.K + (item & 0x1FFFFFFFu) * E.CB + coff : kNowhere);
+        live[u] = pos[u] != kNowhere ? 0xFFFFFFFFu : 0u;
+        raw[u] = mat_load<AL>(all, pos[u]);
+    }
+    const bool edge = (rule >> 31) != 0;
+    const uint8_t *A8 = reinterpret_cast<const uint8_t *>(E.A) + 16 * lane;
+    auto operand = [&](uint32_t off) -> u32x4 { return *reinterpret_cast<const u32x4 *>(A8 + off); };
+    u32x4 Aself[2], Ahalo[NH][2], Arec[NR];
+#pragma unroll
+    for (int k = 0; k < NR; ++k) Arec[k] = operand(mat_rec_off(NH, k));
+#pragma unroll
+    for (int k = 0; k < 2; ++k) Aself[k] = operand(mat_self_off(NH, edge, k));
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) Ahalo[h][k] = operand(mat_halo_off(NH, edge, h, k));
+    uint32_t waddr[GPW], raddr[GPW][4 * NH];
+#pragma unroll
+    for (int u = 0; u < GPW; ++u) {
+        const uint32_t g = wave * GPW + u, b = g * bpg + slot;
+        waddr[u] = lds_at(lds_m, 4 * (min(b, E.ntot) * E.rs + sub * NR));
+#pragma unroll
+        for (int d = 0; d < 2 * NH; ++d) {
+            const uint32_t a = E.raddr[(g * 64 + lane) * (2 * NH) + d];
+            raddr[u][2 * d] = lds_at(lds_m, a & 0xFFFFu);
+            raddr[u][2 * d + 1] = lds_at(lds_m, a >> 16);
+        }
+    }
+    if (tid < 2) *reinterpret_cast<uint32_t *>(lds_m + tid * BUF + E.zero) = 0;
+    const RuleTables RT = rule_tables(rule);
+    const bool tables = RT.perm || edge;
+    const bool all_live = (wave * GPW + GPW) * bpg <= E.nblk && (wave * GPW + GPW) * bpg * E.CB <= bytes;
+    // A wavefront without a block (of an instance below the tile level) leaves
+    // its blocks' records at zero and only keeps the barriers.
+    if (BATCH && wave * GPW * bpg * E.CB >= bytes && (wave * GPW + GPW) * bpg <= E.nblk) {
+#pragma unroll
+        for (int u = 0; u < GPW; ++u)
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                lds_put(waddr[u] + 4 * k, 0);
+                lds_put(waddr[u] + BUF + 4 * k, 0);
+            }
+        for (uint32_t g = 0; g < gens; ++g) __syncthreads();
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < GPW; ++u) x[u] = mat_align<AL>(raw[u], pos[u]);
+
+    auto generation = [&](auto parity) {
+        constexpr int P = decltype(parity)::value * BUF;
+        const i32x4 zero = {0, 0, 0, 0};
+#pragma unroll
+        for (int u = 0; u < GPW; ++u)
+#pragma unroll
+            for (int k = 0; k < NR; ++k)
+                lds_put(waddr[u] + P + 4 * k, mat_bytes(mat_mul(Arec[k], x[u], zero)));
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < GPW; ++u) {
+            i32x4 d0 = mat_mul(Aself[0], x[u], zero), d1 = mat_mul(Aself[1], x[u], zero);
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+                u32x4 r;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) r[d] = lds_get(raddr[u][4 * h + d] + P);
+                d0 = mat_mul(Ahalo[h][0], r, d0);
+                d1 = mat_mul(Ahalo[h][1], r, d1);
+            }
+            const uint32_t c0 = mat_bytes(d0), c1 = mat_bytes(d1);
+            x[u][0] = mat_rule<RULE>(c0 & 0x0F0F0F0Fu, x[u][0], rule, RT, tables);
+            x[u][1] = mat_rule<RULE>((c0 >> 4) & 0x0F0F0F0Fu, x[u][1], rule, RT, tables);
+            x[u][2] = mat_rule<RULE>(c1 & 0x0F0F0F0Fu, x[u][2], rule, RT, tables);
+            x[u][3] = mat_rule<RULE>((c1 >> 4) & 0x0F0F0F0Fu, x[u][3], rule, RT, tables);
+        }
+        // blocks that do not exist stay dead (uniform branch)
+        if (!all_live)
+#pragma unroll
+            for (int u = 0; u < GPW; ++u)
+#pragma unroll
+                for (int d = 0; d < 4; ++d) x[u][d] &= live[u];
+    };
+    for (uint32_t g = 0; g < gens; g += 2) {
+        generation(std::integral_constant<int, 0>());
+        if (g + 1 < gens) generation(std::integral_constant<int, 1>());
+    }
+    const __amdgpu_buffer_rsrc_t gout = mat_rsrc(out + base + toff, bytes);
+#pragma unroll
+    for (int u = 0; u < GPW; ++u) __builtin_amdgcn_raw_buffer_store_b128(x[u], gout, soff[u], 0, 0);
+}
+
+template <int AL, int NR, int NH, int GPW, int BUF, bool BATCH, int RULE>
+static hipError_t launch_hold_t(const HoldParams &E, uint8_t *in, uint8_t *out, uint32_t rule, uint32_t gens,
+                                const uint32_t *rec, const uint32_t *steps_of, uint32_t launch, uint32_t in_place,
+                                hipStream_t st) {
+    if (!E.ntiles) return hipSuccess;
+    const uint32_t lds = BUF + E.zero + 4;
+    hipLaunchKernelGGL((k_step_hold<AL, NR, NH, GPW, BUF, BATCH, RULE>), dim3(E.ntiles), dim3(64 * E.waves), lds, st, E,
+                       in, out, rule, gens, rec, steps_of, launch, in_place);
+    return hipGetLastError();
+}
+
 // The instantiation for a plan: exact operand counts (the kernel's operand
 // offsets follow them).
 template <int AL, bool BATCH, int RULE>
@@ -345,6 +524,31 @@ static hipError_t launch_matrix_shape(const MatParams &E, uint32_t nr, uint32_t 
     NBB_MAT_CASES(3, 2);
 #undef NBB_MAT_CASES
 #undef NBB_MAT_CASE
+    return hipErrorInvalidValue;
+}
+template <int AL, bool BATCH, int RULE>
+static hipError_t launch_hold_shape(const HoldParams &E, uint32_t nr, uint32_t nh, uint32_t gpw, uint8_t *in,
+                                    uint8_t *out, uint32_t rule, uint32_t gens, const uint32_t *rec,
+                                    const uint32_t *steps_of, uint32_t launch, uint32_t in_place, hipStream_t st) {
+    const bool small = E.zero + 4 <= 8192;
+#define NBB_HOLD_CASE(R, H, G)                                                                                    \
+    if (nr == R && nh == H && gpw == G)                                                                           \
+    return small ? launch_hold_t<AL, R, H, G, 8192, BATCH, RULE>(E, in, out, rule, gens, rec, steps_of, launch,   \
+                                                                 in_place, st)                                    \
+                 : launch_hold_t<AL, R, H, G, int(kHoldBuf), BATCH, RULE>(E, in, out, rule, gens, rec, steps_of,  \
+                                                                          launch, in_place, st)
+#define NBB_HOLD_CASES(R, H) \
+    NBB_HOLD_CASE(R, H, 1);  \
+    NBB_HOLD_CASE(R, H, 2);  \
+    NBB_HOLD_CASE(R, H, 4)
+    NBB_HOLD_CASES(1, 1);
+    NBB_HOLD_CASES(2, 1);
+    NBB_HOLD_CASES(3, 1);
+    NBB_HOLD_CASES(1, 2);
+    NBB_HOLD_CASES(2, 2);
+    NBB_HOLD_CASES(3, 2);
+#undef NBB_HOLD_CASES
+#undef NBB_HOLD_CASE
     return hipErrorInvalidValue;
 }
 

@@ -20,4 +20,15 @@ template hipError_t launch_matrix_inst<bool(NBB_INST_BATCH), NBB_INST_RULE, NBB_
     const MatParams &, uint32_t, uint32_t, uint32_t, const uint8_t *, uint8_t *, uint32_t, const uint32_t *, int,
     hipStream_t);
 
+template <bool BATCH, int RULE, int AL>
+hipError_t launch_hold_inst(const HoldParams &E, uint32_t nr, uint32_t nh, uint32_t gpw, uint8_t *in,
+                            uint8_t *out, uint32_t rule, uint32_t gens, const uint32_t *rec, const uint32_t *steps_of,
+                            uint32_t launch, uint32_t in_place, hipStream_t st) {
+    return launch_hold_shape<AL, BATCH, RULE>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, in_place, st);
+}
+
+template hipError_t launch_hold_inst<bool(NBB_INST_BATCH), NBB_INST_RULE, NBB_INST_AL>(
+    const HoldParams &, uint32_t, uint32_t, uint32_t, uint8_t *, uint8_t *, uint32_t, uint32_t, const uint32_t *,
+    const uint32_t *, uint32_t, uint32_t, hipStream_t);
+
 }  // namespace nbb

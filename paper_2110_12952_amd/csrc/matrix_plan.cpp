@@ -230,37 +230,14 @@ static uint32_t pick_gpw(uint32_t groups, uint32_t hgroups, uint64_t tiles, uint
     return gpw;
 }
 
-static bool build_mat_shape(const Fractal &f, const BlockShape &s, uint32_t m, uint32_t gpw, MatPlan *p,
-                            std::string *msg, bool with_nbr) {
-    std::vector<uint32_t> source;
-    if (!build_ring(f, s, m, p, &source, msg)) return false;
-    const uint32_t bpg = 64 / s.lanes, hgroups = (p->nhalo + bpg - 1) / bpg;
-    p->gpw = gpw ? gpw : pick_gpw(p->groups, hgroups, p->ntiles, 256);
-    p->waves = p->gpw ? std::max((p->groups + p->gpw - 1) / p->gpw, hgroups) : 0;
-    if (!p->gpw || p->waves > kMatMaxWaves) {
-        *msg = "more groups than a work-group takes";
-        return false;
-    }
-    // record reads: read i is dword i % 4 of lane (i / 4) % lanes, halo operand i / (4 lanes)
-    const uint32_t zero = 4 * s.lanes * s.nr * p->nrecs;
-    p->raddr.assign(size_t(p->waves) * p->gpw * 64 * 2 * p->nh, zero | zero << 16);
-    for (uint32_t b = 0; b < p->nblk; ++b)
-        for (size_t i = 0; i < s.reads.size(); ++i) {
-            const uint32_t src = source[b * s.reads.size() + i];
-            if (src == kNone) continue;
-            const uint32_t h = uint32_t(i) / (4 * s.lanes), sub = uint32_t(i) / 4 % s.lanes, d = uint32_t(i) % 4;
-            const uint32_t in = b % bpg;  // block of the group: 16 columns by 4 / lanes
-            const uint32_t lane = (in / 16 * s.lanes + sub) * 16 + in % 16;
-            uint32_t &w = p->raddr[((size_t(b / bpg) * 64 + lane) * 2 * p->nh) + 2 * h + d / 2];
-            const uint32_t addr = 4 * (s.reads[i].second * p->nrecs + src);
-            w = d % 2 ? (w & 0xFFFFu) | addr << 16 : (w & 0xFFFF0000u) | addr;
-        }
+// The constant operands of a block shape (MatParams::A).
+static void mat_operands(const BlockShape &s, std::vector<int8_t> *A) {
     // operands: lane l of an operand holds row l % 16, products 16 (l / 16) ..
     const uint32_t nh = s.nh;
-    p->A.assign(size_t(1024) * (2 * (2 + 2 * nh) + s.nr), 0);
+    A->assign(size_t(1024) * (2 * (2 + 2 * nh) + s.nr), 0);
     auto first_cell = [&](uint32_t sub) { return std::min(16 * sub, s.CB - 16); };
     auto put = [&](uint32_t off, uint32_t row, uint32_t quarter, uint32_t byte, int w) {
-        p->A[off + (quarter * 16 + row) * 16 + byte] = int8_t(p->A[off + (quarter * 16 + row) * 16 + byte] + w);
+        (*A)[off + (quarter * 16 + row) * 16 + byte] = int8_t((*A)[off + (quarter * 16 + row) * 16 + byte] + w);
     };
     for (int edge = 0; edge < 2; ++edge) {
         auto adjacent = [&](int64_t dx, int64_t dy) {
@@ -310,9 +287,183 @@ static bool build_mat_shape(const Fractal &f, const BlockShape &s, uint32_t m, u
                 const uint32_t sub = uint32_t(e) / 16;  // its first holder
                 put(mat_rec_off(nh, t), 4 * g + i, g / s.lanes * s.lanes + sub, uint32_t(e) - first_cell(sub), 1);
             }
+}
+
+static bool build_mat_shape(const Fractal &f, const BlockShape &s, uint32_t m, uint32_t gpw, MatPlan *p,
+                            std::string *msg, bool with_nbr) {
+    std::vector<uint32_t> source;
+    if (!build_ring(f, s, m, p, &source, msg)) return false;
+    const uint32_t bpg = 64 / s.lanes, hgroups = (p->nhalo + bpg - 1) / bpg;
+    p->gpw = gpw ? gpw : pick_gpw(p->groups, hgroups, p->ntiles, 256);
+    p->waves = p->gpw ? std::max((p->groups + p->gpw - 1) / p->gpw, hgroups) : 0;
+    if (!p->gpw || p->waves > kMatMaxWaves) {
+        *msg = "more groups than a work-group takes";
+        return false;
+    }
+    // record reads: read i is dword i % 4 of lane (i / 4) % lanes, halo operand i / (4 lanes)
+    const uint32_t zero = 4 * s.lanes * s.nr * p->nrecs;
+    p->raddr.assign(size_t(p->waves) * p->gpw * 64 * 2 * p->nh, zero | zero << 16);
+    for (uint32_t b = 0; b < p->nblk; ++b)
+        for (size_t i = 0; i < s.reads.size(); ++i) {
+            const uint32_t src = source[b * s.reads.size() + i];
+            if (src == kNone) continue;
+            const uint32_t h = uint32_t(i) / (4 * s.lanes), sub = uint32_t(i) / 4 % s.lanes, d = uint32_t(i) % 4;
+            const uint32_t in = b % bpg;  // block of the group: 16 columns by 4 / lanes
+            const uint32_t lane = (in / 16 * s.lanes + sub) * 16 + in % 16;
+            uint32_t &w = p->raddr[((size_t(b / bpg) * 64 + lane) * 2 * p->nh) + 2 * h + d / 2];
+            const uint32_t addr = 4 * (s.reads[i].second * p->nrecs + src);
+            w = d % 2 ? (w & 0xFFFFu) | addr << 16 : (w & 0xFFFF0000u) | addr;
+        }
+    mat_operands(s, &p->A);
     if (with_nbr) mat_neighbours(f, m, &p->nbr);
     p->ok = true;
     return true;
+}
+
+// The members of the tile at level m: its own blocks, then every block of
+// the neighbour tiles within `rings` blocks of one of them.
+static bool hold_members(const Fractal &f, const BlockShape &s, uint32_t m, uint32_t rings, HoldPlan *p,
+                         std::vector<std::pair<int64_t, int64_t>> *at, std::string *msg) {
+    *p = HoldPlan();
+    const int64_t G = m < s.q || m > f.r ? 0 : int64_t(ipow(f.s, m - s.q));
+    if (!G || rings > G || (rings == 0 && m != f.r)) {
+        *msg = "q <= m <= r, at most a tile's side of rings, and none only for a tile that is the whole state";
+        return false;
+    }
+    const uint32_t bpg = 64 / s.lanes, most = kHoldMaxWaves * 4 * bpg;
+    const uint64_t nb = ipow(f.k, m - s.q);
+    if (nb > most) {
+        *msg = "more groups than a work-group holds";
+        return false;
+    }
+    p->m = m;
+    p->q = s.q;
+    p->K = uint32_t(ipow(f.k, m));
+    p->CB = s.CB;
+    p->lanes = s.lanes;
+    p->nr = s.nr;
+    p->nh = s.nh;
+    p->nblk = uint32_t(nb);
+    p->ntiles = ipow(f.k, f.r - m);
+    p->gens = rings ? rings * s.BS : kHoldMaxGens;
+    for (uint64_t b = 0; b < nb; ++b) {
+        int64_t X, Y;
+        lambda_levels(f, m - s.q, b, &X, &Y);
+        at->push_back({X, Y});
+    }
+    const int64_t D = rings;
+    std::vector<uint8_t> near(size_t(G + 2 * D) * size_t(G + 2 * D), 0);
+    auto mark = [&](int64_t x, int64_t y) -> uint8_t & { return near[size_t(y + D) * (G + 2 * D) + size_t(x + D)]; };
+    for (uint64_t b = 0; b < nb && D; ++b)
+        for (int64_t dy = -D; dy <= D; ++dy)
+            for (int64_t dx = -D; dx <= D; ++dx) mark((*at)[b].first + dx, (*at)[b].second + dy) = 1;
+    for (uint32_t d = 0; d < 8 && D; ++d)
+        for (uint64_t b = 0; b < nb; ++b) {
+            const int64_t X = (*at)[b].first + kDirX[d] * G, Y = (*at)[b].second + kDirY[d] * G;
+            if (X < -D || Y < -D || X >= G + D || Y >= G + D || !mark(X, Y)) continue;
+            p->halo.push_back(d << 29 | uint32_t(b));
+            at->push_back({X, Y});
+        }
+    p->ntot = uint32_t(at->size());
+    p->groups = (p->ntot + bpg - 1) / bpg;
+    // a record in consecutive dwords, an odd number of them where a multiple
+    // of eight would put the same dword of every record into few LDS banks
+    p->rs = s.lanes * s.nr + (s.lanes * s.nr % 8 == 0 ? 1 : 0);
+    const uint64_t words = uint64_t(p->ntot + 1) * p->rs + 1;  // one record never read, one dword of zeros
+    p->zero = uint32_t(4 * (words - 1));
+    if (p->ntot > most || words * 4 > kHoldBuf) {
+        *msg = "more groups or records than a work-group holds";
+        return false;
+    }
+    return true;
+}
+
+// Groups per wavefront: one up to five groups, two up to 22, else four (four
+// wavefronts or more share the groups, registers for several work-groups per
+// CU).  One / two / four: triangle r16 at level 8 (8 groups, 20 generations)
+// 128 / 111 / 118 us, carpet r9 at 4 (7 groups, 10 generations) 283 / 265 /
+// 275, H r8 at 4 (5 groups) 50 / 53 / 63, chandelier r13 at 7 (17) - / 142 /
+// 169, full square r12 at 7 (21) - / 74 / 103, H r10 at 5 (27) - / 631 / 548.
+static uint32_t hold_gpw(uint32_t groups) { return groups <= 5 ? 1 : (groups <= 22 ? 2 : 4); }
+
+bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw, HoldPlan *p, std::string *msg) {
+    BlockShape s;
+    if (!pick_shape(f, &s)) {
+        *msg = "no block level of this fractal fits the matrix form";
+        return false;
+    }
+    std::vector<std::pair<int64_t, int64_t>> at;
+    if (!hold_members(f, s, m, rings, p, &at, msg)) return false;
+    p->gpw = gpw ? gpw : hold_gpw(p->groups);
+    p->waves = (p->groups + p->gpw - 1) / p->gpw;
+    if (p->waves > kHoldMaxWaves) {
+        *msg = "more groups than a work-group holds";
+        return false;
+    }
+    std::map<std::pair<int64_t, int64_t>, uint32_t> index;
+    for (uint32_t b = 0; b < p->ntot; ++b) index[at[b]] = b;
+    const uint32_t bpg = 64 / s.lanes;
+    p->raddr.assign(size_t(p->waves) * p->gpw * 64 * 2 * p->nh, p->zero | p->zero << 16);
+    for (uint32_t b = 0; b < p->ntot; ++b)
+        for (size_t i = 0; i < s.reads.size(); ++i) {
+            const auto it = index.find({at[b].first + kDirX[s.reads[i].first], at[b].second + kDirY[s.reads[i].first]});
+            if (it == index.end()) continue;
+            const uint32_t h = uint32_t(i) / (4 * s.lanes), sub = uint32_t(i) / 4 % s.lanes, d = uint32_t(i) % 4;
+            const uint32_t in = b % bpg, lane = (in / 16 * s.lanes + sub) * 16 + in % 16;
+            uint32_t &w = p->raddr[((size_t(b / bpg) * 64 + lane) * 2 * p->nh) + 2 * h + d / 2];
+            const uint32_t rd = s.reads[i].second;
+            const uint32_t addr = 4 * (it->second * p->rs + rd % s.lanes * s.nr + rd / s.lanes);
+            w = d % 2 ? (w & 0xFFFFu) | addr << 16 : (w & 0xFFFF0000u) | addr;
+        }
+    mat_operands(s, &p->A);
+    if (p->halo.empty()) p->halo.push_back(0);
+    p->ok = true;
+    return true;
+}
+
+std::vector<HoldDims> hold_dims(const Fractal &f) {
+    std::vector<HoldDims> out;
+    BlockShape s;
+    if (!pick_shape(f, &s)) return out;
+    for (uint32_t m = s.q; m <= f.r; ++m)
+        for (uint32_t rings = m == f.r ? 0 : 1; rings <= (m == f.r ? 0u : kHoldMaxRings); ++rings) {
+            HoldPlan p;
+            std::vector<std::pair<int64_t, int64_t>> at;
+            std::string msg;
+            if (!hold_members(f, s, m, rings, &p, &at, &msg)) continue;
+            out.push_back({m, rings, p.groups, p.gens});
+        }
+    return out;
+}
+
+// Estimated time per generation in us: a launch (4 us, and the state through
+// memory once) over its generations (counted up to 24, what a call often
+// asks for at least), and a generation: 0.25 us for a barrier and the round
+// through LDS, 0.022 us per group on the busiest CU (more beyond 30 groups,
+// where one work-group leaves no room for a second), 0.03 us per group of a
+// work-group alone on its CU.  Fitted to sweeps over triangle r7 - r16, carpet
+// r5 - r9, H r8 - r10, Vicsek r10, chandelier r13 and full square r12; more
+// rings only for a gain of 5 %.
+bool pick_hold(const std::vector<HoldDims> &dims, uint32_t k, const std::vector<uint32_t> &levels, uint32_t cus,
+               HoldDims *out, uint32_t *gpw) {
+    cus = std::max(cus, 1u);
+    uint64_t cells = 0;
+    for (uint32_t r : levels) cells += ipow(k, r);
+    bool found = false;
+    double best = 0.0;
+    for (const HoldDims &d : dims) {
+        uint64_t tiles = 0;
+        for (uint32_t r : levels) tiles += r > d.m ? ipow(k, r - d.m) : 1;
+        const double work = double((tiles + cus - 1) / cus) * d.groups;
+        const double gen = std::max({0.25, (d.groups > 30 ? 0.035 : 0.022) * work, 0.03 * d.groups});
+        const double t = (4.0 + double(cells) * 1.6e-7) / (d.rings ? std::min(d.gens, 24u) : 64u) + gen;
+        if (found && t >= (d.rings > out->rings ? 0.95 * best : best)) continue;
+        found = true;
+        best = t;
+        *out = d;
+        *gpw = hold_gpw(d.groups);
+    }
+    return found;
 }
 
 bool build_mat_plan(const Fractal &f, uint32_t m, uint32_t gpw, MatPlan *p, std::string *msg, bool with_nbr) {

@@ -174,6 +174,23 @@ struct MatParams {
     uint64_t limit;          // bytes of the input that may be read (the state, or the whole arena)
 };
 
+// Several generations per launch in the matrix form: the tile's blocks and
+// those of its neighbour tiles around it, all held in registers.  Records in
+// consecutive dwords: dword t of lane `sub` of record b at 4 (b rs + sub nr + t).
+struct HoldParams {
+    uint32_t K, CB, lanes;
+    uint32_t nblk, ntot;     // own blocks; with the neighbour tiles'
+    uint32_t rs, zero;       // dwords per record; LDS offset of a dword of zeros
+    uint32_t waves;
+    uint32_t gens;           // generations per launch at most
+    uint32_t ntiles;
+    const int8_t *A;         // as MatParams
+    const uint32_t *raddr;
+    const uint32_t *halo;    // per neighbour block: direction << 29 | block
+    const uint32_t *nbr;
+    uint64_t limit;
+};
+
 // Temporal blocking (several generations per launch): work-group t holds
 // tile t's square and a ring of depth h as a B x B box (pitch P bytes) in
 // LDS, three times: two state copies and the member mask.

@@ -129,6 +129,38 @@ std::vector<MatDims> mat_dims(const Fractal &f);
 uint32_t pick_mat_level(const std::vector<MatDims> &dims, uint32_t k, const std::vector<uint32_t> &levels, uint32_t cus,
                         uint32_t *gpw);
 
+// Several generations per launch in the matrix form: a work-group holds the
+// blocks of tile t (level m) and every block of the eight neighbour tiles
+// within `rings` blocks of one of them in registers and takes up to
+// rings * s^q generations on all of them, records in LDS between them.  What
+// the missing blocks outside would change advances by one cell per
+// generation, so it does not reach the tile's own cells by then.  With the
+// whole state as one tile (m = r, no rings) any number of generations.
+struct HoldPlan {
+    bool ok = false;
+    uint32_t m = 0, q = 0, K = 0, CB = 0, lanes = 0, nr = 0, nh = 0;
+    uint32_t nblk = 0, ntot = 0;  // own blocks, and with the neighbours'
+    uint32_t gens = 0;            // generations per launch at most
+    uint32_t groups = 0, gpw = 0, waves = 0;
+    uint32_t rs = 0, zero = 0;    // dwords per record, offset of a dword of zeros
+    uint64_t ntiles = 0;
+    std::vector<int8_t> A;
+    std::vector<uint32_t> raddr, halo;
+};
+constexpr uint32_t kHoldMaxWaves = 16;
+constexpr uint32_t kHoldMaxGens = 4096;   // per launch, whatever the plan (a launch of milliseconds at most)
+constexpr uint32_t kHoldMaxRings = 4;
+constexpr uint32_t kHoldBuf = 32 * 1024;  // one record buffer at most
+bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw, HoldPlan *p, std::string *msg);
+struct HoldDims {
+    uint32_t m, rings, groups, gens;
+};
+std::vector<HoldDims> hold_dims(const Fractal &f);
+// The plan of launches over instances of the fractal at these levels r with
+// the least estimated time per generation; false if there is none.
+bool pick_hold(const std::vector<HoldDims> &dims, uint32_t k, const std::vector<uint32_t> &levels, uint32_t cus,
+               HoldDims *out, uint32_t *gpw);
+
 // Several generations per launch (temporal blocking) for small instances: a
 // work-group holds tile t's S x S square and a ring of depth h around it (the
 // cells of the eight neighbour tiles within h of the square) as a box of side

@@ -137,6 +137,100 @@ static void check(const Fractal &f, const MatPlan &p, std::mt19937 &rng, bool ed
     }
 }
 
+// Several generations of a random rule on tiles held with their rings.
+static void check_hold(const Fractal &f, const HoldPlan &p, std::mt19937 &rng) {
+    const uint32_t rule = rng() & 0x01FF01FFu;
+    const bool edge = rng() & 1;
+    const uint32_t gens = std::min(p.gens, 10u), bpg = 64 / p.lanes;
+    std::vector<uint8_t> st(f.cells);
+    for (auto &c : st) c = rng() & 1;
+    std::vector<uint8_t> ref = st;
+    for (uint32_t g = 0; g < gens; ++g) {
+        std::vector<uint8_t> next(f.cells);
+        for (uint64_t i = 0; i < f.cells; ++i) {
+            const int n = count_ref(f, ref, i, edge);
+            next[i] = (rule >> (ref[i] ? 16 + n : n)) & 1;
+        }
+        ref.swap(next);
+    }
+    std::vector<uint32_t> nbr;
+    mat_neighbours(f, p.m, &nbr);
+    for (uint64_t tile = 0; tile < p.ntiles; ++tile) {
+        if (p.ntiles > 4 && rng() % (p.ntiles / 2)) continue;
+        const uint32_t groups = p.waves * p.gpw;
+        std::vector<std::vector<uint8_t>> X(groups, std::vector<uint8_t>(1024));
+        std::vector<uint8_t> live(groups * 64);
+        for (uint32_t g = 0; g < groups; ++g)
+            for (int l = 0; l < 64; ++l) {
+                const uint32_t in = (l / 16) / p.lanes * 16 + l % 16, sub = (l / 16) % p.lanes, b = g * bpg + in;
+                if (b >= p.ntot) continue;
+                uint64_t t = tile;
+                uint32_t lb = b;
+                if (b >= p.nblk) {
+                    const uint32_t item = p.halo[b - p.nblk];
+                    t = nbr[tile * 8 + (item >> 29)];
+                    lb = item & 0x1FFFFFFFu;
+                    if (t == 0xFFFFFFFFu) continue;
+                }
+                live[g * 64 + l] = 1;
+                for (uint32_t j = 0; j < 16; ++j)
+                    X[g][16 * l + j] = st[t * p.K + lb * p.CB + std::min(16 * sub, p.CB - 16) + j];
+            }
+        for (uint32_t gen = 0; gen < gens; ++gen) {
+            std::vector<uint8_t> lds(p.zero + 4, 0xEE);
+            for (int i = 0; i < 4; ++i) lds[p.zero + i] = 0;
+            for (uint32_t g = 0; g < groups; ++g)
+                for (uint32_t t = 0; t < p.nr; ++t) {
+                    int D[64][4] = {};
+                    contract(p.A.data() + mat_rec_off(p.nh, t), X[g], D);
+                    for (int l = 0; l < 64; ++l) {
+                        const uint32_t in = (l / 16) / p.lanes * 16 + l % 16, sub = (l / 16) % p.lanes;
+                        const uint32_t a = 4 * (std::min(g * bpg + in, p.ntot) * p.rs + sub * p.nr + t);
+                        if (a + 4 > p.zero) std::abort();
+                        for (int i = 0; i < 4; ++i) lds[a + i] = uint8_t(D[l][i]);
+                    }
+                }
+            for (uint32_t g = 0; g < groups; ++g) {
+                std::vector<uint8_t> N(1024);
+                for (uint32_t t = 0; t < 2; ++t) {
+                    int D[64][4] = {};
+                    contract(p.A.data() + mat_self_off(p.nh, edge, t), X[g], D);
+                    for (uint32_t h = 0; h < p.nh; ++h) {
+                        std::vector<uint8_t> R(1024);
+                        for (int l = 0; l < 64; ++l)
+                            for (int d = 0; d < 4; ++d) {
+                                const uint32_t w = p.raddr[(size_t(g) * 64 + l) * 2 * p.nh + 2 * h + d / 2];
+                                const uint32_t a = d & 1 ? w >> 16 : w & 0xFFFFu;
+                                if (a > p.zero) std::abort();
+                                for (int i = 0; i < 4; ++i) R[16 * l + 4 * d + i] = lds[a + i];
+                            }
+                        contract(p.A.data() + mat_halo_off(p.nh, edge, h, t), R, D);
+                    }
+                    for (int l = 0; l < 64; ++l)
+                        for (int i = 0; i < 4; ++i)
+                            for (int hi = 0; hi < 2; ++hi) {
+                                const int n = hi ? D[l][i] >> 4 : D[l][i] & 15;
+                                const int j = 16 * l + 8 * t + 4 * hi + i;
+                                N[j] = live[g * 64 + l] && n <= 8 && (rule >> (X[g][j] ? 16 + n : n)) & 1;
+                            }
+                }
+                X[g].swap(N);
+            }
+        }
+        for (uint32_t b = 0; b < p.nblk; ++b)
+            for (uint32_t sub = 0; sub < p.lanes; ++sub)
+                for (uint32_t j = 0; j < 16; ++j) {
+                    const uint32_t c = std::min(16 * sub, p.CB - 16) + j, in = b % bpg;
+                    const uint32_t lane = (in / 16 * p.lanes + sub) * 16 + in % 16;
+                    if (X[b / bpg][16 * lane + j] != ref[tile * p.K + b * p.CB + c]) {
+                        std::printf("held mismatch k %u s %u r %u m %u gens %u tile %llu block %u cell %u\n", f.k, f.s, f.r,
+                                    p.m, gens, (unsigned long long)tile, b, c);
+                        std::exit(1);
+                    }
+                }
+    }
+}
+
 static bool make(uint32_t s, const std::vector<int32_t> &off, uint32_t r, Fractal *f) {
     std::string msg;
     return validate_fractal(uint32_t(off.size() / 2), s, off.data(), r, f, &msg) == 0;
@@ -144,7 +238,7 @@ static bool make(uint32_t s, const std::vector<int32_t> &off, uint32_t r, Fracta
 
 int main(int argc, char **argv) {
     std::mt19937 rng(7);
-    int plans = 0;
+    int plans = 0, held = 0;
     std::vector<std::pair<uint32_t, std::vector<int32_t>>> named = {
         {2, {0, 0, 1, 0, 0, 1}},                                      // triangle
         {3, {0, 0, 1, 0, 2, 0, 0, 1, 2, 1, 0, 2, 1, 2, 2, 2}},        // carpet
@@ -166,6 +260,16 @@ int main(int argc, char **argv) {
                 if (!build_mat_plan(f, m, rng() % 2 ? 0 : 1u << rng() % 3, &p, &msg)) continue;
                 for (bool edge : {false, true}) check(f, p, rng, edge);
                 ++plans;
+                for (uint32_t rings = 0; rings <= 2; ++rings) {
+                    HoldPlan h;
+                    if (f.cells > 20000 || !build_hold_plan(f, m, rings, rng() % 2 ? 0 : 1u << rng() % 3, &h, &msg))
+                        continue;
+                    check_hold(f, h, rng);
+                    ++held;
+                    if (argc > 1)
+                        std::printf("# held k %u r %u m %u rings %u: nblk %u ntot %u groups %u gpw %u waves %u zero %u\n",
+                                    f.k, f.r, m, rings, h.nblk, h.ntot, h.groups, h.gpw, h.waves, h.zero);
+                }
                 if (r == 7 || argc > 1)
                     std::printf("# k %u s %u r %u m %u: q %u CB %u lanes %u nblk %u nhalo %u nr %u nh %u gpw %u waves %u buf %u\n",
                                 f.k, f.s, r, m, p.q, p.CB, p.lanes, p.nblk, p.nhalo, p.nr, p.nh, p.gpw, p.waves,
@@ -190,6 +294,11 @@ int main(int argc, char **argv) {
             if (!build_mat_plan(f, m, rng() % 2 ? 0 : 1u << rng() % 3, &p, &msg)) continue;
             check(f, p, rng, rng() & 1);
             ++plans;
+            HoldPlan h;
+            if (f.cells <= 5000 && build_hold_plan(f, m, m == f.r ? 0 : 1 + rng() % 2, 0, &h, &msg)) {
+                check_hold(f, h, rng);
+                ++held;
+            }
         }
         // whatever level and groups per wavefront a launch picks can be built
         const std::vector<MatDims> dims = mat_dims(f);
@@ -201,6 +310,6 @@ int main(int argc, char **argv) {
             if (a && (!build_mat_plan(f, a, gpw, &p, &msg, false) || p.gpw != gpw)) std::abort();
         }
     }
-    std::printf("plans %d\n", plans);
+    std::printf("held %d plans %d\n", held, plans);
     return 0;
 }

@@ -114,3 +114,80 @@ def test_batch_of_many_levels(N, name, levels):
                 ha[off:off + len(st)] = 1
                 hb[off:off + len(st)] = 1
             assert (ha == 1).all() and (hb == 1).all()
+
+
+HELD = [("triangle", r) for r in (3, 5, 7, 9, 10, 12)] + [("carpet", r) for r in (2, 3, 4, 5, 6)] + \
+       [("hfractal", r) for r in (2, 3, 4, 5, 6)] + [("chandelier", r) for r in (3, 5, 7, 8, 9)] + \
+       [("fullsquare", r) for r in (3, 6, 8)] + [("vicsek", r) for r in (2, 4, 6, 7)] + \
+       [("xfractal", 6), ("cantordust", 6), ("cantor", 9)]
+
+
+@gpu
+@pytest.mark.parametrize("name,r", HELD)
+def test_several_generations_per_call_against_oracle(N, name, r):
+    # step counts around the generations a launch takes (8, 9, 16, 18, ...), of
+    # both parities: the result and the generation before it in the other
+    # buffer, for the default plan and for TEMPORAL's automatic one
+    fd = W.FRACTALS[name]
+    o, g, t = (O.Fractal(fd.s, fd.offsets, r), N.Fractal(fd.s, fd.offsets, r), N.Fractal(fd.s, fd.offsets, r))
+    t.configure_temporal()
+    st0 = o.init_compact(21, 0.45)
+    for rule in ("B3/S23", "B1357/S02468", "vN:B2/S12"):
+        rm = W.rule_mask(rule)
+        states = [st0]
+        for _ in range(41):
+            states.append(o.compact_steps(states[-1], rm, 1))
+        for steps in (3, 4, 5, 9, 10, 18, 19, 28, 41):
+            a = torch.from_numpy(st0).cuda()
+            b = torch.full_like(a, 0xEE)
+            res = g.step_compact(a, b, steps, rm)
+            assert (res is b) == bool(steps & 1)
+            other = a if res is b else b
+            np.testing.assert_array_equal(res.cpu().numpy(), states[steps], err_msg=f"{name} r={r} {rule} {steps}")
+            np.testing.assert_array_equal(other.cpu().numpy(), states[steps - 1],
+                                          err_msg=f"{name} r={r} {rule} {steps}: the generation before")
+            a = torch.from_numpy(st0).cuda()
+            res = t.step_compact(a, torch.full_like(a, 0xEE), steps, rm)
+            np.testing.assert_array_equal(res.cpu().numpy(), states[steps], err_msg=f"temporal {name} {rule} {steps}")
+
+
+@gpu
+@pytest.mark.parametrize("resident", [True, False])
+@pytest.mark.parametrize("name,levels", [("triangle", (3, 6, 8, 9, 11)), ("carpet", (2, 4, 5, 6)),
+                                         ("hfractal", (2, 4, 5)), ("chandelier", (3, 5, 7, 9)),
+                                         ("vicsek", (2, 4, 6))])
+def test_batch_several_generations(N, name, levels, resident):
+    # whole batches and per-instance counts that take several launches of
+    # several generations; guard bytes between the instances
+    fd = W.FRACTALS[name]
+    rs = [levels[(3 * i) % len(levels)] for i in range(2 * len(levels))]
+    frs = [N.Fractal(fd.s, fd.offsets, r) for r in rs]
+    for f in frs:
+        f.configure(N.STRATEGY_TILED, min(levels))
+    offs, top = [], 0
+    for f in frs:
+        offs.append(top)
+        top = (top + f.cells + 15) // 16 * 16 + 32
+    batch = N.Batch(frs, offsets=offs, resident=resident)
+    orcs = [O.Fractal(fd.s, fd.offsets, r) for r in rs]
+    st0 = [o.init_compact(31 + i, 0.4) for i, o in enumerate(orcs)]
+    arena = np.ones(top + 64, np.uint8)
+    for off, st in zip(offs, st0):
+        arena[off:off + len(st)] = st
+    for rule in ("B3/S23", "B1357/S02468"):
+        rm = W.rule_mask(rule)
+        for counts in ([11] * len(rs), [20] * len(rs), [max(0, 37 - 5 * i) for i in range(len(rs))]):
+            a = torch.from_numpy(arena).cuda()
+            b = torch.full_like(a, 1)
+            if len(set(counts)) == 1:
+                batch.step(a, b, counts[0], rm)
+            else:
+                batch.step_each(a, b, counts, rm)
+            ha, hb = a.cpu().numpy(), b.cpu().numpy()
+            for i, (off, st, o) in enumerate(zip(offs, st0, orcs)):
+                got = (hb if counts[i] & 1 else ha)[off:off + len(st)]
+                np.testing.assert_array_equal(got, o.compact_steps(st, rm, counts[i]),
+                                              err_msg=f"{name} r={rs[i]} {rule} steps={counts[i]}")
+                ha[off:off + len(st)] = 1
+                hb[off:off + len(st)] = 1
+            assert (ha == 1).all() and (hb == 1).all()
