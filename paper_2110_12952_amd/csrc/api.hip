@@ -129,7 +129,7 @@ struct nbb_temporal_plan {
 // matrix form: `hp` with the set's tiles and their neighbours.
 struct HeldSet {
     bool ok = false;
-    bool in_place = false;            // every tile is a whole instance: results without alternating arenas
+    bool whole = false;               // every tile is a whole instance: results without alternating arenas
     HoldParams hp{};
     uint32_t al = 0, nr = 0, nh = 0, gpw = 0;
     const uint32_t *rec = nullptr;
@@ -394,10 +394,10 @@ uint32_t mat_align_of(uint32_t CB) { return CB % 16 == 0 ? 16 : (CB % 4 == 0 ? 4
 // Uploads the matrix plan's tables (operands, record addresses, halo blocks,
 // neighbour tiles) into one allocation.
 nbb_status upload_matrix(const MatPlan &p, DevBlob *blob, MatParams *T) {
-    const void *src[4] = {p.A.data(), p.raddr.data(), p.halo.data(), p.nbr.data()};
-    size_t bytes[4] = {p.A.size(), p.raddr.size() * 4, p.halo.size() * 4, p.nbr.size() * 4};
-    void *dst[4];
-    nbb_status s = upload(blob, src, bytes, 4, dst);
+    const void *src[5] = {p.A.data(), p.raddr.data(), p.halo.data(), p.nbr.data(), p.sel.data()};
+    size_t bytes[5] = {p.A.size(), p.raddr.size() * 4, p.halo.size() * 4, p.nbr.size() * 4, p.sel.size() * 4};
+    void *dst[5];
+    nbb_status s = upload(blob, src, bytes, 5, dst);
     if (s != NBB_OK) return s;
     *T = MatParams{};
     T->K = p.K;
@@ -413,15 +413,16 @@ nbb_status upload_matrix(const MatPlan &p, DevBlob *blob, MatParams *T) {
     T->raddr = static_cast<const uint32_t *>(dst[1]);
     T->halo = static_cast<const uint32_t *>(dst[2]);
     T->nbr = static_cast<const uint32_t *>(dst[3]);
+    T->sel = static_cast<const uint32_t *>(dst[4]);
     return NBB_OK;
 }
 
 // The same for a held plan; `nbr`: its tiles' neighbours.
 nbb_status upload_hold(const HoldPlan &p, const std::vector<uint32_t> &nbr, DevBlob *blob, HoldParams *T) {
-    const void *src[4] = {p.A.data(), p.raddr.data(), p.halo.data(), nbr.data()};
-    size_t bytes[4] = {p.A.size(), p.raddr.size() * 4, p.halo.size() * 4, nbr.size() * 4};
-    void *dst[4];
-    nbb_status s = upload(blob, src, bytes, 4, dst);
+    const void *src[5] = {p.A.data(), p.raddr.data(), p.halo.data(), nbr.data(), p.sel.data()};
+    size_t bytes[5] = {p.A.size(), p.raddr.size() * 4, p.halo.size() * 4, nbr.size() * 4, p.sel.size() * 4};
+    void *dst[5];
+    nbb_status s = upload(blob, src, bytes, 5, dst);
     if (s != NBB_OK) return s;
     *T = HoldParams{};
     T->K = p.K;
@@ -438,6 +439,7 @@ nbb_status upload_hold(const HoldPlan &p, const std::vector<uint32_t> &nbr, DevB
     T->raddr = static_cast<const uint32_t *>(dst[1]);
     T->halo = static_cast<const uint32_t *>(dst[2]);
     T->nbr = static_cast<const uint32_t *>(dst[3]);
+    T->sel = static_cast<const uint32_t *>(dst[4]);
     return NBB_OK;
 }
 
@@ -464,7 +466,7 @@ nbb_status setup_matrix(nbb_fractal *F) {
         !build_hold_plan(F->f, d.m, d.rings, gpw, &h, &msg))
         return NBB_OK;
     std::vector<uint32_t> nbr;
-    mat_neighbours(F->f, d.m, &nbr);
+    neighbour_table(F->f, F->f.r - d.m, &nbr);
     st = upload_hold(h, nbr, &F->dhold, &F->holdp);
     if (st != NBB_OK) return st;
     h.A.clear();
@@ -505,7 +507,7 @@ const uint32_t *batch_mat_nbr(const nbb_fractal *F, uint32_t m) {
     auto it = F->mat_nbrs.find(m);
     if (it == F->mat_nbrs.end()) {
         std::vector<uint32_t> nbr;
-        mat_neighbours(F->f, m, &nbr);
+        neighbour_table(F->f, F->f.r - m, &nbr);
         const void *src[1] = {nbr.data()};
         size_t bytes[1] = {nbr.size() * 4};
         void *dst[1];
@@ -582,6 +584,13 @@ nbb_status upload_box(nbb_fractal *F) {
     return NBB_OK;
 }
 
+// Launches of a held plan of at most `h` generations each that take T
+// generations, in a number of the parity of T where they alternate buffers.
+uint32_t held_launches(uint32_t T, uint32_t h, bool alternate) {
+    uint32_t L = T / h + (T % h != 0);
+    if (alternate) L += (L ^ T) & 1;
+    return L;
+}
 nbb_status check_device(const nbb_fractal *f) {
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
@@ -1493,7 +1502,7 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             batch_free(B);
             return hip_fail(e, "batch table build");
         }
-        S.in_place = true;
+        S.whole = true;
         B->small.push_back(std::move(S));
         B->cu_count = H.top->cu_count;
     }
@@ -1721,19 +1730,22 @@ static hipError_t batch_fork_groups(const nbb_batch *B, hipStream_t s) {
 static hipStream_t batch_group_stream(const nbb_batch *B, size_t k, hipStream_t s) {
     return (k == 0 || B->gstream.empty()) ? s : B->gstream[(k - 1) % B->gstream.size()];
 }
-// Launches of a held set that take `n` generations of an instance.
-static uint32_t held_launches(const HeldSet &S, uint32_t n) {
-    uint32_t L = n / S.hp.gens + (n % S.hp.gens != 0);
-    if (!S.in_place) L += (L ^ n) & 1;
-    return L;
-}
 // `steps` generations of every instance of the set, or counts[i] of instance
-// i; *used = false (nothing enqueued) where that takes about as many launches
-// as one per generation.
+// i.  Sets of whole instances take all of them in place and write the result
+// where it belongs; others take all but the last several at a time and the
+// last by itself, so that the other arena ends with the generation before, as
+// with one launch per generation.  *used = false (nothing enqueued) where
+// that takes about as many launches as one per generation.  *last: the last
+// generation is still to be taken, from *in to *out (never with counts).
 static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t arena_len, uint32_t steps,
-                            const uint32_t *counts, uint32_t rule, hipStream_t s, bool *used) {
+                            const uint32_t *counts, uint32_t rule, hipStream_t s, bool *used, bool *last = nullptr,
+                            uint8_t **in_ = nullptr, uint8_t **out_ = nullptr) {
     *used = false;
     if (!S.ok) return hipSuccess;
+    const uint32_t h = S.hp.gens;
+    auto launches = [&](uint32_t n) {
+        return S.whole ? held_launches(n, h, false) : (n ? held_launches(n - 1, h, true) : 0u);
+    };
     uint32_t L = 0, most = steps;
     std::vector<uint32_t> n;
     if (counts) {
@@ -1742,35 +1754,45 @@ static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t a
         for (size_t j = 0; j < n.size(); ++j) {
             n[j] = counts[S.index[j]];
             most = std::max(most, n[j]);
-            L = std::max(L, held_launches(S, n[j]));
+            L = std::max(L, launches(n[j]));
         }
     } else {
-        L = held_launches(S, steps);
+        L = launches(steps);
     }
-    if (!S.in_place && 2 * uint64_t(L) > most) return hipSuccess;
+    if (!S.whole && 2 * uint64_t(L) + 2 > most) return hipSuccess;
     *used = true;
-    if (!L) return hipSuccess;
+    if (!most) return hipSuccess;
     if (counts) {
         hipError_t e = launch_set_words(S.steps, n.data(), uint32_t(n.size()), s);
         if (e != hipSuccess) return e;
     }
+    auto go = [&](const HoldParams &E, uint8_t *in, uint8_t *out, uint32_t g, uint32_t i, uint32_t mode) {
+        return launch_step_hold(E, S.al, S.nr, S.nh, S.gpw, in, out, arena_len, rule, g, S.rec,
+                                counts ? S.steps : nullptr, i, mode, s);
+    };
     uint8_t *in = a, *out = b;
     size_t live = S.index.size();
+    const uint32_t T = S.whole ? steps : steps - 1;
     for (uint32_t i = 0; i < L; ++i) {
         HoldParams E = S.hp;
-        if (counts) {
-            while (live && held_launches(S, n[live - 1]) <= i) --live;  // (instances before may be done too: those tiles end at once)
+        if (counts) {  // (an instance before the last live one may be done too: its tiles end at once)
+            while (live && launches(n[live - 1]) <= i) --live;
             if (!live) break;
             E.ntiles = uint32_t(S.tiles_end[live - 1]);
         }
-        // in place: back to a until the last launch of a whole-batch call
-        uint8_t *dst = S.in_place && !counts && (i + 1 < L || !(steps & 1)) ? a : out;
-        const uint32_t g = counts ? 0 : steps / L + (i < steps % L ? 1u : 0u);
-        hipError_t e = launch_step_hold(E, S.al, S.nr, S.nh, S.gpw, in, dst, arena_len, rule, g, S.rec,
-                                        counts ? S.steps : nullptr, i, S.in_place ? 1u : 0u, s);
+        uint8_t *dst = S.whole && !counts && (i + 1 < L || !(steps & 1)) ? a : out;
+        hipError_t e = go(E, in, dst, counts ? 0 : T / L + (i < T % L ? 1u : 0u), i, S.whole ? kHoldWhole : kHoldMost);
         if (e != hipSuccess) return e;
-        if (!S.in_place) std::swap(in, out);
+        if (!S.whole) std::swap(in, out);
     }
+    if (S.whole) return hipSuccess;
+    if (counts) {
+        hipError_t e = go(S.hp, a, b, 1, 0, kHoldOdd);
+        return e == hipSuccess ? go(S.hp, b, a, 1, 0, kHoldEven) : e;
+    }
+    *last = true;
+    *in_ = in;
+    *out_ = out;
     return hipSuccess;
 }
 static hipError_t held_step_small(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t arena_len, uint32_t steps,
@@ -1816,10 +1838,11 @@ nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t a
     for (size_t k = 0; k < B->groups.size() && e == hipSuccess; ++k) {
         const BatchGroup &G = B->groups[k];
         const hipStream_t gs = batch_group_stream(B, k, s);
-        bool used = false;
-        e = held_step(G.held, a, b, arena_len, steps, nullptr, rule, gs, &used);
+        bool used = false, last = false;
         uint8_t *in = a, *out = b;
-        for (uint32_t i = 0; i < steps && e == hipSuccess && !used; ++i) {
+        e = held_step(G.held, a, b, arena_len, steps, nullptr, rule, gs, &used, &last, &in, &out);
+        const uint32_t left = !used ? steps : (last ? 1u : 0u);
+        for (uint32_t i = 0; i < left && e == hipSuccess; ++i) {
             e = G.matrix  ? launch_step_matrix(G.mp, G.al, G.nr, G.nh, G.gpw, in, out, arena_len, rule, G.rec,
                                                B->cu_count, gs)
                 : G.edges ? launch_step_edges(G.ep, G.BS, G.nsrc, in, out, arena_len, rule, G.rec, B->cu_count, gs)
@@ -2212,13 +2235,17 @@ nbb_status nbb_step_compact(const nbb_fractal *F, uint8_t *a, uint8_t *b, uint64
     if (result_in_b) *result_in_b = int(steps & 1);
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *in = a, *out = b;
-    if (F->strategy == NBB_STRATEGY_TEMPORAL && F->temporal_auto && F->hold.ok) {
+    if (F->strategy == NBB_STRATEGY_TEMPORAL && F->temporal_auto && F->hold.ok && F->hold.gens >= F->tmp.h) {
+        // The buffers end as with the ring plan's launches (below): the other
+        // one with the generation before its last launch.
         const HoldPlan &h = F->hold;
-        uint32_t L = steps / h.gens + (steps % h.gens != 0);
-        L += (L ^ steps) & 1;
-        for (uint32_t i = 0; i < L; ++i) {
-            hipError_t e = launch_step_hold(F->holdp, mat_align_of(h.CB), h.nr, h.nh, h.gpw, in, out, F->f.cells, rule,
-                                            steps / L + (i < steps % L ? 1u : 0u), nullptr, nullptr, 0, 0, s);
+        const uint32_t L0 = held_launches(steps, F->tmp.h, true), g0 = L0 ? steps / L0 : 0, T = steps - g0;
+        uint32_t L = held_launches(T, h.gens, false);
+        L += (L ^ (L0 - 1)) & 1;
+        for (uint32_t i = 0; i < (L0 ? L + 1 : 0); ++i) {
+            const uint32_t g = i == L ? g0 : T / L + (i < T % L ? 1u : 0u);
+            hipError_t e = launch_step_hold(F->holdp, mat_align_of(h.CB), h.nr, h.nh, h.gpw, in, out, F->f.cells, rule, g,
+                                            nullptr, nullptr, 0, 0, s);
             if (e != hipSuccess) return hip_fail(e, "held step launch");
             std::swap(in, out);
         }
@@ -2243,9 +2270,7 @@ nbb_status nbb_step_compact(const nbb_fractal *F, uint8_t *a, uint8_t *b, uint64
         // with one launch per generation.
         if (F->hold.ok && steps >= 4) {
             const HoldPlan &h = F->hold;
-            const uint32_t T = steps - 1;
-            uint32_t L = T / h.gens + (T % h.gens != 0);
-            L += (L ^ T) & 1;
+            const uint32_t T = steps - 1, L = held_launches(T, h.gens, true);
             for (uint32_t i = 0; i < L && 2 * L <= T; ++i) {
                 const uint32_t g = T / L + (i < T % L ? 1u : 0u);
                 hipError_t e = launch_step_hold(F->holdp, mat_align_of(h.CB), h.nr, h.nh, h.gpw, in, out, F->f.cells,

@@ -1171,17 +1171,17 @@ hipError_t launch_step_matrix(const MatParams &E0, uint32_t al, uint32_t nr, uin
 }
 hipError_t launch_step_hold(const HoldParams &E0, uint32_t al, uint32_t nr, uint32_t nh, uint32_t gpw,
                             uint8_t *in, uint8_t *out, uint64_t limit, uint32_t rule, uint32_t gens,
-                            const uint32_t *rec, const uint32_t *steps_of, uint32_t launch, uint32_t in_place, hipStream_t st) {
+                            const uint32_t *rec, const uint32_t *steps_of, uint32_t launch, uint32_t mode, hipStream_t st) {
     HoldParams E = E0;
     E.limit = limit;
     const bool life = rule == kRuleB3S23;
 #define NBB_HOLD_GO(B, R)                                                                                          \
     do {                                                                                                            \
         if (al == 16)                                                                                               \
-            return launch_hold_inst<B, R, 16>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, in_place, st);      \
+            return launch_hold_inst<B, R, 16>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, mode, st);      \
         if (al == 4)                                                                                                \
-            return launch_hold_inst<B, R, 4>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, in_place, st);       \
-        return launch_hold_inst<B, R, 1>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, in_place, st);           \
+            return launch_hold_inst<B, R, 4>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, mode, st);       \
+        return launch_hold_inst<B, R, 1>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, mode, st);           \
     } while (0)
     if (rec) {
         if (life) NBB_HOLD_GO(true, 0);

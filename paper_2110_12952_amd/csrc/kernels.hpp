@@ -58,7 +58,7 @@ hipError_t launch_step_matrix(const MatParams &E, uint32_t al, uint32_t nr, uint
 // `launch` of a call, see k_step_hold.
 hipError_t launch_step_hold(const HoldParams &E, uint32_t al, uint32_t nr, uint32_t nh, uint32_t gpw,
                             uint8_t *in, uint8_t *out, uint64_t limit, uint32_t rule, uint32_t gens,
-                            const uint32_t *rec, const uint32_t *steps_of, uint32_t launch, uint32_t in_place, hipStream_t st);
+                            const uint32_t *rec, const uint32_t *steps_of, uint32_t launch, uint32_t mode, hipStream_t st);
 // The tiled step over the tiles of a batch (tables from launch_batch_tiles,
 // T.ntiles = batch tiles, T.nbr = the batch neighbour table).
 hipError_t launch_step_tiled_batch(const TileParams &T, const uint32_t *rec, const uint8_t *arena_in,

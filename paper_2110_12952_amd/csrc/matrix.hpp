@@ -19,7 +19,7 @@
 //
 // Per tile a work-group
 //   1. publishes the record of every block (the cells its neighbours need, as
-//      bytes; a contraction with 0/1 rows picks them) in LDS, own blocks and
+//      bytes; two v_perm per dword pick them) in LDS, own blocks and
 //      the blocks of the eight neighbour tiles that a block of the tile reads
 //      (zeros where a neighbour tile does not exist: their loads are out of
 //      the buffer's range);
@@ -119,6 +119,11 @@ __device__ __forceinline__ uint32_t lds_at(const uint8_t *base, uint32_t off) {
 __device__ __forceinline__ uint32_t lds_get(uint32_t a) { return *reinterpret_cast<lds_u32 *>(uintptr_t(a)); }
 __device__ __forceinline__ void lds_put(uint32_t a, uint32_t v) { *reinterpret_cast<lds_u32 *>(uintptr_t(a)) = v; }
 
+// A record dword out of a lane's 16 cells.
+__device__ __forceinline__ uint32_t mat_pick(const u32x4 &x, uint32_t lo, uint32_t hi) {
+    return __builtin_amdgcn_perm(x[1], x[0], lo) | __builtin_amdgcn_perm(x[3], x[2], hi);
+}
+
 // Next states of four cells: n their live-neighbour counts, o the cells.
 template <int RULE>
 __device__ __forceinline__ uint32_t mat_rule(uint32_t n, uint32_t o, uint32_t rule, const RuleTables &RT, bool tables) {
@@ -159,7 +164,8 @@ __global__ __launch_bounds__(64 * kMatMaxWaves) void k_step_matrix(MatParams E, 
     const bool edge = (rule >> 31) != 0;
     const uint8_t *A8 = reinterpret_cast<const uint8_t *>(E.A) + 16 * lane;
     auto operand = [&](uint32_t off) -> u32x4 { return *reinterpret_cast<const u32x4 *>(A8 + off); };
-    u32x4 Aself[2], Ahalo[NH][2], Arec[NR];
+    u32x4 Aself[2], Ahalo[NH][2];
+    uint32_t sel[NR][2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) Aself[t] = operand(mat_self_off(NH, edge, t));
 #pragma unroll
@@ -167,7 +173,9 @@ __global__ __launch_bounds__(64 * kMatMaxWaves) void k_step_matrix(MatParams E, 
 #pragma unroll
         for (int t = 0; t < 2; ++t) Ahalo[h][t] = operand(mat_halo_off(NH, edge, h, t));
 #pragma unroll
-    for (int t = 0; t < NR; ++t) Arec[t] = operand(mat_rec_off(NH, t));
+    for (int t = 0; t < NR; ++t)
+#pragma unroll
+        for (int d = 0; d < 2; ++d) sel[t][d] = E.sel[2 * (4 * t + sub) + d];
     const uint32_t rstride = 4 * L * E.nrecs;  // from one record result's dwords to the next's
     uint32_t voff[GPW], waddr[GPW], raddr[GPW][2 * NH];
 #pragma unroll
@@ -247,12 +255,12 @@ __global__ __launch_bounds__(64 * kMatMaxWaves) void k_step_matrix(MatParams E, 
             x[u] = mat_align<AL>(P.raw[u], AL == 1 ? voff[u] + P.phase : 0u);
 #pragma unroll
             for (int t = 0; t < NR; ++t)
-                *reinterpret_cast<uint32_t *>(lds_m + waddr[u] + t * rstride) = mat_bytes(mat_mul(Arec[t], x[u], zero));
+                *reinterpret_cast<uint32_t *>(lds_m + waddr[u] + t * rstride) = mat_pick(x[u], sel[t][0], sel[t][1]);
         }
         const u32x4 hx = mat_align<AL>(P.hraw, P.hpos);
 #pragma unroll
         for (int t = 0; t < NR; ++t)
-            *reinterpret_cast<uint32_t *>(lds_m + hwaddr + t * rstride) = mat_bytes(mat_mul(Arec[t], hx, zero));
+            *reinterpret_cast<uint32_t *>(lds_m + hwaddr + t * rstride) = mat_pick(hx, sel[t][0], sel[t][1]);
         const __amdgpu_buffer_rsrc_t gout = mat_rsrc(P.dst, P.bytes);
         // the next tile's loads, the neighbour tile of the one after it
         const uint32_t nt1 = nt;
@@ -346,20 +354,23 @@ static hipError_t launch_matrix_t(const MatParams &E, const uint8_t *in, uint8_t
 // generation of a small state costs a barrier instead of a launch.
 //   BUF: the second record buffer's offset (an instruction offset).
 //   BATCH: rec as above; word 3 of a tile's record indexes steps_of, the
-//   generations its instance takes in the whole call (steps_of NULL: every
-//   instance takes `gens` now).  The call's launches number `launch` from 0;
-//   an instance takes its generations in as few launches as E.gens allows
-//   and nothing in launches past those.  in_place 0: launches alternate the
-//   buffers, so there is one more where needed for their number to have the
-//   parity of its generations (the result's buffer).  in_place 1 (tiles that
-//   are whole instances): every launch writes back to `in`, an instance's last
-//   one to `out` if its count is odd.
+//   generations n its instance takes in the whole call (steps_of NULL: every
+//   instance takes `gens` now).  mode says which of a call's launches it is:
+//     kHoldMost  number `launch` (from 0) of those that take all but the last
+//                generation, in as few launches as E.gens allows plus one where
+//                their number would not have the parity of n - 1 (launches
+//                alternate the buffers); nothing past an instance's own
+//     kHoldOdd, kHoldEven  the last generation of the instances of odd n
+//                (from a to b), of even n (from b to a)
+//     kHoldWhole  number `launch` of those that take all n (tiles that are
+//                whole instances): back to `in`, an instance's last one to
+//                `out` if n is odd
 template <int AL, int NR, int NH, int GPW, int BUF, bool BATCH, int RULE>
 __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, uint8_t *in, uint8_t *out,
                                                                   uint32_t rule, uint32_t gens,
                                                                   const uint32_t *__restrict__ rec,
                                                                   const uint32_t *__restrict__ steps_of,
-                                                                  uint32_t launch, uint32_t in_place) {
+                                                                  uint32_t launch, uint32_t mode) {
     extern __shared__ __align__(16) uint8_t lds_m[];
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
@@ -375,11 +386,17 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
         bytes = min(E.K, r[2]);
         if (steps_of) {
             const uint32_t n = steps_of[r[3]];
-            uint32_t L = n / E.gens + (n % E.gens != 0);
-            if (!in_place) L += (L ^ n) & 1;
-            if (launch >= L) return;
-            gens = n / L + (launch < n % L ? 1u : 0u);
-            if (in_place && (launch + 1 < L || !(n & 1))) out = in;
+            if (mode == kHoldOdd || mode == kHoldEven) {
+                if (n == 0 || (n & 1) != (mode == kHoldOdd ? 1u : 0u)) return;
+                gens = 1;
+            } else {
+                const uint32_t T = mode == kHoldWhole ? n : max(n, 1u) - 1;
+                uint32_t L = T / E.gens + (T % E.gens != 0);
+                if (mode == kHoldMost) L += (L ^ T) & 1;
+                if (launch >= L) return;
+                gens = T / L + (launch < T % L ? 1u : 0u);
+                if (mode == kHoldWhole && (launch + 1 < L || !(n & 1))) out = in;
+            }
         }
     }
     const uint32_t L = E.lanes, quarter = lane >> 4, col = lane & 15;
@@ -410,9 +427,12 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
     const bool edge = (rule >> 31) != 0;
     const uint8_t *A8 = reinterpret_cast<const uint8_t *>(E.A) + 16 * lane;
     auto operand = [&](uint32_t off) -> u32x4 { return *reinterpret_cast<const u32x4 *>(A8 + off); };
-    u32x4 Aself[2], Ahalo[NH][2], Arec[NR];
+    u32x4 Aself[2], Ahalo[NH][2];
+    uint32_t sel[NR][2];
 #pragma unroll
-    for (int k = 0; k < NR; ++k) Arec[k] = operand(mat_rec_off(NH, k));
+    for (int k = 0; k < NR; ++k)
+#pragma unroll
+        for (int d = 0; d < 2; ++d) sel[k][d] = E.sel[2 * (4 * k + sub) + d];
 #pragma unroll
     for (int k = 0; k < 2; ++k) Aself[k] = operand(mat_self_off(NH, edge, k));
 #pragma unroll
@@ -458,7 +478,7 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
         for (int u = 0; u < GPW; ++u)
 #pragma unroll
             for (int k = 0; k < NR; ++k)
-                lds_put(waddr[u] + P + 4 * k, mat_bytes(mat_mul(Arec[k], x[u], zero)));
+                lds_put(waddr[u] + P + 4 * k, mat_pick(x[u], sel[k][0], sel[k][1]));
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < GPW; ++u) {
@@ -495,12 +515,12 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
 
 template <int AL, int NR, int NH, int GPW, int BUF, bool BATCH, int RULE>
 static hipError_t launch_hold_t(const HoldParams &E, uint8_t *in, uint8_t *out, uint32_t rule, uint32_t gens,
-                                const uint32_t *rec, const uint32_t *steps_of, uint32_t launch, uint32_t in_place,
+                                const uint32_t *rec, const uint32_t *steps_of, uint32_t launch, uint32_t mode,
                                 hipStream_t st) {
     if (!E.ntiles) return hipSuccess;
     const uint32_t lds = BUF + E.zero + 4;
     hipLaunchKernelGGL((k_step_hold<AL, NR, NH, GPW, BUF, BATCH, RULE>), dim3(E.ntiles), dim3(64 * E.waves), lds, st, E,
-                       in, out, rule, gens, rec, steps_of, launch, in_place);
+                       in, out, rule, gens, rec, steps_of, launch, mode);
     return hipGetLastError();
 }
 
@@ -529,14 +549,14 @@ static hipError_t launch_matrix_shape(const MatParams &E, uint32_t nr, uint32_t 
 template <int AL, bool BATCH, int RULE>
 static hipError_t launch_hold_shape(const HoldParams &E, uint32_t nr, uint32_t nh, uint32_t gpw, uint8_t *in,
                                     uint8_t *out, uint32_t rule, uint32_t gens, const uint32_t *rec,
-                                    const uint32_t *steps_of, uint32_t launch, uint32_t in_place, hipStream_t st) {
+                                    const uint32_t *steps_of, uint32_t launch, uint32_t mode, hipStream_t st) {
     const bool small = E.zero + 4 <= 8192;
 #define NBB_HOLD_CASE(R, H, G)                                                                                    \
     if (nr == R && nh == H && gpw == G)                                                                           \
     return small ? launch_hold_t<AL, R, H, G, 8192, BATCH, RULE>(E, in, out, rule, gens, rec, steps_of, launch,   \
-                                                                 in_place, st)                                    \
+                                                                 mode, st)                                    \
                  : launch_hold_t<AL, R, H, G, int(kHoldBuf), BATCH, RULE>(E, in, out, rule, gens, rec, steps_of,  \
-                                                                          launch, in_place, st)
+                                                                          launch, mode, st)
 #define NBB_HOLD_CASES(R, H) \
     NBB_HOLD_CASE(R, H, 1);  \
     NBB_HOLD_CASE(R, H, 2);  \

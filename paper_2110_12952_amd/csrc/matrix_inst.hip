@@ -23,8 +23,8 @@ template hipError_t launch_matrix_inst<bool(NBB_INST_BATCH), NBB_INST_RULE, NBB_
 template <bool BATCH, int RULE, int AL>
 hipError_t launch_hold_inst(const HoldParams &E, uint32_t nr, uint32_t nh, uint32_t gpw, uint8_t *in,
                             uint8_t *out, uint32_t rule, uint32_t gens, const uint32_t *rec, const uint32_t *steps_of,
-                            uint32_t launch, uint32_t in_place, hipStream_t st) {
-    return launch_hold_shape<AL, BATCH, RULE>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, in_place, st);
+                            uint32_t launch, uint32_t mode, hipStream_t st) {
+    return launch_hold_shape<AL, BATCH, RULE>(E, nr, nh, gpw, in, out, rule, gens, rec, steps_of, launch, mode, st);
 }
 
 template hipError_t launch_hold_inst<bool(NBB_INST_BATCH), NBB_INST_RULE, NBB_INST_AL>(

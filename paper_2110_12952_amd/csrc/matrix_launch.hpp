@@ -14,7 +14,7 @@ hipError_t launch_matrix_inst(const MatParams &E, uint32_t nr, uint32_t nh, uint
 template <bool BATCH, int RULE, int AL>
 hipError_t launch_hold_inst(const HoldParams &E, uint32_t nr, uint32_t nh, uint32_t gpw, uint8_t *in,
                             uint8_t *out, uint32_t rule, uint32_t gens, const uint32_t *rec, const uint32_t *steps_of,
-                            uint32_t launch, uint32_t in_place, hipStream_t st);
+                            uint32_t launch, uint32_t mode, hipStream_t st);
 
 #define NBB_MAT_INST_DECL(B, R, AL)                                                                             \
     extern template hipError_t launch_matrix_inst<B, R, AL>(const MatParams &, uint32_t, uint32_t, uint32_t,    \

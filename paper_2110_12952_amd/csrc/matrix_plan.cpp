@@ -1,5 +1,7 @@
 // Host-side plan of the matrix-core form of the tiled step.  See MatParams in
 // params.hpp for the scheme.
+#include <stddef.h>
+
 #include <algorithm>
 #include <map>
 
@@ -24,7 +26,7 @@ struct BlockShape {
     uint32_t q = 0, CB = 0, BS = 0, lanes = 0, nr = 0, nh = 0;
     std::vector<int64_t> x, y;               // the block's cells
     std::vector<std::vector<uint32_t>> need;  // per direction: cells of that neighbour next to one of ours
-    std::vector<int32_t> rec;                // lanes * nr * 4 record bytes: cell or -1
+    std::vector<int32_t> rec;                // lanes * nr * 4 record bytes: cell or -1; dword t lanes + sub is lane sub's t-th
     std::vector<std::pair<uint32_t, uint32_t>> reads;  // (direction, record dword)
 };
 
@@ -75,42 +77,56 @@ bool block_shape(const Fractal &f, uint32_t q, BlockShape *s) {
                     break;
                 }
         }
-    // Two ways to lay the record out, the better kept: every needed cell once
-    // (few cells in all: fewer record dwords), or each direction's cells in
-    // dwords of their own (fewer reads per block).
-    bool found = false;
-    for (int way = 0; way < 2; ++way) {
-        std::vector<int32_t> rec;
-        std::vector<uint32_t> order = {3, 4, 1, 6, 0, 2, 5, 7};
-        std::stable_sort(order.begin(), order.end(),
-                         [&](uint32_t a, uint32_t b) { return s->need[a].size() > s->need[b].size(); });
-        for (uint32_t d : order) {
-            std::vector<uint32_t> fresh;
-            std::vector<uint32_t> missing;
+    // The record: dwords of up to four needed cells held by one lane each.  A
+    // direction's cells of one lane go four at a time into a dword that has
+    // them or room for them, else into a new one, so that a direction is read
+    // in few dwords; cells that two lanes hold (the last lane overlaps the one
+    // before) go to the lane with fewer dwords.
+    std::vector<std::vector<std::vector<uint32_t>>> dw(s->lanes);
+    auto first_cell = [&](uint32_t sub) { return std::min(16 * sub, s->CB - 16); };
+    std::vector<uint32_t> order = {0, 1, 2, 3, 4, 5, 6, 7};
+    std::stable_sort(order.begin(), order.end(),
+                     [&](uint32_t a, uint32_t b) { return s->need[a].size() > s->need[b].size(); });
+    for (uint32_t d : order)
+        for (uint32_t sub = 0; sub < s->lanes; ++sub) {
+            std::vector<uint32_t> mine;
             for (uint32_t e : s->need[d])
-                if (std::find(rec.begin(), rec.end(), int32_t(e)) == rec.end()) missing.push_back(e);
-            // a direction whose cells are already in at most one more dword
-            // than a run of its own would take reads those
-            fresh = way == 0 || missing.empty() || s->need[d].size() == 1 ? missing : s->need[d];
-            for (uint32_t e : fresh) rec.push_back(int32_t(e));
-            if (way == 1)
-                while (rec.size() % 4) rec.push_back(-1);
+                if (e / 16 == sub) mine.push_back(e);
+            for (size_t i = 0; i < mine.size(); i += 4) {
+                const std::vector<uint32_t> part(mine.begin() + ptrdiff_t(i),
+                                                 mine.begin() + ptrdiff_t(std::min(i + 4, mine.size())));
+                std::vector<uint32_t> *home = nullptr;
+                size_t grow = 5;
+                uint32_t fresh = sub;
+                for (uint32_t l = 0; l < s->lanes; ++l) {
+                    if (part.front() < first_cell(l) || part.back() >= first_cell(l) + 16) continue;
+                    if (dw[l].size() < dw[fresh].size()) fresh = l;
+                    for (auto &w : dw[l]) {
+                        size_t more = 0;
+                        for (uint32_t e : part) more += !std::count(w.begin(), w.end(), e);
+                        if (w.size() + more > 4 || more >= grow) continue;
+                        grow = more;
+                        home = &w;
+                    }
+                }
+                if (!home) {
+                    dw[fresh].emplace_back();
+                    home = &dw[fresh].back();
+                }
+                for (uint32_t e : part)
+                    if (!std::count(home->begin(), home->end(), e)) home->push_back(e);
+            }
         }
-        while (rec.size() % 4) rec.push_back(-1);
-        std::vector<std::pair<uint32_t, uint32_t>> reads;
-        for (uint32_t d = 0; d < 8; ++d) reads_of(rec, d, s->need[d], &reads);
-        const uint32_t nr = std::max<uint32_t>(1, uint32_t((rec.size() / 4 + s->lanes - 1) / s->lanes));
-        const uint32_t nh = std::max<uint32_t>(1, uint32_t((reads.size() + 4 * s->lanes - 1) / (4 * s->lanes)));
-        if (nr > 3 || nh > 2) continue;
-        if (found && (nh > s->nh || (nh == s->nh && nr >= s->nr))) continue;
-        found = true;
-        s->nr = nr;
-        s->nh = nh;
-        s->rec = rec;
-        s->rec.resize(size_t(nr) * s->lanes * 4, -1);
-        s->reads = reads;
-    }
-    return found;
+    s->nr = 1;
+    for (const auto &l : dw) s->nr = std::max<uint32_t>(s->nr, uint32_t(l.size()));
+    s->rec.assign(size_t(s->nr) * s->lanes * 4, -1);
+    for (uint32_t l = 0; l < s->lanes; ++l)
+        for (size_t t = 0; t < dw[l].size(); ++t)
+            for (size_t j = 0; j < dw[l][t].size(); ++j)
+                s->rec[4 * (t * s->lanes + l) + j] = int32_t(dw[l][t][j]);
+    for (uint32_t d = 0; d < 8; ++d) reads_of(s->rec, d, s->need[d], &s->reads);
+    s->nh = std::max<uint32_t>(1, uint32_t((s->reads.size() + 4 * s->lanes - 1) / (4 * s->lanes)));
+    return s->nr <= 3 && s->nh <= 2;
 }
 
 // The largest block level with 16 to 64 cells whose ring fits.
@@ -129,19 +145,6 @@ bool pick_shape(const Fractal &f, BlockShape *s) {
 }
 
 }  // namespace
-
-void mat_neighbours(const Fractal &f, uint32_t m, std::vector<uint32_t> *nbr) {
-    const uint64_t tiles = ipow(f.k, f.r - m);
-    nbr->assign(size_t(tiles) * 8, 0xFFFFFFFFu);
-    for (uint64_t t = 0; t < tiles; ++t) {
-        int64_t X, Y;
-        lambda_levels(f, f.r - m, t, &X, &Y);
-        for (uint32_t d = 0; d < 8; ++d) {
-            const int64_t v = nu_levels(f, f.r - m, X + kDirX[d], Y + kDirY[d]);
-            if (v >= 0) (*nbr)[size_t(t) * 8 + d] = uint32_t(v);
-        }
-    }
-}
 
 // The blocks of the tile at level m and of its neighbour tiles: `source`
 // gets the record of every read of every block (an own block, a halo block
@@ -234,7 +237,7 @@ static uint32_t pick_gpw(uint32_t groups, uint32_t hgroups, uint64_t tiles, uint
 static void mat_operands(const BlockShape &s, std::vector<int8_t> *A) {
     // operands: lane l of an operand holds row l % 16, products 16 (l / 16) ..
     const uint32_t nh = s.nh;
-    A->assign(size_t(1024) * (2 * (2 + 2 * nh) + s.nr), 0);
+    A->assign(size_t(1024) * 2 * (2 + 2 * nh), 0);
     auto first_cell = [&](uint32_t sub) { return std::min(16 * sub, s.CB - 16); };
     auto put = [&](uint32_t off, uint32_t row, uint32_t quarter, uint32_t byte, int w) {
         (*A)[off + (quarter * 16 + row) * 16 + byte] = int8_t((*A)[off + (quarter * 16 + row) * 16 + byte] + w);
@@ -278,14 +281,20 @@ static void mat_operands(const BlockShape &s, std::vector<int8_t> *A) {
                             }
                     }
     }
-    // record result t: lane `sub` of a block gets record dword t lanes + sub
-    for (uint32_t g = 0; g < 4; ++g)
-        for (uint32_t i = 0; i < 4; ++i)
-            for (uint32_t t = 0; t < s.nr; ++t) {
-                const int32_t e = s.rec[4 * (t * s.lanes + g % s.lanes) + i];
+}
+
+// Selectors of record dword t of lane sub, at 2 (4 t + sub): its bytes out of
+// the lane's first two dwords and out of its last two (12: a zero byte).
+static void mat_selectors(const BlockShape &s, std::vector<uint32_t> *sel) {
+    sel->assign(size_t(8) * s.nr, 0x0C0C0C0Cu);
+    for (uint32_t t = 0; t < s.nr; ++t)
+        for (uint32_t sub = 0; sub < s.lanes; ++sub)
+            for (uint32_t j = 0; j < 4; ++j) {
+                const int32_t e = s.rec[4 * (t * s.lanes + sub) + j];
                 if (e < 0) continue;
-                const uint32_t sub = uint32_t(e) / 16;  // its first holder
-                put(mat_rec_off(nh, t), 4 * g + i, g / s.lanes * s.lanes + sub, uint32_t(e) - first_cell(sub), 1);
+                const uint32_t at = uint32_t(e) - std::min(16 * sub, s.CB - 16);  // the lane's byte
+                uint32_t &w = (*sel)[2 * (4 * t + sub) + (at >= 8)];
+                w = (w & ~(0xFFu << (8 * j))) | (at & 7) << (8 * j);
             }
 }
 
@@ -315,7 +324,8 @@ static bool build_mat_shape(const Fractal &f, const BlockShape &s, uint32_t m, u
             w = d % 2 ? (w & 0xFFFFu) | addr << 16 : (w & 0xFFFF0000u) | addr;
         }
     mat_operands(s, &p->A);
-    if (with_nbr) mat_neighbours(f, m, &p->nbr);
+    mat_selectors(s, &p->sel);
+    if (with_nbr) neighbour_table(f, f.r - m, &p->nbr);
     p->ok = true;
     return true;
 }
@@ -366,9 +376,11 @@ static bool hold_members(const Fractal &f, const BlockShape &s, uint32_t m, uint
         }
     p->ntot = uint32_t(at->size());
     p->groups = (p->ntot + bpg - 1) / bpg;
-    // a record in consecutive dwords, an odd number of them where a multiple
-    // of eight would put the same dword of every record into few LDS banks
-    p->rs = s.lanes * s.nr + (s.lanes * s.nr % 8 == 0 ? 1 : 0);
+    // A record in consecutive dwords, one more of them where their number is a
+    // multiple of four: the 32 banks of a half wavefront's read then serve
+    // records at an odd distance (a bank model that agrees with the conflict
+    // counters gives 5.3 -> 4.0 cycles per read on H, 6.4 -> 4.6 on the carpet).
+    p->rs = s.lanes * s.nr + (s.lanes * s.nr % 4 == 0 ? 1 : 0);
     const uint64_t words = uint64_t(p->ntot + 1) * p->rs + 1;  // one record never read, one dword of zeros
     p->zero = uint32_t(4 * (words - 1));
     if (p->ntot > most || words * 4 > kHoldBuf) {
@@ -378,13 +390,13 @@ static bool hold_members(const Fractal &f, const BlockShape &s, uint32_t m, uint
     return true;
 }
 
-// Groups per wavefront: one up to five groups, two up to 22, else four (four
+// Groups per wavefront: one up to five groups, two up to 24, else four (four
 // wavefronts or more share the groups, registers for several work-groups per
-// CU).  One / two / four: triangle r16 at level 8 (8 groups, 20 generations)
-// 128 / 111 / 118 us, carpet r9 at 4 (7 groups, 10 generations) 283 / 265 /
-// 275, H r8 at 4 (5 groups) 50 / 53 / 63, chandelier r13 at 7 (17) - / 142 /
-// 169, full square r12 at 7 (21) - / 74 / 103, H r10 at 5 (27) - / 631 / 548.
-static uint32_t hold_gpw(uint32_t groups) { return groups <= 5 ? 1 : (groups <= 22 ? 2 : 4); }
+// CU).  One / two / four: triangle r16 at level 8 (8 groups, 97 generations)
+// 515 / 409 / 441 us, at 9 (24 groups) - / 394 / 464, carpet r9 at 4 (7
+// groups, 46 generations) 1,069 / 933 / 953, H r8 at 4 (5 groups, 91) 167 /
+// 171 / 229, H r10 at 5 (27 groups, 46) - / 2,519 / 2,029.
+static uint32_t hold_gpw(uint32_t groups) { return groups <= 5 ? 1 : (groups <= 24 ? 2 : 4); }
 
 bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw, HoldPlan *p, std::string *msg) {
     BlockShape s;
@@ -416,6 +428,7 @@ bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw,
             w = d % 2 ? (w & 0xFFFFu) | addr << 16 : (w & 0xFFFF0000u) | addr;
         }
     mat_operands(s, &p->A);
+    mat_selectors(s, &p->sel);
     if (p->halo.empty()) p->halo.push_back(0);
     p->ok = true;
     return true;
@@ -437,13 +450,13 @@ std::vector<HoldDims> hold_dims(const Fractal &f) {
 }
 
 // Estimated time per generation in us: a launch (4 us, and the state through
-// memory once) over its generations (counted up to 24, what a call often
-// asks for at least), and a generation: 0.25 us for a barrier and the round
-// through LDS, 0.022 us per group on the busiest CU (more beyond 30 groups,
-// where one work-group leaves no room for a second), 0.03 us per group of a
-// work-group alone on its CU.  Fitted to sweeps over triangle r7 - r16, carpet
-// r5 - r9, H r8 - r10, Vicsek r10, chandelier r13 and full square r12; more
-// rings only for a gain of 5 %.
+// memory once) over its generations (counted up to 24 for small states, where
+// the launch is what counts, up to 12 for others: a call may ask for fewer),
+// and a generation: 0.2 us for the barrier and the round through LDS and 0.02
+// us per group on the busiest CU, 15 % more where a work-group has more than
+// 16 groups, 75 % more beyond 30 (one or two work-groups per CU).  Fitted to
+// sweeps over triangle r7 - r16, carpet r5 - r9, H r5 - r10, Vicsek r10,
+// chandelier r13 and full square r12; more rings only for a gain of 5 %.
 bool pick_hold(const std::vector<HoldDims> &dims, uint32_t k, const std::vector<uint32_t> &levels, uint32_t cus,
                HoldDims *out, uint32_t *gpw) {
     cus = std::max(cus, 1u);
@@ -455,8 +468,10 @@ bool pick_hold(const std::vector<HoldDims> &dims, uint32_t k, const std::vector<
         uint64_t tiles = 0;
         for (uint32_t r : levels) tiles += r > d.m ? ipow(k, r - d.m) : 1;
         const double work = double((tiles + cus - 1) / cus) * d.groups;
-        const double gen = std::max({0.25, (d.groups > 30 ? 0.035 : 0.022) * work, 0.03 * d.groups});
-        const double t = (4.0 + double(cells) * 1.6e-7) / (d.rings ? std::min(d.gens, 24u) : 64u) + gen;
+        const double gen = std::max(0.2 + (d.groups > 30 ? 0.035 : (d.groups > 16 ? 0.023 : 0.02)) * work,
+                                    0.03 * d.groups);
+        const double t = (4.0 + double(cells) * 1.6e-7) / (d.rings ? std::min(d.gens, cells < 4000000 ? 24u : 12u) : 64u) +
+                         gen;
         if (found && t >= (d.rings > out->rings ? 0.95 * best : best)) continue;
         found = true;
         best = t;

@@ -157,9 +157,9 @@ constexpr uint32_t edge_lds_bytes(uint32_t bpt, uint32_t hpt) { return 16 * edge
 // (weight 1) and 8 t + 4 + i (weight 16) of the lanes of quarter g, so the
 // counts arrive in the lanes that hold the cells, two per byte.
 // The cells around the block come the same way from 4 nh record dwords per
-// lane: block b publishes the cells its neighbours need (lanes x nr dwords,
-// picked by a contraction with 0/1 rows) in LDS, dword rd of record b at
-// 4 (rd nrecs + b).
+// lane: block b publishes the cells its neighbours need in LDS (nr dwords per
+// lane, each four bytes picked out of the lane's sixteen), dword
+// t lanes + sub of record b at 4 ((t lanes + sub) nrecs + b).
 struct MatParams {
     uint32_t K, CB, lanes;   // cells per tile, per block; lanes per block
     uint32_t nblk, nhalo;    // blocks per tile, blocks of neighbour tiles that are read
@@ -167,12 +167,16 @@ struct MatParams {
     uint32_t buf_bytes;      // one record buffer (a multiple of 16); LDS holds two
     uint32_t waves;          // wavefronts per work-group
     uint32_t ntiles;
-    const int8_t *A;         // 1 KiB operands: Moore self x 2, halo x 2 nh; four-cell the same; records x nr
+    const int8_t *A;         // 1 KiB operands: Moore self x 2, halo x 2 nh; four-cell the same
+    const uint32_t *sel;     // v_perm selectors of record dword t of lane sub: two at 2 (4 t + sub)
     const uint32_t *raddr;   // per group and lane 2 nh dwords: two LDS offsets each
     const uint32_t *halo;    // per halo block: direction << 29 | block
     const uint32_t *nbr;     // 8 neighbour tiles per tile (0xFFFFFFFF = none)
     uint64_t limit;          // bytes of the input that may be read (the state, or the whole arena)
 };
+
+// Which of a batch call's launches a held launch is (k_step_hold).
+constexpr uint32_t kHoldMost = 0, kHoldOdd = 1, kHoldEven = 2, kHoldWhole = 3;
 
 // Several generations per launch in the matrix form: the tile's blocks and
 // those of its neighbour tiles around it, all held in registers.  Records in
@@ -185,6 +189,7 @@ struct HoldParams {
     uint32_t gens;           // generations per launch at most
     uint32_t ntiles;
     const int8_t *A;         // as MatParams
+    const uint32_t *sel;
     const uint32_t *raddr;
     const uint32_t *halo;    // per neighbour block: direction << 29 | block
     const uint32_t *nbr;

@@ -121,6 +121,46 @@ static uint64_t ipow64(uint64_t b, uint32_t e) {
     return p;
 }
 
+// Level by level: a cell of level l is a replica of a cell of level l - 1; its
+// neighbour is another replica of the same cell, or a replica of that cell's
+// neighbour, by the digit pair alone.
+void neighbour_table(const Fractal &f, uint32_t levels, std::vector<uint32_t> *nbr) {
+    const uint32_t none = 0xFFFFFFFFu;
+    // per replica and direction: the direction to step in one level up (8:
+    // none), and the replica arrived at
+    struct Move {
+        uint32_t up, child;
+    };
+    std::vector<Move> move(size_t(f.k) * 8);
+    for (uint32_t d = 0; d < f.k; ++d) {
+        uint32_t dir = 0;
+        for (int dy = -1; dy <= 1; ++dy)
+            for (int dx = -1; dx <= 1; ++dx) {
+                if (!dx && !dy) continue;
+                const int s = int(f.s), x = f.ox[d] + dx, y = f.oy[d] + dy;
+                const int ux = x < 0 ? -1 : (x >= s ? 1 : 0), uy = y < 0 ? -1 : (y >= s ? 1 : 0);
+                const uint32_t at = uint32_t((uy + 1) * 3 + ux + 1);  // 0..8, 4 = stay
+                const uint8_t h = f.hl[(x - ux * s) + s * (y - uy * s)];
+                move[d * 8 + dir++] = {at == 4 ? 8u : (at > 4 ? at - 1 : at), h == 0xFF ? none : h};
+            }
+    }
+    std::vector<uint32_t> above(8, none), here;
+    uint64_t n = 1;
+    for (uint32_t l = 0; l < levels; ++l) {
+        here.resize(size_t(n) * f.k * 8);
+        for (uint64_t t = 0; t < n; ++t)
+            for (uint32_t d = 0; d < f.k; ++d)
+                for (uint32_t e = 0; e < 8; ++e) {
+                    const Move &m = move[d * 8 + e];
+                    const uint32_t p = m.up == 8 ? uint32_t(t) : above[size_t(t) * 8 + m.up];
+                    here[(size_t(t) * f.k + d) * 8 + e] = m.child == none || p == none ? none : p * f.k + m.child;
+                }
+        above.swap(here);
+        n *= f.k;
+    }
+    nbr->swap(above);
+}
+
 void build_map_tables(const Fractal &f, MapTables *t) {
     // lambda chunk: k^jl <= 4096 entries (two tables <= 32 KB of LDS), s^jl <= 32768
     // so x, y fit 16 bits.
@@ -440,18 +480,7 @@ bool build_tile_plan(const Fractal &f, uint32_t m, TilePlan *p, std::string *msg
         *msg = "too many tiles for the neighbour table";
         return false;
     }
-    p->nbr.resize(p->ntiles * 8);
-    for (uint64_t t = 0; t < p->ntiles; ++t) {
-        int64_t X, Y;
-        lambda_levels(f, p->rm, t, &X, &Y);
-        uint32_t d8 = 0;
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                if (dx == 0 && dy == 0) continue;
-                int64_t v = nu_levels(f, p->rm, X + dx, Y + dy);
-                p->nbr[t * 8 + d8++] = v < 0 ? 0xFFFFFFFFu : uint32_t(v);
-            }
-    }
+    neighbour_table(f, p->rm, &p->nbr);
     p->ok = true;
     return true;
 }
@@ -681,18 +710,7 @@ bool build_temporal_plan(const Fractal &f, uint32_t m, uint32_t h, uint32_t lds_
             }
             ++d8;
         }
-    p->nbr.resize(p->ntiles * 8);
-    for (uint64_t t = 0; t < p->ntiles; ++t) {
-        int64_t X, Y;
-        lambda_levels(f, rm, t, &X, &Y);
-        uint32_t e = 0;
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                if (dx == 0 && dy == 0) continue;
-                const int64_t v = nu_levels(f, rm, X + dx, Y + dy);
-                p->nbr[t * 8 + e++] = v < 0 ? 0xFFFFFFFFu : uint32_t(v);
-            }
-    }
+    neighbour_table(f, rm, &p->nbr);
     p->ok = true;
     return true;
 }

@@ -29,6 +29,10 @@ int validate_fractal(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r,
 void lambda_levels(const Fractal &f, uint32_t levels, uint64_t i, int64_t *x, int64_t *y);
 int64_t nu_levels(const Fractal &f, uint32_t levels, int64_t x, int64_t y);  // -1 outside
 
+// The eight neighbours of every compact index at `levels` levels (row-major
+// over dy, dx in -1..1 without the centre; 0xFFFFFFFF: none).
+void neighbour_table(const Fractal &f, uint32_t levels, std::vector<uint32_t> *nbr);
+
 struct MapTables {
     uint32_t jl = 0, jl_top = 0, nchunks_l = 0, jn = 0, jn_top = 0, nchunks_n = 0;
     std::vector<uint32_t> lam;  // low table then top table
@@ -90,7 +94,7 @@ bool build_edge_plan(const Fractal &f, uint32_t m, EdgePlan *p, std::string *msg
 struct MatPlan {
     bool ok = false;
     uint32_t m = 0, q = 0, K = 0, CB = 0, lanes = 0, nblk = 0, nhalo = 0, nrecs = 0;
-    uint32_t nr = 0;    // record results (lanes dwords of a block's record each)
+    uint32_t nr = 0;    // record dwords per lane
     uint32_t nh = 0;    // halo operands (4 record dwords per lane each)
     uint32_t gpw = 0;   // groups per wavefront
     uint32_t waves = 0; // wavefronts per work-group
@@ -98,6 +102,7 @@ struct MatPlan {
     uint32_t buf_bytes = 0;
     uint64_t ntiles = 0;
     std::vector<int8_t> A;       // see MatParams
+    std::vector<uint32_t> sel;
     std::vector<uint32_t> raddr; // waves * gpw groups
     std::vector<uint32_t> halo;
     std::vector<uint32_t> nbr;
@@ -108,14 +113,12 @@ constexpr uint32_t mat_self_off(uint32_t nh, bool edge, uint32_t t) { return 102
 constexpr uint32_t mat_halo_off(uint32_t nh, bool edge, uint32_t h, uint32_t t) {
     return 1024 * ((edge ? 2 + 2 * nh : 0) + 2 + 2 * h + t);
 }
-constexpr uint32_t mat_rec_off(uint32_t nh, uint32_t t) { return 1024 * (2 * (2 + 2 * nh) + t); }
 // false (with *msg) where the form does not apply: no block level with 16 to
 // 64 cells, more record dwords around a block than two operands hold, or more
 // groups than a work-group of kMatMaxWaves wavefronts takes.  gpw: groups per
 // wavefront (0: chosen for the fractal's own tiles); with_nbr: also the
 // neighbour table (8 entries per tile).
 bool build_mat_plan(const Fractal &f, uint32_t m, uint32_t gpw, MatPlan *p, std::string *msg, bool with_nbr = true);
-void mat_neighbours(const Fractal &f, uint32_t m, std::vector<uint32_t> *nbr);
 // The levels the form has plans at (up to r), and their groups of own and of
 // halo blocks (`halo`: the latter as a fraction).
 struct MatDims {
@@ -145,7 +148,7 @@ struct HoldPlan {
     uint32_t rs = 0, zero = 0;    // dwords per record, offset of a dword of zeros
     uint64_t ntiles = 0;
     std::vector<int8_t> A;
-    std::vector<uint32_t> raddr, halo;
+    std::vector<uint32_t> sel, raddr, halo;
 };
 constexpr uint32_t kHoldMaxWaves = 16;
 constexpr uint32_t kHoldMaxGens = 4096;   // per launch, whatever the plan (a launch of milliseconds at most)

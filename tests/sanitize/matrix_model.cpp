@@ -37,6 +37,13 @@ static void contract(const int8_t *A, const std::vector<uint8_t> &B, int (&D)[64
         }
 }
 
+// Byte i of record dword t of a lane whose 16 cells are x.
+static uint8_t pick(const std::vector<uint32_t> &sel, uint32_t t, uint32_t sub, int i, const uint8_t *x) {
+    const uint32_t a = sel[2 * (4 * t + sub)] >> (8 * i) & 0xFF, b = sel[2 * (4 * t + sub) + 1] >> (8 * i) & 0xFF;
+    if ((a > 7 && a != 12) || (b > 7 && b != 12) || (a < 8 && b < 8)) std::abort();
+    return a < 8 ? x[a] : (b < 8 ? x[8 + b] : 0);
+}
+
 static void check(const Fractal &f, const MatPlan &p, std::mt19937 &rng, bool edge) {
     std::vector<uint8_t> st(f.cells);
     for (auto &c : st) c = rng() & 1;
@@ -53,13 +60,12 @@ static void check(const Fractal &f, const MatPlan &p, std::mt19937 &rng, bool ed
         };
         auto publish = [&](const std::vector<uint8_t> &B, const std::vector<int64_t> &rec) {
             for (uint32_t t = 0; t < p.nr; ++t) {
-                int D[64][4] = {};
-                contract(p.A.data() + mat_rec_off(p.nh, t), B, D);
                 for (int l = 0; l < 64; ++l) {
                     const uint32_t in = (l / 16) / p.lanes * 16 + l % 16, sub = (l / 16) % p.lanes;
                     if (rec[in] < 0) continue;
                     for (int i = 0; i < 4; ++i)
-                        lds[4 * ((t * p.lanes + sub) * p.nrecs + rec[in]) + i] = uint8_t(D[l][i]);
+                        lds[4 * ((t * p.lanes + sub) * p.nrecs + rec[in]) + i] =
+                            pick(p.sel, t, sub, i, B.data() + 16 * l);
                 }
             }
         };
@@ -154,7 +160,7 @@ static void check_hold(const Fractal &f, const HoldPlan &p, std::mt19937 &rng) {
         ref.swap(next);
     }
     std::vector<uint32_t> nbr;
-    mat_neighbours(f, p.m, &nbr);
+    neighbour_table(f, f.r - p.m, &nbr);
     for (uint64_t tile = 0; tile < p.ntiles; ++tile) {
         if (p.ntiles > 4 && rng() % (p.ntiles / 2)) continue;
         const uint32_t groups = p.waves * p.gpw;
@@ -181,13 +187,11 @@ static void check_hold(const Fractal &f, const HoldPlan &p, std::mt19937 &rng) {
             for (int i = 0; i < 4; ++i) lds[p.zero + i] = 0;
             for (uint32_t g = 0; g < groups; ++g)
                 for (uint32_t t = 0; t < p.nr; ++t) {
-                    int D[64][4] = {};
-                    contract(p.A.data() + mat_rec_off(p.nh, t), X[g], D);
                     for (int l = 0; l < 64; ++l) {
                         const uint32_t in = (l / 16) / p.lanes * 16 + l % 16, sub = (l / 16) % p.lanes;
                         const uint32_t a = 4 * (std::min(g * bpg + in, p.ntot) * p.rs + sub * p.nr + t);
                         if (a + 4 > p.zero) std::abort();
-                        for (int i = 0; i < 4; ++i) lds[a + i] = uint8_t(D[l][i]);
+                        for (int i = 0; i < 4; ++i) lds[a + i] = pick(p.sel, t, sub, i, X[g].data() + 16 * l);
                     }
                 }
             for (uint32_t g = 0; g < groups; ++g) {

@@ -188,6 +188,12 @@ def test_batch_several_generations(N, name, levels, resident):
                 got = (hb if counts[i] & 1 else ha)[off:off + len(st)]
                 np.testing.assert_array_equal(got, o.compact_steps(st, rm, counts[i]),
                                               err_msg=f"{name} r={rs[i]} {rule} steps={counts[i]}")
+                other = (ha if counts[i] & 1 else hb)[off:off + len(st)]
+                if not resident and counts[i]:  # the generation before, in the other arena
+                    np.testing.assert_array_equal(other, o.compact_steps(st, rm, counts[i] - 1),
+                                                  err_msg=f"{name} r={rs[i]} {rule} steps={counts[i]}: before")
+                elif resident and batch.info().groups == 0:  # stepped whole: untouched
+                    np.testing.assert_array_equal(other, st if counts[i] & 1 else np.ones_like(st))
                 ha[off:off + len(st)] = 1
                 hb[off:off + len(st)] = 1
             assert (ha == 1).all() and (hb == 1).all()
