@@ -39,7 +39,7 @@ def units():
                         [f"-DNBB_INST_BATCH={batch}", f"-DNBB_INST_EDGE={edge}", f"-DNBB_INST_RULE={rule}"]))
     for batch in (0, 1):
         for rule in (0, 1):
-            for al in (1, 4, 16):
+            for al in ((0, 1, 4, 16) if not batch else (1, 4, 16)):
                 out.append(("matrix_inst.hip", f"matrix_b{batch}_r{rule}_a{al}.o",
                             [f"-DNBB_INST_BATCH={batch}", f"-DNBB_INST_RULE={rule}", f"-DNBB_INST_AL={al}"]))
     return out

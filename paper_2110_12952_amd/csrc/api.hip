@@ -66,7 +66,6 @@ struct nbb_fractal {
     std::vector<MatDims> mat_levels;
     // Several generations per launch in the same form, for calls of several.
     HoldPlan hold;
-    DevBlob dhold;
     HoldParams holdp{};
     std::vector<HoldDims> hold_levels;
     // For batches, made on first use and kept: plans without neighbours by
@@ -133,7 +132,7 @@ struct HeldSet {
     HoldParams hp{};
     uint32_t al = 0, nr = 0, nh = 0, gpw = 0;
     const uint32_t *rec = nullptr;
-    uint32_t *steps = nullptr;        // device: one generation count per instance (nbb_batch_step_each)
+    uint32_t *steps = nullptr;        // device: one generation count per instance (nbb_batch_step_each), in B->counts
     std::vector<uint32_t> index;      // the instances (caller's numbering), in tile order
     std::vector<uint64_t> tiles_end;  // tiles of the first j+1 of them
 };
@@ -179,6 +178,7 @@ struct nbb_batch {
     uint64_t cells = 0, tiles = 0, arena_bytes = 0;
     std::vector<BatchGroup> groups;
     ResidentSet resident;
+    uint32_t *counts = nullptr;  // device: the held sets' generation counts, groups' sets first, then small's
     std::vector<HeldSet> small;  // instances counted as resident that one work-group each holds in registers
     std::vector<BatchDirect> direct;
     DevBlob dtab;
@@ -210,7 +210,7 @@ void blob_free(DevBlob *b) {
 nbb_status upload(DevBlob *blob, const void *const *src, const size_t *bytes, int nparts,
                   void **dst) {
     size_t total = 0;
-    size_t off[8];
+    size_t off[10];
     for (int i = 0; i < nparts; ++i) {
         off[i] = total;
         total += align256(std::max<size_t>(bytes[i], 1));
@@ -391,14 +391,15 @@ nbb_status upload_edges(const EdgePlan &p, const TileParams &T, DevBlob *blob, E
 // whole blocks.
 uint32_t mat_align_of(uint32_t CB) { return CB % 16 == 0 ? 16 : (CB % 4 == 0 ? 4 : 1); }
 
-// Uploads the matrix plan's tables (operands, record addresses, halo blocks,
-// neighbour tiles) into one allocation.
-nbb_status upload_matrix(const MatPlan &p, DevBlob *blob, MatParams *T) {
-    const void *src[5] = {p.A.data(), p.raddr.data(), p.halo.data(), p.nbr.data(), p.sel.data()};
-    size_t bytes[5] = {p.A.size(), p.raddr.size() * 4, p.halo.size() * 4, p.nbr.size() * 4, p.sel.size() * 4};
-    void *dst[5];
-    nbb_status s = upload(blob, src, bytes, 5, dst);
-    if (s != NBB_OK) return s;
+// The device tables of a matrix plan (operands, record addresses, halo blocks,
+// neighbour tiles, record selectors) and of a held plan: five parts each.
+void matrix_parts(const MatPlan &p, const void **src, size_t *bytes) {
+    const void *v[5] = {p.A.data(), p.raddr.data(), p.halo.data(), p.nbr.data(), p.sel.data()};
+    const size_t n[5] = {p.A.size(), p.raddr.size() * 4, p.halo.size() * 4, p.nbr.size() * 4, p.sel.size() * 4};
+    std::copy(v, v + 5, src);
+    std::copy(n, n + 5, bytes);
+}
+void matrix_params(const MatPlan &p, void *const *dst, MatParams *T) {
     *T = MatParams{};
     T->K = p.K;
     T->CB = p.CB;
@@ -414,16 +415,14 @@ nbb_status upload_matrix(const MatPlan &p, DevBlob *blob, MatParams *T) {
     T->halo = static_cast<const uint32_t *>(dst[2]);
     T->nbr = static_cast<const uint32_t *>(dst[3]);
     T->sel = static_cast<const uint32_t *>(dst[4]);
-    return NBB_OK;
 }
-
-// The same for a held plan; `nbr`: its tiles' neighbours.
-nbb_status upload_hold(const HoldPlan &p, const std::vector<uint32_t> &nbr, DevBlob *blob, HoldParams *T) {
-    const void *src[5] = {p.A.data(), p.raddr.data(), p.halo.data(), nbr.data(), p.sel.data()};
-    size_t bytes[5] = {p.A.size(), p.raddr.size() * 4, p.halo.size() * 4, nbr.size() * 4, p.sel.size() * 4};
-    void *dst[5];
-    nbb_status s = upload(blob, src, bytes, 5, dst);
-    if (s != NBB_OK) return s;
+void hold_parts(const HoldPlan &p, const std::vector<uint32_t> &nbr, const void **src, size_t *bytes) {
+    const void *v[5] = {p.A.data(), p.raddr.data(), p.halo.data(), nbr.data(), p.sel.data()};
+    const size_t n[5] = {p.A.size(), p.raddr.size() * 4, p.halo.size() * 4, nbr.size() * 4, p.sel.size() * 4};
+    std::copy(v, v + 5, src);
+    std::copy(n, n + 5, bytes);
+}
+void hold_params(const HoldPlan &p, void *const *dst, HoldParams *T) {
     *T = HoldParams{};
     T->K = p.K;
     T->CB = p.CB;
@@ -440,7 +439,6 @@ nbb_status upload_hold(const HoldPlan &p, const std::vector<uint32_t> &nbr, DevB
     T->halo = static_cast<const uint32_t *>(dst[2]);
     T->nbr = static_cast<const uint32_t *>(dst[3]);
     T->sel = static_cast<const uint32_t *>(dst[4]);
-    return NBB_OK;
 }
 
 // Builds and uploads the matrix plan of a descriptor at its own tile level
@@ -452,23 +450,31 @@ nbb_status setup_matrix(nbb_fractal *F) {
     std::string msg;
     MatPlan p;
     if (!m || !build_mat_plan(F->f, m, gpw, &p, &msg)) return NBB_OK;
-    nbb_status st = upload_matrix(p, &F->dmat, &F->matp);
+    F->hold_levels = hold_dims(F->f);
+    HoldDims d{};
+    HoldPlan h;
+    std::vector<uint32_t> nbr;
+    const bool held = pick_hold(F->hold_levels, F->f.k, {F->f.r}, uint32_t(F->cu_count), &d, &gpw) &&
+                      build_hold_plan(F->f, d.m, d.rings, gpw, &h, &msg);
+    const void *src[10];
+    size_t bytes[10];
+    void *dst[10];
+    matrix_parts(p, src, bytes);
+    if (held) {
+        if (d.m != m) neighbour_table(F->f, F->f.r - d.m, &nbr);
+        hold_parts(h, nbr, src + 5, bytes + 5);
+    }
+    nbb_status st = upload(&F->dmat, src, bytes, held ? 10 : 5, dst);
     if (st != NBB_OK) return st;
+    matrix_params(p, dst, &F->matp);
     p.A.clear();
     p.raddr.clear();
     p.halo.clear();
     p.nbr.clear();
     F->mat = std::move(p);
-    F->hold_levels = hold_dims(F->f);
-    HoldDims d{};
-    HoldPlan h;
-    if (!pick_hold(F->hold_levels, F->f.k, {F->f.r}, uint32_t(F->cu_count), &d, &gpw) ||
-        !build_hold_plan(F->f, d.m, d.rings, gpw, &h, &msg))
-        return NBB_OK;
-    std::vector<uint32_t> nbr;
-    neighbour_table(F->f, F->f.r - d.m, &nbr);
-    st = upload_hold(h, nbr, &F->dhold, &F->holdp);
-    if (st != NBB_OK) return st;
+    if (!held) return NBB_OK;
+    if (d.m == m) dst[8] = dst[3];
+    hold_params(h, dst + 5, &F->holdp);
     h.A.clear();
     h.raddr.clear();
     h.halo.clear();
@@ -487,7 +493,12 @@ const nbb_fractal::MatTables *batch_mat_plan(const nbb_fractal *F, uint32_t m, u
     std::string msg;
     if (!build_mat_plan(F->f, m, gpw, &t.plan, &msg, false)) return nullptr;
     t.plan.nbr.assign(8, 0xFFFFFFFFu);
-    if (upload_matrix(t.plan, &t.blob, &t.p) != NBB_OK) return nullptr;
+    const void *src[5];
+    size_t bytes[5];
+    void *dst[5];
+    matrix_parts(t.plan, src, bytes);
+    if (upload(&t.blob, src, bytes, 5, dst) != NBB_OK) return nullptr;
+    matrix_params(t.plan, dst, &t.p);
     return &(F->mat_plans[key] = std::move(t));
 }
 const nbb_fractal::HoldTables *batch_hold_plan(const nbb_fractal *F, const HoldDims &d, uint32_t gpw) {
@@ -498,7 +509,12 @@ const nbb_fractal::HoldTables *batch_hold_plan(const nbb_fractal *F, const HoldD
     nbb_fractal::HoldTables t;
     std::string msg;
     if (!build_hold_plan(F->f, d.m, d.rings, gpw, &t.plan, &msg)) return nullptr;
-    if (upload_hold(t.plan, std::vector<uint32_t>(8, 0xFFFFFFFFu), &t.blob, &t.p) != NBB_OK) return nullptr;
+    const void *src[5];
+    size_t bytes[5];
+    void *dst[5];
+    hold_parts(t.plan, {}, src, bytes);
+    if (upload(&t.blob, src, bytes, 5, dst) != NBB_OK) return nullptr;
+    hold_params(t.plan, dst, &t.p);
     return &(F->hold_plans[key] = std::move(t));
 }
 const uint32_t *batch_mat_nbr(const nbb_fractal *F, uint32_t m) {
@@ -781,7 +797,6 @@ nbb_status nbb_create(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r
         blob_free(&F->dtile);
         blob_free(&F->dedge);
         blob_free(&F->dmat);
-        blob_free(&F->dhold);
         blob_free(&F->dmfma);
         delete F;
         return st;
@@ -803,7 +818,6 @@ void nbb_destroy(nbb_fractal *F) {
     blob_free(&F->dtile);
     blob_free(&F->dedge);
     blob_free(&F->dmat);
-    blob_free(&F->dhold);
     blob_free(&F->dmfma);
     delete F;
 }
@@ -829,7 +843,7 @@ nbb_status nbb_query(const nbb_fractal *F, nbb_info *info) {
         info->tile_side = 1;
     }
     info->bbox_pitch = box_pitch(F->f);
-    info->device_table_bytes = F->dmap.bytes + F->dbox.bytes + F->dtile.bytes + F->dedge.bytes + F->dmat.bytes + F->dhold.bytes + F->dmfma.bytes;
+    info->device_table_bytes = F->dmap.bytes + F->dbox.bytes + F->dtile.bytes + F->dedge.bytes + F->dmat.bytes + F->dmfma.bytes;
     uint32_t ebpt = 0, ehpt = 0;
     if (F->use_edges && edge_case(F->edge.nblk, F->edge.nhalo, &ebpt, &ehpt)) info->lds_bytes = edge_lds_bytes(ebpt, ehpt);
     info->tiled_form = F->strategy == NBB_STRATEGY_DIRECT ? 0u : (F->use_edges ? 1u : 2u);
@@ -1436,11 +1450,18 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         total += align256(H.tiles * 16);
         H.off_nbr = total;
         total += align256(H.tiles * 32);
-        H.off_steps = total;
-        total += align256(H.members.size() * 4);
     };
     for (HeldBuild &H : held) place_held(H);
     for (HeldBuild &H : small) place_held(H);
+    const size_t off_counts = total;
+    size_t ncounts = 0;
+    for (std::vector<HeldBuild> *v : {&held, &small})
+        for (HeldBuild &H : *v)
+            if (H.plan) {
+                H.off_steps = off_counts + 4 * ncounts;
+                ncounts += H.members.size();
+            }
+    total += ncounts ? align256(4 * ncounts) : 0;
     size_t nres = 0;
     for (size_t g = 0; g < nr; ++g) {
         for (const BatchInstance &I : res.members[g]) B->tiles += I.ntiles;
@@ -1469,6 +1490,7 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *base = fixed ? reinterpret_cast<char *>(fixed) : static_cast<char *>(B->dtab.ptr);
+    if (ncounts) B->counts = reinterpret_cast<uint32_t *>(base + off_counts);
     auto make_held = [&](const HeldBuild &H, HeldSet *S) -> hipError_t {
         if (!H.plan) return hipSuccess;
         auto *inst = reinterpret_cast<MatInstance *>(base + H.off_inst);
@@ -1762,10 +1784,6 @@ static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t a
     if (!S.whole && 2 * uint64_t(L) + 2 > most) return hipSuccess;
     *used = true;
     if (!most) return hipSuccess;
-    if (counts) {
-        hipError_t e = launch_set_words(S.steps, n.data(), uint32_t(n.size()), s);
-        if (e != hipSuccess) return e;
-    }
     auto go = [&](const HoldParams &E, uint8_t *in, uint8_t *out, uint32_t g, uint32_t i, uint32_t mode) {
         return launch_step_hold(E, S.al, S.nr, S.nh, S.gpw, in, out, arena_len, rule, g, S.rec,
                                 counts ? S.steps : nullptr, i, mode, s);
@@ -1787,8 +1805,7 @@ static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t a
     }
     if (S.whole) return hipSuccess;
     if (counts) {
-        hipError_t e = go(S.hp, a, b, 1, 0, kHoldOdd);
-        return e == hipSuccess ? go(S.hp, b, a, 1, 0, kHoldEven) : e;
+        return go(S.hp, a, b, 1, 0, kHoldLast);
     }
     *last = true;
     *in_ = in;
@@ -1899,6 +1916,15 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
     bool res_launched = false;
     e = batch_fork_resident(B, a, b, rule, steps, 0, s, &res_launched);
     if (e != hipSuccess) return hip_fail(e, "batch resident step launch");
+    if (B->counts) {
+        std::vector<uint32_t> n;
+        for (const BatchGroup &G : B->groups)
+            for (uint32_t i : G.held.index) n.push_back(steps[i]);
+        for (const HeldSet &S : B->small)
+            for (uint32_t i : S.index) n.push_back(steps[i]);
+        e = launch_set_words(B->counts, n.data(), uint32_t(n.size()), s);
+        if (e != hipSuccess) return hip_fail(e, "batch step counts");
+    }
     e = batch_fork_groups(B, s);
     if (e != hipSuccess) return hip_fail(e, "batch group fork");
     for (size_t k = 0; k < B->groups.size() && e == hipSuccess; ++k) {
@@ -2488,6 +2514,21 @@ nbb_status nbb_step_packed(const nbb_fractal *F, uint8_t *a, uint8_t *b, uint64_
     if (st != NBB_OK) return st;
     if (result_in_b) *result_in_b = int(steps & 1);
     if (!steps) return NBB_OK;
+    if (F->use_matrix && F->strategy == NBB_STRATEGY_TILED && F->hold.ok) {
+        // the held form on bits: all but the last generation several at a
+        // time, as nbb_step_compact
+        const HoldPlan &h = F->hold;
+        const uint32_t T = steps - 1, L = held_launches(T, h.gens, true);
+        uint8_t *in = a, *out = b;
+        for (uint32_t i = 0; i <= L; ++i) {
+            const uint32_t g = i == L ? 1 : T / L + (i < T % L ? 1u : 0u);
+            hipError_t e = launch_step_hold(F->holdp, 0, h.nr, h.nh, h.gpw, in, out, len, rule, g, nullptr, nullptr, 0, 0,
+                                            static_cast<hipStream_t>(stream));
+            if (e != hipSuccess) return hip_fail(e, "packed held step launch");
+            std::swap(in, out);
+        }
+        return NBB_OK;
+    }
     const uint16_t *lut = nullptr;
     uint32_t stride = 0;
     st = packed_table(F, &lut, &stride);

@@ -1187,6 +1187,9 @@ hipError_t launch_step_hold(const HoldParams &E0, uint32_t al, uint32_t nr, uint
         if (life) NBB_HOLD_GO(true, 0);
         NBB_HOLD_GO(true, 1);
     }
+    if (al == 0)
+        return life ? launch_hold_inst<false, 0, 0>(E, nr, nh, gpw, in, out, rule, gens, nullptr, nullptr, 0, 0, st)
+                    : launch_hold_inst<false, 1, 0>(E, nr, nh, gpw, in, out, rule, gens, nullptr, nullptr, 0, 0, st);
     if (life) NBB_HOLD_GO(false, 0);
     NBB_HOLD_GO(false, 1);
 #undef NBB_HOLD_GO

@@ -53,7 +53,8 @@ hipError_t launch_step_edges(const EdgeParams &E, uint32_t BS, uint32_t nsrc, co
 hipError_t launch_step_matrix(const MatParams &E, uint32_t al, uint32_t nr, uint32_t nh, uint32_t gpw,
                               const uint8_t *in, uint8_t *out, uint64_t limit, uint32_t rule, const uint32_t *rec,
                               int cu_count, hipStream_t st);
-// `gens` <= E.gens generations of every tile of a held plan in one launch; in a
+// `gens` <= E.gens generations of every tile of a held plan in one launch (al
+// as above, or 0 for a state at one bit per cell, `limit` its bytes); in a
 // batch with steps_of (device array, one count per instance) launch number
 // `launch` of a call, see k_step_hold.
 hipError_t launch_step_hold(const HoldParams &E, uint32_t al, uint32_t nr, uint32_t nh, uint32_t gpw,

@@ -353,6 +353,11 @@ static hipError_t launch_matrix_t(const MatParams &E, const uint8_t *in, uint8_t
 // read and written once per launch instead of once per generation, and a
 // generation of a small state costs a barrier instead of a launch.
 //   BUF: the second record buffer's offset (an instruction offset).
+//   AL 0: the state at one bit per cell (in and out are words, E.limit their
+//   bytes; not BATCH).  A lane's 16 bits come out of two words and spread to
+//   bytes once per launch; the next states are gathered as the tile's words
+//   in LDS, and the words shared with the neighbouring tiles are stored by an
+//   atomic AND and OR of the tile's own bits.
 //   BATCH: rec as above; word 3 of a tile's record indexes steps_of, the
 //   generations n its instance takes in the whole call (steps_of NULL: every
 //   instance takes `gens` now).  mode says which of a call's launches it is:
@@ -360,8 +365,8 @@ static hipError_t launch_matrix_t(const MatParams &E, const uint8_t *in, uint8_t
 //                generation, in as few launches as E.gens allows plus one where
 //                their number would not have the parity of n - 1 (launches
 //                alternate the buffers); nothing past an instance's own
-//     kHoldOdd, kHoldEven  the last generation of the instances of odd n
-//                (from a to b), of even n (from b to a)
+//     kHoldLast  the last generation: from `in` to `out` for odd n, from `out`
+//                to `in` for even n
 //     kHoldWhole  number `launch` of those that take all n (tiles that are
 //                whole instances): back to `in`, an instance's last one to
 //                `out` if n is odd
@@ -386,9 +391,14 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
         bytes = min(E.K, r[2]);
         if (steps_of) {
             const uint32_t n = steps_of[r[3]];
-            if (mode == kHoldOdd || mode == kHoldEven) {
-                if (n == 0 || (n & 1) != (mode == kHoldOdd ? 1u : 0u)) return;
+            if (mode == kHoldLast) {
+                if (n == 0) return;
                 gens = 1;
+                if (!(n & 1)) {
+                    uint8_t *o = out;
+                    out = in;
+                    in = o;
+                }
             } else {
                 const uint32_t T = mode == kHoldWhole ? n : max(n, 1u) - 1;
                 uint32_t L = T / E.gens + (T % E.gens != 0);
@@ -422,7 +432,13 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
         pos[u] = own ? toff + b * E.CB + coff
                      : (ring && nt != kOutside ? nt * E.K + (item & 0x1FFFFFFFu) * E.CB + coff : kNowhere);
         live[u] = pos[u] != kNowhere ? 0xFFFFFFFFu : 0u;
-        raw[u] = mat_load<AL>(all, pos[u]);
+        if (AL == 0) {
+            const uint32_t w = pos[u] == kNowhere ? kNowhere : pos[u] >> 5 << 2;
+            raw[u].v[0] = __builtin_amdgcn_raw_buffer_load_b32(all, w, 0, 0);
+            raw[u].hi = __builtin_amdgcn_raw_buffer_load_b32(all, w + 4, 0, 0);
+        } else {
+            raw[u] = mat_load<AL>(all, pos[u]);
+        }
     }
     const bool edge = (rule >> 31) != 0;
     const uint8_t *A8 = reinterpret_cast<const uint8_t *>(E.A) + 16 * lane;
@@ -469,7 +485,15 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
         return;
     }
 #pragma unroll
-    for (int u = 0; u < GPW; ++u) x[u] = mat_align<AL>(raw[u], pos[u]);
+    for (int u = 0; u < GPW; ++u) {
+        if (AL == 0) {
+            const uint32_t bits = __builtin_amdgcn_alignbit(raw[u].hi, raw[u].v[0], pos[u]);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) x[u][d] = nibble_to_bytes((bits >> (4 * d)) & 15u);
+        } else {
+            x[u] = mat_align<AL>(raw[u], pos[u]);
+        }
+    }
 
     auto generation = [&](auto parity) {
         constexpr int P = decltype(parity)::value * BUF;
@@ -508,6 +532,38 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
         generation(std::integral_constant<int, 0>());
         if (g + 1 < gens) generation(std::integral_constant<int, 1>());
     }
+    if (AL == 0) {
+        // the tile's words in LDS (over the records), then to memory
+        uint32_t *words = reinterpret_cast<uint32_t *>(lds_m);
+        const uint32_t ph = toff & 31, nw = (ph + E.K + 31) >> 5;
+        __syncthreads();
+        for (uint32_t w = tid; w < nw; w += 64 * E.waves) words[w] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < GPW; ++u) {
+            if (soff[u] == kNowhere) continue;
+            uint32_t bits = 0;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) bits |= (x[u][d] * 0x01020408u >> 24) << (4 * d);
+            const uint32_t at = ph + soff[u];
+            const uint64_t v = uint64_t(bits) << (at & 31);
+            atomicOr(words + (at >> 5), uint32_t(v));
+            if (v >> 32) atomicOr(words + (at >> 5) + 1, uint32_t(v >> 32));
+        }
+        __syncthreads();
+        uint32_t *dst = reinterpret_cast<uint32_t *>(out) + (toff >> 5);
+        for (uint32_t w = tid; w < nw; w += 64 * E.waves) {
+            const uint32_t lo = w == 0 ? ph : 0u, hi = min(ph + E.K - 32 * w, 32u);  // the tile's bits of the word
+            const uint32_t mask = (hi == 32 ? 0xFFFFFFFFu : (1u << hi) - 1) & ~((1u << lo) - 1);
+            if (mask == 0xFFFFFFFFu) {
+                dst[w] = words[w];
+            } else {
+                atomicAnd(dst + w, ~mask);
+                atomicOr(dst + w, words[w] & mask);
+            }
+        }
+        return;
+    }
     const __amdgpu_buffer_rsrc_t gout = mat_rsrc(out + base + toff, bytes);
 #pragma unroll
     for (int u = 0; u < GPW; ++u) __builtin_amdgcn_raw_buffer_store_b128(x[u], gout, soff[u], 0, 0);
@@ -518,7 +574,8 @@ static hipError_t launch_hold_t(const HoldParams &E, uint8_t *in, uint8_t *out, 
                                 const uint32_t *rec, const uint32_t *steps_of, uint32_t launch, uint32_t mode,
                                 hipStream_t st) {
     if (!E.ntiles) return hipSuccess;
-    const uint32_t lds = BUF + E.zero + 4;
+    uint32_t lds = BUF + E.zero + 4;
+    if (AL == 0) lds = std::max(lds, 4 * ((E.K + 62) / 32 + 1));
     hipLaunchKernelGGL((k_step_hold<AL, NR, NH, GPW, BUF, BATCH, RULE>), dim3(E.ntiles), dim3(64 * E.waves), lds, st, E,
                        in, out, rule, gens, rec, steps_of, launch, mode);
     return hipGetLastError();

@@ -1,6 +1,7 @@
 // One (BATCH, RULE, AL) combination of the matrix-core step's launchers, chosen
 // by NBB_INST_BATCH (0/1), NBB_INST_RULE (0: B3/S23, 1: any rule) and
-// NBB_INST_AL (1, 4 or 16); the build compiles this file once per combination.
+// NBB_INST_AL (1, 4 or 16; 0: the bit-packed held step alone); the build
+// compiles this file once per combination.
 #include "matrix.hpp"
 #include "matrix_launch.hpp"
 
@@ -10,6 +11,7 @@
 
 namespace nbb {
 
+#if NBB_INST_AL != 0
 template <bool BATCH, int RULE, int AL>
 hipError_t launch_matrix_inst(const MatParams &E, uint32_t nr, uint32_t nh, uint32_t gpw, const uint8_t *in,
                               uint8_t *out, uint32_t rule, const uint32_t *rec, int cu_count, hipStream_t st) {
@@ -19,6 +21,7 @@ hipError_t launch_matrix_inst(const MatParams &E, uint32_t nr, uint32_t nh, uint
 template hipError_t launch_matrix_inst<bool(NBB_INST_BATCH), NBB_INST_RULE, NBB_INST_AL>(
     const MatParams &, uint32_t, uint32_t, uint32_t, const uint8_t *, uint8_t *, uint32_t, const uint32_t *, int,
     hipStream_t);
+#endif
 
 template <bool BATCH, int RULE, int AL>
 hipError_t launch_hold_inst(const HoldParams &E, uint32_t nr, uint32_t nh, uint32_t gpw, uint8_t *in,

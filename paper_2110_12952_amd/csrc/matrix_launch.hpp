@@ -32,6 +32,14 @@ NBB_MAT_INST_DECLS(false, 0)
 NBB_MAT_INST_DECLS(false, 1)
 NBB_MAT_INST_DECLS(true, 0)
 NBB_MAT_INST_DECLS(true, 1)
+#define NBB_HOLD_PACKED_DECL(R)                                                                                \
+    extern template hipError_t launch_hold_inst<false, R, 0>(const HoldParams &, uint32_t, uint32_t, uint32_t,  \
+                                                             uint8_t *, uint8_t *, uint32_t, uint32_t,          \
+                                                             const uint32_t *, const uint32_t *, uint32_t,      \
+                                                             uint32_t, hipStream_t);
+NBB_HOLD_PACKED_DECL(0)
+NBB_HOLD_PACKED_DECL(1)
+#undef NBB_HOLD_PACKED_DECL
 #undef NBB_MAT_INST_DECLS
 #undef NBB_MAT_INST_DECL
 

@@ -176,7 +176,7 @@ struct MatParams {
 };
 
 // Which of a batch call's launches a held launch is (k_step_hold).
-constexpr uint32_t kHoldMost = 0, kHoldOdd = 1, kHoldEven = 2, kHoldWhole = 3;
+constexpr uint32_t kHoldMost = 0, kHoldLast = 1, kHoldWhole = 2;
 
 // Several generations per launch in the matrix form: the tile's blocks and
 // those of its neighbour tiles around it, all held in registers.  Records in

@@ -197,3 +197,35 @@ def test_batch_several_generations(N, name, levels, resident):
                 ha[off:off + len(st)] = 1
                 hb[off:off + len(st)] = 1
             assert (ha == 1).all() and (hb == 1).all()
+
+
+def bits(state):
+    words = np.zeros((len(state) + 31) // 32 * 32, np.uint8)
+    words[:len(state)] = state
+    return np.packbits(words, bitorder="little")
+
+
+@gpu
+@pytest.mark.parametrize("name,r", HELD)
+def test_packed_generations_against_oracle(N, name, r):
+    # the bit-packed state in the held form: every bit of the result and of
+    # the generation before it, bits past the last cell unchanged
+    fd = W.FRACTALS[name]
+    o, g = O.Fractal(fd.s, fd.offsets, r), N.Fractal(fd.s, fd.offsets, r)
+    st0 = o.init_compact(77, 0.45)
+    past = np.zeros(g.packed_bytes() * 8, np.uint8)
+    past[len(st0):] = 1
+    past = np.packbits(past, bitorder="little")
+    for rule in ("B3/S23", "B1357/S02468"):
+        rm = W.rule_mask(rule)
+        states = [st0]
+        for _ in range(20):
+            states.append(o.compact_steps(states[-1], rm, 1))
+        for steps in (1, 2, 3, 10, 19, 20):
+            a = torch.from_numpy(bits(st0)).cuda()
+            b = torch.full_like(a, 0xFF)
+            res = g.step_packed(a, b, steps, rm)
+            other = a if res is b else b
+            for t, n in ((res, steps), (other, steps - 1)):
+                want = bits(states[n]) | (past if t is b else 0)
+                np.testing.assert_array_equal(t.cpu().numpy(), want, err_msg=f"{name} r={r} {rule} {steps} gen {n}")
