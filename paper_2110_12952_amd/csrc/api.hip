@@ -1851,6 +1851,8 @@ nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t a
     if (e != hipSuccess) return hip_fail(e, "batch resident step launch");
     e = batch_fork_groups(B, s);
     if (e != hipSuccess) return hip_fail(e, "batch group fork");
+    // the small sets first: one long launch each, beside what follows
+    e = held_step_small(B, a, b, arena_len, steps, nullptr, rule, s);
     // each group takes all its generations on its stream
     for (size_t k = 0; k < B->groups.size() && e == hipSuccess; ++k) {
         const BatchGroup &G = B->groups[k];
@@ -1867,7 +1869,6 @@ nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t a
             std::swap(in, out);
         }
     }
-    if (e == hipSuccess) e = held_step_small(B, a, b, arena_len, steps, nullptr, rule, s);
     const char *what = "batch step launch";
     for (size_t j = 0; j < B->direct.size() && e == hipSuccess; ++j) {
         const nbb_fractal *F = B->direct[j].f;
@@ -1927,6 +1928,7 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
     }
     e = batch_fork_groups(B, s);
     if (e != hipSuccess) return hip_fail(e, "batch group fork");
+    e = held_step_small(B, a, b, arena_len, 0, steps, rule, s);
     for (size_t k = 0; k < B->groups.size() && e == hipSuccess; ++k) {
         const BatchGroup &G = B->groups[k];
         const hipStream_t gs = batch_group_stream(B, k, s);
@@ -1954,7 +1956,6 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
             std::swap(in, out);
         }
     }
-    if (e == hipSuccess) e = held_step_small(B, a, b, arena_len, 0, steps, rule, s);
     const char *what = "batch step launch";
     for (size_t j = 0; j < B->direct.size() && e == hipSuccess; ++j) {
         const BatchDirect &d = B->direct[j];
