@@ -229,3 +229,26 @@ def test_packed_generations_against_oracle(N, name, r):
             for t, n in ((res, steps), (other, steps - 1)):
                 want = bits(states[n]) | (past if t is b else 0)
                 np.testing.assert_array_equal(t.cpu().numpy(), want, err_msg=f"{name} r={r} {rule} {steps} gen {n}")
+
+
+@gpu
+@pytest.mark.parametrize("count", [1, 3, 4, 5, 4099])
+@pytest.mark.parametrize("off", [0, 1, 3])
+def test_maps_at_any_alignment(N, count, off):
+    fd = W.TRIANGLE
+    o, g = O.Fractal(fd.s, fd.offsets, 12), N.Fractal(fd.s, fd.offsets, 12)
+    idx = W.random_indices(1, count, 3 ** 12 + 9)
+    t = torch.zeros(count + 4, dtype=torch.int32, device="cuda")
+    t[off:off + count] = torch.from_numpy(idx.astype(np.int32)).cuda()
+    outs = [torch.full((count + 8,), 7, dtype=torch.int32, device="cuda") for _ in range(3)]
+    x, y, back = (v[off:off + count] for v in outs)
+    g.lam(t[off:off + count], out=(x, y))
+    inside = idx < 3 ** 12
+    wx, wy = (np.where(inside, v.astype(np.int64), -1) for v in o.lam_many(np.where(inside, idx, 0).astype(np.uint32)))
+    np.testing.assert_array_equal(x.cpu().numpy(), wx)
+    np.testing.assert_array_equal(y.cpu().numpy(), wy)
+    g.nu(x, y, out=back)
+    np.testing.assert_array_equal(back.cpu().numpy().view(np.uint32), np.where(idx < 3 ** 12, idx, 0xFFFFFFFF))
+    for v in outs:
+        h = v.cpu().numpy()
+        assert (h[:off] == 7).all() and (h[off + count:] == 7).all()
