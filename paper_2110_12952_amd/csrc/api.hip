@@ -67,6 +67,9 @@ struct nbb_fractal {
     // Several generations per launch in the same form, for calls of several.
     HoldPlan hold;
     HoldParams holdp{};
+    double hold_us = 0.0, whole_us = 0.0;  // estimated times of a generation
+    HoldPlan whole;  // the state as one tile of one work-group, where it fits
+    HoldParams wholep{};
     std::vector<HoldDims> hold_levels;
     // For batches, made on first use and kept: plans without neighbours by
     // (tile level, groups per wavefront), neighbour tables by tile level.
@@ -210,7 +213,7 @@ void blob_free(DevBlob *b) {
 nbb_status upload(DevBlob *blob, const void *const *src, const size_t *bytes, int nparts,
                   void **dst) {
     size_t total = 0;
-    size_t off[10];
+    size_t off[16];
     for (int i = 0; i < nparts; ++i) {
         off[i] = total;
         total += align256(std::max<size_t>(bytes[i], 1));
@@ -441,6 +444,9 @@ void hold_params(const HoldPlan &p, void *const *dst, HoldParams *T) {
     T->sel = static_cast<const uint32_t *>(dst[4]);
 }
 
+// Groups per wavefront of a work-group that holds a whole state.
+uint32_t whole_gpw(uint32_t groups) { return groups <= 16 ? 1 : (groups <= 32 ? 2 : 4); }
+
 // Builds and uploads the matrix plan of a descriptor at its own tile level
 // (nothing where the form does not apply).
 nbb_status setup_matrix(nbb_fractal *F) {
@@ -456,15 +462,20 @@ nbb_status setup_matrix(nbb_fractal *F) {
     std::vector<uint32_t> nbr;
     const bool held = pick_hold(F->hold_levels, F->f.k, {F->f.r}, uint32_t(F->cu_count), &d, &gpw) &&
                       build_hold_plan(F->f, d.m, d.rings, gpw, &h, &msg);
-    const void *src[10];
-    size_t bytes[10];
-    void *dst[10];
+    HoldPlan w;
+    for (const HoldDims &x : F->hold_levels)
+        if (held && !x.rings && !w.ok) build_hold_plan(F->f, x.m, 0, whole_gpw(x.groups), &w, &msg);
+    const void *src[15];
+    size_t bytes[15];
+    void *dst[15];
     matrix_parts(p, src, bytes);
     if (held) {
         if (d.m != m) neighbour_table(F->f, F->f.r - d.m, &nbr);
         hold_parts(h, nbr, src + 5, bytes + 5);
     }
-    nbb_status st = upload(&F->dmat, src, bytes, held ? 10 : 5, dst);
+    const std::vector<uint32_t> alone(8, 0xFFFFFFFFu);
+    if (w.ok) hold_parts(w, alone, src + 10, bytes + 10);
+    nbb_status st = upload(&F->dmat, src, bytes, w.ok ? 15 : (held ? 10 : 5), dst);
     if (st != NBB_OK) return st;
     matrix_params(p, dst, &F->matp);
     p.A.clear();
@@ -479,6 +490,15 @@ nbb_status setup_matrix(nbb_fractal *F) {
     h.raddr.clear();
     h.halo.clear();
     F->hold = std::move(h);
+    F->hold_us = d.gen_us;
+    if (!w.ok) return NBB_OK;
+    hold_params(w, dst + 10, &F->wholep);
+    // fitted: triangle r8 / r9 (8 / 24 groups) 0.37 / 0.55 us, H r5 (22) 0.63, carpet r5 (32) 0.77
+    F->whole_us = 0.25 + 0.0145 * w.groups;
+    w.A.clear();
+    w.raddr.clear();
+    w.halo.clear();
+    F->whole = std::move(w);
     return NBB_OK;
 }
 
@@ -1336,7 +1356,7 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             const HoldDims *d = nullptr;
             for (const HoldDims &x : H.top->hold_levels)
                 if (!x.rings) d = &x;
-            if (all && d) H.plan = batch_hold_plan(H.top, *d, d->groups <= 16 ? 1 : (d->groups <= 32 ? 2 : 4));
+            if (all && d) H.plan = batch_hold_plan(H.top, *d, whole_gpw(d->groups));
             if (H.plan && !held_members(H, d->m)) H.plan = nullptr;
             if (H.plan) ++h;
             else small.erase(small.begin() + ptrdiff_t(h));
@@ -2292,6 +2312,19 @@ nbb_status nbb_step_compact(const nbb_fractal *F, uint8_t *a, uint8_t *b, uint64
     } else if (F->use_matrix) {
         const MatPlan &p = F->mat;
         uint32_t left = steps;
+        // A state that fits one work-group takes the whole call in one launch
+        // where that is estimated faster (4 us per launch): triangle r7, two
+        // generations 11.5 us with a launch each.
+        if (F->whole.ok && steps && steps <= F->whole.gens) {
+            const uint32_t L = steps >= 4 ? held_launches(steps - 1, F->hold.gens, true) + 1 : steps;
+            const double others = std::min(4.0 * L + F->hold_us * steps, 4.0 * steps);
+            if (steps > 1 && 4.0 + F->whole_us * steps < others) {
+                const HoldPlan &w = F->whole;
+                hipError_t e = launch_step_hold(F->wholep, mat_align_of(w.CB), w.nr, w.nh, w.gpw, in, out, F->f.cells, rule,
+                                                steps, nullptr, nullptr, 0, kHoldWhole, s);
+                return e == hipSuccess ? NBB_OK : hip_fail(e, "held step launch");
+            }
+        }
         // All but the last generation several at a time, in a number of
         // launches of the same parity, so that both buffers end as they would
         // with one launch per generation.

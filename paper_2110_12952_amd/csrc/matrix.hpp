@@ -370,6 +370,9 @@ static hipError_t launch_matrix_t(const MatParams &E, const uint8_t *in, uint8_t
 //     kHoldWhole  number `launch` of those that take all n (tiles that are
 //                whole instances): back to `in`, an instance's last one to
 //                `out` if n is odd
+//   Not BATCH, kHoldWhole (the state is one tile): the whole call in one
+//   launch, generation `gens` to out if odd, else to in, and the generation
+//   before it to the other (every load has ended before the first barrier).
 template <int AL, int NR, int NH, int GPW, int BUF, bool BATCH, int RULE>
 __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, uint8_t *in, uint8_t *out,
                                                                   uint32_t rule, uint32_t gens,
@@ -528,9 +531,25 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
 #pragma unroll
                 for (int d = 0; d < 4; ++d) x[u][d] &= live[u];
     };
+    uint8_t *before = nullptr;
+    if (!BATCH && AL != 0 && mode == kHoldWhole) {
+        before = gens & 1 ? in : out;
+        if (!(gens & 1)) out = in;
+        if (gens < 2) before = nullptr;  // (it is there already)
+    }
+    auto keep = [&](uint32_t g) {  // the generation before the last (uniform)
+        if (BATCH || AL == 0 || !before || g + 1 != gens) return;
+        const __amdgpu_buffer_rsrc_t r = mat_rsrc(before, bytes);
+#pragma unroll
+        for (int u = 0; u < GPW; ++u) __builtin_amdgcn_raw_buffer_store_b128(x[u], r, soff[u], 0, 0);
+    };
     for (uint32_t g = 0; g < gens; g += 2) {
+        keep(g);
         generation(std::integral_constant<int, 0>());
-        if (g + 1 < gens) generation(std::integral_constant<int, 1>());
+        if (g + 1 < gens) {
+            keep(g + 1);
+            generation(std::integral_constant<int, 1>());
+        }
     }
     if (AL == 0) {
         // the tile's words in LDS (over the records), then to memory

@@ -444,7 +444,7 @@ std::vector<HoldDims> hold_dims(const Fractal &f) {
             std::vector<std::pair<int64_t, int64_t>> at;
             std::string msg;
             if (!hold_members(f, s, m, rings, &p, &at, &msg)) continue;
-            out.push_back({m, rings, p.groups, p.gens});
+            out.push_back({m, rings, p.groups, p.gens, 0.0});
         }
     return out;
 }
@@ -476,6 +476,7 @@ bool pick_hold(const std::vector<HoldDims> &dims, uint32_t k, const std::vector<
         found = true;
         best = t;
         *out = d;
+        out->gen_us = gen;
         *gpw = hold_gpw(d.groups);
     }
     return found;

@@ -157,6 +157,7 @@ constexpr uint32_t kHoldBuf = 32 * 1024;  // one record buffer at most
 bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw, HoldPlan *p, std::string *msg);
 struct HoldDims {
     uint32_t m, rings, groups, gens;
+    double gen_us;  // estimated time of a generation (pick_hold)
 };
 std::vector<HoldDims> hold_dims(const Fractal &f);
 // The plan of launches over instances of the fractal at these levels r with
