@@ -445,9 +445,28 @@ def main():
     ms, res = time_events(torch, lambda: g.step_compact(a, b, K, rule))
     ms_step = ms / K
     value = g.cells * K / (ms * 1e-3)
-    alg_bytes = 2 * g.cells  # read + write one byte per cell per generation
-    achieved = alg_bytes / (ms_step * 1e-3) / 1e9
-    log(f"compact: {ms_step * 1e3:.2f} us/step, {value:.3e} cell-updates/s, {achieved:.0f} GB/s")
+    alg_bytes = 2 * g.cells  # a launch reads and writes one byte per cell
+    log(f"compact: {ms_step * 1e3:.2f} us/step, {value:.3e} cell-updates/s")
+    # The call above takes several generations per launch where the plan allows,
+    # so its time per generation says nothing of the bytes a launch moves: the
+    # roofline is that of one generation per launch, calls of one generation.
+    Ko = max(20, min(K, 200))
+    oa, ob = init.clone(), torch.empty_like(init)
+
+    def one_by_one():
+        x, y = oa, ob
+        for _ in range(Ko):
+            g.step_compact(x, y, 1, rule)
+            x, y = y, x
+        return x
+
+    one_by_one()
+    oa.copy_(init)
+    ms_one, _ = time_events(torch, one_by_one)
+    single = {"us_per_step": ms_one / Ko * 1e3, "steps": Ko}
+    achieved = alg_bytes / (ms_one / Ko * 1e-3) / 1e9
+    log(f"one generation per launch: {single['us_per_step']:.2f} us/step, {achieved:.0f} GB/s")
+    del oa, ob
     # repeats: R more timed runs of at least 100 generations each (the
     # per-generation spread; shorter runs would mostly time events and syncs)
     repeats = None
@@ -625,12 +644,14 @@ def main():
                    "tile_level": info.tile_level},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBPS, "traffic": traffic,
-                     # TILED runs the matrix-core form on every fractal of the workloads
+                     # calls of one generation (one_generation_per_call); TILED runs the
+                     # matrix-core form on every fractal of the workloads
                      "kernel": {N.STRATEGY_DIRECT: "k_step_direct", N.STRATEGY_TILED: "k_step_matrix"}.get(
                          info.strategy, "k_step_tiled"),
                      "alg_bytes_per_launch": alg_bytes},
         "cpu_baseline": cpu,
         "compact_repeats": repeats,
+        "one_generation_per_call": single,
         "bbox": bbox,
         "speedup_vs_bbox": (bbox["ms_per_step"] / ms_step) if bbox else None,
         "compact_equals_bbox": parity,

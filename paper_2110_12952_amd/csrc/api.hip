@@ -461,10 +461,10 @@ nbb_status setup_matrix(nbb_fractal *F) {
     HoldPlan h;
     std::vector<uint32_t> nbr;
     const bool held = pick_hold(F->hold_levels, F->f.k, {F->f.r}, uint32_t(F->cu_count), &d, &gpw) &&
-                      build_hold_plan(F->f, d.m, d.rings, gpw, &h, &msg);
+                      build_hold_plan(F->f, d.m, d.rings, gpw, &h, &msg, false);
     HoldPlan w;
     for (const HoldDims &x : F->hold_levels)
-        if (held && !x.rings && !w.ok) build_hold_plan(F->f, x.m, 0, whole_gpw(x.groups), &w, &msg);
+        if (held && !x.rings && !w.ok) build_hold_plan(F->f, x.m, 0, whole_gpw(x.groups), &w, &msg, false);
     const void *src[15];
     size_t bytes[15];
     void *dst[15];
@@ -484,6 +484,10 @@ nbb_status setup_matrix(nbb_fractal *F) {
     p.nbr.clear();
     F->mat = std::move(p);
     if (!held) return NBB_OK;
+    for (int part : {5, 10}) {  // the operands and selectors are the matrix plan's
+        dst[part] = dst[0];
+        dst[part + 4] = dst[4];
+    }
     if (d.m == m) dst[8] = dst[3];
     hold_params(h, dst + 5, &F->holdp);
     h.A.clear();

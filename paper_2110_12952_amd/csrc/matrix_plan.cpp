@@ -3,7 +3,6 @@
 #include <stddef.h>
 
 #include <algorithm>
-#include <map>
 
 #include "plan.hpp"
 
@@ -146,6 +145,19 @@ bool pick_shape(const Fractal &f, BlockShape *s) {
 
 }  // namespace
 
+// Block numbers of a tile's G x G grid (-1: no block), and the blocks' places.
+static void tile_grid(const Fractal &f, uint32_t levels, int64_t G, std::vector<int32_t> *grid,
+                      std::vector<std::pair<int64_t, int64_t>> *at) {
+    grid->assign(size_t(G) * G, -1);
+    const uint64_t nb = ipow(f.k, levels);
+    for (uint64_t b = 0; b < nb; ++b) {
+        int64_t X, Y;
+        lambda_levels(f, levels, b, &X, &Y);
+        (*grid)[size_t(Y * G + X)] = int32_t(b);
+        at->push_back({X, Y});
+    }
+}
+
 // The blocks of the tile at level m and of its neighbour tiles: `source`
 // gets the record of every read of every block (an own block, a halo block
 // numbered as first met, or none).
@@ -174,35 +186,32 @@ static bool build_ring(const Fractal &f, const BlockShape &s, uint32_t m, MatPla
     p->groups = (p->nblk + bpg - 1) / bpg;
     p->ntiles = ipow(f.k, f.r - m);
     const int64_t G = int64_t(ipow(f.s, m - s.q));
-    std::map<std::pair<int64_t, int64_t>, uint32_t> halo;
+    std::vector<int32_t> grid;
+    std::vector<std::pair<int64_t, int64_t>> at;
+    tile_grid(f, m - s.q, G, &grid, &at);
+    std::vector<uint32_t> ring(size_t(G + 2) * size_t(G + 2), kNone);  // the halo block at a place around the tile
     source->assign(size_t(p->nblk) * s.reads.size(), kNone);
-    for (uint32_t b = 0; b < p->nblk; ++b) {
-        int64_t X, Y;
-        lambda_levels(f, m - s.q, b, &X, &Y);
+    for (uint32_t b = 0; b < p->nblk; ++b)
         for (size_t i = 0; i < s.reads.size(); ++i) {
             const uint32_t d = s.reads[i].first;
-            const int64_t nx = X + kDirX[d], ny = Y + kDirY[d];
-            uint32_t &src = (*source)[b * s.reads.size() + i];
-            if (nx >= 0 && ny >= 0 && nx < G && ny < G) {
-                const int64_t v = nu_levels(f, m - s.q, nx, ny);
-                if (v >= 0) src = uint32_t(v);
-                continue;
-            }
+            const int64_t nx = at[b].first + kDirX[d], ny = at[b].second + kDirY[d];
             const int tx = nx < 0 ? -1 : (nx >= G ? 1 : 0), ty = ny < 0 ? -1 : (ny >= G ? 1 : 0);
-            const int64_t v = nu_levels(f, m - s.q, nx - tx * G, ny - ty * G);
+            const int32_t v = grid[size_t((ny - ty * G) * G + nx - tx * G)];
             if (v < 0) continue;
-            const auto it = halo.find({nx, ny});
-            if (it != halo.end()) {
-                src = it->second;
+            uint32_t &src = (*source)[b * s.reads.size() + i];
+            if (!tx && !ty) {
+                src = uint32_t(v);
                 continue;
             }
-            uint32_t dir = 0;
-            while (kDirX[dir] != tx || kDirY[dir] != ty) ++dir;
-            src = p->nblk + uint32_t(p->halo.size());
-            halo[{nx, ny}] = src;
-            p->halo.push_back(dir << 29 | uint32_t(v));
+            uint32_t &h = ring[size_t(ny + 1) * (G + 2) + size_t(nx + 1)];
+            if (h == kNone) {
+                uint32_t dir = 0;
+                while (kDirX[dir] != tx || kDirY[dir] != ty) ++dir;
+                h = p->nblk + uint32_t(p->halo.size());
+                p->halo.push_back(dir << 29 | uint32_t(v));
+            }
+            src = h;
         }
-    }
     p->nhalo = uint32_t(p->halo.size());
     if (p->halo.empty()) p->halo.push_back(0);
     p->nrecs = p->nblk + p->nhalo + 1;
@@ -356,11 +365,8 @@ static bool hold_members(const Fractal &f, const BlockShape &s, uint32_t m, uint
     p->nblk = uint32_t(nb);
     p->ntiles = ipow(f.k, f.r - m);
     p->gens = rings ? rings * s.BS : kHoldMaxGens;
-    for (uint64_t b = 0; b < nb; ++b) {
-        int64_t X, Y;
-        lambda_levels(f, m - s.q, b, &X, &Y);
-        at->push_back({X, Y});
-    }
+    std::vector<int32_t> grid;
+    tile_grid(f, m - s.q, G, &grid, at);
     const int64_t D = rings;
     std::vector<uint8_t> near(size_t(G + 2 * D) * size_t(G + 2 * D), 0);
     auto mark = [&](int64_t x, int64_t y) -> uint8_t & { return near[size_t(y + D) * (G + 2 * D) + size_t(x + D)]; };
@@ -398,7 +404,8 @@ static bool hold_members(const Fractal &f, const BlockShape &s, uint32_t m, uint
 // 171 / 229, H r10 at 5 (27 groups, 46) - / 2,519 / 2,029.
 static uint32_t hold_gpw(uint32_t groups) { return groups <= 5 ? 1 : (groups <= 24 ? 2 : 4); }
 
-bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw, HoldPlan *p, std::string *msg) {
+bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw, HoldPlan *p, std::string *msg,
+                     bool operands) {
     BlockShape s;
     if (!pick_shape(f, &s)) {
         *msg = "no block level of this fractal fits the matrix form";
@@ -412,23 +419,28 @@ bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw,
         *msg = "more groups than a work-group holds";
         return false;
     }
-    std::map<std::pair<int64_t, int64_t>, uint32_t> index;
-    for (uint32_t b = 0; b < p->ntot; ++b) index[at[b]] = b;
+    // member at a place up to rings + 1 blocks outside the tile
+    const int64_t E = int64_t(rings) + 1, side = int64_t(ipow(f.s, m - s.q)) + 2 * E;
+    std::vector<uint32_t> index(size_t(side) * size_t(side), kNone);
+    auto place = [&](int64_t x, int64_t y) -> uint32_t & { return index[size_t(y + E) * side + size_t(x + E)]; };
+    for (uint32_t b = 0; b < p->ntot; ++b) place(at[b].first, at[b].second) = b;
     const uint32_t bpg = 64 / s.lanes;
     p->raddr.assign(size_t(p->waves) * p->gpw * 64 * 2 * p->nh, p->zero | p->zero << 16);
     for (uint32_t b = 0; b < p->ntot; ++b)
         for (size_t i = 0; i < s.reads.size(); ++i) {
-            const auto it = index.find({at[b].first + kDirX[s.reads[i].first], at[b].second + kDirY[s.reads[i].first]});
-            if (it == index.end()) continue;
+            const uint32_t src = place(at[b].first + kDirX[s.reads[i].first], at[b].second + kDirY[s.reads[i].first]);
+            if (src == kNone) continue;
             const uint32_t h = uint32_t(i) / (4 * s.lanes), sub = uint32_t(i) / 4 % s.lanes, d = uint32_t(i) % 4;
             const uint32_t in = b % bpg, lane = (in / 16 * s.lanes + sub) * 16 + in % 16;
             uint32_t &w = p->raddr[((size_t(b / bpg) * 64 + lane) * 2 * p->nh) + 2 * h + d / 2];
             const uint32_t rd = s.reads[i].second;
-            const uint32_t addr = 4 * (it->second * p->rs + rd % s.lanes * s.nr + rd / s.lanes);
+            const uint32_t addr = 4 * (src * p->rs + rd % s.lanes * s.nr + rd / s.lanes);
             w = d % 2 ? (w & 0xFFFFu) | addr << 16 : (w & 0xFFFF0000u) | addr;
         }
-    mat_operands(s, &p->A);
-    mat_selectors(s, &p->sel);
+    if (operands) {
+        mat_operands(s, &p->A);
+        mat_selectors(s, &p->sel);
+    }
     if (p->halo.empty()) p->halo.push_back(0);
     p->ok = true;
     return true;

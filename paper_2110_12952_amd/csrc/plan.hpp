@@ -154,7 +154,9 @@ constexpr uint32_t kHoldMaxWaves = 16;
 constexpr uint32_t kHoldMaxGens = 4096;   // per launch, whatever the plan (a launch of milliseconds at most)
 constexpr uint32_t kHoldMaxRings = 4;
 constexpr uint32_t kHoldBuf = 32 * 1024;  // one record buffer at most
-bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw, HoldPlan *p, std::string *msg);
+// operands: with A and sel, which are the matrix plan's of the same fractal.
+bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw, HoldPlan *p, std::string *msg,
+                     bool operands = true);
 struct HoldDims {
     uint32_t m, rings, groups, gens;
     double gen_us;  // estimated time of a generation (pick_hold)

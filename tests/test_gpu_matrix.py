@@ -232,7 +232,7 @@ def test_packed_generations_against_oracle(N, name, r):
 
 
 @gpu
-@pytest.mark.parametrize("count", [1, 3, 4, 5, 4099])
+@pytest.mark.parametrize("count", [1, 3, 4099, 2_100_003])
 @pytest.mark.parametrize("off", [0, 1, 3])
 def test_maps_at_any_alignment(N, count, off):
     fd = W.TRIANGLE
