@@ -73,10 +73,13 @@ typedef enum {
 #define NBB_RULE_VON_NEUMANN (1u << 31)
 
 /* How nbb_step_compact evaluates a step (nbb_configure).  TILED runs the step
- * on the matrix cores, at a tile level of its own, for every fractal that has
- * a block level with 16 to 64 cells (k = 2 to 8 and 16); for others, and for
- * the strategies that name a form, it runs in the form and at the level that
- * nbb_query reports.  Every form gives the same states. */
+ * on the matrix cores, at tile levels of its own, for every fractal that has
+ * a block level with 16 to 64 cells (k = 2 to 8 and 16): one generation per
+ * launch, or in calls of several up to the generations that the cells held
+ * around a tile allow (both buffers end as with one launch per generation).
+ * For other fractals, and for the strategies that name a form, it runs in the
+ * form and at the level that nbb_query reports.  Every form gives the same
+ * states. */
 #define NBB_STRATEGY_AUTO 0u   /* TILED when the fractal allows it, else DIRECT */
 #define NBB_STRATEGY_TILED 1u  /* level-m tiles staged in LDS with their halo */
 #define NBB_STRATEGY_DIRECT 2u /* one thread per cell: lambda, 8 x nu, rule */
@@ -172,7 +175,9 @@ nbb_status nbb_configure(nbb_fractal *f, uint32_t strategy, uint32_t tile_level)
  * cells).  The
  * box, its copy and a member mask (3 (S+2h) ceil4(S+2h) bytes) must fit one
  * work-group's LDS.  Needs 2 <= s <= 4; 1 <= tile_level <= r and
- * 1 <= depth <= S when given.  NBB_E_INVALID otherwise (the descriptor keeps
+ * 1 <= depth <= S when given.  With tile_level and depth both 0 the
+ * matrix-core form takes the launches where it applies (the buffers end as
+ * with the plan above).  NBB_E_INVALID otherwise (the descriptor keeps
  * its plan).  nbb_query reports strategy NBB_STRATEGY_TEMPORAL, the level,
  * tiles, ring cells (halo_cells), LDS and temporal_depth; batches step the
  * descriptor with its tile plan as before.  Same conditions as
@@ -298,10 +303,10 @@ nbb_status nbb_step_blocked(const nbb_fractal *f, uint8_t *a, uint8_t *b, uint64
 
 /*
  * Bit-packed compact state (the byte layout at one bit per cell, 8x fewer
- * bytes): a capacity form, for states that would not fit as bytes.  Its step
- * scatters the bits into the byte step's LDS box and runs the byte rule, so it
- * is slower than the byte step (triangle r16: 49 us per generation against
- * 25-28); it does not cut the step's time.  Cell i is bit i % 32 of the
+ * bytes).  Its step runs in the matrix-core form where TILED does (H r9, ten
+ * generations in a call: 95 us, the byte step's time and its 8x smaller state);
+ * elsewhere it scatters the bits into the byte step's LDS box and is slower
+ * than the byte step.  Cell i is bit i % 32 of the
  * little-endian 32-bit word i / 32, i.e. bit i % 8 of byte i / 8.  Needs a
  * TILED or TILED_WAVE plan (NBB_E_INVALID otherwise).
  *   nbb_packed_bytes: 4 ceil(k^r / 32) (0 for NULL).  Bits past the last cell
@@ -315,8 +320,9 @@ nbb_status nbb_step_blocked(const nbb_fractal *f, uint8_t *a, uint8_t *b, uint64
  *   The descriptor's tile plan is used (after nbb_configure, the new one);
  *   NBB_E_INVALID if a tile's output words do not fit the kernel's limits
  *   (at most 1024 blocks, 1024 halo cells and 16 cells per block: every
- *   automatic plan fits).  The first call for a plan builds a 32-phase copy
- *   of its scatter table on the device (kept with the descriptor).
+ *   automatic plan fits).  Outside the matrix-core form the first call for a
+ *   plan builds a 32-phase copy of its scatter table on the device (kept with
+ *   the descriptor).
  */
 uint64_t nbb_packed_bytes(const nbb_fractal *f);
 nbb_status nbb_pack(const nbb_fractal *f, const uint8_t *compact, uint8_t *packed, uint64_t len, void *stream);
@@ -336,7 +342,7 @@ nbb_status nbb_gather(const nbb_fractal *f, const uint8_t *bbox, uint64_t pitch,
  * Autotuner.  The paper picks its block size per method by measurement
  * (section 4: the best rho differs between methods); this does the same for
  * the compact step.  Times `steps` generations (after one untimed one) of
- * each candidate -- TILED_EDGE, TILED_BOX and TILED_WAVE at every tile level
+ * each candidate -- TILED in the matrix-core form, TILED_EDGE, TILED_BOX and TILED_WAVE at every tile level
  * m whose tile holds at least 128 cells, plus the largest level that fits;
  * when steps > 1, TEMPORAL at its automatic plan and at every level of side
  * <= 81 with ring depths 8 and 16; and DIRECT -- on the caller's
@@ -393,9 +399,9 @@ nbb_status nbb_autotune(nbb_fractal *f, uint8_t *a, uint8_t *b, uint64_t len, ui
 typedef struct nbb_batch nbb_batch;
 typedef struct {
     uint32_t instances;
-    uint32_t groups;          /* one launch per generation each */
+    uint32_t groups;          /* launched together: one launch per generation or per several */
     uint32_t direct;          /* instances stepped by their own launch */
-    uint32_t resident;        /* instances stepped in LDS, all generations in one launch */
+    uint32_t resident;        /* instances one work-group each holds (registers or LDS), all generations in one launch */
     uint64_t cells;           /* sum of k_i^r_i */
     uint64_t tiles;           /* tiles of all tiled instances (groups and resident) */
     uint64_t arena_bytes;     /* smallest arena: max(offset + cells) rounded up to 16 */

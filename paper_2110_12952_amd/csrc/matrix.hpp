@@ -33,6 +33,12 @@
 // store out of the buffers' range (dropped by the hardware), so that no
 // memory operation sits behind a branch.
 //
+// What bounds it: memory.  One generation per launch, before (the vector
+// forms) and now: triangle r16 (43 MB of state, in the Infinity Cache) 17.1 ->
+// 15.7 us (a copy of the state takes 12.8), carpet r9 (134 MB) 50 -> 40 (a
+// copy 47), H r10 (282 MB) 161 -> 112 (a copy in this layout 105, of aligned
+// blocks 99), Vicsek r10 14.6 -> 7.6.
+//
 // BATCH: tiles of many instances of one plan in an arena: batch tile g is
 // local tile rec[4g+1] of the state of rec[4g+2] cells at byte 16 rec[4g].  An
 // instance of a lower level than the tile (its cells are the first copy of
@@ -352,6 +358,15 @@ static hipError_t launch_matrix_t(const MatParams &E, const uint8_t *in, uint8_t
 // through LDS (double-buffered, one barrier per generation).  The state is
 // read and written once per launch instead of once per generation, and a
 // generation of a small state costs a barrier instead of a launch.
+// What bounds it: instruction issue.  A group's generation is 16 + 3 NR vector
+// instructions and four MFMAs of 16 cycles, and on the workloads the vector
+// and the matrix pipes are busy for about 85 % of the time together (H r10,
+// nine generations per launch: 237 + 110 of 410 us), the LDS for half of it.
+// Per launch: triangle r16 33.2 us for 8 generations (one per launch: 126),
+// carpet r9 185 us for 9 (360), H r10 419 us for 9 (1,008).  Measured and not
+// kept: every LDS read of a generation issued before the first use (H r10
+// 518 -> 547 us for 10 generations: registers), records picked by a third
+// contraction (548).
 //   BUF: the second record buffer's offset (an instruction offset).
 //   AL 0: the state at one bit per cell (in and out are words, E.limit their
 //   bytes; not BATCH).  A lane's 16 bits come out of two words and spread to
