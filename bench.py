@@ -4,12 +4,13 @@
 Workload (default): Sierpinski triangle F^{3,2} at level r = 16 (n = 65,536,
 43,046,721 compact cells), Bernoulli(0.3) initial state from seed 12952,
 Game of Life B3/S23.  A timed step is one generation of the compact step
-over the whole fractal (one kernel launch).  The same run also times the
+over the whole fractal (a call runs several per kernel launch; calls of one
+generation, one launch each, are timed beside it for the roofline).  The same run also times the
 bounding-box step over the full 65,536^2 box (the paper's baseline) and the
 lambda / nu maps over all 43M indices, checks that the compact and box
 results agree, times the 512-instance batched workload against one launch
-per instance (and its small instances run in LDS against the per-generation
-launches), serves Poisson-arriving requests for p50/p99 latency, and
+per instance (and its small instances run in one work-group each against the
+group launches), serves Poisson-arriving requests for p50/p99 latency, and
 times the CPU oracle on a bounded sample.
 
 Prints one JSON line on stdout; progress goes to stderr.
@@ -152,9 +153,8 @@ def cpu_baseline(W, wl, seconds, one_thread=True):
 
 
 def small_case(torch, N, W, rule):
-    """Triangle r = 10 (59,049 cells), 100 generations: one launch per
-    generation is launch-bound, so the same 100 launches are also captured
-    in a HIP graph and replayed.  Also times the initial-state kernel."""
+    """Triangle r = 10 (59,049 cells), a call of 100 generations, eager and
+    captured in a HIP graph and replayed.  Also times the initial-state kernel."""
     wl = W.SMALL_TRIANGLE
     fd = wl.fractal
     g = N.Fractal(fd.s, fd.offsets, wl.r)
@@ -274,9 +274,8 @@ def batch_run(torch, N, W, args):
 
 
 def small_batch_run(torch, N, items, frs, init, big_batch, rule, steps):
-    """The batch's small instances (those a work-group's LDS holds) on their
-    own: every generation in LDS, one launch for all of them, against the
-    per-generation group launches."""
+    """The batch's small instances (those one work-group holds) on their own:
+    every generation inside their work-group, against the group launches."""
     idx = [i for i, f in enumerate(frs) if 2 * f.cells < 65536]
     sub = [frs[i] for i in idx]
     out = {"instances": len(idx), "cells": int(sum(f.cells for f in sub)), "steps": steps}
@@ -297,7 +296,7 @@ def small_batch_run(torch, N, items, frs, init, big_batch, rule, steps):
         del bt
     out["same"] = bool(torch.equal(res[True], res[False]))
     out["speedup"] = out["group_launches"]["us_per_step"] / out["lds_resident"]["us_per_step"]
-    log(f"batch, {len(idx)} small instances alone: in LDS {out['lds_resident']['us_per_step']:.1f} us/step, "
+    log(f"batch, {len(idx)} small instances alone: one work-group each {out['lds_resident']['us_per_step']:.1f} us/step, "
         f"group launches {out['group_launches']['us_per_step']:.1f} us/step, same={out['same']}")
     return out
 
@@ -396,7 +395,7 @@ def main():
     ap.add_argument("--repeats", type=int, default=10,
                     help="extra timed runs of the compact step for median / mean per-generation times")
     ap.add_argument("--no-small-batch", action="store_true",
-                    help="skip timing the batch's small instances alone (in LDS and in group launches)")
+                    help="skip timing the batch's small instances alone (one work-group each, and in group launches)")
     ap.add_argument("--serve-seconds", type=float, default=60.0,
                     help="arrival window of the served workload (the workload's full 60 s); 0 skips it")
     ap.add_argument("--large-steps", type=int, default=200,
