@@ -443,6 +443,119 @@ __global__ __launch_bounds__(512) void k_gather(MapParams P, uint32_t lam_words,
     }
 }
 
+// The same by strips, where much of the box is cells: a strip is Q.g level-L
+// tiles side by side in the box, a rectangle of Q.W = g S columns (a multiple of
+// 16, as the box's pitch) that its work-group holds in LDS.  Cells go through
+// LDS one byte each (places of a tile's K cells in a table, four cells per
+// thread), compact memory in dwords and the box in 16 bytes.  By single cells
+// both kernels are bound by their byte stores and loads to the box; here by the
+// byte accesses to LDS and by the start of a work-group (table and look-ups;
+// carpet r8 has two strips per work-group).  Expand writes every byte of the box,
+// so no fill goes before it; places of no cell stay zero in LDS, and a tile that
+// is not there has its cells cleared if the last strip with cells left some.
+// Gather skips strips without tiles.  Carpet r8 (60 MB): expand 24.5 us (fill
+// and single cells: 40.7), gather 18.7 (26.2).
+constexpr uint32_t kStripTiles = 16;
+template <bool GATHER>
+__global__ __launch_bounds__(kStripThreads) void k_strips(MapParams P, StripParams Q, const uint8_t *__restrict__ src,
+                                                uint8_t *__restrict__ dst, uint64_t pitch) {
+    typedef uint32_t Piece __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) uint8_t smem_s[];
+    uint8_t *rect = smem_s;
+    Piece *rect_p = reinterpret_cast<Piece *>(smem_s);
+    uint16_t *tab = reinterpret_cast<uint16_t *>(smem_s + Q.tab_off);
+    uint32_t *ids = reinterpret_cast<uint32_t *>(smem_s + Q.ids_off);
+    const uint32_t tid = threadIdx.x, nt = kStripThreads, quads = (Q.K + 3) / 4;
+    uint32_t bx, by;  // lambda(0) = corner of tile 0 + the tile's own cell 0
+    lam_lut(P, P.lam_lut, 0, bx, by);
+    const uint32_t lx = bx % Q.S, ly = by % Q.S;
+    bx -= lx;
+    by -= ly;
+    for (uint32_t j = tid; j < 4 * quads; j += nt) {
+        uint32_t x, y;
+        lam_lut(P, P.lam_lut, min(j, Q.K - 1), x, y);  // the last quad filled up with the last cell
+        tab[j] = uint16_t((y - by) * Q.W + (x - bx));
+    }
+    const uint32_t pieces = Q.S * (Q.W / 16);
+    if (!GATHER)
+        for (uint32_t i = tid; i < pieces; i += nt) rect_p[i] = Piece{};
+    const XcdRange R = xcd_range(blockIdx.x, gridDim.x, uint64_t(Q.nx) * Q.ny);
+    const uint32_t list = nt / kStripTiles;
+    uint32_t dirty = 0;
+    for (uint64_t t0 = R.first; t0 < R.end; t0 += R.step * list) {
+        __syncthreads();
+        {
+            const uint64_t t = t0 + R.step * (tid / kStripTiles);
+            const uint32_t q = tid % kStripTiles;
+            uint32_t id = kOutside;
+            if (t < R.end && q < Q.g) {
+                const uint32_t ty = udiv(Q.divnx, uint32_t(t)), sx = uint32_t(t) - ty * Q.nx;
+                id = nu_lut(P, P.nu_lut, int32_t((sx * Q.g + q) * Q.S + lx), int32_t(ty * Q.S + ly));
+            }
+            ids[tid] = id;
+        }
+        __syncthreads();
+        for (uint32_t l = 0; l < list && t0 + R.step * l < R.end; ++l) {
+            const uint32_t t = uint32_t(t0 + R.step * l);
+            const uint32_t ty = udiv(Q.divnx, t), sx = t - ty * Q.nx;
+            const uint32_t *id = ids + l * kStripTiles;
+            const uint32_t here = uint32_t(__ballot(id[tid % kStripTiles] != kOutside)) & 0xFFFFu;
+            uint8_t *const out = GATHER ? nullptr : dst + uint64_t(ty) * Q.S * pitch;
+            const uint8_t *const in = GATHER ? src + uint64_t(ty) * Q.S * pitch : nullptr;
+            if (GATHER) {
+                if (!here) continue;
+                for (uint32_t i = tid; i < pieces; i += nt) {
+                    const uint32_t row = udiv(Q.divrow, i), col = sx * Q.W + 16 * (i - row * (Q.W / 16));
+                    if (col < pitch) rect_p[i] = *reinterpret_cast<const Piece *>(in + row * pitch + col);
+                }
+                __syncthreads();
+            }
+            if (here) {
+                for (uint32_t i = tid; i < Q.g * quads; i += nt) {
+                    const uint32_t q = udiv(Q.divquads, i), j = 4 * (i - q * quads);
+                    const uint32_t n = min(4u, Q.K - j);
+                    uint8_t *const at = rect + q * Q.S;
+                    const uint2 e = reinterpret_cast<const uint2 *>(tab)[i - q * quads];
+                    const uint32_t o4[4] = {e.x & 0xFFFFu, e.x >> 16, e.y & 0xFFFFu, e.y >> 16};
+                    uint32_t v = 0;
+                    if (GATHER) {
+                        if (!((here >> q) & 1)) continue;
+                        for (uint32_t b = 0; b < 4; ++b) v |= uint32_t(at[o4[b]]) << (8 * b);
+                        uint8_t *o = dst + id[q] + j;
+                        if (n == 4)
+                            __builtin_memcpy(o, &v, 4);
+                        else
+                            for (uint32_t b = 0; b < n; ++b) o[b] = uint8_t(v >> (8 * b));
+                    } else {
+                        if (!(((here | dirty) >> q) & 1)) continue;
+                        if ((here >> q) & 1) {
+                            const uint8_t *c = src + id[q] + j;
+                            if (n == 4)
+                                __builtin_memcpy(&v, c, 4);
+                            else
+                                for (uint32_t b = 0; b < n; ++b) v |= uint32_t(c[b]) << (8 * b);
+                        }
+                        for (uint32_t b = 0; b < 4; ++b)
+                            if (b < n) at[o4[b]] = uint8_t(v >> (8 * b));
+                    }
+                }
+                __syncthreads();
+            }
+            if (!GATHER) {
+                // a strip without cells does not read the rectangle: a wavefront ahead may be filling it
+                for (uint32_t i = tid; i < pieces; i += nt) {
+                    const uint32_t row = udiv(Q.divrow, i), col = sx * Q.W + 16 * (i - row * (Q.W / 16));
+                    if (col < pitch) *reinterpret_cast<Piece *>(out + row * pitch + col) = here ? rect_p[i] : Piece{};
+                }
+                if (here) {
+                    __syncthreads();
+                    dirty = here;
+                }
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Compact step, one thread per cell: the paper's stencil procedure as
 // written (section 3): lambda(i), the eight neighbour coordinates, nu of each,
@@ -1093,6 +1206,14 @@ hipError_t launch_expand(const MapParams &P, uint32_t lam_words, const uint8_t *
 hipError_t launch_gather(const MapParams &P, uint32_t lam_words, const uint8_t *box, uint64_t pitch,
                          uint8_t *compact, int grid, hipStream_t st) {
     hipLaunchKernelGGL(k_gather, dim3(grid), dim3(512), lam_words * 4, st, P, lam_words, box, pitch, compact);
+    return hipGetLastError();
+}
+hipError_t launch_strips(bool gather, const MapParams &P, const StripParams &Q, const uint8_t *src, uint8_t *dst,
+                         uint64_t pitch, uint32_t grid, hipStream_t st) {
+    if (gather)
+        hipLaunchKernelGGL(k_strips<true>, dim3(grid), dim3(kStripThreads), Q.lds, st, P, Q, src, dst, pitch);
+    else
+        hipLaunchKernelGGL(k_strips<false>, dim3(grid), dim3(kStripThreads), Q.lds, st, P, Q, src, dst, pitch);
     return hipGetLastError();
 }
 hipError_t launch_step_direct(const MapParams &P, uint32_t lam_words, uint32_t nu_halves, const uint8_t *in,

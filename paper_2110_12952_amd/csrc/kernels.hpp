@@ -28,6 +28,8 @@ hipError_t launch_expand(const MapParams &P, uint32_t lam_words, const uint8_t *
                          uint64_t pitch, int grid, hipStream_t st);
 hipError_t launch_gather(const MapParams &P, uint32_t lam_words, const uint8_t *box, uint64_t pitch,
                          uint8_t *compact, int grid, hipStream_t st);
+hipError_t launch_strips(bool gather, const MapParams &P, const StripParams &Q, const uint8_t *src, uint8_t *dst,
+                         uint64_t pitch, uint32_t grid, hipStream_t st);
 hipError_t launch_step_direct(const MapParams &P, uint32_t lam_words, uint32_t nu_halves, const uint8_t *in,
                               uint8_t *out, uint32_t rule, int grid, hipStream_t st);
 hipError_t launch_blocked_scatter(const TileParams &T, const uint8_t *compact, uint8_t *blocked, uint64_t cells,

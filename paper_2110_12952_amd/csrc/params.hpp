@@ -260,4 +260,15 @@ struct BoxParams {
     const uint8_t *high;
 };
 
+// Conversion between box and compact by strips of g level-L tiles.
+constexpr uint32_t kStripThreads = 256;
+struct StripParams {
+    uint32_t S, K;        // s^L, k^L
+    uint32_t g, W;        // tiles of a strip (<= 16) and its columns, g S (a multiple of 16)
+    uint32_t nx, ny;      // strips per tile row (they cover the pitch), tile rows
+    UDiv divnx, divrow;   // by nx; by the 16-byte pieces of a strip's row
+    UDiv divquads;        // by ceil(K / 4)
+    uint32_t tab_off, ids_off, lds;
+};
+
 }  // namespace nbb
