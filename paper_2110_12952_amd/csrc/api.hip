@@ -289,7 +289,13 @@ nbb_status upload_maps(nbb_fractal *F) {
     P.sn = uint32_t(sn);
     P.kn = uint32_t(kn);
     P.sn_top = uint32_t(st);
-    P.divsn = make_udiv(P.sn);
+    uint32_t l = 0;
+    while (uint64_t(1) << l < sn) ++l;
+    if (l) {
+        P.nu_shift = uint64_t(1) << l == sn ? l : 0;
+        P.nu_mul = uint32_t(((uint64_t(1) << (31 + l)) + sn - 1) / sn);
+        P.nu_mul_shift = l - 1;
+    }
     P.nu_top_off = t.nu_top_off;
     P.lam_lut = static_cast<const uint32_t *>(dst[0]);
     P.nu_lut = static_cast<const uint16_t *>(dst[1]);

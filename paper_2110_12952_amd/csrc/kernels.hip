@@ -46,23 +46,39 @@ __device__ __forceinline__ void lam_lut(const MapParams &P, const uint32_t *lam,
     y = py;
 }
 
+// Divisions and products dominate nu's instructions, so they are shifts or one
+// mulhi and 24-bit products where the operands allow it (a 32-bit product or
+// mulhi issues in 16 cycles, a 24-bit product in 4): 20M random points, one per
+// thread, triangle r16 49.3 -> 43.1 us, carpet r9 49.0 -> 46.8, H r10 49.7 -> 48.1
+// (points in the caches; from memory, triangle, 61.8 -> 57.2, bound by the loads).
 __device__ __forceinline__ uint32_t nu_lut(const MapParams &P, const uint16_t *nu, int32_t x,
                                            int32_t y) {
     if (uint32_t(x) >= P.n || uint32_t(y) >= P.n) return kOutside;
     uint32_t ux = uint32_t(x), uy = uint32_t(y), idx = 0, w = 1, bad = 0;
     for (uint32_t c = 0; c + 1 < P.nchunks_n; ++c) {
-        uint32_t qx = udiv(P.divsn, ux), qy = udiv(P.divsn, uy);
-        uint32_t v = nu[(uy - qy * P.sn) * P.sn + (ux - qx * P.sn)];
+        uint32_t qx, qy, rx, ry;
+        if (P.nu_shift) {
+            qx = ux >> P.nu_shift;
+            qy = uy >> P.nu_shift;
+            rx = ux & (P.sn - 1);
+            ry = uy & (P.sn - 1);
+        } else {
+            qx = __umulhi(ux, P.nu_mul) >> P.nu_mul_shift;
+            qy = __umulhi(uy, P.nu_mul) >> P.nu_mul_shift;
+            rx = (ux - __umul24(qx, P.sn)) & 0xFFFFFFu;  // right modulo 2^24, and below sn
+            ry = (uy - __umul24(qy, P.sn)) & 0xFFFFFFu;
+        }
+        uint32_t v = nu[__umul24(ry, P.sn) + rx];
         bad |= (v == 0xFFFFu);
-        idx += v * w;
+        idx += w >> 24 ? v * w : __umul24(v, w);
         w *= P.kn;
         ux = qx;
         uy = qy;
     }
     if (P.nchunks_n) {
-        uint32_t v = nu[P.nu_top_off + uy * P.sn_top + ux];
+        uint32_t v = nu[P.nu_top_off + __umul24(uy, P.sn_top) + ux];
         bad |= (v == 0xFFFFu);
-        idx += v * w;
+        idx += w >> 24 ? v * w : __umul24(v, w);
     }
     return bad ? kOutside : idx;
 }
@@ -78,8 +94,8 @@ __device__ __forceinline__ void load_map_tables(const MapParams &P, uint32_t lam
 
 // Four consecutive items per thread (VEC, arrays 16-aligned): one 16-byte load
 // or store per array and four independent look-ups: 20M random indices of the
-// triangle r16 44.5 us, 51 with one item per thread.  (nu does not gain: 62
-// against 59, its look-ups and not its loads bound it.)
+// triangle r16 44.5 us, 51 with one item per thread.  (nu does not gain: 60.4
+// against 57.2 on points that are not in the caches.)
 struct alignas(16) Quad {
     uint32_t v[4];
 };

@@ -34,7 +34,11 @@ struct MapParams {
     // or 0xFFFF, indexed yc * s^jn + xc; the top chunk has its own table.
     uint32_t jn, jn_top, nchunks_n;
     uint32_t sn, kn, sn_top;
-    UDiv divsn;
+    // division of coordinates (< 2^31) by sn: a shift where sn is a power of two
+    // (nu_shift > 0), else q = mulhi(a, nu_mul) >> nu_mul_shift, nu_mul =
+    // ceil(2^(31 + l) / sn) < 2^32, l = ceil(log2 sn), nu_mul_shift = l - 1: nu_mul is too large by
+    // less than sn / 2^(31 + l) of its value, so a 31-bit a has the exact quotient.
+    uint32_t nu_shift, nu_mul, nu_mul_shift;
     uint32_t nu_top_off;
     const uint32_t *lam_lut;
     const uint16_t *nu_lut;

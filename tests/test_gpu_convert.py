@@ -45,3 +45,31 @@ def test_strips(name, r, extra, off):
     back = pad.cpu().numpy()
     np.testing.assert_array_equal(back[16 + off:16 + off + g.cells], st)
     assert (back[:16 + off] == 9).all() and (back[16 + off + g.cells:] == 9).all()
+
+
+@pytest.mark.parametrize("name,r", [("triangle", 16), ("triangle", 20), ("carpet", 7), ("carpet", 10), ("hfractal", 9),
+                                    ("grid4_12", 8), ("chandelier", 10), ("cross5", 9), ("fullsquare", 15), ("cantor", 19)])
+@pytest.mark.parametrize("count", [4097, 300_003])
+def test_nu_divisions(name, r, count):
+    """Coordinates at the edges of every level's copies, inside and outside the
+    box, and cells of the fractal."""
+    from paper_2110_12952_amd import nbbfrac as N
+    s, offsets = FRACTALS[name]
+    o, g = O.Fractal(s, offsets, r), N.Fractal(s, offsets, r)
+    rng = np.random.default_rng(3)
+    n = s ** r
+
+    def axis():
+        v = rng.integers(-2, n + 2, count)
+        step = s ** rng.integers(0, r + 1, count)
+        edge = rng.integers(0, 2, count).astype(bool)
+        v = np.where(edge, v // step * step + rng.integers(-1, 2, count), v)
+        return np.clip(v, -3, 2 ** 31 - 1).astype(np.int32)
+
+    x, y = axis(), axis()
+    inside = rng.integers(0, o.cells, count // 2, dtype=np.uint64).astype(np.uint32)
+    x[:count // 2], y[:count // 2] = o.lam_many(inside)
+    want = o.nu_many(x, y)
+    got = g.nu(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()).cpu().numpy().view(np.uint32)
+    np.testing.assert_array_equal(got, np.asarray(want).astype(np.int64).astype(np.uint32))
+    np.testing.assert_array_equal(got[:count // 2], inside)
