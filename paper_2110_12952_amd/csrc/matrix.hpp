@@ -166,7 +166,7 @@ __global__ __launch_bounds__(64 * kMatMaxWaves) void k_step_matrix(MatParams E, 
     const uint32_t L = E.lanes, quarter = lane >> 4, col = lane & 15;
     const uint32_t sub = quarter & (L - 1), bpg = 64 / L;
     const uint32_t slot = (L == 4 ? 0u : (L == 2 ? quarter >> 1 : quarter)) * 16 + col;
-    const uint32_t coff = min(16 * sub, E.CB - 16);
+    const uint32_t coff = mat_first_cell(sub, E.CB);
     const bool edge = (rule >> 31) != 0;
     const uint8_t *A8 = reinterpret_cast<const uint8_t *>(E.A) + 16 * lane;
     auto operand = [&](uint32_t off) -> u32x4 { return *reinterpret_cast<const u32x4 *>(A8 + off); };
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
     const uint32_t L = E.lanes, quarter = lane >> 4, col = lane & 15;
     const uint32_t sub = quarter & (L - 1), bpg = 64 / L;
     const uint32_t slot = (L == 4 ? 0u : (L == 2 ? quarter >> 1 : quarter)) * 16 + col;
-    const uint32_t coff = min(16 * sub, E.CB - 16);
+    const uint32_t coff = mat_first_cell(sub, E.CB);
     const uint8_t *src = in + base;
     const uint64_t room = (E.limit - base + 3) & ~uint64_t(3);
     const __amdgpu_buffer_rsrc_t all = mat_rsrc(src, room > kNowhere ? kNowhere : uint32_t(room));
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
 #pragma unroll
     for (int u = 0; u < GPW; ++u) {
         const uint32_t b = (wave * GPW + u) * bpg + slot;
-        const bool own = b < E.nblk && b * E.CB < bytes, ring = b >= E.nblk && b < E.ntot;
+        const bool own = b < E.nblk && mat_lane_owns(b, E.CB, coff, bytes), ring = b >= E.nblk && b < E.ntot;
         const uint32_t item = E.halo[ring ? b - E.nblk : 0u];
         const uint32_t nt = E.nbr[uint64_t(t) * 8 + (item >> 29)];
         soff[u] = own ? b * E.CB + coff : kNowhere;

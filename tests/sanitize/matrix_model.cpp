@@ -44,18 +44,24 @@ static uint8_t pick(const std::vector<uint32_t> &sel, uint32_t t, uint32_t sub, 
     return a < 8 ? x[a] : (b < 8 ? x[8 + b] : 0);
 }
 
-static void check(const Fractal &f, const MatPlan &p, std::mt19937 &rng, bool edge) {
-    std::vector<uint8_t> st(f.cells);
-    for (auto &c : st) c = rng() & 1;
+// `inst`: the same fractal at a level below the plan's tile, as a batch's
+// instance is one cut tile without neighbours, with live bytes behind it.
+static void check(const Fractal &f, const MatPlan &p, std::mt19937 &rng, bool edge, const Fractal *inst = nullptr) {
+    const Fractal &of = inst ? *inst : f;
+    const uint64_t ntiles = inst ? 1 : p.ntiles;
+    const uint32_t bytes = uint32_t(std::min<uint64_t>(p.K, of.cells));
+    std::vector<uint8_t> st(std::max<uint64_t>(of.cells, p.K), 1);
+    for (uint64_t i = 0; i < of.cells; ++i) st[i] = rng() & 1;
     const uint32_t bpg = 64 / p.lanes;
-    for (uint64_t tile = 0; tile < p.ntiles; ++tile) {
-        if (p.ntiles > 40 && rng() % (p.ntiles / 20)) continue;
+    for (uint64_t tile = 0; tile < ntiles; ++tile) {
+        if (ntiles > 40 && rng() % (p.ntiles / 20)) continue;
         std::vector<uint8_t> lds(p.buf_bytes, 0xEE);
         const uint32_t zero = (p.lanes * p.nr * p.nrecs) * 4;
         if (zero + 4 > p.buf_bytes) std::abort();
         for (int i = 0; i < 4; ++i) lds[zero + i] = 0;
         auto load = [&](uint64_t t, uint32_t b, uint32_t sub, uint8_t *dst) {
-            const uint32_t off = std::min(16 * sub, p.CB - 16);
+            const uint32_t off = mat_first_cell(sub, p.CB);
+            if (inst && !mat_lane_owns(b, p.CB, off, bytes)) return;  // loads as zeros
             for (uint32_t j = 0; j < 16; ++j) dst[j] = st[t * p.K + b * p.CB + off + j];
         };
         auto publish = [&](const std::vector<uint8_t> &B, const std::vector<int64_t> &rec) {
@@ -91,7 +97,7 @@ static void check(const Fractal &f, const MatPlan &p, std::mt19937 &rng, bool ed
             return true;
         };
         auto halo = [&](uint32_t h, uint64_t *t, uint32_t *lb) {
-            const uint32_t nt = p.nbr[tile * 8 + (p.halo[h] >> 29)];
+            const uint32_t nt = inst ? 0xFFFFFFFFu : p.nbr[tile * 8 + (p.halo[h] >> 29)];
             *t = nt;
             *lb = p.halo[h] & 0x1FFFFFFFu;
             return nt != 0xFFFFFFFFu;
@@ -128,8 +134,9 @@ static void check(const Fractal &f, const MatPlan &p, std::mt19937 &rng, bool ed
                     if (b >= p.nblk) continue;
                     for (int i = 0; i < 4; ++i)
                         for (int hi = 0; hi < 2; ++hi) {
-                            const uint32_t c = std::min(16 * sub, p.CB - 16) + 8 * t + 4 * hi + i;
-                            const int want = count_ref(f, st, tile * p.K + b * p.CB + c, edge);
+                            const uint32_t c = mat_first_cell(sub, p.CB) + 8 * t + 4 * hi + i;
+                            if (b * p.CB + c >= bytes) continue;
+                            const int want = count_ref(of, st, tile * p.K + b * p.CB + c, edge);
                             const int got = hi ? D[l][i] >> 4 : D[l][i] & 15;
                             if (want != got || D[l][i] < 0 || D[l][i] > 255) {
                                 std::printf("mismatch k %u s %u r %u m %u tile %llu block %u cell %u: %d %d\n", f.k, f.s,
@@ -144,25 +151,29 @@ static void check(const Fractal &f, const MatPlan &p, std::mt19937 &rng, bool ed
 }
 
 // Several generations of a random rule on tiles held with their rings.
-static void check_hold(const Fractal &f, const HoldPlan &p, std::mt19937 &rng) {
+static void check_hold(const Fractal &f, const HoldPlan &p, std::mt19937 &rng, const Fractal *inst = nullptr) {
+    const Fractal &of = inst ? *inst : f;
+    const uint64_t ntiles = inst ? 1 : p.ntiles;
+    const uint32_t bytes = uint32_t(std::min<uint64_t>(p.K, of.cells));
     const uint32_t rule = rng() & 0x01FF01FFu;
     const bool edge = rng() & 1;
     const uint32_t gens = std::min(p.gens, 10u), bpg = 64 / p.lanes;
-    std::vector<uint8_t> st(f.cells);
-    for (auto &c : st) c = rng() & 1;
-    std::vector<uint8_t> ref = st;
+    std::vector<uint8_t> st(std::max<uint64_t>(of.cells, p.K), 1);
+    for (uint64_t i = 0; i < of.cells; ++i) st[i] = rng() & 1;
+    std::vector<uint8_t> ref(st.begin(), st.begin() + std::ptrdiff_t(of.cells));
     for (uint32_t g = 0; g < gens; ++g) {
-        std::vector<uint8_t> next(f.cells);
-        for (uint64_t i = 0; i < f.cells; ++i) {
-            const int n = count_ref(f, ref, i, edge);
+        std::vector<uint8_t> next(of.cells);
+        for (uint64_t i = 0; i < of.cells; ++i) {
+            const int n = count_ref(of, ref, i, edge);
             next[i] = (rule >> (ref[i] ? 16 + n : n)) & 1;
         }
         ref.swap(next);
     }
     std::vector<uint32_t> nbr;
-    neighbour_table(f, f.r - p.m, &nbr);
-    for (uint64_t tile = 0; tile < p.ntiles; ++tile) {
-        if (p.ntiles > 4 && rng() % (p.ntiles / 2)) continue;
+    if (inst) nbr.assign(8, 0xFFFFFFFFu);
+    else neighbour_table(f, f.r - p.m, &nbr);
+    for (uint64_t tile = 0; tile < ntiles; ++tile) {
+        if (ntiles > 4 && rng() % (ntiles / 2)) continue;
         const uint32_t groups = p.waves * p.gpw;
         std::vector<std::vector<uint8_t>> X(groups, std::vector<uint8_t>(1024));
         std::vector<uint8_t> live(groups * 64);
@@ -177,10 +188,12 @@ static void check_hold(const Fractal &f, const HoldPlan &p, std::mt19937 &rng) {
                     t = nbr[tile * 8 + (item >> 29)];
                     lb = item & 0x1FFFFFFFu;
                     if (t == 0xFFFFFFFFu) continue;
+                } else if (!mat_lane_owns(b, p.CB, mat_first_cell(sub, p.CB), bytes)) {
+                    continue;
                 }
                 live[g * 64 + l] = 1;
                 for (uint32_t j = 0; j < 16; ++j)
-                    X[g][16 * l + j] = st[t * p.K + lb * p.CB + std::min(16 * sub, p.CB - 16) + j];
+                    X[g][16 * l + j] = st[t * p.K + lb * p.CB + mat_first_cell(sub, p.CB) + j];
             }
         for (uint32_t gen = 0; gen < gens; ++gen) {
             std::vector<uint8_t> lds(p.zero + 4, 0xEE);
@@ -224,7 +237,8 @@ static void check_hold(const Fractal &f, const HoldPlan &p, std::mt19937 &rng) {
         for (uint32_t b = 0; b < p.nblk; ++b)
             for (uint32_t sub = 0; sub < p.lanes; ++sub)
                 for (uint32_t j = 0; j < 16; ++j) {
-                    const uint32_t c = std::min(16 * sub, p.CB - 16) + j, in = b % bpg;
+                    const uint32_t c = mat_first_cell(sub, p.CB) + j, in = b % bpg;
+                    if (b * p.CB + c >= bytes) continue;
                     const uint32_t lane = (in / 16 * p.lanes + sub) * 16 + in % 16;
                     if (X[b / bpg][16 * lane + j] != ref[tile * p.K + b * p.CB + c]) {
                         std::printf("held mismatch k %u s %u r %u m %u gens %u tile %llu block %u cell %u\n", f.k, f.s, f.r,
@@ -280,6 +294,31 @@ int main(int argc, char **argv) {
                                 p.buf_bytes);
             }
         }
+    // instances below the tile level of the launch's plan, of every level that
+    // has a plan of its own; block levels differ between them for k = 2 and 4
+    int cut = 0;
+    named.push_back({2, {0, 0, 1, 1}});                               // diagonal
+    for (auto &n : named)
+        for (uint32_t r = 2; r <= 9; ++r) {
+            Fractal f, low;
+            if (!make(n.first, n.second, r, &f) || f.cells > 5000) continue;
+            for (uint32_t lr = 1; lr < r; ++lr) {
+                MatPlan p;
+                HoldPlan h;
+                std::string msg;
+                make(n.first, n.second, lr, &low);
+                if (mat_dims(low).empty()) continue;
+                for (uint32_t m = lr + 1; m <= r; ++m) {
+                    if (build_mat_plan(f, m, 0, &p, &msg))
+                        for (bool edge : {false, true}) check(f, p, rng, edge, &low);
+                    if (build_hold_plan(f, m, m == r ? 0 : 1, 0, &h, &msg)) {
+                        for (int i = 0; i < 4; ++i) check_hold(f, h, rng, &low);
+                        ++cut;
+                    }
+                }
+            }
+        }
+    std::printf("cut %d\n", cut);
     for (int it = 0; it < 300; ++it) {
         const uint32_t s = 2 + rng() % 3, k = 1 + rng() % (s * s);
         std::vector<int> cells(s * s);

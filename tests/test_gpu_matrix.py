@@ -116,6 +116,17 @@ def test_batch_of_many_levels(N, name, levels):
             assert (ha == 1).all() and (hb == 1).all()
 
 
+# Levels of one batch whose own plans have different blocks: 16 and 64 cells
+# (k = 4), 16, 32 and 64 (k = 2); an instance may be a quarter of a block
+BLOCK_LEVELS = [("chandelier", (2, 3, 4, 6)), ("cantor", (4, 5, 6, 8)), ("cantor", (4, 5)), ("cantordust", (2, 3, 5))]
+
+
+@gpu
+@pytest.mark.parametrize("name,levels", BLOCK_LEVELS)
+def test_batch_of_many_block_levels(N, name, levels):
+    test_batch_of_many_levels(N, name, levels)
+
+
 HELD = [("triangle", r) for r in (3, 5, 7, 9, 10, 12)] + [("carpet", r) for r in (2, 3, 4, 5, 6)] + \
        [("hfractal", r) for r in (2, 3, 4, 5, 6)] + [("chandelier", r) for r in (3, 5, 7, 8, 9)] + \
        [("fullsquare", r) for r in (3, 6, 8)] + [("vicsek", r) for r in (2, 4, 6, 7)] + \
@@ -197,6 +208,13 @@ def test_batch_several_generations(N, name, levels, resident):
                 ha[off:off + len(st)] = 1
                 hb[off:off + len(st)] = 1
             assert (ha == 1).all() and (hb == 1).all()
+
+
+@gpu
+@pytest.mark.parametrize("resident", [True, False])
+@pytest.mark.parametrize("name,levels", BLOCK_LEVELS)
+def test_batch_of_many_block_levels_several_generations(N, name, levels, resident):
+    test_batch_several_generations(N, name, levels, resident)
 
 
 def bits(state):
