@@ -145,15 +145,51 @@ bool pick_shape(const Fractal &f, BlockShape *s) {
 
 }  // namespace
 
-// Block numbers of a tile's G x G grid (-1: no block), and the blocks' places.
-static void tile_grid(const Fractal &f, uint32_t levels, int64_t G, std::vector<int32_t> *grid,
-                      std::vector<std::pair<int64_t, int64_t>> *at) {
-    grid->assign(size_t(G) * G, -1);
+const uint32_t kNone = 0xFFFFFFFFu;
+
+// Numbers by place in [lo, hi)^2, at most `most` of them: a table of the whole
+// square up to 1 MB, else a hash table, as a sparse fractal has few blocks in a
+// square of any side (the Cantor set 1,024 in a row of 59,049, whose square
+// would take 14 GB).  The plans of the triangle r16 and the chandelier r9 take
+// 0.4 and 0.5 ms from tables, 1.1 and 1.3 from hash tables.
+class PlaceMap {
+   public:
+    PlaceMap(int64_t lo, int64_t hi, uint64_t most) : lo_(lo), side_(uint64_t(hi - lo)) {
+        dense_ = side_ <= 512;
+        uint64_t n = dense_ ? side_ * side_ : 16;
+        for (; !dense_ && n < 2 * most; n *= 2) --shift_;
+        if (!dense_) key_.assign(size_t(n), 0);
+        val_.assign(size_t(n), kNone);
+    }
+    // the number at (x, y), or kNone; a reference to set it (to anything else)
+    uint32_t &at(int64_t x, int64_t y) {
+        const uint64_t u = uint64_t(x - lo_), v = uint64_t(y - lo_);
+        if (dense_) return val_[size_t(v * side_ + u)];
+        const uint64_t key = v << 32 | u;
+        size_t i = size_t((key * 0x9E3779B97F4A7C15ull) >> shift_);
+        while (val_[i] != kNone && key_[i] != key) i = (i + 1) & (val_.size() - 1);
+        key_[i] = key;
+        return val_[i];
+    }
+
+   private:
+    int64_t lo_;
+    uint64_t side_;
+    bool dense_ = false;
+    uint32_t shift_ = 60;
+    std::vector<uint64_t> key_;
+    std::vector<uint32_t> val_;
+};
+
+// The places of the blocks of a tile, `levels` block levels: the numbers by
+// place and the places by number.
+static void tile_places(const Fractal &f, uint32_t levels, PlaceMap *block,
+                        std::vector<std::pair<int64_t, int64_t>> *at) {
     const uint64_t nb = ipow(f.k, levels);
     for (uint64_t b = 0; b < nb; ++b) {
         int64_t X, Y;
         lambda_levels(f, levels, b, &X, &Y);
-        (*grid)[size_t(Y * G + X)] = int32_t(b);
+        block->at(X, Y) = uint32_t(b);
         at->push_back({X, Y});
     }
 }
@@ -161,7 +197,6 @@ static void tile_grid(const Fractal &f, uint32_t levels, int64_t G, std::vector<
 // The blocks of the tile at level m and of its neighbour tiles: `source`
 // gets the record of every read of every block (an own block, a halo block
 // numbered as first met, or none).
-const uint32_t kNone = 0xFFFFFFFFu;
 static bool build_ring(const Fractal &f, const BlockShape &s, uint32_t m, MatPlan *p, std::vector<uint32_t> *source,
                        std::string *msg) {
     *p = MatPlan();
@@ -186,29 +221,28 @@ static bool build_ring(const Fractal &f, const BlockShape &s, uint32_t m, MatPla
     p->groups = (p->nblk + bpg - 1) / bpg;
     p->ntiles = ipow(f.k, f.r - m);
     const int64_t G = int64_t(ipow(f.s, m - s.q));
-    std::vector<int32_t> grid;
+    PlaceMap block(0, G, nb), ring(-1, G + 1, 8 * nb);  // ring: the halo block at a place around the tile
     std::vector<std::pair<int64_t, int64_t>> at;
-    tile_grid(f, m - s.q, G, &grid, &at);
-    std::vector<uint32_t> ring(size_t(G + 2) * size_t(G + 2), kNone);  // the halo block at a place around the tile
+    tile_places(f, m - s.q, &block, &at);
     source->assign(size_t(p->nblk) * s.reads.size(), kNone);
     for (uint32_t b = 0; b < p->nblk; ++b)
         for (size_t i = 0; i < s.reads.size(); ++i) {
             const uint32_t d = s.reads[i].first;
             const int64_t nx = at[b].first + kDirX[d], ny = at[b].second + kDirY[d];
             const int tx = nx < 0 ? -1 : (nx >= G ? 1 : 0), ty = ny < 0 ? -1 : (ny >= G ? 1 : 0);
-            const int32_t v = grid[size_t((ny - ty * G) * G + nx - tx * G)];
-            if (v < 0) continue;
+            const uint32_t v = block.at(nx - tx * G, ny - ty * G);
+            if (v == kNone) continue;
             uint32_t &src = (*source)[b * s.reads.size() + i];
             if (!tx && !ty) {
-                src = uint32_t(v);
+                src = v;
                 continue;
             }
-            uint32_t &h = ring[size_t(ny + 1) * (G + 2) + size_t(nx + 1)];
+            uint32_t &h = ring.at(nx, ny);
             if (h == kNone) {
                 uint32_t dir = 0;
                 while (kDirX[dir] != tx || kDirY[dir] != ty) ++dir;
                 h = p->nblk + uint32_t(p->halo.size());
-                p->halo.push_back(dir << 29 | uint32_t(v));
+                p->halo.push_back(dir << 29 | v);
             }
             src = h;
         }
@@ -365,18 +399,19 @@ static bool hold_members(const Fractal &f, const BlockShape &s, uint32_t m, uint
     p->nblk = uint32_t(nb);
     p->ntiles = ipow(f.k, f.r - m);
     p->gens = rings ? rings * s.BS : kHoldMaxGens;
-    std::vector<int32_t> grid;
-    tile_grid(f, m - s.q, G, &grid, at);
     const int64_t D = rings;
-    std::vector<uint8_t> near(size_t(G + 2 * D) * size_t(G + 2 * D), 0);
-    auto mark = [&](int64_t x, int64_t y) -> uint8_t & { return near[size_t(y + D) * (G + 2 * D) + size_t(x + D)]; };
-    for (uint64_t b = 0; b < nb && D; ++b)
-        for (int64_t dy = -D; dy <= D; ++dy)
-            for (int64_t dx = -D; dx <= D; ++dx) mark((*at)[b].first + dx, (*at)[b].second + dy) = 1;
+    PlaceMap block(-2 * D, G + 2 * D, nb);
+    tile_places(f, m - s.q, &block, at);
+    auto near = [&](int64_t x, int64_t y) {
+        for (int64_t v = y - D; v <= y + D; ++v)
+            for (int64_t u = x - D; u <= x + D; ++u)
+                if (block.at(u, v) != kNone) return true;
+        return false;
+    };
     for (uint32_t d = 0; d < 8 && D; ++d)
         for (uint64_t b = 0; b < nb; ++b) {
             const int64_t X = (*at)[b].first + kDirX[d] * G, Y = (*at)[b].second + kDirY[d] * G;
-            if (X < -D || Y < -D || X >= G + D || Y >= G + D || !mark(X, Y)) continue;
+            if (X < -D || Y < -D || X >= G + D || Y >= G + D || !near(X, Y)) continue;
             p->halo.push_back(d << 29 | uint32_t(b));
             at->push_back({X, Y});
         }
@@ -419,16 +454,14 @@ bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw,
         *msg = "more groups than a work-group holds";
         return false;
     }
-    // member at a place up to rings + 1 blocks outside the tile
-    const int64_t E = int64_t(rings) + 1, side = int64_t(ipow(f.s, m - s.q)) + 2 * E;
-    std::vector<uint32_t> index(size_t(side) * size_t(side), kNone);
-    auto place = [&](int64_t x, int64_t y) -> uint32_t & { return index[size_t(y + E) * side + size_t(x + E)]; };
-    for (uint32_t b = 0; b < p->ntot; ++b) place(at[b].first, at[b].second) = b;
+    const int64_t E = int64_t(rings) + 1;  // looked up to a block outside the rings
+    PlaceMap member(-E, int64_t(ipow(f.s, m - s.q)) + E, p->ntot);
+    for (uint32_t b = 0; b < p->ntot; ++b) member.at(at[b].first, at[b].second) = b;
     const uint32_t bpg = 64 / s.lanes;
     p->raddr.assign(size_t(p->waves) * p->gpw * 64 * 2 * p->nh, p->zero | p->zero << 16);
     for (uint32_t b = 0; b < p->ntot; ++b)
         for (size_t i = 0; i < s.reads.size(); ++i) {
-            const uint32_t src = place(at[b].first + kDirX[s.reads[i].first], at[b].second + kDirY[s.reads[i].first]);
+            const uint32_t src = member.at(at[b].first + kDirX[s.reads[i].first], at[b].second + kDirY[s.reads[i].first]);
             if (src == kNone) continue;
             const uint32_t h = uint32_t(i) / (4 * s.lanes), sub = uint32_t(i) / 4 % s.lanes, d = uint32_t(i) % 4;
             const uint32_t in = b % bpg, lane = (in / 16 * s.lanes + sub) * 16 + in % 16;

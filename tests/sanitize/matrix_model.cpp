@@ -319,6 +319,20 @@ int main(int argc, char **argv) {
             }
         }
     std::printf("cut %d\n", cut);
+    // few blocks in a wide square
+    for (const auto &n : std::vector<std::pair<uint32_t, std::vector<int32_t>>>{{3, {0, 0, 2, 0}}, {4, {0, 0, 1, 1}}}) {
+        Fractal f;
+        const uint32_t r = n.first == 3 ? 12 : 11;
+        if (!make(n.first, n.second, r, &f)) std::abort();
+        for (uint32_t m = r - 1; m <= r; ++m) {
+            MatPlan p;
+            HoldPlan h;
+            std::string msg;
+            if (!build_mat_plan(f, m, 0, &p, &msg) || !build_hold_plan(f, m, m < r ? 2 : 0, 0, &h, &msg)) std::abort();
+            check(f, p, rng, false);
+            check_hold(f, h, rng);
+        }
+    }
     for (int it = 0; it < 300; ++it) {
         const uint32_t s = 2 + rng() % 3, k = 1 + rng() % (s * s);
         std::vector<int> cells(s * s);

@@ -60,6 +60,13 @@ def test_random_fractals_against_oracle(N, seed):
 
 
 @gpu
+@pytest.mark.parametrize("s,offsets,r", [(3, ((0, 0), (2, 0)), 17), (4, ((0, 0), (1, 1)), 15), (4, ((2, 1), (2, 2)), 14)])
+def test_sparse_fractals_at_large_levels(N, s, offsets, r):
+    # few cells in a box of up to 2^30 a side: the plans hold the blocks alone
+    check(N, W.FractalDef("sparse", s, offsets), r, RULES[:1] + RULES[4:5])
+
+
+@gpu
 def test_full_rule_words(N):
     # births and survivals at eight neighbours (the bit-extract form) on the
     # fractals that have such cells

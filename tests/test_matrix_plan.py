@@ -27,3 +27,18 @@ def test_matrix_plan_model(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, timeout=600, env=env)
     assert r.returncode == 0 and "runtime error" not in r.stderr, r.stdout[-2000:] + r.stderr[-2000:]
     assert int(r.stdout.split()[-1]) > 300
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_sparse_fractals_within_time_and_memory(tmp_path):
+    # a square of s^(m - q) blocks a side must not be held whole: up to the
+    # largest r, 1 GiB of address space and half a second for each descriptor
+    exe = str(tmp_path / "sparse_plans")
+    r = subprocess.run(["g++", "-std=c++17", "-O2", "-I", CSRC, os.path.join(ROOT, "tests", "sanitize", "sparse_plans.cpp"),
+                        os.path.join(CSRC, "plan.cpp"), os.path.join(CSRC, "matrix_plan.cpp"), "-o", exe],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+    made, longest = r.stdout.split()
+    assert int(made) > 100 and float(longest) < 0.5
