@@ -8,6 +8,7 @@
 #include <cstring>
 #include <functional>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <numeric>
@@ -32,6 +33,16 @@ nbb_status fail(nbb_status s, const std::string &msg) {
 nbb_status hip_fail(hipError_t e, const char *what) {
     return fail(NBB_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
+// What an entry point returns for an exception, none of which may cross the
+// interface: only containers and strings throw here, when memory runs out.
+nbb_status no_memory() noexcept {
+    try {
+        return fail(NBB_E_NOMEM, "host allocation failed");
+    } catch (...) {
+        return NBB_E_NOMEM;  // (the message stays the last one)
+    }
+}
+#define NBB_CATCH catch (const std::exception &) { return no_memory(); }
 
 // One device allocation holding a set of tables; offsets are 256-aligned.
 struct DevBlob {
@@ -519,33 +530,43 @@ const nbb_fractal::MatTables *batch_mat_plan(const nbb_fractal *F, uint32_t m, u
     const auto key = std::make_pair(m, gpw);
     auto it = F->mat_plans.find(key);
     if (it != F->mat_plans.end()) return &it->second;
-    nbb_fractal::MatTables t;
+    nbb_fractal::MatTables made;
     std::string msg;
-    if (!build_mat_plan(F->f, m, gpw, &t.plan, &msg, false)) return nullptr;
-    t.plan.nbr.assign(8, 0xFFFFFFFFu);
+    if (!build_mat_plan(F->f, m, gpw, &made.plan, &msg, false)) return nullptr;
+    made.plan.nbr.assign(8, 0xFFFFFFFFu);
+    it = F->mat_plans.emplace(key, std::move(made)).first;  // (may throw: before its device memory)
+    nbb_fractal::MatTables &t = it->second;
     const void *src[5];
     size_t bytes[5];
     void *dst[5];
     matrix_parts(t.plan, src, bytes);
-    if (upload(&t.blob, src, bytes, 5, dst) != NBB_OK) return nullptr;
+    if (upload(&t.blob, src, bytes, 5, dst) != NBB_OK) {
+        F->mat_plans.erase(it);
+        return nullptr;
+    }
     matrix_params(t.plan, dst, &t.p);
-    return &(F->mat_plans[key] = std::move(t));
+    return &t;
 }
 const nbb_fractal::HoldTables *batch_hold_plan(const nbb_fractal *F, const HoldDims &d, uint32_t gpw) {
     std::lock_guard<std::mutex> lock(F->mat_mu);
     const std::array<uint32_t, 3> key = {d.m, d.rings, gpw};
     auto it = F->hold_plans.find(key);
     if (it != F->hold_plans.end()) return &it->second;
-    nbb_fractal::HoldTables t;
+    nbb_fractal::HoldTables made;
     std::string msg;
-    if (!build_hold_plan(F->f, d.m, d.rings, gpw, &t.plan, &msg)) return nullptr;
+    if (!build_hold_plan(F->f, d.m, d.rings, gpw, &made.plan, &msg)) return nullptr;
+    it = F->hold_plans.emplace(key, std::move(made)).first;  // (may throw: before its device memory)
+    nbb_fractal::HoldTables &t = it->second;
     const void *src[5];
     size_t bytes[5];
     void *dst[5];
     hold_parts(t.plan, {}, src, bytes);
-    if (upload(&t.blob, src, bytes, 5, dst) != NBB_OK) return nullptr;
+    if (upload(&t.blob, src, bytes, 5, dst) != NBB_OK) {
+        F->hold_plans.erase(it);
+        return nullptr;
+    }
     hold_params(t.plan, dst, &t.p);
-    return &(F->hold_plans[key] = std::move(t));
+    return &t;
 }
 const uint32_t *batch_mat_nbr(const nbb_fractal *F, uint32_t m) {
     if (m == F->mat.m && F->matp.nbr) return F->matp.nbr;
@@ -557,9 +578,11 @@ const uint32_t *batch_mat_nbr(const nbb_fractal *F, uint32_t m) {
         const void *src[1] = {nbr.data()};
         size_t bytes[1] = {nbr.size() * 4};
         void *dst[1];
-        DevBlob blob;
-        if (upload(&blob, src, bytes, 1, dst) != NBB_OK) return nullptr;
-        it = F->mat_nbrs.emplace(m, blob).first;
+        it = F->mat_nbrs.emplace(m, DevBlob()).first;
+        if (upload(&it->second, src, bytes, 1, dst) != NBB_OK) {
+            F->mat_nbrs.erase(it);
+            return nullptr;
+        }
     }
     return static_cast<const uint32_t *>(it->second.ptr);
 }
@@ -736,22 +759,15 @@ const char *nbb_status_string(nbb_status s) {
 }
 
 nbb_status nbb_plan_build(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r,
-                          uint32_t tile_level, nbb_plan **out, nbb_plan_view *view) {
+                          uint32_t tile_level, nbb_plan **out, nbb_plan_view *view) try {
     if (!out || !view) return fail(NBB_E_INVALID, "out and view must not be NULL");
     *out = nullptr;
-    nbb_plan *p = new (std::nothrow) nbb_plan;
-    if (!p) return fail(NBB_E_NOMEM, "host allocation failed");
+    std::unique_ptr<nbb_plan> p(new nbb_plan);
     std::string msg;
     int v = validate_fractal(k, s, offsets, r, &p->f, &msg);
-    if (v) {
-        delete p;
-        return fail(v == 2 ? NBB_E_RANGE : NBB_E_INVALID, msg);
-    }
+    if (v) return fail(v == 2 ? NBB_E_RANGE : NBB_E_INVALID, msg);
     uint32_t m = tile_level ? tile_level : auto_tile_level(p->f);
-    if (!build_tile_plan(p->f, m, &p->tile, &msg)) {
-        delete p;
-        return fail(NBB_E_INVALID, msg);
-    }
+    if (!build_tile_plan(p->f, m, &p->tile, &msg)) return fail(NBB_E_INVALID, msg);
     const TilePlan &t = p->tile;
     view->tile_level = t.m;
     view->tile_side = t.S;
@@ -784,29 +800,24 @@ nbb_status nbb_plan_build(uint32_t k, uint32_t s, const int32_t *offsets, uint32
     }
     view->edge_blk = e.blk.data();
     view->edge_halo = e.halo.data();
-    *out = p;
+    *out = p.release();
     return NBB_OK;
 }
+NBB_CATCH
 
 void nbb_plan_free(nbb_plan *p) { delete p; }
 
 nbb_status nbb_temporal_plan_build(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r, uint32_t tile_level,
                                    uint32_t depth, uint32_t lds_limit, nbb_temporal_plan **out,
-                                   nbb_temporal_view *view) {
+                                   nbb_temporal_view *view) try {
     if (!out || !view) return fail(NBB_E_INVALID, "null argument");
     *out = nullptr;
-    auto *p = new (std::nothrow) nbb_temporal_plan;
-    if (!p) return fail(NBB_E_NOMEM, "host allocation failed");
+    std::unique_ptr<nbb_temporal_plan> p(new nbb_temporal_plan);
     std::string msg;
     int v = validate_fractal(k, s, offsets, r, &p->f, &msg);
-    if (v) {
-        delete p;
-        return fail(v == 2 ? NBB_E_RANGE : NBB_E_INVALID, msg);
-    }
-    if (!build_temporal_plan(p->f, tile_level, depth, lds_limit ? lds_limit : 163840u, &p->plan, &msg)) {
-        delete p;
+    if (v) return fail(v == 2 ? NBB_E_RANGE : NBB_E_INVALID, msg);
+    if (!build_temporal_plan(p->f, tile_level, depth, lds_limit ? lds_limit : 163840u, &p->plan, &msg))
         return fail(NBB_E_INVALID, msg);
-    }
     const TemporalPlan &t = p->plan;
     std::memset(view, 0, sizeof(*view));
     view->tile_level = t.m;
@@ -821,26 +832,23 @@ nbb_status nbb_temporal_plan_build(uint32_t k, uint32_t s, const int32_t *offset
     view->self = t.self.data();
     view->halo = t.halo.data();
     view->nbr = t.nbr.data();
-    *out = p;
+    *out = p.release();
     return NBB_OK;
 }
+NBB_CATCH
 
 void nbb_temporal_plan_free(nbb_temporal_plan *p) { delete p; }
 
-nbb_status nbb_create(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r, nbb_fractal **out) {
+nbb_status nbb_create(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r, nbb_fractal **out) try {
     if (!out) return fail(NBB_E_INVALID, "out is NULL");
     *out = nullptr;
-    nbb_fractal *F = new (std::nothrow) nbb_fractal;
-    if (!F) return fail(NBB_E_NOMEM, "host allocation failed");
+    std::unique_ptr<nbb_fractal, void (*)(nbb_fractal *)> own(new nbb_fractal, nbb_destroy);
+    nbb_fractal *F = own.get();
     std::string msg;
     int v = validate_fractal(k, s, offsets, r, &F->f, &msg);
-    if (v) {
-        delete F;
-        return fail(v == 2 ? NBB_E_RANGE : NBB_E_INVALID, msg);
-    }
+    if (v) return fail(v == 2 ? NBB_E_RANGE : NBB_E_INVALID, msg);
     hipError_t e = hipGetDevice(&F->device);
     if (e != hipSuccess) {
-        delete F;
         (void)hipGetLastError();
         return hip_fail(e, "hipGetDevice");
     }
@@ -858,24 +866,19 @@ nbb_status nbb_create(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r
             if (build_tile_plan(F->f, auto_tile_level(F->f), &F->tile, &msg)) {
                 st = upload_tile(F, F->tile, &F->dtile, &F->tp);
                 if (st == NBB_OK) F->strategy = NBB_STRATEGY_TILED;
-                if (st == NBB_OK) st = setup_matrix(F);
+                if (st == NBB_OK) {
+                    st = setup_matrix(F);
+                    if (st == NBB_E_NOMEM) st = NBB_OK;  // without its tables the vector form takes the steps
+                }
                 if (st == NBB_OK) st = setup_edges(F);
             }
         }
     }
-    if (st != NBB_OK) {
-        blob_free(&F->dmap);
-        blob_free(&F->dbox);
-        blob_free(&F->dtile);
-        blob_free(&F->dedge);
-        blob_free(&F->dmat);
-        blob_free(&F->dmfma);
-        delete F;
-        return st;
-    }
-    *out = F;
+    if (st != NBB_OK) return st;
+    *out = own.release();
     return NBB_OK;
 }
+NBB_CATCH
 
 void nbb_destroy(nbb_fractal *F) {
     if (!F) return;
@@ -935,7 +938,7 @@ nbb_status nbb_query(const nbb_fractal *F, nbb_info *info) {
     return NBB_OK;
 }
 
-nbb_status nbb_configure(nbb_fractal *F, uint32_t strategy, uint32_t tile_level) {
+nbb_status nbb_configure(nbb_fractal *F, uint32_t strategy, uint32_t tile_level) try {
     if (!F) return fail(NBB_E_INVALID, "null descriptor");
     nbb_status st = check_device(F);
     if (st != NBB_OK) return st;
@@ -986,9 +989,23 @@ nbb_status nbb_configure(nbb_fractal *F, uint32_t strategy, uint32_t tile_level)
     }
     return setup_edges(F, strategy == NBB_STRATEGY_TILED_EDGE);
 }
+NBB_CATCH
 
 // Most LDS one work-group may take on the current device.
 static uint32_t device_lds_per_group();
+
+// A pair of events to time launches between.
+struct TimingEvents {
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    hipError_t create() {
+        hipError_t e = hipEventCreate(&e0);
+        return e == hipSuccess ? hipEventCreate(&e1) : e;
+    }
+    ~TimingEvents() {
+        if (e0) (void)hipEventDestroy(e0);
+        if (e1) (void)hipEventDestroy(e1);
+    }
+};
 
 // Automatic temporal plan: over the tile levels of side S <= 81 with ring
 // depth h = min(16, S), the one with the least estimated time per generation
@@ -1029,7 +1046,7 @@ static void auto_temporal(const Fractal &f, uint32_t cu_count, uint32_t *m, uint
     }
 }
 
-nbb_status nbb_configure_temporal(nbb_fractal *F, uint32_t tile_level, uint32_t depth) {
+nbb_status nbb_configure_temporal(nbb_fractal *F, uint32_t tile_level, uint32_t depth) try {
     if (!F) return fail(NBB_E_INVALID, "null descriptor");
     nbb_status st = check_device(F);
     if (st != NBB_OK) return st;
@@ -1052,9 +1069,10 @@ nbb_status nbb_configure_temporal(nbb_fractal *F, uint32_t tile_level, uint32_t 
     F->strategy = NBB_STRATEGY_TEMPORAL;
     return NBB_OK;
 }
+NBB_CATCH
 
 nbb_status nbb_autotune(nbb_fractal *F, uint8_t *a, uint8_t *b, uint64_t len, uint32_t steps, uint32_t rule,
-                        void *stream, nbb_info *info) {
+                        void *stream, nbb_info *info) try {
     if (!F || !a || !b) return fail(NBB_E_INVALID, "null argument");
     if (steps == 0) return fail(NBB_E_INVALID, "steps must be >= 1");
     if (len != F->f.cells) return fail(NBB_E_INVALID, "len must equal k^r");
@@ -1106,13 +1124,10 @@ nbb_status nbb_autotune(nbb_fractal *F, uint8_t *a, uint8_t *b, uint64_t len, ui
     }
     cand.push_back({NBB_STRATEGY_DIRECT, 0, 0});
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    hipError_t e = hipEventCreate(&e0);
-    if (e == hipSuccess) e = hipEventCreate(&e1);
-    if (e != hipSuccess) {
-        if (e0) (void)hipEventDestroy(e0);
-        return hip_fail(e, "hipEventCreate");
-    }
+    TimingEvents ev;
+    hipError_t e = ev.create();
+    if (e != hipSuccess) return hip_fail(e, "hipEventCreate");
+    const hipEvent_t e0 = ev.e0, e1 = ev.e1;
     float best_ms = -1.0f;
     Cand best{0, 0, 0};
     auto apply = [&](const Cand &c) {
@@ -1134,14 +1149,13 @@ nbb_status nbb_autotune(nbb_fractal *F, uint8_t *a, uint8_t *b, uint64_t len, ui
             best = c;
         }
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     if (st != NBB_OK) return st;
     if (best_ms < 0.0f) return fail(NBB_E_INVALID, "no strategy could be configured");
     st = apply(best);
     if (st == NBB_OK && info) st = nbb_query(F, info);
     return st;
 }
+NBB_CATCH
 
 nbb_status nbb_batch_create(const nbb_fractal *const *fractals, const uint64_t *offsets, uint32_t count,
                             void *stream, nbb_batch **out) {
@@ -1236,6 +1250,10 @@ static void batch_free(nbb_batch *B) {
     blob_free(&B->dtab);
     delete B;
 }
+struct BatchFree {
+    void operator()(nbb_batch *B) const { batch_free(B); }
+};
+using BatchOwner = std::unique_ptr<nbb_batch, BatchFree>;
 
 // Builds a batch.  Its device tables go to one fresh allocation, or, when
 // `fixed` is given, to those `fixed_cap` bytes (no allocation: the instance
@@ -1266,15 +1284,14 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
     std::vector<uint32_t> order(count);
     std::iota(order.begin(), order.end(), 0u);
     std::sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return offsets[x] < offsets[y]; });
-    nbb_batch *B = new (std::nothrow) nbb_batch;
-    if (!B) return fail(NBB_E_NOMEM, "host allocation failed");
+    BatchOwner own(new nbb_batch);
+    nbb_batch *B = own.get();
     B->device = dev;
     B->count = count;
     for (uint32_t j = 0; j < count; ++j) {
         const uint32_t i = order[j];
         const uint64_t end = offsets[i] + fractals[i]->f.cells;
         if (j + 1 < count && end > offsets[order[j + 1]]) {
-            delete B;
             return fail(NBB_E_INVALID, "instance ranges overlap");
         }
         B->cells += fractals[i]->f.cells;
@@ -1502,7 +1519,6 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             t += I.ntiles;
         }
         if (t * 8 > (uint64_t(1) << 31)) {
-            delete B;
             return fail(NBB_E_RANGE, "too many tiles in one group of the batch");
         }
         ntiles[g] = t;
@@ -1546,7 +1562,6 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
     const size_t off_rsteps = total;
     total += nres ? align256(nres * sizeof(uint32_t)) : 0;
     if (fixed && total > fixed_cap) {
-        delete B;
         return fail(NBB_E_RANGE, "batch tables (" + std::to_string(total) + " bytes) exceed the " +
                                      std::to_string(fixed_cap) + "-byte no-allocation scratch");
     }
@@ -1554,7 +1569,6 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         e = hipMalloc(&B->dtab.ptr, total);
         if (e != hipSuccess) {
             (void)hipGetLastError();
-            delete B;
             return e == hipErrorOutOfMemory ? fail(NBB_E_NOMEM, "batch table allocation failed")
                                             : hip_fail(e, "hipMalloc");
         }
@@ -1593,7 +1607,6 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         HeldSet S;
         e = make_held(H, &S);
         if (e != hipSuccess) {
-            batch_free(B);
             return hip_fail(e, "batch table build");
         }
         S.whole = true;
@@ -1612,7 +1625,6 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             if (e == hipSuccess)
                 e = launch_batch_tiles_matrix(minst, uint32_t(mem.size()), uint32_t(ntiles[g]), rec, nbr, s);
             if (e != hipSuccess) {
-                batch_free(B);
                 return hip_fail(e, "batch table build");
             }
             BatchGroup G;
@@ -1631,7 +1643,6 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             for (const MatInstance &I : mem) G.tiles_end.push_back(uint64_t(I.tile0) + I.ntiles);
             e = make_held(held[g], &G.held);
             if (e != hipSuccess) {
-                batch_free(B);
                 return hip_fail(e, "batch table build");
             }
             B->groups.push_back(std::move(G));
@@ -1651,7 +1662,6 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         if (e == hipSuccess)
             e = launch_batch_tiles(inst, uint32_t(launch.members[g].size()), uint32_t(ntiles[g]), rec, nbr, s);
         if (e != hipSuccess) {
-            batch_free(B);
             return hip_fail(e, "batch table build");
         }
         BatchGroup G;
@@ -1707,7 +1717,6 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             e = hipMemcpyAsync(dinst, rinst.data(), rinst.size() * sizeof(ResidentInstance), hipMemcpyHostToDevice, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host tables go out of scope
         if (e != hipSuccess) {
-            batch_free(B);
             return hip_fail(e, "batch table build");
         }
         R.plans = dplans;
@@ -1722,12 +1731,13 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         if (e == hipSuccess) e = hipEventCreateWithFlags(&B->join, hipEventDisableTiming);
         if (e != hipSuccess) {
             B->side = nullptr;
-            batch_free(B);
             return hip_fail(e, "batch stream");
         }
     }
     if (!fixed && B->groups.size() + B->small.size() > 1) {
         const size_t ns = std::min<size_t>(B->groups.size() + B->small.size() - 1, kGroupStreams);
+        B->gstream.reserve(ns);
+        B->gjoin.reserve(ns);
         e = hipEventCreateWithFlags(&B->gfork, hipEventDisableTiming);
         for (size_t i = 0; i < ns && e == hipSuccess; ++i) {
             hipStream_t gs = nullptr;
@@ -1740,18 +1750,18 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             }
         }
         if (e != hipSuccess) {
-            batch_free(B);
             return hip_fail(e, "batch group streams");
         }
     }
-    *out = B;
+    *out = own.release();
     return NBB_OK;
 }
 
 nbb_status nbb_batch_create_ex(const nbb_fractal *const *fractals, const uint64_t *offsets, uint32_t count,
-                               uint32_t flags, void *stream, nbb_batch **out) {
+                               uint32_t flags, void *stream, nbb_batch **out) try {
     return batch_create(fractals, offsets, count, flags, stream, nullptr, 0, out);
 }
+NBB_CATCH
 
 void nbb_batch_destroy(nbb_batch *B) {
     if (B) batch_free(B);
@@ -1841,14 +1851,11 @@ static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t a
         return S.whole ? held_launches(n, h, false) : (n ? held_launches(n - 1, h, true) : 0u);
     };
     uint32_t L = 0, most = steps;
-    std::vector<uint32_t> n;
     if (counts) {
         most = 0;
-        n.resize(S.index.size());
-        for (size_t j = 0; j < n.size(); ++j) {
-            n[j] = counts[S.index[j]];
-            most = std::max(most, n[j]);
-            L = std::max(L, launches(n[j]));
+        for (uint32_t i : S.index) {
+            most = std::max(most, counts[i]);
+            L = std::max(L, launches(counts[i]));
         }
     } else {
         L = launches(steps);
@@ -1866,7 +1873,7 @@ static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t a
     for (uint32_t i = 0; i < L; ++i) {
         HoldParams E = S.hp;
         if (counts) {  // (an instance before the last live one may be done too: its tiles end at once)
-            while (live && launches(n[live - 1]) <= i) --live;
+            while (live && launches(counts[S.index[live - 1]]) <= i) --live;
             if (!live) break;
             E.ntiles = uint32_t(S.tiles_end[live - 1]);
         }
@@ -1904,7 +1911,7 @@ static hipError_t batch_join_groups(const nbb_batch *B, hipStream_t s) {
 }
 
 nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t arena_len, uint32_t steps,
-                          uint32_t rule, int *result_in_b, void *stream) {
+                          uint32_t rule, int *result_in_b, void *stream) try {
     if (!B) return fail(NBB_E_INVALID, "null batch");
     if (B->count && (!a || !b)) return fail(NBB_E_INVALID, "null arena");
     if (arena_len < B->arena_bytes) return fail(NBB_E_INVALID, "arena shorter than the batch needs");
@@ -1961,9 +1968,10 @@ nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t a
     e = batch_join_resident(B, s, res_launched);
     return e == hipSuccess ? NBB_OK : hip_fail(e, "batch resident join");
 }
+NBB_CATCH
 
 nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t arena_len,
-                               const uint32_t *steps, uint32_t rule, void *stream) {
+                               const uint32_t *steps, uint32_t rule, void *stream) try {
     if (!B) return fail(NBB_E_INVALID, "null batch");
     if (B->count && (!a || !b || !steps)) return fail(NBB_E_INVALID, "null argument");
     if (arena_len < B->arena_bytes) return fail(NBB_E_INVALID, "arena shorter than the batch needs");
@@ -1986,17 +1994,20 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
     // than g steps; instance i's state alternates a -> b -> a ... like the
     // whole batch's, so its result ends in b iff steps[i] is odd.
     hipStream_t s = static_cast<hipStream_t>(stream);
-    bool res_launched = false;
-    e = batch_fork_resident(B, a, b, rule, steps, 0, s, &res_launched);
-    if (e != hipSuccess) return hip_fail(e, "batch resident step launch");
+    std::vector<uint32_t> n;  // (before the forks: an allocation that fails must not skip the joins)
     if (B->counts) {
-        std::vector<uint32_t> n;
         for (const BatchGroup &G : B->groups)
             for (uint32_t i : G.held.index) n.push_back(steps[i]);
         for (const HeldSet &S : B->small)
             for (uint32_t i : S.index) n.push_back(steps[i]);
-        e = launch_set_words(B->counts, n.data(), uint32_t(n.size()), s);
-        if (e != hipSuccess) return hip_fail(e, "batch step counts");
+    }
+    bool res_launched = false;
+    e = batch_fork_resident(B, a, b, rule, steps, 0, s, &res_launched);
+    if (e != hipSuccess) return hip_fail(e, "batch resident step launch");
+    if (B->counts) e = launch_set_words(B->counts, n.data(), uint32_t(n.size()), s);
+    if (e != hipSuccess) {
+        (void)batch_join_resident(B, s, res_launched);
+        return hip_fail(e, "batch step counts");
     }
     e = batch_fork_groups(B, s);
     if (e != hipSuccess) return hip_fail(e, "batch group fork");
@@ -2047,6 +2058,7 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
     if (e != hipSuccess) return hip_fail(e, "batch resident join");
     return NBB_OK;
 }
+NBB_CATCH
 
 // ---- tile plans of a batch chosen by measurement ----------------------------
 // Results kept for the process: (device, k, s, offsets, smallest and largest
@@ -2056,7 +2068,7 @@ static std::map<std::vector<uint32_t>, std::pair<uint32_t, uint32_t>> g_tune_cac
 
 nbb_status nbb_batch_autotune(nbb_fractal *const *fractals, const uint64_t *offsets, uint32_t count, uint8_t *a,
                               uint8_t *b, uint64_t arena_len, uint32_t steps, uint32_t rule, uint32_t flags,
-                              void *stream) {
+                              void *stream) try {
     if (count && (!fractals || !offsets || !a || !b)) return fail(NBB_E_INVALID, "null argument");
     if (steps == 0) return fail(NBB_E_INVALID, "steps must be >= 1");
     if (flags & ~uint32_t(NBB_TUNE_NO_CACHE)) return fail(NBB_E_INVALID, "unknown flag bits");
@@ -2084,13 +2096,10 @@ nbb_status nbb_batch_autotune(nbb_fractal *const *fractals, const uint64_t *offs
         sets[g].push_back(i);
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    e = hipEventCreate(&e0);
-    if (e == hipSuccess) e = hipEventCreate(&e1);
-    if (e != hipSuccess) {
-        if (e0) (void)hipEventDestroy(e0);
-        return hip_fail(e, "hipEventCreate");
-    }
+    TimingEvents ev;
+    e = ev.create();
+    if (e != hipSuccess) return hip_fail(e, "hipEventCreate");
+    const hipEvent_t e0 = ev.e0, e1 = ev.e1;
     nbb_status st = NBB_OK;
     for (const std::vector<uint32_t> &set : sets) {
         std::vector<nbb_fractal *> desc;  // distinct descriptors of the set
@@ -2149,6 +2158,7 @@ nbb_status nbb_batch_autotune(nbb_fractal *const *fractals, const uint64_t *offs
                     st = batch_create(inst.data(), offs.data(), uint32_t(inst.size()), NBB_BATCH_NO_RESIDENT,
                                       stream, nullptr, 0, &B);
                     if (st != NBB_OK) break;
+                    BatchOwner own(B);
                     float ms = 0.0f;
                     st = nbb_batch_step(B, a, b, arena_len, 1, rule, nullptr, stream);
                     if (st == NBB_OK && (e = hipEventRecord(e0, s)) != hipSuccess) st = hip_fail(e, "hipEventRecord");
@@ -2158,7 +2168,6 @@ nbb_status nbb_batch_autotune(nbb_fractal *const *fractals, const uint64_t *offs
                         st = hip_fail(e, "hipEventSynchronize");
                     if (st == NBB_OK && (e = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess)
                         st = hip_fail(e, "hipEventElapsedTime");
-                    batch_free(B);
                     if (st != NBB_OK) break;
                     if (best_ms < 0.0f || ms < best_ms) {
                         best_ms = ms;
@@ -2174,10 +2183,9 @@ nbb_status nbb_batch_autotune(nbb_fractal *const *fractals, const uint64_t *offs
         st = configure_all(best.first, best.second);
         if (st != NBB_OK) break;
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     return st;
 }
+NBB_CATCH
 
 // ---- the batched step without allocation ---------------------------------
 // The batch tables of nbb_batch_step_each_noalloc live in this array, one
@@ -2207,7 +2215,7 @@ static nbb_status scratch_address(int dev, uint8_t **out) {
 
 nbb_status nbb_batch_step_each_noalloc(const nbb_fractal *const *fractals, const uint64_t *offsets, uint32_t count,
                                        uint8_t *a, uint8_t *b, uint64_t arena_len, const uint32_t *steps,
-                                       uint32_t rule, void *stream) {
+                                       uint32_t rule, void *stream) try {
     // the arena checks of nbb_batch_step_each, before any table is enqueued
     if (count && (!fractals || !offsets || !steps || !a || !b)) return fail(NBB_E_INVALID, "null argument");
     if (!aligned16(a) || !aligned16(b)) return fail(NBB_E_INVALID, "arenas must be 16-byte aligned");
@@ -2230,10 +2238,10 @@ nbb_status nbb_batch_step_each_noalloc(const nbb_fractal *const *fractals, const
     st = batch_create(fractals, offsets, count, NBB_BATCH_NO_RESIDENT, stream, tables, NBB_NOALLOC_SCRATCH_BYTES,
                       &B);
     if (st != NBB_OK) return st;
-    st = nbb_batch_step_each(B, a, b, arena_len, steps, rule, stream);
-    batch_free(B);  // host bookkeeping only: B owns no device memory
-    return st;
+    const BatchOwner own(B);  // host bookkeeping only: B owns no device memory
+    return nbb_batch_step_each(B, a, b, arena_len, steps, rule, stream);
 }
+NBB_CATCH
 
 uint64_t nbb_bbox_pitch(const nbb_fractal *F) { return F ? box_pitch(F->f) : 0; }
 
@@ -2588,7 +2596,7 @@ static nbb_status packed_table(const nbb_fractal *F, const uint16_t **lut, uint3
 }
 
 nbb_status nbb_step_packed(const nbb_fractal *F, uint8_t *a, uint8_t *b, uint64_t len, uint32_t steps,
-                           uint32_t rule, int *result_in_b, void *stream) {
+                           uint32_t rule, int *result_in_b, void *stream) try {
     if (!F || !a || !b) return fail(NBB_E_INVALID, "null argument");
     nbb_status st = check_packed(F, a, len);
     if (st == NBB_OK) st = check_packed(F, b, len);
@@ -2628,6 +2636,7 @@ nbb_status nbb_step_packed(const nbb_fractal *F, uint8_t *a, uint8_t *b, uint64_
     }
     return NBB_OK;
 }
+NBB_CATCH
 
 nbb_status nbb_expand(const nbb_fractal *F, const uint8_t *compact, uint8_t *bbox, uint64_t pitch, uint64_t len,
                       void *stream) {

@@ -2,6 +2,9 @@
 exports what include/nbbfrac.h declares, argument validation, and the tile
 plan tables against the oracle."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -9,6 +12,8 @@ import pytest
 from oracle import oracle as O
 from paper_2110_12952_amd import nbbfrac as N
 from paper_2110_12952_amd import workloads as W
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def test_library_exports_every_declared_symbol():
@@ -309,3 +314,27 @@ def test_binding_fails_loudly_without_the_library(tmp_path):
     env = dict(os.environ, NBB_LIBRARY=str(tmp_path / "absent.so"))
     r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "raised" in r.stdout, r.stdout + r.stderr
+
+
+def test_no_exception_crosses_the_interface():
+    # a plan whose neighbour table (512 MB) does not fit the address space:
+    # an error, not the end of the process
+    code = f"""
+import resource, sys
+sys.path.insert(0, {ROOT!r})
+from paper_2110_12952_amd import nbbfrac as N, workloads as W
+N.lib()
+vm = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (vm + (256 << 20), resource.RLIM_INFINITY))
+for build in (lambda: N.plan_tables(3, W.CARPET.offsets, 9, 1),
+              lambda: N.temporal_plan_tables(3, W.CARPET.offsets, 9, 1, 1)):
+    try:
+        build()
+    except N.NbbError as e:
+        print(e.status == N.NBB_E_NOMEM, e)
+print("alive", N.plan_tables(3, W.CARPET.offsets, 4)["tile_level"] > 0)
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    lines = r.stdout.splitlines()
+    assert len(lines) == 3 and all(l.split()[0] == "True" for l in lines[:2]) and lines[2] == "alive True", r.stdout
