@@ -347,7 +347,9 @@ nbb_status nbb_gather(const nbb_fractal *f, const uint8_t *bbox, uint64_t pitch,
  * when steps > 1, TEMPORAL at its automatic plan and at every level of side
  * <= 81 with ring depths 8 and 16; and DIRECT -- on the caller's
  * buffers a and b (their contents are overwritten: pass a copy of a
- * representative state), then configures the fastest, as nbb_configure would.
+ * representative state), then configures the fastest, as nbb_configure would
+ * (the matrix-core form over the fastest of the TILED_EDGE and TILED_BOX
+ * plans).
  * Waits for `stream`.  Arguments as nbb_step_compact (a and b 16-byte
  * aligned, not overlapping); steps >= 1.  If info is
  * not NULL it receives nbb_query's result for the chosen plan.  Must not
@@ -455,10 +457,12 @@ nbb_status nbb_batch_step_each(const nbb_batch *batch, uint8_t *a, uint8_t *b, u
  * for each group every candidate plan that all its descriptors accept - the
  * tile levels up to the group's smallest r whose tiles hold at least 64
  * cells (and the largest level), each in the edge-record and in the
- * byte-scatter form - is timed on a batch of exactly the group's instances
+ * byte-scatter form, and once the matrix-core form, which has levels of its
+ * own - is timed on a batch of exactly the group's instances
  * (group launches, none in LDS) for `steps` generations after one warm-up
- * generation, and every descriptor of the group is configured to the
- * fastest.  Results are kept for the process, keyed by device, fractal, the
+ * generation.  Every descriptor of the group is configured to the fastest
+ * vector plan (what nbb_batch_step_each_noalloc and the blocked layout take)
+ * and steps in the matrix-core form if that was faster still.  Results are kept for the process, keyed by device, fractal, the
  * group's smallest and largest r and the rule's form (B3/S23, table rule,
  * any rule), and reused without timing unless flags has NBB_TUNE_NO_CACHE.
  * The states in a and b are stepped (their values are then unspecified);

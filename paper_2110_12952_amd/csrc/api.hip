@@ -1128,8 +1128,8 @@ nbb_status nbb_autotune(nbb_fractal *F, uint8_t *a, uint8_t *b, uint64_t len, ui
     hipError_t e = ev.create();
     if (e != hipSuccess) return hip_fail(e, "hipEventCreate");
     const hipEvent_t e0 = ev.e0, e1 = ev.e1;
-    float best_ms = -1.0f;
-    Cand best{0, 0, 0};
+    float best_ms = -1.0f, plan_ms = -1.0f;
+    Cand best{0, 0, 0}, plan{0, 0, 0};  // plan: the fastest tile plan of the vector forms
     auto apply = [&](const Cand &c) {
         return c.strategy == NBB_STRATEGY_TEMPORAL ? nbb_configure_temporal(F, c.level, c.depth)
                                                    : nbb_configure(F, c.strategy, c.level);
@@ -1148,10 +1148,21 @@ nbb_status nbb_autotune(nbb_fractal *F, uint8_t *a, uint8_t *b, uint64_t len, ui
             best_ms = ms;
             best = c;
         }
+        if ((c.strategy == NBB_STRATEGY_TILED_EDGE || c.strategy == NBB_STRATEGY_TILED_BOX) &&
+            (plan_ms < 0.0f || ms < plan_ms)) {
+            plan_ms = ms;
+            plan = c;
+        }
     }
     if (st != NBB_OK) return st;
     if (best_ms < 0.0f) return fail(NBB_E_INVALID, "no strategy could be configured");
-    st = apply(best);
+    if (best.strategy == NBB_STRATEGY_TILED && plan_ms >= 0.0f) {
+        // the matrix form, over the tile plan for what takes that
+        st = apply(plan);
+        F->use_matrix = st == NBB_OK;
+    } else {
+        st = apply(best);
+    }
     if (st == NBB_OK && info) st = nbb_query(F, info);
     return st;
 }
@@ -2062,9 +2073,14 @@ NBB_CATCH
 
 // ---- tile plans of a batch chosen by measurement ----------------------------
 // Results kept for the process: (device, k, s, offsets, smallest and largest
-// r of the set, rule form) -> (strategy, tile level).
+// r of the set, rule form) -> the fastest tile plan of the vector forms, and
+// whether the matrix form is faster than it.
+struct TunedPlan {
+    uint32_t strategy, level;
+    bool matrix;
+};
 static std::mutex g_tune_mu;
-static std::map<std::vector<uint32_t>, std::pair<uint32_t, uint32_t>> g_tune_cache;
+static std::map<std::vector<uint32_t>, TunedPlan> g_tune_cache;
 
 nbb_status nbb_batch_autotune(nbb_fractal *const *fractals, const uint64_t *offsets, uint32_t count, uint8_t *a,
                               uint8_t *b, uint64_t arena_len, uint32_t steps, uint32_t rule, uint32_t flags,
@@ -2123,8 +2139,9 @@ nbb_status nbb_batch_autotune(nbb_fractal *const *fractals, const uint64_t *offs
             }
             return NBB_OK;
         };
-        std::pair<uint32_t, uint32_t> best{0, 0};
-        bool cached = false;
+        TunedPlan best{0, 0, false};
+        bool cached = false, all_matrix = true;
+        for (const nbb_fractal *F : desc) all_matrix = all_matrix && F->mat.ok;
         if (!(flags & NBB_TUNE_NO_CACHE)) {
             std::lock_guard<std::mutex> lock(g_tune_mu);
             auto it = g_tune_cache.find(key);
@@ -2143,17 +2160,16 @@ nbb_status nbb_batch_autotune(nbb_fractal *const *fractals, const uint64_t *offs
                 offs.push_back(offsets[i]);
                 inst.push_back(fractals[i]);
             }
-            float best_ms = -1.0f;
+            float best_ms = -1.0f, matrix_ms = -1.0f;
             uint64_t K = 1;
-            bool matrix_timed = false;
             for (uint32_t m = 1; m <= rmin && st == NBB_OK; ++m) {
                 K *= f0.k;
                 if (K < 64 && m < rmin) continue;
                 for (uint32_t strategy : {NBB_STRATEGY_TILED, NBB_STRATEGY_TILED_EDGE, NBB_STRATEGY_TILED_BOX}) {
                     // (the matrix form has a level of its own: timed once)
-                    if (strategy == NBB_STRATEGY_TILED && (matrix_timed || !desc[0]->mat.ok)) continue;
+                    const bool matrix = strategy == NBB_STRATEGY_TILED;
+                    if (matrix && (matrix_ms >= 0.0f || !all_matrix)) continue;
                     if (configure_all(strategy, m) != NBB_OK) continue;  // does not fit: skip it
-                    matrix_timed = matrix_timed || strategy == NBB_STRATEGY_TILED;
                     nbb_batch *B = nullptr;
                     st = batch_create(inst.data(), offs.data(), uint32_t(inst.size()), NBB_BATCH_NO_RESIDENT,
                                       stream, nullptr, 0, &B);
@@ -2169,19 +2185,25 @@ nbb_status nbb_batch_autotune(nbb_fractal *const *fractals, const uint64_t *offs
                     if (st == NBB_OK && (e = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess)
                         st = hip_fail(e, "hipEventElapsedTime");
                     if (st != NBB_OK) break;
-                    if (best_ms < 0.0f || ms < best_ms) {
+                    if (matrix) {
+                        matrix_ms = ms;
+                    } else if (best_ms < 0.0f || ms < best_ms) {
                         best_ms = ms;
-                        best = {strategy, m};
+                        best = {strategy, m, false};
                     }
                 }
             }
             if (st != NBB_OK) break;
             if (best_ms < 0.0f) continue;  // nothing fits: the descriptors keep what they had
+            best.matrix = matrix_ms >= 0.0f && matrix_ms < best_ms;
             std::lock_guard<std::mutex> lock(g_tune_mu);
             g_tune_cache[key] = best;
         }
-        st = configure_all(best.first, best.second);
+        // also where the matrix form takes the steps: the batch without
+        // allocation runs the vector forms, with tables as large as its tiles
+        st = configure_all(best.strategy, best.level);
         if (st != NBB_OK) break;
+        for (nbb_fractal *F : desc) F->use_matrix = best.matrix && F->mat.ok;
     }
     return st;
 }

@@ -166,6 +166,34 @@ def test_noalloc_refuses_tables_beyond_the_array(N):
         assert torch.equal(b[o:o + f.cells], rb[o:o + f.cells])
 
 
+def test_noalloc_after_batch_autotune(N):
+    # the plans that the batch autotuner leaves must serve this call too: at
+    # its smallest candidate tiles (81 cells) the tables of eight instances
+    # would need more than the array, at those of the fastest vector plan 1 MB
+    fd = W.TRIANGLE
+    frs = [N.Fractal(fd.s, fd.offsets, r) for r in (14, 14, 14, 14, 14, 14, 14, 14, 11)]
+    offsets, length = N.pack_offsets([f.cells for f in frs])
+    assert 8 * 3 ** (14 - 4) * 40 > N.NOALLOC_SCRATCH_BYTES
+    a = torch.zeros(length, dtype=torch.uint8, device="cuda")
+    b = torch.zeros_like(a)
+    for i, f in enumerate(frs):
+        f.init_compact(i, 0.4, out=a[offsets[i]:offsets[i] + f.cells])
+    init = a.clone()
+    N.batch_autotune(frs, offsets, a, b, steps=3, use_cache=False)
+    assert len({(f.info().tile_level, f.info().tiled_form) for f in frs}) == 1
+    steps = [5] * 8 + [4]
+    ref_a, ref_b = init.clone(), torch.zeros_like(b)
+    N.Batch(frs, offsets, resident=False).step_each(ref_a, ref_b, steps)
+    a.copy_(init)
+    N.batch_step_each_noalloc(frs, offsets, a, b, steps)
+    torch.cuda.synchronize()
+    for f, o, t in zip(frs, offsets, steps):
+        assert torch.equal((b if t & 1 else a)[o:o + f.cells], (ref_b if t & 1 else ref_a)[o:o + f.cells])
+    o = O.Fractal(fd.s, fd.offsets, 11)
+    np.testing.assert_array_equal(a[offsets[8]:offsets[8] + o.cells].cpu().numpy(),
+                                  o.compact_steps(init[offsets[8]:offsets[8] + o.cells].cpu().numpy(), B3S23, 4))
+
+
 def test_noalloc_argument_errors(N):
     fd = W.CARPET
     f = N.Fractal(fd.s, fd.offsets, 3)
