@@ -28,7 +28,9 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E, published
 STRATEGY_NAMES = {1: "tiled", 2: "direct", 3: "tiled_wave", 5: "temporal"}
-FORM_NAMES = {0: None, 1: "edge_records", 2: "byte_scatter", 3: "temporal"}
+FORM_NAMES = {0: "direct", 1: "edge_records", 2: "byte_scatter", 3: "temporal", 4: "matrix"}
+# the kernel of a call of one generation
+FORM_KERNELS = {0: "k_step_direct", 1: "k_step_edges", 2: "k_step_tiled", 3: "k_step_temporal", 4: "k_step_matrix"}
 COUNTERS = os.path.join(ROOT, "profiles", "compact_step_triangle_r16_counters.txt")
 CSRC = os.path.join(ROOT, "paper_2110_12952_amd", "csrc")
 # the device code of the step kernels: a counter summary taken on other sources is stale
@@ -62,6 +64,18 @@ def warm_up(torch, run, steps, min_ms):
         torch.cuda.synchronize()
         done += chunk
     return done
+
+
+def step_form(g):
+    """The form that calls of g's compact step run in, its tiles and, where
+    there are launches of several generations, theirs."""
+    s = g.step_info()
+    out = {"form": FORM_NAMES[s.form], "tile_level": int(s.tile_level), "tiles": int(s.tiles),
+           "lds_bytes": int(s.lds_bytes)}
+    if s.held_generations:
+        out["held"] = {"generations_per_launch": int(s.held_generations), "tile_level": int(s.held_level),
+                       "tiles": int(s.held_tiles), "lds_bytes": int(s.held_lds_bytes)}
+    return out
 
 
 def time_events(torch, fn, reps=1):
@@ -182,13 +196,13 @@ def small_case(torch, N, W, rule):
     # several generations per launch (temporal blocking), automatic plan
     gt = N.Fractal(fd.s, fd.offsets, wl.r)
     gt.configure_temporal(0, 0)
-    tinf = gt.info()
+    tinf = gt.step_info()
+    launch_gens = int(tinf.held_generations)
     ta, tb = a0.clone(), torch.empty_like(a0)
     gt.step_compact(ta.clone(), tb, 2, rule)
     ms_temp, tres = time_events(torch, lambda: gt.step_compact(ta, tb, T, rule))
-    temporal = {"us_per_step": ms_temp / T * 1e3, "tile_level": int(tinf.tile_level),
-                "depth": int(tinf.temporal_depth), "launches": -(-T // int(tinf.temporal_depth)),
-                "equals_tiled": bool(torch.equal(tres, eager))}
+    temporal = {"us_per_step": ms_temp / T * 1e3, "form": FORM_NAMES[tinf.form], "tile_level": int(tinf.held_level),
+                "generations_per_launch": launch_gens, "equals_tiled": bool(torch.equal(tres, eager))}
     # the initial-state kernel on the large triangle (1 byte written per cell)
     big = W.LARGE_TRIANGLE
     gb = N.Fractal(big.fractal.s, big.fractal.offsets, big.r)
@@ -200,8 +214,8 @@ def small_case(torch, N, W, rule):
            "init_triangle_r16_us": ms_init / 10 * 1e3,
            "init_triangle_r16_gbps": gb.cells / (ms_init / 10 * 1e-3) / 1e9}
     log(f"small triangle r10: eager {out['eager_us_per_step']:.2f} us/step, graph "
-        f"{out['graph_us_per_step']:.2f} us/step, same={same}; temporal (m={temporal['tile_level']}, "
-        f"h={temporal['depth']}) {temporal['us_per_step']:.2f} us/step, same={temporal['equals_tiled']}; "
+        f"{out['graph_us_per_step']:.2f} us/step, same={same}; temporal ({temporal['form']}, m={temporal['tile_level']}, "
+        f"up to {launch_gens} per launch) {temporal['us_per_step']:.2f} us/step, same={temporal['equals_tiled']}; "
         f"init r16 {out['init_triangle_r16_us']:.1f} us")
     return out
 
@@ -256,11 +270,14 @@ def batch_run(torch, N, W, args):
     ba = init.clone()
     bres = batch.step(ba, torch.empty_like(ba), Ts, rule)
     same = all(torch.equal(batch.state(bres, i), batch.state(seq_res, i)) for i in range(len(frs)))
+    # the tuned tile plans: of the vector forms, and of the groups
     levels = sorted({(it.fractal.name, f.info().tile_level, STRATEGY_NAMES[f.info().strategy],
                       FORM_NAMES[f.info().tiled_form]) for it, f in zip(items, frs)})
+    forms = batch.step_info()
     out = {"workload": bw.name, "instances": len(items), "cells": int(inf.cells), "groups": int(inf.groups),
            "autotune_s": tune_s,
-           "tiles": int(inf.tiles), "plans": [list(x) for x in levels], "steps": Kb, "ms_per_step": ms_step,
+           "instances_by_form": {n: int(getattr(forms, n)) for n, _ in forms._fields_ if n != "tiles"},
+           "tiles": int(forms.tiles), "tile_plans": [list(x) for x in levels], "steps": Kb, "ms_per_step": ms_step,
            "cell_updates_per_s": inf.cells * Kb / (ms * 1e-3),
            "alg_gbps": 2 * inf.cells / (ms_step * 1e-3) / 1e9,
            "sequential_ms_per_step": ms_seq / Ts, "sequential_steps": Ts,
@@ -344,7 +361,7 @@ def large_case(torch, N, W, name, rule, steps, warm_ms=50.0):
     warm_up(torch, lambda n: g.step_compact(a.clone(), b, n, rule), 2, warm_ms)
     ms, res = time_events(torch, lambda: g.step_compact(a, b, steps, rule))
     alg = 2 * g.cells
-    out = {"cells": g.cells, "n": g.n, "steps": steps, "tile_level": g.info().tile_level,
+    out = {"cells": g.cells, "n": g.n, "steps": steps, "step": step_form(g),
            "ms_per_step": ms / steps, "cell_updates_per_s": g.cells * steps / (ms * 1e-3),
            "alg_gbps": alg / (ms / steps * 1e-3) / 1e9}
     out["roofline_frac"] = out["alg_gbps"] / HBM_PEAK_GBPS
@@ -424,7 +441,8 @@ def main():
     info = g.info()
     rule = W.rule_mask(wl.rule)
     K, Wu = args.steps, args.warmup
-    log(f"{wl.name}: n={g.n} cells={g.cells} strategy={info.strategy} tile_level={info.tile_level}")
+    form = step_form(g)
+    log(f"{wl.name}: n={g.n} cells={g.cells} strategy={info.strategy} {form}")
 
     if args.copy_probe_mib:
         src = torch.zeros(args.copy_probe_mib << 20, dtype=torch.uint8, device="cuda")
@@ -486,7 +504,7 @@ def main():
             f"mean {repeats['mean_us']:.2f} us")
 
     # ---- the same step in the byte-scatter form (the tile scattered into an
-    # LDS box) at the same tile level, for comparison with the edge-record form
+    # LDS box) at the tile plan's level, for comparison with the form that runs
     box_form = None
     if info.strategy == N.STRATEGY_TILED and info.tiled_form == 1:
         Kf = max(100, min(K, 200))
@@ -498,8 +516,8 @@ def main():
         refe = g.step_compact(init.clone(), torch.empty_like(init), Kf, rule)
         box_form = {"us_per_step": msf / Kf * 1e3, "steps": Kf,
                     "alg_gbps": alg_bytes / (msf / Kf * 1e-3) / 1e9,
-                    "equals_edge_form": bool(torch.equal(resf, refe))}
-        log(f"byte-scatter form: {box_form['us_per_step']:.2f} us/step, same: {box_form['equals_edge_form']}")
+                    "equals_default_form": bool(torch.equal(resf, refe))}
+        log(f"byte-scatter form: {box_form['us_per_step']:.2f} us/step, same: {box_form['equals_default_form']}")
         del fa, fb, resf, refe
 
     # ---- the same generations on the bit-packed state (1 bit per cell; a
@@ -622,6 +640,7 @@ def main():
 
     # the committed counter summary covers the triangle r = 16 workload only
     traffic = measured_traffic(alg_bytes) if wl.name == "triangle_r16" else None
+    kernel = {v: FORM_KERNELS[k] for k, v in FORM_NAMES.items()}[form["form"]]
     out = {
         "metric": "compact cell-updates/sec + % HBM roofline vs bbox; batched p50/p99 latency",
         "value": value,
@@ -638,15 +657,11 @@ def main():
         "data": "synthetic",
         "config": {"workload": wl.name, "fractal": f"F^{{{fd.k},{fd.s}}} {fd.name}", "r": wl.r, "n": g.n,
                    "cells": g.cells, "p": wl.p, "seed": wl.seeds[0], "rule": wl.rule,
-                   "strategy": STRATEGY_NAMES[info.strategy],
-                   "tiled_form": FORM_NAMES[info.tiled_form],
-                   "tile_level": info.tile_level},
+                   "strategy": STRATEGY_NAMES[info.strategy], **form},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBPS, "traffic": traffic,
-                     # calls of one generation (one_generation_per_call); TILED runs the
-                     # matrix-core form on every fractal of the workloads
-                     "kernel": {N.STRATEGY_DIRECT: "k_step_direct", N.STRATEGY_TILED: "k_step_matrix"}.get(
-                         info.strategy, "k_step_tiled"),
+                     # calls of one generation (one_generation_per_call)
+                     "kernel": kernel,
                      "alg_bytes_per_launch": alg_bytes},
         "cpu_baseline": cpu,
         "compact_repeats": repeats,

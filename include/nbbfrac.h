@@ -79,7 +79,7 @@ typedef enum {
  * around a tile allow (both buffers end as with one launch per generation).
  * For other fractals, and for the strategies that name a form, it runs in the
  * form and at the level that nbb_query reports.  Every form gives the same
- * states. */
+ * states.  nbb_query_step tells which one runs. */
 #define NBB_STRATEGY_AUTO 0u   /* TILED when the fractal allows it, else DIRECT */
 #define NBB_STRATEGY_TILED 1u  /* level-m tiles staged in LDS with their halo */
 #define NBB_STRATEGY_DIRECT 2u /* one thread per cell: lambda, 8 x nu, rule */
@@ -109,7 +109,8 @@ typedef struct {
     uint32_t box_low_side;  /* SL */
     uint32_t box_high_side; /* NH (0 when the box is too large to exist) */
     /* The vector form of a tiled strategy (the form TILED takes where the
-     * matrix-core form does not apply): 1 = edge records (each block's
+     * matrix-core form does not apply; the form that nbb_step_compact runs is
+     * nbb_query_step's): 1 = edge records (each block's
      * cells loaded into registers, only the blocks' edge rows and columns
      * exchanged through LDS; TILED_EDGE, and TILED where the level allows
      * the form and its blocks fill at least three quarters of the work-group
@@ -136,13 +137,42 @@ nbb_status nbb_create(uint32_t k, uint32_t s, const int32_t *offsets, uint32_t r
 /* Free a descriptor (NULL is a no-op).  No enqueued work may still use it. */
 void nbb_destroy(nbb_fractal *f);
 
-/* Describe a descriptor.  NBB_E_INVALID for NULL arguments. */
+/* Describe a descriptor: its sizes and its tile plan (tiles, tile_level,
+ * tile_side, halo_cells, lds_bytes), that of the vector forms, the blocked
+ * layout and the batch groups.  NBB_E_INVALID for NULL arguments. */
 nbb_status nbb_query(const nbb_fractal *f, nbb_info *info);
+
+/* What nbb_step_compact runs on a descriptor as it is configured.
+ * NBB_E_INVALID for NULL arguments. */
+#define NBB_FORM_DIRECT 0u       /* one thread per cell */
+#define NBB_FORM_EDGE_RECORDS 1u /* vector forms: as nbb_info.tiled_form */
+#define NBB_FORM_BYTE_SCATTER 2u
+#define NBB_FORM_TEMPORAL 3u     /* the ring plan of nbb_configure_temporal */
+#define NBB_FORM_MATRIX 4u       /* on the matrix cores */
+typedef struct {
+    uint32_t form;              /* NBB_FORM_* */
+    uint32_t tile_level;        /* of launches of one generation (0 for DIRECT; of every launch for TEMPORAL) */
+    uint32_t tile_side;
+    uint32_t lds_bytes;         /* of one work-group */
+    uint64_t tiles;
+    /* launches of several generations (TEMPORAL; MATRIX in calls of four or
+     * more, nbb_step_packed's every launch): the most one takes, 0 where there
+     * are none, and their tiles */
+    uint32_t held_generations;
+    uint32_t held_level;
+    uint32_t held_lds_bytes;
+    uint32_t whole_generations; /* > 0: calls of up to so many may take one launch of one work-group */
+    uint64_t held_tiles;
+} nbb_step_info;
+nbb_status nbb_query_step(const nbb_fractal *f, nbb_step_info *info);
 
 /*
  * Choose how nbb_step_compact runs: strategy NBB_STRATEGY_* and, for TILED,
  * TILED_BOX and TILED_WAVE, the tile level m (0 = automatic; otherwise
- * 1 <= m <= r).  TILED_BOX is TILED held to the byte-scatter form, TILED_EDGE
+ * 1 <= m <= r).  The level is that of the tile plan (nbb_query); where TILED
+ * runs in the matrix-core form, its steps and batches keep that form's own
+ * levels whatever m is, and a step is held to a level by the strategies that
+ * name a form.  TILED_BOX is TILED held to the byte-scatter form, TILED_EDGE
  * TILED held to the edge-record form (nbb_query then reports strategy TILED
  * with tiled_form 2 or 1; TILED_EDGE fails where the form does not apply:
  * blocks of side other than 3 or 4, tiles below two loads' width, more than
@@ -405,7 +435,7 @@ typedef struct {
     uint32_t direct;          /* instances stepped by their own launch */
     uint32_t resident;        /* instances one work-group each holds (registers or LDS), all generations in one launch */
     uint64_t cells;           /* sum of k_i^r_i */
-    uint64_t tiles;           /* tiles of all tiled instances (groups and resident) */
+    uint64_t tiles;           /* tiles of all tiled instances, by their tile plans */
     uint64_t arena_bytes;     /* smallest arena: max(offset + cells) rounded up to 16 */
     uint64_t device_table_bytes;
 } nbb_batch_info;
@@ -422,6 +452,20 @@ nbb_status nbb_batch_create_ex(const nbb_fractal *const *fractals, const uint64_
                                uint32_t flags, void *stream, nbb_batch **out);
 void nbb_batch_destroy(nbb_batch *batch);
 nbb_status nbb_batch_query(const nbb_batch *batch, nbb_batch_info *info);
+
+/* The forms that a batch's instances are stepped in, and the tiles of the
+ * plans that run (nbb_batch_info.tiles counts those of the descriptors' tile
+ * plans).  NBB_E_INVALID for NULL arguments. */
+typedef struct {
+    uint32_t matrix;        /* instances in group launches, on the matrix cores */
+    uint32_t edge_records;  /* in group launches, vector forms */
+    uint32_t byte_scatter;
+    uint32_t direct;        /* by a launch of their own */
+    uint32_t held_whole;    /* by one work-group each, on the matrix cores, the state in registers */
+    uint32_t lds_resident;  /* by one work-group each, in LDS */
+    uint64_t tiles;         /* of one generation, by those plans (DIRECT instances have none) */
+} nbb_batch_step_info;
+nbb_status nbb_batch_query_step(const nbb_batch *batch, nbb_batch_step_info *info);
 
 /*
  * `steps` generations of `rule` for every instance of the batch, states

@@ -190,6 +190,7 @@ struct nbb_batch {
     int cu_count = 256;
     uint32_t count = 0;
     uint64_t cells = 0, tiles = 0, arena_bytes = 0;
+    uint64_t step_tiles = 0;  // of the plans that run (tiles: of the descriptors' tile plans)
     std::vector<BatchGroup> groups;
     ResidentSet resident;
     uint32_t *counts = nullptr;  // device: the held sets' generation counts, groups' sets first, then small's
@@ -938,6 +939,53 @@ nbb_status nbb_query(const nbb_fractal *F, nbb_info *info) {
     return NBB_OK;
 }
 
+// The conditions are those of nbb_step_compact.
+static bool temporal_held(const nbb_fractal *F) {
+    return F->strategy == NBB_STRATEGY_TEMPORAL && F->temporal_auto && F->hold.ok && F->hold.gens >= F->tmp.h;
+}
+nbb_status nbb_query_step(const nbb_fractal *F, nbb_step_info *info) try {
+    if (!F || !info) return fail(NBB_E_INVALID, "null argument");
+    nbb_info vec;
+    nbb_status st = nbb_query(F, &vec);
+    if (st != NBB_OK) return st;
+    std::memset(info, 0, sizeof(*info));
+    auto side = [&](uint32_t m) {
+        uint32_t S = 1;
+        while (m--) S *= F->f.s;
+        return S;
+    };
+    const bool temporal = F->strategy == NBB_STRATEGY_TEMPORAL, held = temporal_held(F);
+    if (held || (!temporal && F->use_matrix)) {
+        info->form = NBB_FORM_MATRIX;
+        const HoldPlan &h = F->hold;
+        if (h.ok) {
+            info->held_generations = h.gens;
+            info->held_level = h.m;
+            info->held_lds_bytes = hold_lds_bytes(h.zero);
+            info->held_tiles = h.ntiles;
+        }
+        info->tile_level = held ? h.m : F->mat.m;
+        info->lds_bytes = held ? info->held_lds_bytes : 2 * F->mat.buf_bytes;
+        info->tiles = held ? h.ntiles : F->mat.ntiles;
+        info->tile_side = side(info->tile_level);
+        info->whole_generations = !held && F->whole.ok ? F->whole.gens : 0;
+        return NBB_OK;
+    }
+    info->form = vec.tiled_form;  // (0: DIRECT)
+    info->tile_level = vec.tile_level;
+    info->tile_side = vec.tile_side;
+    info->lds_bytes = vec.lds_bytes;
+    info->tiles = vec.tiles;
+    if (temporal) {
+        info->held_generations = vec.temporal_depth;
+        info->held_level = vec.tile_level;
+        info->held_lds_bytes = vec.lds_bytes;
+        info->held_tiles = vec.tiles;
+    }
+    return NBB_OK;
+}
+NBB_CATCH
+
 nbb_status nbb_configure(nbb_fractal *F, uint32_t strategy, uint32_t tile_level) try {
     if (!F) return fail(NBB_E_INVALID, "null descriptor");
     nbb_status st = check_device(F);
@@ -1517,6 +1565,7 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             for (const BatchInstance &I : launch.members[g]) B->tiles += I.ntiles;
             t = mat[g].members.back().tile0 + mat[g].members.back().ntiles;
             ntiles[g] = t;
+            B->step_tiles += t;
             off_inst[g] = total;
             total += align256(mat[g].members.size() * sizeof(MatInstance));
             off_rec[g] = total;
@@ -1529,6 +1578,7 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             I.tile0 = uint32_t(t);
             t += I.ntiles;
         }
+        B->step_tiles += t;
         if (t * 8 > (uint64_t(1) << 31)) {
             return fail(NBB_E_RANGE, "too many tiles in one group of the batch");
         }
@@ -1563,7 +1613,10 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
     total += ncounts ? align256(4 * ncounts) : 0;
     size_t nres = 0;
     for (size_t g = 0; g < nr; ++g) {
-        for (const BatchInstance &I : res.members[g]) B->tiles += I.ntiles;
+        for (const BatchInstance &I : res.members[g]) {
+            B->tiles += I.ntiles;
+            B->step_tiles += I.ntiles;
+        }
         nres += res.members[g].size();
     }
     const size_t off_plans = total;
@@ -1621,6 +1674,7 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             return hip_fail(e, "batch table build");
         }
         S.whole = true;
+        B->step_tiles += H.tiles;
         B->small.push_back(std::move(S));
         B->cu_count = H.top->cu_count;
     }
@@ -1792,6 +1846,19 @@ nbb_status nbb_batch_query(const nbb_batch *B, nbb_batch_info *info) {
     info->device_table_bytes = B->dtab.bytes;
     return NBB_OK;
 }
+
+nbb_status nbb_batch_query_step(const nbb_batch *B, nbb_batch_step_info *info) try {
+    if (!B || !info) return fail(NBB_E_INVALID, "null argument");
+    std::memset(info, 0, sizeof(*info));
+    for (const BatchGroup &G : B->groups)
+        (G.matrix ? info->matrix : G.edges ? info->edge_records : info->byte_scatter) += uint32_t(G.index.size());
+    info->direct = uint32_t(B->direct.size());
+    for (const HeldSet &S : B->small) info->held_whole += uint32_t(S.index.size());
+    info->lds_resident = uint32_t(B->resident.index.size());
+    info->tiles = B->step_tiles;
+    return NBB_OK;
+}
+NBB_CATCH
 
 // Enqueues the resident launch (instance i of the batch takes steps[i]
 // generations, or steps_all if steps is NULL; the per-instance counts go to
@@ -2364,7 +2431,7 @@ nbb_status nbb_step_compact(const nbb_fractal *F, uint8_t *a, uint8_t *b, uint64
     if (result_in_b) *result_in_b = int(steps & 1);
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *in = a, *out = b;
-    if (F->strategy == NBB_STRATEGY_TEMPORAL && F->temporal_auto && F->hold.ok && F->hold.gens >= F->tmp.h) {
+    if (temporal_held(F)) {
         // The buffers end as with the ring plan's launches (below): the other
         // one with the generation before its last launch.
         const HoldPlan &h = F->hold;

@@ -608,7 +608,7 @@ static hipError_t launch_hold_t(const HoldParams &E, uint8_t *in, uint8_t *out, 
                                 const uint32_t *rec, const uint32_t *steps_of, uint32_t launch, uint32_t mode,
                                 hipStream_t st) {
     if (!E.ntiles) return hipSuccess;
-    uint32_t lds = BUF + E.zero + 4;
+    uint32_t lds = hold_lds_bytes(E.zero);  // (BUF is hold_buf(E.zero))
     if (AL == 0) lds = std::max(lds, 4 * ((E.K + 62) / 32 + 1));
     hipLaunchKernelGGL((k_step_hold<AL, NR, NH, GPW, BUF, BATCH, RULE>), dim3(E.ntiles), dim3(64 * E.waves), lds, st, E,
                        in, out, rule, gens, rec, steps_of, launch, mode);
@@ -641,11 +641,11 @@ template <int AL, bool BATCH, int RULE>
 static hipError_t launch_hold_shape(const HoldParams &E, uint32_t nr, uint32_t nh, uint32_t gpw, uint8_t *in,
                                     uint8_t *out, uint32_t rule, uint32_t gens, const uint32_t *rec,
                                     const uint32_t *steps_of, uint32_t launch, uint32_t mode, hipStream_t st) {
-    const bool small = E.zero + 4 <= 8192;
+    const bool small = hold_buf(E.zero) == kHoldBufSmall;
 #define NBB_HOLD_CASE(R, H, G)                                                                                    \
     if (nr == R && nh == H && gpw == G)                                                                           \
-    return small ? launch_hold_t<AL, R, H, G, 8192, BATCH, RULE>(E, in, out, rule, gens, rec, steps_of, launch,   \
-                                                                 mode, st)                                    \
+    return small ? launch_hold_t<AL, R, H, G, int(kHoldBufSmall), BATCH, RULE>(E, in, out, rule, gens, rec,       \
+                                                                               steps_of, launch, mode, st)      \
                  : launch_hold_t<AL, R, H, G, int(kHoldBuf), BATCH, RULE>(E, in, out, rule, gens, rec, steps_of,  \
                                                                           launch, mode, st)
 #define NBB_HOLD_CASES(R, H) \

@@ -154,6 +154,11 @@ constexpr uint32_t kHoldMaxWaves = 16;
 constexpr uint32_t kHoldMaxGens = 4096;   // per launch, whatever the plan (a launch of milliseconds at most)
 constexpr uint32_t kHoldMaxRings = 4;
 constexpr uint32_t kHoldBuf = 32 * 1024;  // one record buffer at most
+// The second record buffer's offset, for a plan whose dword of zeros is at
+// `zero`, and a work-group's LDS.
+constexpr uint32_t kHoldBufSmall = 8 * 1024;
+constexpr uint32_t hold_buf(uint32_t zero) { return zero + 4 <= kHoldBufSmall ? kHoldBufSmall : kHoldBuf; }
+constexpr uint32_t hold_lds_bytes(uint32_t zero) { return hold_buf(zero) + zero + 4; }
 // operands: with A and sel, which are the matrix plan's of the same fractal.
 bool build_hold_plan(const Fractal &f, uint32_t m, uint32_t rings, uint32_t gpw, HoldPlan *p, std::string *msg,
                      bool operands = true);

@@ -29,6 +29,7 @@ NBB_BATCH_RESIDENT = 2     # nbb_batch_create_ex: every small instance stepped i
 (STRATEGY_AUTO, STRATEGY_TILED, STRATEGY_DIRECT, STRATEGY_TILED_WAVE, STRATEGY_TILED_BOX, STRATEGY_TEMPORAL,
  STRATEGY_TILED_EDGE) = range(7)
 MAP_LUT, MAP_DIGITS, MAP_MFMA = 0, 1, 2
+FORM_DIRECT, FORM_EDGE_RECORDS, FORM_BYTE_SCATTER, FORM_TEMPORAL, FORM_MATRIX = range(5)  # nbb_step_info.form
 
 
 class NbbError(RuntimeError):
@@ -82,6 +83,19 @@ class BatchInfo(ctypes.Structure):
                 ("arena_bytes", ctypes.c_uint64), ("device_table_bytes", ctypes.c_uint64)]
 
 
+class StepInfo(ctypes.Structure):
+    _fields_ = [("form", ctypes.c_uint32), ("tile_level", ctypes.c_uint32), ("tile_side", ctypes.c_uint32),
+                ("lds_bytes", ctypes.c_uint32), ("tiles", ctypes.c_uint64), ("held_generations", ctypes.c_uint32),
+                ("held_level", ctypes.c_uint32), ("held_lds_bytes", ctypes.c_uint32),
+                ("whole_generations", ctypes.c_uint32), ("held_tiles", ctypes.c_uint64)]
+
+
+class BatchStepInfo(ctypes.Structure):
+    _fields_ = [("matrix", ctypes.c_uint32), ("edge_records", ctypes.c_uint32), ("byte_scatter", ctypes.c_uint32),
+                ("direct", ctypes.c_uint32), ("held_whole", ctypes.c_uint32), ("lds_resident", ctypes.c_uint32),
+                ("tiles", ctypes.c_uint64)]
+
+
 _lib = None
 
 
@@ -102,6 +116,8 @@ def lib() -> ctypes.CDLL:
     L.nbb_destroy.restype = None
     L.nbb_query.argtypes = [vp, ctypes.POINTER(Info)]
     L.nbb_query.restype = st
+    L.nbb_query_step.argtypes = [vp, ctypes.POINTER(StepInfo)]
+    L.nbb_query_step.restype = st
     L.nbb_configure.argtypes = [vp, u32, u32]
     L.nbb_configure.restype = st
     L.nbb_lambda.argtypes = [vp, vp, u64, vp, vp, vp]
@@ -152,6 +168,8 @@ def lib() -> ctypes.CDLL:
     L.nbb_batch_destroy.restype = None
     L.nbb_batch_query.argtypes = [vp, ctypes.POINTER(BatchInfo)]
     L.nbb_batch_query.restype = st
+    L.nbb_batch_query_step.argtypes = [vp, ctypes.POINTER(BatchStepInfo)]
+    L.nbb_batch_query_step.restype = st
     L.nbb_batch_step.argtypes = [vp, vp, vp, u64, u32, u32, ctypes.POINTER(ctypes.c_int), vp]
     L.nbb_batch_step.restype = st
     L.nbb_batch_step_each.argtypes = [vp, vp, vp, u64, vp, u32, vp]
@@ -294,6 +312,12 @@ class Fractal:
     def info(self) -> Info:
         inf = Info()
         _check(lib().nbb_query(self._h, ctypes.byref(inf)))
+        return inf
+
+    def step_info(self) -> StepInfo:
+        """What step_compact runs as the descriptor is configured (nbb_query_step)."""
+        inf = StepInfo()
+        _check(lib().nbb_query_step(self._h, ctypes.byref(inf)))
         return inf
 
     def configure(self, strategy: int = STRATEGY_AUTO, tile_level: int = 0) -> None:
@@ -553,6 +577,12 @@ class Batch:
     def info(self) -> BatchInfo:
         inf = BatchInfo()
         _check(lib().nbb_batch_query(self._h, ctypes.byref(inf)))
+        return inf
+
+    def step_info(self) -> BatchStepInfo:
+        """The forms the instances are stepped in (nbb_batch_query_step)."""
+        inf = BatchStepInfo()
+        _check(lib().nbb_batch_query_step(self._h, ctypes.byref(inf)))
         return inf
 
     def new_arena(self):

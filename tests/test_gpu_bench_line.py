@@ -51,6 +51,26 @@ def test_bench_prints_one_complete_json_line():
         assert "traffic_over_alg" in lw and "bbox_traffic_over_alg" in lw
 
 
+def test_bench_names_the_form_that_runs():
+    from paper_2110_12952_amd import nbbfrac as N
+    from paper_2110_12952_amd import workloads as W
+    cmd = [sys.executable, os.path.join(ROOT, "bench.py"), "--steps", "4", "--warmup", "1", "--warmup-ms", "0",
+           "--no-bbox", "--map-reps", "1", "--no-cpu-baseline", "--repeats", "0", "--batch-steps", "2",
+           "--batch-seq-steps", "1", "--no-small-batch", "--serve-seconds", "0", "--large-steps", "0"]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-2000:]
+    d = json.loads(r.stdout)
+    s = N.Fractal(2, W.TRIANGLE.offsets, 16).step_info()
+    assert s.form == N.FORM_MATRIX
+    c = d["config"]
+    assert (c["form"], c["tile_level"], c["tiles"]) == ("matrix", s.tile_level, s.tiles)
+    assert c["held"]["generations_per_launch"] == s.held_generations and c["held"]["tile_level"] == s.held_level
+    assert d["roofline"]["kernel"] == "k_step_matrix"
+    assert d["small_triangle_r10"]["temporal"]["form"] == "matrix"
+    by_form = d["batch"]["instances_by_form"]
+    assert sum(by_form.values()) == 512 and by_form["matrix"] == 512
+
+
 def test_bench_refuses_several_gpus():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True,
                        text=True, timeout=120)

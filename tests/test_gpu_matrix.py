@@ -277,3 +277,52 @@ def test_maps_at_any_alignment(N, count, off):
     for v in outs:
         h = v.cpu().numpy()
         assert (h[:off] == 7).all() and (h[off + count:] == 7).all()
+
+
+@gpu
+def test_step_info_names_what_runs(N):
+    fd = W.TRIANGLE
+    f = N.Fractal(fd.s, fd.offsets, 10)
+    level = f.info().tile_level
+    d = f.step_info()
+    assert d.form == N.FORM_MATRIX and d.tiles == 3 ** (10 - d.tile_level) and d.tile_side == 2 ** d.tile_level
+    assert d.held_generations > 1 and d.held_tiles == 3 ** (10 - d.held_level) and 0 < d.lds_bytes <= 65536
+    for strategy, form in ((N.STRATEGY_TILED_EDGE, N.FORM_EDGE_RECORDS), (N.STRATEGY_TILED_BOX, N.FORM_BYTE_SCATTER),
+                           (N.STRATEGY_TILED_WAVE, N.FORM_BYTE_SCATTER)):
+        m = 5 if strategy == N.STRATEGY_TILED_WAVE else level
+        f.configure(strategy, m)
+        s, v = f.step_info(), f.info()
+        assert (s.form, s.tile_level, s.tiles, s.lds_bytes) == (form, m, v.tiles, v.lds_bytes)
+        assert s.held_generations == 0 and s.whole_generations == 0
+    f.configure(N.STRATEGY_DIRECT)
+    s = f.step_info()
+    assert (s.form, s.tile_level, s.held_generations) == (N.FORM_DIRECT, 0, 0)
+    f.configure_temporal(4, 8)
+    s = f.step_info()
+    assert (s.form, s.tile_level, s.held_generations) == (N.FORM_TEMPORAL, 4, 8)
+    f.configure_temporal()
+    s = f.step_info()
+    assert (s.form, s.tile_level, s.held_generations) == (N.FORM_MATRIX, d.held_level, d.held_generations)
+    f.configure(N.STRATEGY_TILED, 4)  # the tile plan's level: the matrix form keeps its own
+    s = f.step_info()
+    assert f.info().tile_level == 4
+    assert all(getattr(s, n) == getattr(d, n) for n, _ in s._fields_)
+    g = N.Fractal(2, ((0, 0), (1, 1)), 3)  # 8 cells: no block of 16
+    assert g.step_info().form in (N.FORM_EDGE_RECORDS, N.FORM_BYTE_SCATTER)
+    whole = N.Fractal(fd.s, fd.offsets, 7).step_info()
+    assert whole.whole_generations > 0
+
+
+@gpu
+def test_batch_step_info_names_what_runs(N):
+    tri = [N.Fractal(2, W.TRIANGLE.offsets, r) for r in (11, 7)]
+    car = [N.Fractal(3, W.CARPET.offsets, r) for r in (6, 3)]
+    car[0].configure(N.STRATEGY_TILED_BOX, 3)
+    direct = N.Fractal(2, W.TRIANGLE.offsets, 5)
+    direct.configure(N.STRATEGY_DIRECT)
+    frs = tri + car + [direct]
+    s = N.Batch(frs, resident=False).step_info()
+    assert (s.matrix, s.edge_records, s.byte_scatter, s.direct, s.held_whole, s.lds_resident) == (3, 0, 1, 1, 0, 0)
+    assert s.tiles >= 8 ** 3 + 3  # the box plan's own, at least one of every other
+    s = N.Batch(frs, resident=True).step_info()
+    assert (s.matrix, s.byte_scatter, s.direct, s.held_whole, s.lds_resident) == (1, 1, 1, 2, 0)

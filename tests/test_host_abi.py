@@ -338,3 +338,9 @@ print("alive", N.plan_tables(3, W.CARPET.offsets, 4)["tile_level"] > 0)
     assert r.returncode == 0, r.stderr[-2000:]
     lines = r.stdout.splitlines()
     assert len(lines) == 3 and all(l.split()[0] == "True" for l in lines[:2]) and lines[2] == "alive True", r.stdout
+
+
+def test_step_queries_reject_null():
+    L = N.lib()
+    assert L.nbb_query_step(None, ctypes.byref(N.StepInfo())) == N.NBB_E_INVALID
+    assert L.nbb_batch_query_step(None, ctypes.byref(N.BatchStepInfo())) == N.NBB_E_INVALID
