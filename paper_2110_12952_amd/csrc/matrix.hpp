@@ -55,10 +55,10 @@
 #include <stdint.h>
 
 #include <algorithm>
-#include <atomic>
 #include <type_traits>
 
 #include "device_common.hpp"
+#include "occupancy_cache.hpp"
 #include "plan.hpp"
 
 namespace nbb {
@@ -318,19 +318,13 @@ template <int AL, int NR, int NH, int GPW, bool BATCH, int RULE>
 static hipError_t launch_matrix_t(const MatParams &E, const uint8_t *in, uint8_t *out, uint32_t rule,
                                   const uint32_t *rec, int cu_count, hipStream_t st) {
     const uint32_t lds = 2 * E.buf_bytes, threads = 64 * E.waves;
-    static std::atomic<uint64_t> cached{0};  // lds << 32 | threads << 8 | work-groups per CU
+    static OccupancyCache cache;
     int per_cu = 0;
-    const uint64_t key = uint64_t(lds) << 32 | threads << 8;
-    const uint64_t c = cached.load(std::memory_order_relaxed);
-    if ((c & ~uint64_t(0xFF)) == key && (c & 0xFF)) {
-        per_cu = int(c & 0xFF);
-    } else {
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, k_step_matrix<AL, NR, NH, GPW, BATCH, RULE>, int(threads), lds);
-        if (e != hipSuccess) return e;
-        per_cu = std::max(1, std::min(per_cu, 255));
-        cached.store(key | uint64_t(per_cu), std::memory_order_relaxed);
-    }
+    hipError_t e = cache.get(lds, threads, &per_cu, [&](int *n) {
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_step_matrix<AL, NR, NH, GPW, BATCH, RULE>, int(threads),
+                                                            lds);
+    });
+    if (e != hipSuccess) return e;
     // Work-groups per CU: the fewest tile rounds times work-groups (the tiles
     // the busiest CU works through) that leaves six wavefronts on a CU, fewer
     // work-groups first.  Triangle r16 (6,561 tiles, two wavefronts each) with

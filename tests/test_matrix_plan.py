@@ -42,3 +42,14 @@ def test_sparse_fractals_within_time_and_memory(tmp_path):
     assert r.returncode == 0, r.stdout + r.stderr
     made, longest = r.stdout.split()
     assert int(made) > 100 and float(longest) < 0.5
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_occupancy_is_asked_once_per_launch_shape(tmp_path):
+    exe = str(tmp_path / "occupancy_cache")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", CSRC,
+                        os.path.join(ROOT, "tests", "sanitize", "occupancy_cache.cpp"), "-o", exe],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout + r.stderr
