@@ -1912,35 +1912,41 @@ static hipError_t batch_fork_groups(const nbb_batch *B, hipStream_t s) {
 static hipStream_t batch_group_stream(const nbb_batch *B, size_t k, hipStream_t s) {
     return (k == 0 || B->gstream.empty()) ? s : B->gstream[(k - 1) % B->gstream.size()];
 }
+// Launches that a held set takes n generations in, without the last one where
+// the set is not of whole instances.
+static uint32_t held_set_launches(const HeldSet &S, uint32_t n) {
+    return S.whole ? held_launches(n, S.hp.gens, false) : (n ? held_launches(n - 1, S.hp.gens, true) : 0u);
+}
+// Whether a call of `steps` generations, or counts[i] of instance i, takes the
+// held launches of the set: not where they are about as many as one per
+// generation.  *launches: their number, *most: the most generations.
+static bool held_use(const HeldSet &S, uint32_t steps, const uint32_t *counts, uint32_t *launches, uint32_t *most) {
+    *launches = *most = 0;
+    if (!S.ok) return false;
+    if (counts) {
+        for (uint32_t i : S.index) {
+            *most = std::max(*most, counts[i]);
+            *launches = std::max(*launches, held_set_launches(S, counts[i]));
+        }
+    } else {
+        *most = steps;
+        *launches = held_set_launches(S, steps);
+    }
+    return S.whole || 2 * uint64_t(*launches) + 2 <= *most;
+}
 // `steps` generations of every instance of the set, or counts[i] of instance
 // i.  Sets of whole instances take all of them in place and write the result
 // where it belongs; others take all but the last several at a time and the
 // last by itself, so that the other arena ends with the generation before, as
 // with one launch per generation.  *used = false (nothing enqueued) where
-// that takes about as many launches as one per generation.  *last: the last
+// held_use says so.  *last: the last
 // generation is still to be taken, from *in to *out (never with counts).
 static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t arena_len, uint32_t steps,
                             const uint32_t *counts, uint32_t rule, hipStream_t s, bool *used, bool *last = nullptr,
                             uint8_t **in_ = nullptr, uint8_t **out_ = nullptr) {
-    *used = false;
-    if (!S.ok) return hipSuccess;
-    const uint32_t h = S.hp.gens;
-    auto launches = [&](uint32_t n) {
-        return S.whole ? held_launches(n, h, false) : (n ? held_launches(n - 1, h, true) : 0u);
-    };
-    uint32_t L = 0, most = steps;
-    if (counts) {
-        most = 0;
-        for (uint32_t i : S.index) {
-            most = std::max(most, counts[i]);
-            L = std::max(L, launches(counts[i]));
-        }
-    } else {
-        L = launches(steps);
-    }
-    if (!S.whole && 2 * uint64_t(L) + 2 > most) return hipSuccess;
-    *used = true;
-    if (!most) return hipSuccess;
+    uint32_t L = 0, most = 0;
+    *used = held_use(S, steps, counts, &L, &most);
+    if (!*used || !most) return hipSuccess;
     auto go = [&](const HoldParams &E, uint8_t *in, uint8_t *out, uint32_t g, uint32_t i, uint32_t mode) {
         return launch_step_hold(E, S.al, S.nr, S.nh, S.gpw, in, out, arena_len, rule, g, S.rec,
                                 counts ? S.steps : nullptr, i, mode, s);
@@ -1951,7 +1957,7 @@ static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t a
     for (uint32_t i = 0; i < L; ++i) {
         HoldParams E = S.hp;
         if (counts) {  // (an instance before the last live one may be done too: its tiles end at once)
-            while (live && launches(counts[S.index[live - 1]]) <= i) --live;
+            while (live && held_set_launches(S, counts[S.index[live - 1]]) <= i) --live;
             if (!live) break;
             E.ntiles = uint32_t(S.tiles_end[live - 1]);
         }
@@ -2072,8 +2078,14 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
     // than g steps; instance i's state alternates a -> b -> a ... like the
     // whole batch's, so its result ends in b iff steps[i] is odd.
     hipStream_t s = static_cast<hipStream_t>(stream);
+    // The held sets' counts, where a held launch reads them: a launch of its
+    // own (one large instance, one generation: 13.2 us with it, 9.4 without).
+    bool count = false;
+    uint32_t L = 0, n_most = 0;
+    for (const BatchGroup &G : B->groups) count = count || (held_use(G.held, 0, steps, &L, &n_most) && n_most);
+    for (const HeldSet &S : B->small) count = count || (held_use(S, 0, steps, &L, &n_most) && n_most);
     std::vector<uint32_t> n;  // (before the forks: an allocation that fails must not skip the joins)
-    if (B->counts) {
+    if (count) {
         for (const BatchGroup &G : B->groups)
             for (uint32_t i : G.held.index) n.push_back(steps[i]);
         for (const HeldSet &S : B->small)
@@ -2082,7 +2094,7 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
     bool res_launched = false;
     e = batch_fork_resident(B, a, b, rule, steps, 0, s, &res_launched);
     if (e != hipSuccess) return hip_fail(e, "batch resident step launch");
-    if (B->counts) e = launch_set_words(B->counts, n.data(), uint32_t(n.size()), s);
+    if (count) e = launch_set_words(B->counts, n.data(), uint32_t(n.size()), s);
     if (e != hipSuccess) {
         (void)batch_join_resident(B, s, res_launched);
         return hip_fail(e, "batch step counts");
