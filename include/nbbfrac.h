@@ -394,27 +394,31 @@ nbb_status nbb_autotune(nbb_fractal *f, uint8_t *a, uint8_t *b, uint64_t len, ui
  * buffer: instance i occupies bytes [offsets[i], offsets[i] + k_i^r_i) of
  * both arenas passed to nbb_batch_step.  Instances whose descriptors use the
  * same tiled strategy at the same tile level for the same (k, s, offsets) form one
- * group and are stepped by one launch per generation over all their tiles
+ * group and are stepped by one launch over all their tiles per generation, or
+ * per several generations where all of them run in the matrix-core form
  * (configure a common tile level with nbb_configure to group instances of
  * different r); instances with the DIRECT strategy are stepped one launch
  * each.  Small tiled instances, those whose state fits one work-group's LDS
  * twice over, with the tile boxes and the neighbour table (160 KiB on gfx950;
  * e.g. up to 3^9 triangle or 7^5 H cells), and whose generation takes at most
- * 8 passes of up to 4 tiles, may instead be stepped in LDS (by default when
+ * 8 passes of up to 4 tiles, may instead be stepped resident (by default when
  * they hold at least 1/8 of the batch's tiled cells; see
  * nbb_batch_create_ex): one work-group per instance runs all of the call's
  * generations of it in one launch, with no global traffic between
- * generations, at a tile level of its own (the one with the fewest passes;
- * built with the descriptor on the first batch that needs it, and independent
- * of nbb_configure).  All of them share one launch; beside group or direct
- * launches it runs on a side stream of the library (one per device, kept
- * until the process ends) that is forked from `stream` at the start of each
- * step call and joined back to it before the call's last enqueued work (so,
- * seen from `stream`, the call's work is ordered as before).  With more than
- * one group, groups after the first run on up to three more streams of the
- * library (per device, kept until the process ends), forked and joined the
- * same way, so that one group's launches fill the start and the end of
- * another's; the batch built by nbb_batch_step_each_noalloc runs every group
+ * generations.  In LDS it does so at a tile level of its own (the one with the
+ * fewest passes; built with the descriptor on the first batch that needs it,
+ * and independent of nbb_configure), and all such instances share one launch.
+ * Where all small instances of a fractal run in the matrix-core form, a launch
+ * of that fractal holds their states in registers, faster by the generation;
+ * each call takes whichever of one LDS launch and a launch per fractal it
+ * estimates to be faster for its step counts.
+ * What does not fit one launch runs on up to three streams of the library
+ * beside `stream` (per device, kept until the process ends; a fourth for
+ * resident instances beside four groups or more), so that one group's launches
+ * fill the start and the end of another's.  They are forked from `stream` at
+ * the start of each step call and joined back to it before the call's last
+ * enqueued work, so that, seen from `stream`, the call's work is ordered as if
+ * it ran there; the batch built by nbb_batch_step_each_noalloc runs every group
  * on `stream`.  Step calls on one batch
  * share its small device tables: enqueue them from one host thread, and order
  * calls made on different streams (an event) before the later one starts.
@@ -442,9 +446,9 @@ typedef struct {
 nbb_status nbb_batch_create(const nbb_fractal *const *fractals, const uint64_t *offsets, uint32_t count,
                             void *stream, nbb_batch **out);
 /* As nbb_batch_create (flags 0: the default choice above), with flags:
- * NBB_BATCH_NO_RESIDENT steps every tiled instance by the per-generation group
- * launches, small ones included; NBB_BATCH_RESIDENT steps every small one in
- * LDS, whatever its share of the cells.  NBB_E_INVALID for unknown flag bits
+ * NBB_BATCH_NO_RESIDENT steps every tiled instance by the group launches, small
+ * ones included; NBB_BATCH_RESIDENT steps every small one resident, whatever
+ * its share of the cells.  NBB_E_INVALID for unknown flag bits
  * or both flags. */
 #define NBB_BATCH_NO_RESIDENT 1u
 #define NBB_BATCH_RESIDENT 2u
@@ -461,7 +465,8 @@ typedef struct {
     uint32_t edge_records;  /* in group launches, vector forms */
     uint32_t byte_scatter;
     uint32_t direct;        /* by a launch of their own */
-    uint32_t held_whole;    /* by one work-group each, on the matrix cores, the state in registers */
+    uint32_t held_whole;    /* by one work-group each, on the matrix cores, the state in registers (in LDS in
+                             * calls where one launch for all of them is estimated faster) */
     uint32_t lds_resident;  /* by one work-group each, in LDS */
     uint64_t tiles;         /* of one generation, by those plans (DIRECT instances have none) */
 } nbb_batch_step_info;
@@ -487,7 +492,7 @@ nbb_status nbb_batch_step(const nbb_batch *batch, uint8_t *a, uint8_t *b, uint64
  * steps[i] > g, so instance i's result ends in b iff steps[i] is odd and an
  * instance with 0 steps is left untouched.  Within each group the step
  * counts must not increase in the order the instances were given to
- * nbb_batch_create (NBB_E_INVALID otherwise; instances stepped in LDS are
+ * nbb_batch_create (NBB_E_INVALID otherwise; resident instances are
  * exempt): list instances by decreasing step count.  steps is a host array of
  * nbb_batch_info.instances entries.
  */

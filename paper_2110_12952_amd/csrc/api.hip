@@ -143,6 +143,7 @@ struct nbb_temporal_plan {
 struct HeldSet {
     bool ok = false;
     bool whole = false;               // every tile is a whole instance: results without alternating arenas
+    double gen_us = 0.0;              // estimated time of a generation (whole sets)
     HoldParams hp{};
     uint32_t al = 0, nr = 0, nh = 0, gpw = 0;
     const uint32_t *rec = nullptr;
@@ -180,6 +181,8 @@ struct ResidentSet {
     std::vector<uint32_t> index;           // the instances (caller's numbering)
     std::vector<uint32_t> passes;          // passes per generation of each
     uint32_t lds = 0;                      // LDS of the largest
+    uint32_t most_passes = 0;
+    uint32_t rounds = 1;                   // of work-groups that the chip holds at once
 };
 // An instance is stepped in LDS only if a generation takes at most this many
 // passes (each about a microsecond: a tile scatter, the rule, two barriers):
@@ -192,7 +195,8 @@ struct nbb_batch {
     uint64_t cells = 0, tiles = 0, arena_bytes = 0;
     uint64_t step_tiles = 0;  // of the plans that run (tiles: of the descriptors' tile plans)
     std::vector<BatchGroup> groups;
-    ResidentSet resident;
+    ResidentSet resident;      // the instances stepped in LDS beside the held sets of `small`
+    ResidentSet resident_all;  // all that are counted as resident, for calls that leave `small` alone
     uint32_t *counts = nullptr;  // device: the held sets' generation counts, groups' sets first, then small's
     std::vector<HeldSet> small;  // instances counted as resident that one work-group each holds in registers
     std::vector<BatchDirect> direct;
@@ -460,6 +464,15 @@ void hold_params(const HoldPlan &p, void *const *dst, HoldParams *T) {
     T->halo = static_cast<const uint32_t *>(dst[2]);
     T->nbr = static_cast<const uint32_t *>(dst[3]);
     T->sel = static_cast<const uint32_t *>(dst[4]);
+}
+
+// Estimated time of a generation of a set of whole instances of `groups`
+// groups each.  Fitted to sets of 8 / 1,024 instances: 1 group 0.13 to 0.18 /
+// 0.13 to 0.19 us, 4 (carpet r4, H r4) 0.21, 0.19 / 0.32, 0.32, 8 (triangle r8)
+// 0.20 / 0.47, 16 (chandelier r7) 0.31 / 0.92, 23 (triangle r9) 0.42 / 1.29, 22
+// (H r5) 0.52 / 1.61.
+double set_gen_us(uint32_t groups, size_t instances, uint32_t cus) {
+    return std::max(0.12 + 0.015 * groups, 0.016 * groups * double((instances + cus - 1) / cus));
 }
 
 // Groups per wavefront of a work-group that holds a whole state.
@@ -1301,6 +1314,13 @@ static hipError_t device_stream(int dev, int slot, hipStream_t *out) {
 }
 static hipError_t resident_stream(int dev, hipStream_t *out) { return device_stream(dev, 0, out); }
 
+// Lanes of a batch's calls: its groups, or its DIRECT instances where it has
+// none, then resident and held sets (resident_use); the first stays on the
+// caller's stream.
+static size_t batch_base_lanes(const nbb_batch *B) {
+    return B->groups.empty() ? size_t(!B->direct.empty()) : B->groups.size();
+}
+
 static void batch_free(nbb_batch *B) {
     if (B->fork) (void)hipEventDestroy(B->fork);
     if (B->join) (void)hipEventDestroy(B->join);
@@ -1391,7 +1411,7 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             index[g].push_back(i);
             members[g].push_back(I);
         }
-    } launch, res;
+    } launch, res, res_all;
     // Small instances go to LDS when asked to, or by default when they hold
     // at least 1/8 of the tiled cells: beside a few large instances they are
     // cheap in the group launches, while a long resident launch takes issue
@@ -1500,9 +1520,10 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
                 if (taken[i]) B->tiles += res.members[g][j].ntiles;
                 else rest.add(fractals[i], i, res.members[g][j], same_resident);
             }
+        if (small.size() + !rest.reps.empty() > 1) res_all = std::move(res);
         res = std::move(rest);
     }
-    const size_t ng = launch.reps.size(), nr = res.reps.size();
+    const size_t ng = launch.reps.size();
     std::vector<HeldBuild> held(ng);
     // A group whose descriptors all run the matrix form takes it, at one tile
     // level for all of its instances (those below it are one tile each).  Not
@@ -1611,20 +1632,26 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
                 ncounts += H.members.size();
             }
     total += ncounts ? align256(4 * ncounts) : 0;
-    size_t nres = 0;
-    for (size_t g = 0; g < nr; ++g) {
-        for (const BatchInstance &I : res.members[g]) {
+    for (const auto &members : res.members)
+        for (const BatchInstance &I : members) {
             B->tiles += I.ntiles;
             B->step_tiles += I.ntiles;
         }
-        nres += res.members[g].size();
+    struct ResidentBuild {
+        const Part &part;
+        ResidentSet &set;
+        size_t off_plans = 0, off_inst = 0, off_steps = 0;
+    } resident_build[2] = {{res, B->resident}, {res_all, B->resident_all}};
+    for (ResidentBuild &R : resident_build) {
+        size_t n = 0;
+        for (const auto &members : R.part.members) n += members.size();
+        R.off_plans = total;
+        total += n ? align256(R.part.reps.size() * sizeof(TileParams)) : 0;
+        R.off_inst = total;
+        total += n ? align256(n * sizeof(ResidentInstance)) : 0;
+        R.off_steps = total;
+        total += n ? align256(n * sizeof(uint32_t)) : 0;
     }
-    const size_t off_plans = total;
-    total += nr ? align256(nr * sizeof(TileParams)) : 0;
-    const size_t off_rinst = total;
-    total += nres ? align256(nres * sizeof(ResidentInstance)) : 0;
-    const size_t off_rsteps = total;
-    total += nres ? align256(nres * sizeof(uint32_t)) : 0;
     if (fixed && total > fixed_cap) {
         return fail(NBB_E_RANGE, "batch tables (" + std::to_string(total) + " bytes) exceed the " +
                                      std::to_string(fixed_cap) + "-byte no-allocation scratch");
@@ -1674,6 +1701,7 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             return hip_fail(e, "batch table build");
         }
         S.whole = true;
+        S.gen_us = set_gen_us(H.plan->plan.groups, H.tiles, uint32_t(H.top->cu_count));
         B->step_tiles += H.tiles;
         B->small.push_back(std::move(S));
         B->cu_count = H.top->cu_count;
@@ -1750,17 +1778,20 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         B->groups.push_back(std::move(G));
         B->cu_count = launch.reps[g]->cu_count;
     }
-    if (nr) {
+    for (const ResidentBuild &build : resident_build) {
+        const Part &part = build.part;
+        const size_t np = part.reps.size();
+        if (!np) continue;
         // tiles per pass per plan: as many (up to 4) as the registers and LDS
         // allow for the plan's largest instance
         const uint32_t lds_budget = device_lds_per_group();
-        std::vector<TileParams> plans(nr);
+        std::vector<TileParams> plans(np);
         std::vector<ResidentInstance> rinst;
-        ResidentSet &R = B->resident;
-        for (size_t g = 0; g < nr; ++g) {
-            plans[g] = res.reps[g]->res_tp;
+        ResidentSet &R = build.set;
+        for (size_t g = 0; g < np; ++g) {
+            plans[g] = part.reps[g]->res_tp;
             uint32_t most = 1;
-            for (const BatchInstance &I : res.members[g]) most = std::max(most, I.ntiles);
+            for (const BatchInstance &I : part.members[g]) most = std::max(most, I.ntiles);
             uint32_t teams = 1;
             for (uint32_t t : {4u, 2u})
                 if (t <= most && resident_fits(plans[g], t) && resident_lds_bytes(plans[g], most, t) <= lds_budget) {
@@ -1768,29 +1799,34 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
                     break;
                 }
             R.lds = std::max(R.lds, resident_lds_bytes(plans[g], most, teams));
-            for (size_t j = 0; j < res.members[g].size(); ++j) {
-                const BatchInstance &I = res.members[g][j];
+            for (size_t j = 0; j < part.members[g].size(); ++j) {
+                const BatchInstance &I = part.members[g][j];
                 rinst.push_back({I.nbr, I.base16, I.ntiles, uint32_t(g), teams});
-                R.index.push_back(res.index[g][j]);
+                R.index.push_back(part.index[g][j]);
                 R.passes.push_back((I.ntiles + teams - 1) / teams);
+                R.most_passes = std::max(R.most_passes, R.passes.back());
             }
         }
-        auto *dplans = reinterpret_cast<TileParams *>(base + off_plans);
-        auto *dinst = reinterpret_cast<ResidentInstance *>(base + off_rinst);
-        e = hipMemcpyAsync(dplans, plans.data(), nr * sizeof(TileParams), hipMemcpyHostToDevice, s);
+        auto *dplans = reinterpret_cast<TileParams *>(base + build.off_plans);
+        auto *dinst = reinterpret_cast<ResidentInstance *>(base + build.off_inst);
+        e = hipMemcpyAsync(dplans, plans.data(), np * sizeof(TileParams), hipMemcpyHostToDevice, s);
         if (e == hipSuccess)
             e = hipMemcpyAsync(dinst, rinst.data(), rinst.size() * sizeof(ResidentInstance), hipMemcpyHostToDevice, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host tables go out of scope
         if (e != hipSuccess) {
             return hip_fail(e, "batch table build");
         }
+        const uint32_t fit = uint32_t(part.reps[0]->cu_count) * std::max(1u, std::min(8u, lds_budget / std::max(R.lds, 1u)));
+        R.rounds = uint32_t((R.index.size() + fit - 1) / fit);
         R.plans = dplans;
         R.inst = dinst;
-        R.steps = reinterpret_cast<uint32_t *>(base + off_rsteps);
+        R.steps = reinterpret_cast<uint32_t *>(base + build.off_steps);
     }
     for (const BatchDirect &d : B->direct) B->cu_count = d.f->cu_count;
-    // a side stream if the resident launch has group or direct launches beside it
-    if (!B->resident.index.empty() && (!B->groups.empty() || !B->direct.empty())) {
+    // a side stream where resident and held sets run beside as many groups as
+    // have streams (not otherwise: five streams share the four hardware queues,
+    // eight spread sets took 103 us instead of 88)
+    if ((!B->resident.index.empty() || !B->small.empty()) && batch_base_lanes(B) > size_t(kGroupStreams)) {
         e = resident_stream(dev, &B->side);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&B->fork, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&B->join, hipEventDisableTiming);
@@ -1799,8 +1835,9 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             return hip_fail(e, "batch stream");
         }
     }
-    if (!fixed && B->groups.size() + B->small.size() > 1) {
-        const size_t ns = std::min<size_t>(B->groups.size() + B->small.size() - 1, kGroupStreams);
+    const size_t lanes = batch_base_lanes(B) + !B->resident.index.empty() + B->small.size();
+    if (!fixed && lanes > 1) {
+        const size_t ns = std::min<size_t>(lanes - 1, kGroupStreams);
         B->gstream.reserve(ns);
         B->gjoin.reserve(ns);
         e = hipEventCreateWithFlags(&B->gfork, hipEventDisableTiming);
@@ -1839,7 +1876,7 @@ nbb_status nbb_batch_query(const nbb_batch *B, nbb_batch_info *info) {
     info->groups = uint32_t(B->groups.size());
     info->direct = uint32_t(B->direct.size());
     info->resident = uint32_t(B->resident.index.size());
-    for (const HeldSet &S : B->small) info->resident += uint32_t(S.index.size());
+    for (const HeldSet &S : B->small) info->resident += uint32_t(S.index.size());  // (resident_all: the same instances)
     info->cells = B->cells;
     info->tiles = B->tiles;
     info->arena_bytes = B->arena_bytes;
@@ -1860,53 +1897,43 @@ nbb_status nbb_batch_query_step(const nbb_batch *B, nbb_batch_step_info *info) t
 }
 NBB_CATCH
 
-// Enqueues the resident launch (instance i of the batch takes steps[i]
-// generations, or steps_all if steps is NULL; the per-instance counts go to
-// the batch's device array first): on the caller's stream if nothing else
-// runs, else on the side stream, forked from it here; batch_join_resident
-// joins it back.  *launched tells whether anything was enqueued.
-static hipError_t batch_fork_resident(const nbb_batch *B, uint8_t *a, uint8_t *b, uint32_t rule,
-                                      const uint32_t *steps, uint32_t steps_all, hipStream_t s, bool *launched_) {
-    *launched_ = false;
-    const ResidentSet &R = B->resident;
+// The side stream, forked from the caller's and joined back to it.
+static hipError_t batch_fork_side(const nbb_batch *B, hipStream_t s) {
+    hipError_t e = hipEventRecord(B->fork, s);
+    return e == hipSuccess ? hipStreamWaitEvent(B->side, B->fork, 0) : e;
+}
+static hipError_t batch_join_side(const nbb_batch *B, hipStream_t s) {
+    hipError_t e = hipEventRecord(B->join, B->side);
+    return e == hipSuccess ? hipStreamWaitEvent(s, B->join, 0) : e;
+}
+// Enqueues the launch of a resident set: its instances take steps_all
+// generations, or, where `n` holds one count for each, those, which go to the
+// batch's device array first.
+static hipError_t batch_step_resident(const ResidentSet &R, uint8_t *a, uint8_t *b, uint32_t rule,
+                                      const std::vector<uint32_t> &n, uint32_t steps_all, hipStream_t rs) {
     const uint32_t count = uint32_t(R.index.size());
-    if (!count) return hipSuccess;
-    std::vector<uint32_t> n;
     bool any = steps_all != 0;
-    if (steps) {
-        n.resize(count);
-        for (uint32_t j = 0; j < count; ++j) any |= (n[j] = steps[R.index[j]]) != 0;
-    }
-    if (!any) return hipSuccess;
-    hipStream_t rs = s;
-    if (B->side) {
-        hipError_t e = hipEventRecord(B->fork, s);
-        if (e == hipSuccess) e = hipStreamWaitEvent(B->side, B->fork, 0);
-        if (e != hipSuccess) return e;
-        rs = B->side;
-    }
-    if (steps) {
+    for (uint32_t v : n) any |= v != 0;
+    if (!count || !any) return hipSuccess;
+    if (!n.empty()) {
         hipError_t e = launch_set_words(R.steps, n.data(), count, rs);
         if (e != hipSuccess) return e;
     }
-    hipError_t e = launch_step_resident(R.plans, R.inst, count, steps ? R.steps : nullptr, steps_all, R.lds, a, b,
-                                        rule, rs);
-    if (e == hipSuccess && B->side) e = hipEventRecord(B->join, B->side);
-    *launched_ = e == hipSuccess;
-    return e;
-}
-static hipError_t batch_join_resident(const nbb_batch *B, hipStream_t s, bool launched_) {
-    return (launched_ && B->side) ? hipStreamWaitEvent(s, B->join, 0) : hipSuccess;
+    return launch_step_resident(R.plans, R.inst, count, n.empty() ? nullptr : R.steps, steps_all, R.lds, a, b, rule, rs);
 }
 // The group streams start after the work enqueued on s so far; group k's
 // launches go to batch_group_stream(B, k, s); batch_join_groups makes s wait
 // for all of them.  Groups touch disjoint instance ranges of the arenas
 // (a window read past a block's bytes may reach into another instance's
 // range, but those bytes are not used), so they need no order between them.
-static hipError_t batch_fork_groups(const nbb_batch *B, hipStream_t s) {
-    if (B->gstream.empty()) return hipSuccess;
+static size_t batch_lane_streams(const nbb_batch *B, size_t lanes) {
+    return std::min(B->gstream.size(), lanes ? lanes - 1 : size_t(0));
+}
+static hipError_t batch_fork_groups(const nbb_batch *B, size_t lanes, hipStream_t s) {
+    const size_t n = batch_lane_streams(B, lanes);
+    if (!n) return hipSuccess;
     hipError_t e = hipEventRecord(B->gfork, s);
-    for (size_t i = 0; i < B->gstream.size() && e == hipSuccess; ++i) e = hipStreamWaitEvent(B->gstream[i], B->gfork, 0);
+    for (size_t i = 0; i < n && e == hipSuccess; ++i) e = hipStreamWaitEvent(B->gstream[i], B->gfork, 0);
     return e;
 }
 static hipStream_t batch_group_stream(const nbb_batch *B, size_t k, hipStream_t s) {
@@ -1975,23 +2002,92 @@ static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t a
     *out_ = out;
     return hipSuccess;
 }
-static hipError_t held_step_small(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t arena_len, uint32_t steps,
-                                  const uint32_t *counts, uint32_t rule, hipStream_t s) {
-    hipError_t e = hipSuccess;
-    for (size_t k = 0; k < B->small.size() && e == hipSuccess; ++k) {
-        bool used = false;
-        e = held_step(B->small[k], a, b, arena_len, steps, counts, rule,
-                      batch_group_stream(B, B->groups.size() + k, s), &used);
+// What a call does with the instances counted as resident: one LDS launch of
+// all of them, or the held sets of `small`, one after the other or spread over
+// the group streams, and an LDS launch of the rest.
+struct ResidentUse {
+    bool held;               // `small` takes its launches
+    bool spread;             // over the group streams
+    const ResidentSet *lds;  // the set of the LDS launch
+    bool side;               // it, and held sets in turn, run on the side stream, else in lane `own`
+    size_t own, first;       // ...; lane of the first set where they are spread
+    size_t lanes;            // all lanes: the groups (or the DIRECT instances), and these
+};
+// The least estimated time.  An LDS launch costs one launch and kLdsPassUs per
+// pass of the longest instance, each held set a launch of its own kernel and
+// less per generation, streams their forks and joins.  Measured (us per call;
+// LDS / held sets on streams of their own): 64 instances of 400 to 3,000 cells
+// of 2 / 4 / 8 fractals, 4 generations 9 / 35, 10 / 60, 10 / 81, 32 generations
+// 41 / 36, 48 / 59, 48 / 82; of 3,000 to 20,000 cells 38 / 35, 38 / 59, 47 / 78
+// and 230 / 36, 229 / 65, 312 / 83.  One fractal is one launch in either form: held.
+constexpr double kLdsPassUs = 1.15, kLaunchUs = 4.2, kLaunchFixedUs = 2.7, kForkUs = 17.6, kStreamUs = 8.7;
+static ResidentUse resident_use(const nbb_batch *B, uint32_t steps, const uint32_t *counts) {
+    ResidentUse u{!B->small.empty(), false, &B->resident, false, 0, 0, 0};
+    const size_t base = batch_base_lanes(B), n = B->small.size(), rest = B->resident.index.empty() ? 0 : 1;
+    if (!B->resident_all.index.empty()) {
+        auto lds_us = [&](const ResidentSet &R) {
+            uint64_t passes = uint64_t(R.most_passes) * steps;
+            for (size_t j = 0; j < R.index.size() && counts; ++j)
+                passes = std::max(passes, uint64_t(R.passes[j]) * counts[R.index[j]]);
+            return passes ? std::max(kLaunchUs, kLaunchFixedUs + kLdsPassUs * R.rounds * double(passes)) : 0.0;
+        };
+        const double lds = lds_us(B->resident_all);
+        double in_turn = lds_us(B->resident), longest = in_turn;
+        for (const HeldSet &S : B->small) {
+            uint32_t most = counts ? 0 : steps;
+            if (counts)
+                for (uint32_t i : S.index) most = std::max(most, counts[i]);
+            const double t = kLaunchFixedUs + S.gen_us * most;
+            in_turn += most ? std::max(kLaunchUs, t) : 0.0;
+            longest = std::max(longest, t);
+        }
+        const size_t streams = batch_lane_streams(B, base + rest + n) - batch_lane_streams(B, base);
+        const double spread = std::max(kForkUs + kStreamUs * double(streams) + kLaunchUs * double(n + rest), longest);
+        u.held = std::min(in_turn, spread) < lds;
+        u.spread = u.held && spread < in_turn;
+        if (!u.held) u.lds = &B->resident_all;
     }
-    return e;
+    const bool alone = !u.lds->index.empty() || (u.held && !u.spread);
+    u.side = alone && B->side;
+    u.own = base;
+    u.first = base + (alone && !u.side);
+    u.lanes = u.first + (u.spread ? n : 0);
+    return u;
 }
-static hipError_t batch_join_groups(const nbb_batch *B, hipStream_t s) {
+static hipError_t batch_join_groups(const nbb_batch *B, size_t lanes, hipStream_t s) {
     hipError_t e = hipSuccess;
-    for (size_t i = 0; i < B->gstream.size() && e == hipSuccess; ++i) {
+    const size_t n = batch_lane_streams(B, lanes);
+    for (size_t i = 0; i < n && e == hipSuccess; ++i) {
         e = hipEventRecord(B->gjoin[i], B->gstream[i]);
         if (e == hipSuccess) e = hipStreamWaitEvent(s, B->gjoin[i], 0);
     }
     return e;
+}
+
+// Forks the streams of a call, and enqueues its resident and held sets (counts:
+// nbb_batch_step_each's, with n_lds those of use.lds).  What was forked has to be
+// joined also after an error, so that s does not run ahead of what was enqueued
+// on the other streams.
+static hipError_t batch_step_small(const nbb_batch *B, const ResidentUse &use, uint8_t *a, uint8_t *b,
+                                   uint64_t arena_len, uint32_t steps, const uint32_t *counts,
+                                   const std::vector<uint32_t> &n_lds, uint32_t rule, hipStream_t s) {
+    hipError_t e = use.side ? batch_fork_side(B, s) : hipSuccess;
+    const hipError_t eg = batch_fork_groups(B, use.lanes, s);
+    if (e == hipSuccess) e = eg;
+    const hipStream_t rs = use.side ? B->side : batch_group_stream(B, use.own, s);
+    if (e == hipSuccess) e = batch_step_resident(*use.lds, a, b, rule, n_lds, steps, rs);
+    for (size_t k = 0; k < B->small.size() && use.held && e == hipSuccess; ++k) {
+        bool used = false;
+        e = held_step(B->small[k], a, b, arena_len, steps, counts, rule,
+                      use.spread ? batch_group_stream(B, use.first + k, s) : rs, &used);
+    }
+    return e;
+}
+static nbb_status batch_joined(const nbb_batch *B, const ResidentUse &use, hipStream_t s, hipError_t e) {
+    const hipError_t eg = batch_join_groups(B, use.lanes, s), es = use.side ? batch_join_side(B, s) : hipSuccess;
+    if (e != hipSuccess) return hip_fail(e, "batch step launch");
+    if (eg != hipSuccess) return hip_fail(eg, "batch group join");
+    return es == hipSuccess ? NBB_OK : hip_fail(es, "batch side join");
 }
 
 nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t arena_len, uint32_t steps,
@@ -2009,13 +2105,9 @@ nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t a
     if (result_in_b) *result_in_b = int(steps & 1);
     if (!steps) return NBB_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    bool res_launched = false;
-    e = batch_fork_resident(B, a, b, rule, nullptr, steps, s, &res_launched);
-    if (e != hipSuccess) return hip_fail(e, "batch resident step launch");
-    e = batch_fork_groups(B, s);
-    if (e != hipSuccess) return hip_fail(e, "batch group fork");
+    const ResidentUse use = resident_use(B, steps, nullptr);
     // the small sets first: one long launch each, beside what follows
-    e = held_step_small(B, a, b, arena_len, steps, nullptr, rule, s);
+    e = batch_step_small(B, use, a, b, arena_len, steps, nullptr, {}, rule, s);
     // each group takes all its generations on its stream
     for (size_t k = 0; k < B->groups.size() && e == hipSuccess; ++k) {
         const BatchGroup &G = B->groups[k];
@@ -2032,7 +2124,6 @@ nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t a
             std::swap(in, out);
         }
     }
-    const char *what = "batch step launch";
     for (size_t j = 0; j < B->direct.size() && e == hipSuccess; ++j) {
         const nbb_fractal *F = B->direct[j].f;
         const uint64_t off = B->direct[j].offset;
@@ -2042,15 +2133,8 @@ nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t a
                                    map_grid(F, F->f.cells), s);
             std::swap(in, out);
         }
-        what = "batch direct step launch";
     }
-    // joined also after a failed launch, so that s does not run ahead of
-    // what was enqueued on the other streams
-    const hipError_t ej = batch_join_groups(B, s);
-    if (e != hipSuccess) return hip_fail(e, what);
-    if (ej != hipSuccess) return hip_fail(ej, "batch group join");
-    e = batch_join_resident(B, s, res_launched);
-    return e == hipSuccess ? NBB_OK : hip_fail(e, "batch resident join");
+    return batch_joined(B, use, s, e);
 }
 NBB_CATCH
 
@@ -2074,6 +2158,7 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
             most = std::max(most, steps[G.index[j]]);
         }
     for (const BatchDirect &d : B->direct) most = std::max(most, steps[d.index]);
+    const ResidentUse use = resident_use(B, 0, steps);
     // Generation g steps, in each group, the prefix of instances with more
     // than g steps; instance i's state alternates a -> b -> a ... like the
     // whole batch's, so its result ends in b iff steps[i] is odd.
@@ -2083,25 +2168,20 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
     bool count = false;
     uint32_t L = 0, n_most = 0;
     for (const BatchGroup &G : B->groups) count = count || (held_use(G.held, 0, steps, &L, &n_most) && n_most);
-    for (const HeldSet &S : B->small) count = count || (held_use(S, 0, steps, &L, &n_most) && n_most);
-    std::vector<uint32_t> n;  // (before the forks: an allocation that fails must not skip the joins)
+    for (const HeldSet &S : B->small)
+        count = count || (use.held && held_use(S, 0, steps, &L, &n_most) && n_most);
+    std::vector<uint32_t> n, n_lds;  // (before the forks: an allocation that fails must not skip the joins)
     if (count) {
         for (const BatchGroup &G : B->groups)
             for (uint32_t i : G.held.index) n.push_back(steps[i]);
         for (const HeldSet &S : B->small)
             for (uint32_t i : S.index) n.push_back(steps[i]);
     }
-    bool res_launched = false;
-    e = batch_fork_resident(B, a, b, rule, steps, 0, s, &res_launched);
-    if (e != hipSuccess) return hip_fail(e, "batch resident step launch");
+    for (uint32_t i : use.lds->index) n_lds.push_back(steps[i]);
+    // before the forks: launches on any of the streams read them
     if (count) e = launch_set_words(B->counts, n.data(), uint32_t(n.size()), s);
-    if (e != hipSuccess) {
-        (void)batch_join_resident(B, s, res_launched);
-        return hip_fail(e, "batch step counts");
-    }
-    e = batch_fork_groups(B, s);
-    if (e != hipSuccess) return hip_fail(e, "batch group fork");
-    e = held_step_small(B, a, b, arena_len, 0, steps, rule, s);
+    if (e != hipSuccess) return hip_fail(e, "batch step counts");
+    e = batch_step_small(B, use, a, b, arena_len, 0, steps, n_lds, rule, s);
     for (size_t k = 0; k < B->groups.size() && e == hipSuccess; ++k) {
         const BatchGroup &G = B->groups[k];
         const hipStream_t gs = batch_group_stream(B, k, s);
@@ -2129,7 +2209,6 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
             std::swap(in, out);
         }
     }
-    const char *what = "batch step launch";
     for (size_t j = 0; j < B->direct.size() && e == hipSuccess; ++j) {
         const BatchDirect &d = B->direct[j];
         const nbb_fractal *F = d.f;
@@ -2139,14 +2218,8 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
                                    map_grid(F, F->f.cells), s);
             std::swap(in, out);
         }
-        what = "batch direct step launch";
     }
-    const hipError_t ej = batch_join_groups(B, s);
-    if (e != hipSuccess) return hip_fail(e, what);
-    if (ej != hipSuccess) return hip_fail(ej, "batch group join");
-    e = batch_join_resident(B, s, res_launched);
-    if (e != hipSuccess) return hip_fail(e, "batch resident join");
-    return NBB_OK;
+    return batch_joined(B, use, s, e);
 }
 NBB_CATCH
 

@@ -58,3 +58,56 @@ def test_step_counts_upload_only_for_launches_that_read_them(N, counts, launches
     o = O.Fractal(2, W.TRIANGLE.offsets, 11)
     np.testing.assert_array_equal(batch.state(b if counts[0] & 1 else a, 0).cpu().numpy(),
                                   o.compact_steps(o.init_compact(0, 0.45), B3S23, counts[0]))
+
+
+SETS = [("triangle", 5), ("carpet", 3), ("hfractal", 3), ("chandelier", 5)]
+
+
+def test_short_calls_on_many_fractals_take_one_launch(N):
+    # small instances of four fractals: one LDS launch while the generations
+    # are few, a held launch for each fractal where that pays
+    frs, batch, a, b = make(N, SETS * 3)
+    s = batch.step_info()
+    assert s.held_whole == 12 and s.lds_resident == 0 and batch.info().groups == 0
+    for steps in (1, 2, 4):
+        assert nodes(lambda st: batch.step(a, b, steps, stream=st)) == 1
+    assert nodes(lambda st: batch.step(a, b, 200, stream=st)) == 4
+    assert nodes(lambda st: batch.step_each(a, b, [1] * 12, stream=st)) == 2  # with the counts
+    frs, batch, a, b = make(N, SETS[:1] * 12)  # one fractal: one launch in either form
+    assert nodes(lambda st: batch.step(a, b, 1, stream=st)) == 1
+
+
+# held sets of several fractals; beside them what only the LDS launch takes
+# (small squares and a 12-cell block), instances of groups, per-cell ones
+REST = [("grid4_12", 2), ("fullsquare", 2)]
+GROUPS = [("triangle", 12), ("carpet", 6), ("hfractal", 7), ("chandelier", 9), ("vicsek", 8)]
+
+
+@pytest.mark.parametrize("kinds", [SETS, SETS + REST, SETS + GROUPS[:1], SETS + REST + GROUPS[:2], SETS + REST + GROUPS,
+                                   SETS[:1] + REST + GROUPS, SETS + ["direct"], SETS + REST + GROUPS[:2] + ["direct"]])
+def test_every_route_against_oracle(N, kinds):
+    specs = [k for k in kinds if k != "direct"]
+    frs = [N.Fractal(W.FRACTALS[n].s, W.FRACTALS[n].offsets, r) for n, r in specs]
+    if "direct" in kinds:
+        frs.append(N.Fractal(2, W.TRIANGLE.offsets, 6))
+        frs[-1].configure(N.STRATEGY_DIRECT)
+    batch = N.Batch(frs, resident=True)
+    orcs = [O.Fractal(f.s, f.offsets, f.r) for f in frs]
+    a, b = batch.new_arena(), batch.new_arena()
+    st0 = [o.init_compact(90 + i, 0.45) for i, o in enumerate(orcs)]
+    for steps in (1, 3, 8, 20, 70):
+        for each in (False, True):
+            a.fill_(7)
+            b.fill_(7)
+            for i, st in enumerate(st0):
+                batch.state(a, i).copy_(torch.from_numpy(st))
+            counts = [max(0, steps - (i % 3)) if each else steps for i in range(len(frs))]
+            if each:
+                batch.step_each(a, b, counts)
+            else:
+                batch.step(a, b, steps)
+            ha, hb = a.cpu().numpy(), b.cpu().numpy()
+            for i, (o, st, off) in enumerate(zip(orcs, st0, batch.offsets)):
+                got = (hb if counts[i] & 1 else ha)[off:off + len(st)]
+                np.testing.assert_array_equal(got, o.compact_steps(st, B3S23, counts[i]),
+                                              err_msg=f"{frs[i].k},{frs[i].r} {counts[i]} generations")
