@@ -1575,54 +1575,101 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         H.plan = batch_hold_plan(top, d, gpw);
         if (H.plan && held_members(H, d.m)) held[g] = std::move(H);
     }
-    // One device allocation: per group the instance table, the records
-    // (2 words per tile, 4 for the matrix form) and the neighbour table (8
-    // words per tile); per resident group its instance table.
-    std::vector<size_t> off_inst(ng), off_rec(ng), off_nbr(ng), ntiles(ng);
+    struct ResidentBuild {
+        const Part &part;
+        ResidentSet &set;
+        std::vector<TileParams> plans;
+        std::vector<ResidentInstance> inst;
+        size_t off_plans = 0, off_inst = 0, off_steps = 0;
+    } resident_build[2] = {{res, B->resident, {}, {}}, {res_all, B->resident_all, {}, {}}};
+    for (ResidentBuild &build : resident_build) {
+        const Part &part = build.part;
+        if (part.reps.empty()) continue;
+        // tiles per pass per plan: as many (up to 4) as the registers and LDS
+        // allow for the plan's largest instance
+        const uint32_t lds_budget = device_lds_per_group();
+        ResidentSet &R = build.set;
+        for (size_t g = 0; g < part.reps.size(); ++g) {
+            const TileParams &tp = part.reps[g]->res_tp;
+            build.plans.push_back(tp);
+            uint32_t most = 1;
+            for (const BatchInstance &I : part.members[g]) most = std::max(most, I.ntiles);
+            uint32_t teams = 1;
+            for (uint32_t t : {4u, 2u})
+                if (t <= most && resident_fits(tp, t) && resident_lds_bytes(tp, most, t) <= lds_budget) {
+                    teams = t;
+                    break;
+                }
+            R.lds = std::max(R.lds, resident_lds_bytes(tp, most, teams));
+            for (size_t j = 0; j < part.members[g].size(); ++j) {
+                const BatchInstance &I = part.members[g][j];
+                build.inst.push_back({I.nbr, I.base16, I.ntiles, uint32_t(g), teams});
+                R.index.push_back(part.index[g][j]);
+                R.passes.push_back((I.ntiles + teams - 1) / teams);
+                R.most_passes = std::max(R.most_passes, R.passes.back());
+            }
+        }
+        const uint32_t fit = uint32_t(part.reps[0]->cu_count) * std::max(1u, std::min(8u, lds_budget / std::max(R.lds, 1u)));
+        R.rounds = uint32_t((R.index.size() + fit - 1) / fit);
+    }
+    // One device allocation.  First the tables made here, one copy and one wait
+    // for all of them: per group and held set the instances, per resident set
+    // plans and instances.
     size_t total = 0;
+    struct HostTable {
+        const void *src;
+        size_t bytes, off;
+    };
+    std::vector<HostTable> tables;
+    auto place = [&](const void *src, size_t bytes) {
+        tables.push_back({src, bytes, total});
+        total += align256(bytes);
+        return tables.back().off;
+    };
+    std::vector<size_t> off_inst(ng), off_rec(ng), off_nbr(ng), ntiles(ng);
     for (size_t g = 0; g < ng; ++g) {
         uint64_t t = 0;
         if (mat[g].plan) {
             for (const BatchInstance &I : launch.members[g]) B->tiles += I.ntiles;
             t = mat[g].members.back().tile0 + mat[g].members.back().ntiles;
-            ntiles[g] = t;
-            B->step_tiles += t;
-            off_inst[g] = total;
-            total += align256(mat[g].members.size() * sizeof(MatInstance));
-            off_rec[g] = total;
-            total += align256(t * 16);
-            off_nbr[g] = total;
-            total += align256(t * 32);
-            continue;
-        }
-        for (BatchInstance &I : launch.members[g]) {
-            I.tile0 = uint32_t(t);
-            t += I.ntiles;
-        }
-        B->step_tiles += t;
-        if (t * 8 > (uint64_t(1) << 31)) {
-            return fail(NBB_E_RANGE, "too many tiles in one group of the batch");
+            off_inst[g] = place(mat[g].members.data(), mat[g].members.size() * sizeof(MatInstance));
+        } else {
+            for (BatchInstance &I : launch.members[g]) {
+                I.tile0 = uint32_t(t);
+                t += I.ntiles;
+            }
+            if (t * 8 > (uint64_t(1) << 31)) return fail(NBB_E_RANGE, "too many tiles in one group of the batch");
+            B->tiles += t;
+            off_inst[g] = place(launch.members[g].data(), launch.members[g].size() * sizeof(BatchInstance));
         }
         ntiles[g] = t;
-        B->tiles += t;
-        off_inst[g] = total;
-        total += align256(launch.members[g].size() * sizeof(BatchInstance));
-        off_rec[g] = total;
-        total += align256(std::max<size_t>(t * 8, 1));
-        off_nbr[g] = total;
-        total += align256(std::max<size_t>(t * 32, 1));
+        B->step_tiles += t;
     }
-    auto place_held = [&](HeldBuild &H) {
-        if (!H.plan) return;
-        H.off_inst = total;
-        total += align256(H.members.size() * sizeof(MatInstance));
-        H.off_rec = total;
-        total += align256(H.tiles * 16);
-        H.off_nbr = total;
-        total += align256(H.tiles * 32);
-    };
-    for (HeldBuild &H : held) place_held(H);
-    for (HeldBuild &H : small) place_held(H);
+    for (std::vector<HeldBuild> *v : {&held, &small})
+        for (HeldBuild &H : *v)
+            if (H.plan) H.off_inst = place(H.members.data(), H.members.size() * sizeof(MatInstance));
+    for (ResidentBuild &R : resident_build)
+        if (!R.inst.empty()) {
+            R.off_plans = place(R.plans.data(), R.plans.size() * sizeof(TileParams));
+            R.off_inst = place(R.inst.data(), R.inst.size() * sizeof(ResidentInstance));
+        }
+    const size_t host_bytes = total;
+    // then those made on the device: the records (2 words per tile, 4 for the
+    // matrix form) and the neighbour tables (8 words per tile), and step counts
+    for (size_t g = 0; g < ng; ++g) {
+        off_rec[g] = total;
+        total += align256(ntiles[g] * (mat[g].plan ? 16 : 8));
+        off_nbr[g] = total;
+        total += align256(ntiles[g] * 32);
+    }
+    for (std::vector<HeldBuild> *v : {&held, &small})
+        for (HeldBuild &H : *v)
+            if (H.plan) {
+                H.off_rec = total;
+                total += align256(H.tiles * 16);
+                H.off_nbr = total;
+                total += align256(H.tiles * 32);
+            }
     const size_t off_counts = total;
     size_t ncounts = 0;
     for (std::vector<HeldBuild> *v : {&held, &small})
@@ -1631,27 +1678,16 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
                 H.off_steps = off_counts + 4 * ncounts;
                 ncounts += H.members.size();
             }
-    total += ncounts ? align256(4 * ncounts) : 0;
+    total += align256(4 * ncounts);
+    for (ResidentBuild &R : resident_build) {
+        R.off_steps = total;
+        total += align256(R.inst.size() * sizeof(uint32_t));
+    }
     for (const auto &members : res.members)
         for (const BatchInstance &I : members) {
             B->tiles += I.ntiles;
             B->step_tiles += I.ntiles;
         }
-    struct ResidentBuild {
-        const Part &part;
-        ResidentSet &set;
-        size_t off_plans = 0, off_inst = 0, off_steps = 0;
-    } resident_build[2] = {{res, B->resident}, {res_all, B->resident_all}};
-    for (ResidentBuild &R : resident_build) {
-        size_t n = 0;
-        for (const auto &members : R.part.members) n += members.size();
-        R.off_plans = total;
-        total += n ? align256(R.part.reps.size() * sizeof(TileParams)) : 0;
-        R.off_inst = total;
-        total += n ? align256(n * sizeof(ResidentInstance)) : 0;
-        R.off_steps = total;
-        total += n ? align256(n * sizeof(uint32_t)) : 0;
-    }
     if (fixed && total > fixed_cap) {
         return fail(NBB_E_RANGE, "batch tables (" + std::to_string(total) + " bytes) exceed the " +
                                      std::to_string(fixed_cap) + "-byte no-allocation scratch");
@@ -1668,16 +1704,27 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *base = fixed ? reinterpret_cast<char *>(fixed) : static_cast<char *>(B->dtab.ptr);
     if (ncounts) B->counts = reinterpret_cast<uint32_t *>(base + off_counts);
+    if (fixed) {
+        static_assert(sizeof(BatchInstance) % 4 == 0, "instance records upload as words");
+        for (const HostTable &t : tables) {
+            e = launch_set_words(reinterpret_cast<uint32_t *>(base + t.off), static_cast<const uint32_t *>(t.src),
+                                 uint32_t(t.bytes / 4), s);
+            if (e != hipSuccess) return hip_fail(e, "batch table build");
+        }
+    } else if (host_bytes) {
+        std::vector<uint8_t> staged(host_bytes);
+        for (const HostTable &t : tables) std::memcpy(staged.data() + t.off, t.src, t.bytes);
+        e = hipMemcpyAsync(base, staged.data(), host_bytes, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);  // `staged` goes out of scope
+        if (e != hipSuccess) return hip_fail(e, "batch table build");
+    }
     auto make_held = [&](const HeldBuild &H, HeldSet *S) -> hipError_t {
         if (!H.plan) return hipSuccess;
         auto *inst = reinterpret_cast<MatInstance *>(base + H.off_inst);
         auto *rec = reinterpret_cast<uint32_t *>(base + H.off_rec);
         auto *nbr = reinterpret_cast<uint32_t *>(base + H.off_nbr);
-        hipError_t err = hipMemcpyAsync(inst, H.members.data(), H.members.size() * sizeof(MatInstance),
-                                        hipMemcpyHostToDevice, s);
-        if (err == hipSuccess) err = hipStreamSynchronize(s);  // the host table goes out of scope
-        if (err == hipSuccess)
-            err = launch_batch_tiles_matrix(inst, uint32_t(H.members.size()), uint32_t(H.tiles), rec, nbr, s);
+        const hipError_t err =
+            launch_batch_tiles_matrix(inst, uint32_t(H.members.size()), uint32_t(H.tiles), rec, nbr, s);
         if (err != hipSuccess) return err;
         const HoldPlan &p = H.plan->plan;
         S->ok = true;
@@ -1713,10 +1760,7 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         if (mat[g].plan) {
             const std::vector<MatInstance> &mem = mat[g].members;
             auto *minst = reinterpret_cast<MatInstance *>(base + off_inst[g]);
-            e = hipMemcpyAsync(minst, mem.data(), mem.size() * sizeof(MatInstance), hipMemcpyHostToDevice, s);
-            if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host table goes out of scope
-            if (e == hipSuccess)
-                e = launch_batch_tiles_matrix(minst, uint32_t(mem.size()), uint32_t(ntiles[g]), rec, nbr, s);
+            e = launch_batch_tiles_matrix(minst, uint32_t(mem.size()), uint32_t(ntiles[g]), rec, nbr, s);
             if (e != hipSuccess) {
                 return hip_fail(e, "batch table build");
             }
@@ -1742,18 +1786,7 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             B->cu_count = launch.reps[g]->cu_count;
             continue;
         }
-        static_assert(sizeof(BatchInstance) % 4 == 0, "instance records upload as words");
-        if (fixed) {
-            e = launch_set_words(reinterpret_cast<uint32_t *>(inst),
-                                 reinterpret_cast<const uint32_t *>(launch.members[g].data()),
-                                 uint32_t(launch.members[g].size() * sizeof(BatchInstance) / 4), s);
-        } else {
-            e = hipMemcpyAsync(inst, launch.members[g].data(), launch.members[g].size() * sizeof(BatchInstance),
-                               hipMemcpyHostToDevice, s);
-            if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host table goes out of scope
-        }
-        if (e == hipSuccess)
-            e = launch_batch_tiles(inst, uint32_t(launch.members[g].size()), uint32_t(ntiles[g]), rec, nbr, s);
+        e = launch_batch_tiles(inst, uint32_t(launch.members[g].size()), uint32_t(ntiles[g]), rec, nbr, s);
         if (e != hipSuccess) {
             return hip_fail(e, "batch table build");
         }
@@ -1778,50 +1811,12 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
         B->groups.push_back(std::move(G));
         B->cu_count = launch.reps[g]->cu_count;
     }
-    for (const ResidentBuild &build : resident_build) {
-        const Part &part = build.part;
-        const size_t np = part.reps.size();
-        if (!np) continue;
-        // tiles per pass per plan: as many (up to 4) as the registers and LDS
-        // allow for the plan's largest instance
-        const uint32_t lds_budget = device_lds_per_group();
-        std::vector<TileParams> plans(np);
-        std::vector<ResidentInstance> rinst;
-        ResidentSet &R = build.set;
-        for (size_t g = 0; g < np; ++g) {
-            plans[g] = part.reps[g]->res_tp;
-            uint32_t most = 1;
-            for (const BatchInstance &I : part.members[g]) most = std::max(most, I.ntiles);
-            uint32_t teams = 1;
-            for (uint32_t t : {4u, 2u})
-                if (t <= most && resident_fits(plans[g], t) && resident_lds_bytes(plans[g], most, t) <= lds_budget) {
-                    teams = t;
-                    break;
-                }
-            R.lds = std::max(R.lds, resident_lds_bytes(plans[g], most, teams));
-            for (size_t j = 0; j < part.members[g].size(); ++j) {
-                const BatchInstance &I = part.members[g][j];
-                rinst.push_back({I.nbr, I.base16, I.ntiles, uint32_t(g), teams});
-                R.index.push_back(part.index[g][j]);
-                R.passes.push_back((I.ntiles + teams - 1) / teams);
-                R.most_passes = std::max(R.most_passes, R.passes.back());
-            }
+    for (const ResidentBuild &R : resident_build)
+        if (!R.inst.empty()) {
+            R.set.plans = reinterpret_cast<TileParams *>(base + R.off_plans);
+            R.set.inst = reinterpret_cast<ResidentInstance *>(base + R.off_inst);
+            R.set.steps = reinterpret_cast<uint32_t *>(base + R.off_steps);
         }
-        auto *dplans = reinterpret_cast<TileParams *>(base + build.off_plans);
-        auto *dinst = reinterpret_cast<ResidentInstance *>(base + build.off_inst);
-        e = hipMemcpyAsync(dplans, plans.data(), np * sizeof(TileParams), hipMemcpyHostToDevice, s);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(dinst, rinst.data(), rinst.size() * sizeof(ResidentInstance), hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host tables go out of scope
-        if (e != hipSuccess) {
-            return hip_fail(e, "batch table build");
-        }
-        const uint32_t fit = uint32_t(part.reps[0]->cu_count) * std::max(1u, std::min(8u, lds_budget / std::max(R.lds, 1u)));
-        R.rounds = uint32_t((R.index.size() + fit - 1) / fit);
-        R.plans = dplans;
-        R.inst = dinst;
-        R.steps = reinterpret_cast<uint32_t *>(base + build.off_steps);
-    }
     for (const BatchDirect &d : B->direct) B->cu_count = d.f->cu_count;
     // a side stream where resident and held sets run beside as many groups as
     // have streams (not otherwise: five streams share the four hardware queues,
