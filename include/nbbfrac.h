@@ -481,7 +481,7 @@ nbb_status nbb_batch_query_step(const nbb_batch *batch, nbb_batch_step_info *inf
  * instance's range, never past arena_len; those bytes are not used).  Only
  * the result is
  * specified: an instance's range in the other arena holds some earlier
- * generation (instances stepped in LDS leave it untouched).
+ * generation (resident instances leave it untouched).
  */
 nbb_status nbb_batch_step(const nbb_batch *batch, uint8_t *a, uint8_t *b, uint64_t arena_len, uint32_t steps,
                           uint32_t rule, int *result_in_b, void *stream);

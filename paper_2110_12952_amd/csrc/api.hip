@@ -1957,8 +1957,8 @@ static bool held_use(const HeldSet &S, uint32_t steps, const uint32_t *counts, u
     return S.whole || 2 * uint64_t(*launches) + 2 <= *most;
 }
 // `steps` generations of every instance of the set, or counts[i] of instance
-// i.  Sets of whole instances take all of them in place and write the result
-// where it belongs; others take all but the last several at a time and the
+// i.  Sets of whole instances take all of them in the arena that the result
+// belongs to and leave the other one as it is; others take all but the last several at a time and the
 // last by itself, so that the other arena ends with the generation before, as
 // with one launch per generation.  *used = false (nothing enqueued) where
 // held_use says so.  *last: the last
@@ -1983,8 +1983,11 @@ static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t a
             if (!live) break;
             E.ntiles = uint32_t(S.tiles_end[live - 1]);
         }
-        uint8_t *dst = S.whole && !counts && (i + 1 < L || !(steps & 1)) ? a : out;
-        hipError_t e = go(E, in, dst, counts ? 0 : T / L + (i < T % L ? 1u : 0u), i, S.whole ? kHoldWhole : kHoldMost);
+        if (S.whole && !counts) {  // (with counts the kernel does it by the instance's own)
+            if (!(steps & 1)) out = a;
+            else if (i) in = b;
+        }
+        hipError_t e = go(E, in, out, counts ? 0 : T / L + (i < T % L ? 1u : 0u), i, S.whole ? kHoldWhole : kHoldMost);
         if (e != hipSuccess) return e;
         if (!S.whole) std::swap(in, out);
     }

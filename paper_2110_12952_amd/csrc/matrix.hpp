@@ -377,8 +377,9 @@ static hipError_t launch_matrix_t(const MatParams &E, const uint8_t *in, uint8_t
 //     kHoldLast  the last generation: from `in` to `out` for odd n, from `out`
 //                to `in` for even n
 //     kHoldWhole  number `launch` of those that take all n (tiles that are
-//                whole instances): back to `in`, an instance's last one to
-//                `out` if n is odd
+//                whole instances): in place in `in` for even n, for odd n from
+//                `in` to `out` by the first and in place there by the others,
+//                so that the other arena is untouched
 //   Not BATCH, kHoldWhole (the state is one tile): the whole call in one
 //   launch, generation `gens` to out if odd, else to in, and the generation
 //   before it to the other (every load has ended before the first barrier).
@@ -417,7 +418,10 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
                 if (mode == kHoldMost) L += (L ^ T) & 1;
                 if (launch >= L) return;
                 gens = T / L + (launch < T % L ? 1u : 0u);
-                if (mode == kHoldWhole && (launch + 1 < L || !(n & 1))) out = in;
+                if (mode == kHoldWhole) {
+                    if (!(n & 1)) out = in;
+                    else if (launch) in = out;
+                }
             }
         }
     }

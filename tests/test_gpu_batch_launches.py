@@ -111,3 +111,21 @@ def test_every_route_against_oracle(N, kinds):
                 got = (hb if counts[i] & 1 else ha)[off:off + len(st)]
                 np.testing.assert_array_equal(got, o.compact_steps(st, B3S23, counts[i]),
                                               err_msg=f"{frs[i].k},{frs[i].r} {counts[i]} generations")
+
+
+@pytest.mark.parametrize("steps", [4097, 4098, 8193, 12291])
+def test_resident_instances_leave_the_other_arena(N, steps):
+    # more generations than one held launch takes, in one, two and four launches
+    frs, batch, a, b = make(N, [("triangle", 3), ("triangle", 5), ("triangle", 4)])
+    assert batch.step_info().held_whole == 3
+    orcs = [O.Fractal(f.s, f.offsets, f.r) for f in frs]
+    a0 = a.clone()
+    for counts in ([steps] * 3, [steps, steps - 1, 5]):
+        a.copy_(a0)
+        b.fill_(9)
+        batch.step_each(a, b, counts) if len(set(counts)) > 1 else batch.step(a, b, steps)
+        for i, o in enumerate(orcs):
+            sa, sb, st = (batch.state(t, i).cpu().numpy() for t in (a, b, a0))
+            got, other = (sb, sa) if counts[i] & 1 else (sa, sb)
+            np.testing.assert_array_equal(got, o.compact_steps(st, B3S23, counts[i]), err_msg=f"{i} {counts}")
+            np.testing.assert_array_equal(other, st if counts[i] & 1 else np.full_like(st, 9), err_msg=f"{i} {counts}")
