@@ -73,10 +73,15 @@ typedef enum {
 #define NBB_RULE_VON_NEUMANN (1u << 31)
 
 /* How nbb_step_compact evaluates a step (nbb_configure).  TILED runs the step
- * on the matrix cores, at tile levels of its own, for every fractal that has
- * a block level with 16 to 64 cells (k = 2 to 8 and 16): one generation per
- * launch, or in calls of several up to the generations that the cells held
- * around a tile allow (both buffers end as with one launch per generation).
+ * on the matrix cores, at tile levels of its own, for fractals of k = 2 to 8
+ * replicas and s = 2 to 4 that have a level-q copy of 16 to 64 cells, q <= r, which
+ * holds what its neighbours need of it in three dwords per 16 cells and needs
+ * of them no more than eight such dwords per 16 cells: nearly every shape and
+ * order of replicas (not the full square and the Cantor dust at r = 2, whose 16
+ * cells are all at the edge; nbb_query_step tells).  There it takes one
+ * generation per launch, or in calls of several up to the generations that the
+ * cells held around a tile allow (both buffers end as with one launch per
+ * generation).
  * For other fractals, and for the strategies that name a form, it runs in the
  * form and at the level that nbb_query reports.  Every form gives the same
  * states.  nbb_query_step tells which one runs. */
@@ -275,7 +280,7 @@ nbb_status nbb_init_bbox(const nbb_fractal *f, uint8_t *state, uint64_t pitch, u
  * starts in a; buffers a and b alternate, and *result_in_b (if not NULL) is
  * set to steps & 1, i.e. whether the result ended in b.  len must be k^r;
  * a and b must not overlap and must both be 16-byte aligned (the tiled step
- * reads 16-byte chunks); the rule may only use bits 0-8, 16-24 and 31; state
+ * reads 16-byte chunks, and the last cell's aligned 4-byte word whole); the rule may only use bits 0-8, 16-24 and 31; state
  * bytes must be 0 or 1.  steps == 0 leaves both buffers untouched.
  * NBB_E_INVALID for a violation of any of these.
  */
@@ -478,7 +483,8 @@ nbb_status nbb_batch_query_step(const nbb_batch *batch, nbb_batch_step_info *inf
  * (*result_in_b = steps & 1).  Both arenas must be 16-byte aligned, at least
  * arena_bytes long (arena_len), and must not overlap; bytes outside the
  * instances' ranges are not written (loads of a block may reach past its
- * instance's range, never past arena_len; those bytes are not used).  Only
+ * instance's range, never past the aligned 4-byte word that holds byte
+ * arena_len - 1; those bytes are not used).  Only
  * the result is
  * specified: an instance's range in the other arena holds some earlier
  * generation (resident instances leave it untouched).

@@ -22,7 +22,8 @@
 //      bytes; two v_perm per dword pick them) in LDS, own blocks and
 //      the blocks of the eight neighbour tiles that a block of the tile reads
 //      (zeros where a neighbour tile does not exist: their loads are out of
-//      the buffer's range);
+//      the buffer's range, which ends with the aligned dword that holds the
+//      state's or arena's last byte);
 //   2. reads, per lane, 4 NH record dwords of the neighbouring blocks
 //      (addresses from the plan), which are the B operand of the halo's
 //      contraction, adds both, applies the rule (v_perm tables on four counts
