@@ -407,7 +407,7 @@ nbb_status nbb_autotune(nbb_fractal *f, uint8_t *a, uint8_t *b, uint64_t len, ui
  * twice over, with the tile boxes and the neighbour table (160 KiB on gfx950;
  * e.g. up to 3^9 triangle or 7^5 H cells), and whose generation takes at most
  * 8 passes of up to 4 tiles, may instead be stepped resident (by default when
- * they hold at least 1/3 of the batch's tiled cells; see
+ * they hold at least 1/8 of the batch's tiled cells; see
  * nbb_batch_create_ex): one work-group per instance runs all of the call's
  * generations of it in one launch, with no global traffic between
  * generations.  In LDS it does so at a tile level of its own (the one with the

@@ -129,11 +129,3 @@ def test_resident_instances_leave_the_other_arena(N, steps):
             got, other = (sb, sa) if counts[i] & 1 else (sa, sb)
             np.testing.assert_array_equal(got, o.compact_steps(st, B3S23, counts[i]), err_msg=f"{i} {counts}")
             np.testing.assert_array_equal(other, st if counts[i] & 1 else np.full_like(st, 9), err_msg=f"{i} {counts}")
-
-
-def test_resident_by_default_from_a_third_of_the_cells(N):
-    fd = W.TRIANGLE
-    big, small = N.Fractal(fd.s, fd.offsets, 11), N.Fractal(fd.s, fd.offsets, 7)  # 81 of the small to one
-    assert N.Batch([big] + [small] * 38).info().resident == 0
-    assert N.Batch([big] + [small] * 42).info().resident == 42
-    assert N.Batch([big] + [small] * 38, resident=True).info().resident == 38
