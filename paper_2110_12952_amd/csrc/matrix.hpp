@@ -442,7 +442,8 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
 #pragma unroll
     for (int u = 0; u < GPW; ++u) {
         const uint32_t b = (wave * GPW + u) * bpg + slot;
-        const bool own = b < E.nblk && mat_lane_owns(b, E.CB, coff, bytes), ring = b >= E.nblk && b < E.ntot;
+        // (a whole tile's lanes all own theirs)
+        const bool own = b < E.nblk && mat_lane_owns(b, E.CB, BATCH ? coff : 0u, bytes), ring = b >= E.nblk && b < E.ntot;
         const uint32_t item = E.halo[ring ? b - E.nblk : 0u];
         const uint32_t nt = E.nbr[uint64_t(t) * 8 + (item >> 29)];
         soff[u] = own ? b * E.CB + coff : kNowhere;
