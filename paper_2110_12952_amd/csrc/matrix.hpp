@@ -419,10 +419,8 @@ __global__ __launch_bounds__(64 * kHoldMaxWaves) void k_step_hold(HoldParams E, 
                 if (mode == kHoldMost) L += (L ^ T) & 1;
                 if (launch >= L) return;
                 gens = T / L + (launch < T % L ? 1u : 0u);
-                if (mode == kHoldWhole) {
-                    if (!(n & 1)) out = in;
-                    else if (launch) in = out;
-                }
+                if (mode == kHoldWhole && !(n & 1)) out = in;
+                if (mode == kHoldWhole && launch) in = out;
             }
         }
     }

@@ -186,7 +186,9 @@ constexpr uint32_t mat_first_cell(uint32_t sub, uint32_t CB) { return 16 * sub <
 // below the tile level may end inside a block, as the blocks of k = 2 and k = 4
 // grow with the level (16, 32 and 64 cells; 16 and 64), and always ends at a
 // lane's end.  What lies behind it in the arena is another instance's.
-constexpr bool mat_lane_owns(uint32_t b, uint32_t CB, uint32_t first, uint32_t bytes) { return b * CB + first < bytes; }
+constexpr bool mat_lane_owns(uint32_t b, uint32_t CB, uint32_t first, uint32_t bytes) {
+    return b * CB < (bytes > first ? bytes - first : 0u);
+}
 
 // Which of a batch call's launches a held launch is (k_step_hold).
 constexpr uint32_t kHoldMost = 0, kHoldLast = 1, kHoldWhole = 2;
