@@ -1825,10 +1825,10 @@ static nbb_status batch_create(const nbb_fractal *const *fractals, const uint64_
             R.set.steps = reinterpret_cast<uint32_t *>(base + R.off_steps);
         }
     for (const BatchDirect &d : B->direct) B->cu_count = d.f->cu_count;
-    // a side stream where resident and held sets run beside as many groups as
-    // have streams (not otherwise: five streams share the four hardware queues,
-    // eight spread sets took 103 us instead of 88)
-    if ((!B->resident.index.empty() || !B->small.empty()) && batch_base_lanes(B) > size_t(kGroupStreams)) {
+    // a side stream for the LDS launch beside as many groups as have streams
+    // (not otherwise: five streams share the four hardware queues, eight spread
+    // sets took 103 us instead of 88)
+    if ((!B->resident.index.empty() || !B->resident_all.index.empty()) && batch_base_lanes(B) > size_t(kGroupStreams)) {
         e = resident_stream(dev, &B->side);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&B->fork, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&B->join, hipEventDisableTiming);
@@ -1948,34 +1948,38 @@ static uint32_t held_set_launches(const HeldSet &S, uint32_t n) {
 }
 // Whether a call of `steps` generations, or counts[i] of instance i, takes the
 // held launches of the set: not where they are about as many as one per
-// generation.  *launches: their number, *most: the most generations.
-static bool held_use(const HeldSet &S, uint32_t steps, const uint32_t *counts, uint32_t *launches, uint32_t *most) {
-    *launches = *most = 0;
-    if (!S.ok) return false;
+// generation.
+struct HeldUse {
+    bool used = false;
+    uint32_t launches = 0, most = 0;  // their number; the most generations
+};
+static HeldUse held_use(const HeldSet &S, uint32_t steps, const uint32_t *counts) {
+    HeldUse u;
+    if (!S.ok) return u;
     if (counts) {
         for (uint32_t i : S.index) {
-            *most = std::max(*most, counts[i]);
-            *launches = std::max(*launches, held_set_launches(S, counts[i]));
+            u.most = std::max(u.most, counts[i]);
+            u.launches = std::max(u.launches, held_set_launches(S, counts[i]));
         }
     } else {
-        *most = steps;
-        *launches = held_set_launches(S, steps);
+        u.most = steps;
+        u.launches = held_set_launches(S, steps);
     }
-    return S.whole || 2 * uint64_t(*launches) + 2 <= *most;
+    u.used = S.whole || 2 * uint64_t(u.launches) + 2 <= u.most;
+    return u;
 }
 // `steps` generations of every instance of the set, or counts[i] of instance
 // i.  Sets of whole instances take all of them in the arena that the result
 // belongs to and leave the other one as it is; others take all but the last several at a time and the
 // last by itself, so that the other arena ends with the generation before, as
-// with one launch per generation.  *used = false (nothing enqueued) where
-// held_use says so.  *last: the last
-// generation is still to be taken, from *in to *out (never with counts).
-static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t arena_len, uint32_t steps,
-                            const uint32_t *counts, uint32_t rule, hipStream_t s, bool *used, bool *last = nullptr,
+// with one launch per generation.  Nothing is enqueued where `use`, held_use's
+// answer, says so.  *last: the last generation is still to be taken, from *in
+// to *out (never with counts).
+static hipError_t held_step(const HeldSet &S, const HeldUse &use, uint8_t *a, uint8_t *b, uint64_t arena_len,
+                            uint32_t steps, const uint32_t *counts, uint32_t rule, hipStream_t s, bool *last = nullptr,
                             uint8_t **in_ = nullptr, uint8_t **out_ = nullptr) {
-    uint32_t L = 0, most = 0;
-    *used = held_use(S, steps, counts, &L, &most);
-    if (!*used || !most) return hipSuccess;
+    if (!use.used || !use.most) return hipSuccess;
+    const uint32_t L = use.launches;
     auto go = [&](const HoldParams &E, uint8_t *in, uint8_t *out, uint32_t g, uint32_t i, uint32_t mode) {
         return launch_step_hold(E, S.al, S.nr, S.nh, S.gpw, in, out, arena_len, rule, g, S.rec,
                                 counts ? S.steps : nullptr, i, mode, s);
@@ -2012,10 +2016,10 @@ static hipError_t held_step(const HeldSet &S, uint8_t *a, uint8_t *b, uint64_t a
 // the group streams, and an LDS launch of the rest.
 struct ResidentUse {
     bool held;               // `small` takes its launches
-    bool spread;             // over the group streams
+    bool spread;             // over the lanes from `first`; else in turn in lane `own`
     const ResidentSet *lds;  // the set of the LDS launch
-    bool side;               // it, and held sets in turn, run on the side stream, else in lane `own`
-    size_t own, first;       // ...; lane of the first set where they are spread
+    bool side;               // which runs on the side stream, else in lane `own`
+    size_t own, first;
     size_t lanes;            // all lanes: the groups (or the DIRECT instances), and these
 };
 // The least estimated time.  An LDS launch costs one launch and kLdsPassUs per
@@ -2037,6 +2041,11 @@ static ResidentUse resident_use(const nbb_batch *B, uint32_t steps, const uint32
             return passes ? std::max(kLaunchUs, kLaunchFixedUs + kLdsPassUs * R.rounds * double(passes)) : 0.0;
         };
         const double lds = lds_us(B->resident_all);
+        const bool forked = batch_lane_streams(B, base) > 0;
+        auto streams_us = [&](size_t lanes) {  // of the forks and joins beyond those of the groups
+            const size_t more = batch_lane_streams(B, base + lanes) - batch_lane_streams(B, base);
+            return more ? (forked ? 0.0 : kForkUs) + kStreamUs * double(more) : 0.0;
+        };
         double in_turn = lds_us(B->resident), longest = in_turn;
         for (const HeldSet &S : B->small) {
             uint32_t most = counts ? 0 : steps;
@@ -2046,16 +2055,15 @@ static ResidentUse resident_use(const nbb_batch *B, uint32_t steps, const uint32
             in_turn += most ? std::max(kLaunchUs, t) : 0.0;
             longest = std::max(longest, t);
         }
-        const size_t streams = batch_lane_streams(B, base + rest + n) - batch_lane_streams(B, base);
-        const double spread = std::max(kForkUs + kStreamUs * double(streams) + kLaunchUs * double(n + rest), longest);
-        u.held = std::min(in_turn, spread) < lds;
+        const double spread = std::max(streams_us(rest + n) + kLaunchUs * double(n + rest), longest);
+        in_turn += streams_us(1);
+        u.held = std::min(in_turn, spread) < lds + (B->side ? kForkUs + kStreamUs : streams_us(1));
         u.spread = u.held && spread < in_turn;
         if (!u.held) u.lds = &B->resident_all;
     }
-    const bool alone = !u.lds->index.empty() || (u.held && !u.spread);
-    u.side = alone && B->side;
+    u.side = B->side && !u.lds->index.empty();
     u.own = base;
-    u.first = base + (alone && !u.side);
+    u.first = base + ((!u.side && !u.lds->index.empty()) || (u.held && !u.spread));
     u.lanes = u.first + (u.spread ? n : 0);
     return u;
 }
@@ -2079,12 +2087,11 @@ static hipError_t batch_step_small(const nbb_batch *B, const ResidentUse &use, u
     hipError_t e = use.side ? batch_fork_side(B, s) : hipSuccess;
     const hipError_t eg = batch_fork_groups(B, use.lanes, s);
     if (e == hipSuccess) e = eg;
-    const hipStream_t rs = use.side ? B->side : batch_group_stream(B, use.own, s);
-    if (e == hipSuccess) e = batch_step_resident(*use.lds, a, b, rule, n_lds, steps, rs);
+    const hipStream_t own = batch_group_stream(B, use.own, s);
+    if (e == hipSuccess) e = batch_step_resident(*use.lds, a, b, rule, n_lds, steps, use.side ? B->side : own);
     for (size_t k = 0; k < B->small.size() && use.held && e == hipSuccess; ++k) {
-        bool used = false;
-        e = held_step(B->small[k], a, b, arena_len, steps, counts, rule,
-                      use.spread ? batch_group_stream(B, use.first + k, s) : rs, &used);
+        e = held_step(B->small[k], held_use(B->small[k], steps, counts), a, b, arena_len, steps, counts, rule,
+                      use.spread ? batch_group_stream(B, use.first + k, s) : own);
     }
     return e;
 }
@@ -2117,10 +2124,11 @@ nbb_status nbb_batch_step(const nbb_batch *B, uint8_t *a, uint8_t *b, uint64_t a
     for (size_t k = 0; k < B->groups.size() && e == hipSuccess; ++k) {
         const BatchGroup &G = B->groups[k];
         const hipStream_t gs = batch_group_stream(B, k, s);
-        bool used = false, last = false;
+        const HeldUse held = held_use(G.held, steps, nullptr);
+        bool last = false;
         uint8_t *in = a, *out = b;
-        e = held_step(G.held, a, b, arena_len, steps, nullptr, rule, gs, &used, &last, &in, &out);
-        const uint32_t left = !used ? steps : (last ? 1u : 0u);
+        e = held_step(G.held, held, a, b, arena_len, steps, nullptr, rule, gs, &last, &in, &out);
+        const uint32_t left = !held.used ? steps : (last ? 1u : 0u);
         for (uint32_t i = 0; i < left && e == hipSuccess; ++i) {
             e = G.matrix  ? launch_step_matrix(G.mp, G.al, G.nr, G.nh, G.gpw, in, out, arena_len, rule, G.rec,
                                                B->cu_count, gs)
@@ -2171,10 +2179,13 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
     // The held sets' counts, where a held launch reads them: a launch of its
     // own (one large instance, one generation: 13.2 us with it, 9.4 without).
     bool count = false;
-    uint32_t L = 0, n_most = 0;
-    for (const BatchGroup &G : B->groups) count = count || (held_use(G.held, 0, steps, &L, &n_most) && n_most);
-    for (const HeldSet &S : B->small)
-        count = count || (use.held && held_use(S, 0, steps, &L, &n_most) && n_most);
+    std::vector<HeldUse> held(B->groups.size());
+    for (size_t k = 0; k < held.size(); ++k) {
+        held[k] = held_use(B->groups[k].held, 0, steps);
+        count = count || (held[k].used && held[k].most);
+    }
+    for (size_t k = 0; k < B->small.size() && use.held && !count; ++k)
+        for (uint32_t i : B->small[k].index) count = count || steps[i];
     std::vector<uint32_t> n, n_lds;  // (before the forks: an allocation that fails must not skip the joins)
     if (count) {
         for (const BatchGroup &G : B->groups)
@@ -2191,10 +2202,9 @@ nbb_status nbb_batch_step_each(const nbb_batch *B, uint8_t *a, uint8_t *b, uint6
         const BatchGroup &G = B->groups[k];
         const hipStream_t gs = batch_group_stream(B, k, s);
         size_t live = G.index.size();
-        bool used = false;
-        e = held_step(G.held, a, b, arena_len, 0, steps, rule, gs, &used);
+        e = held_step(G.held, held[k], a, b, arena_len, 0, steps, rule, gs);
         uint8_t *in = a, *out = b;
-        for (uint32_t g = 0; g < most && e == hipSuccess && !used; ++g) {
+        for (uint32_t g = 0; g < most && e == hipSuccess && !held[k].used; ++g) {
             while (live && steps[G.index[live - 1]] <= g) --live;
             if (!live) break;
             const uint32_t nt = uint32_t(G.tiles_end[live - 1]);
