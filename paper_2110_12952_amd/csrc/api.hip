@@ -201,19 +201,17 @@ struct nbb_batch {
     std::vector<HeldSet> small;  // instances counted as resident that one work-group each holds in registers
     std::vector<BatchDirect> direct;
     DevBlob dtab;
-    // with group or direct launches beside it, the resident launch runs on the
-    // device's side stream, forked from and joined back to the caller's
-    // stream, so that the two overlap
-    hipStream_t side = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
-    // With several groups, group k > 0 runs on gstream[(k - 1) % size] (the
-    // device's group streams, forked from the caller's stream and joined back
-    // to it), so that one group's launches fill the start and the tail of
-    // another's; empty when the batch has one group or was built without
-    // allocation.
+    // The lanes of a call (batch_base_lanes, resident_use): lane 0 is the
+    // caller's stream, lane k > 0 gstream[(k - 1) % size] (the device's group
+    // streams, forked from the caller's and joined back to it), so that one
+    // group's launches fill the start and the tail of another's.  Empty when
+    // there is one lane or the batch was built without allocation.
     std::vector<hipStream_t> gstream;
     std::vector<hipEvent_t> gjoin;  // one per group stream
     hipEvent_t gfork = nullptr;
+    // the LDS launch's stream beside more groups than have streams of their own
+    hipStream_t side = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
 };
 
 namespace {
@@ -1292,8 +1290,8 @@ static const TileParams *resident_plan(const nbb_fractal *F, uint32_t *teams) {
 }
 
 // The device's streams beside the caller's (created on first use, kept
-// until the process ends; default priority, non-blocking): slot 0 for
-// resident launches, slots 1 .. kGroupStreams for the groups of a batch.
+// until the process ends; default priority, non-blocking): slot 0 the side
+// stream, slots 1 .. kGroupStreams the lanes of a batch.
 constexpr int kGroupStreams = 3;
 static hipError_t device_stream(int dev, int slot, hipStream_t *out) {
     static std::mutex mu;

@@ -25,7 +25,7 @@ NBB_OUTSIDE = 0xFFFFFFFF
 NBB_RULE_B3S23 = (1 << 3) | ((1 << 2 | 1 << 3) << 16)
 NBB_RULE_VON_NEUMANN = 1 << 31
 NBB_BATCH_NO_RESIDENT = 1  # nbb_batch_create_ex: small instances stepped by the group launches too
-NBB_BATCH_RESIDENT = 2     # nbb_batch_create_ex: every small instance stepped in LDS
+NBB_BATCH_RESIDENT = 2     # nbb_batch_create_ex: every small instance stepped by one work-group
 (STRATEGY_AUTO, STRATEGY_TILED, STRATEGY_DIRECT, STRATEGY_TILED_WAVE, STRATEGY_TILED_BOX, STRATEGY_TEMPORAL,
  STRATEGY_TILED_EDGE) = range(7)
 MAP_LUT, MAP_DIGITS, MAP_MFMA = 0, 1, 2
@@ -543,8 +543,8 @@ class Batch:
     each arena (default: packed one after another).  The descriptors must stay
     alive and keep their configuration while the batch exists; the batch
     holds references to them.  resident: None = the library's choice, True =
-    every small instance runs all generations in LDS, False = small instances
-    go through the per-generation group launches like the rest."""
+    every small instance runs all generations in one work-group, False = small
+    instances go through the group launches like the rest."""
 
     def __init__(self, fractals: Sequence[Fractal], offsets: Optional[Sequence[int]] = None, stream=None,
                  resident: Optional[bool] = None):
